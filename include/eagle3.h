@@ -202,7 +202,7 @@ int eagle3_draft_chain(eagle3_ctx* ctx, int32_t B, const float* g_new, const int
 /* Section 3.1, first paragraph of the pipeline: during the prefill phase the target model runs over the prompt, the
  * low / mid / high feature sequences of its positions are recorded and fused, and the draft model's context is built
  * from them.  One sequence.  The T prompt tokens are run through every target layer in chunks of
- * min(max_nodes, max_new) positions (each chunk a chain on top of everything cached before it), their keys and
+ * up to 2048 positions (each on top of everything cached before it), their keys and
  * values are appended to the target cache at slots prefix_len .. prefix_len + T - 1, and for every position i whose
  * following token is known (all but the last) the draft layer's key / value of the row (g_i, tokens[i+1]) is appended
  * to the draft cache (a draft row's key and value depend only on that row, so no draft attention runs here).

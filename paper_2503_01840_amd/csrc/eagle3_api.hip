@@ -30,6 +30,11 @@ int fail_hip(hipError_t e, const char* what) {
 
 size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 
+// Rows of a prefill chunk.  bf16: one pass over the weights serves the whole chunk, and from about 2048 rows on the products
+// run at the matrix cores' rate and more rows no longer help (an 8B-shaped prompt of 2048 tokens, 32 layers: 139.6 ms in chunks
+// of 64).  fp32 (small models, exact kernels): enough rows to amortise the launches.
+constexpr int PREFILL_ROWS_BF16 = 2048, PREFILL_ROWS_FP32 = 256;
+
 struct Carver {          // first pass (base == nullptr) measures, second pass hands out pointers
   char* base;
   size_t off = 0;
@@ -60,7 +65,7 @@ struct eagle3_ctx {
   std::vector<Stamp> stamps;
   size_t stamps_used = 0;
 
-  int R_max, Md_max, Rall, a_rows, pool_max;
+  int R_max, Md_max, Rall, a_rows, pool_max;     // Rall: rows of the widest launch, a multiple of 64
   size_t part_floats, attn_floats;
   // workspace
   float* x; void* act_k; void* act_attn; void* act_h; void* q; float* part; float* attn_scratch;
@@ -68,7 +73,7 @@ struct eagle3_ctx {
   float* accept_stats;
   float* z; float* a_buf; int32_t* pos1; float* topk_scratch; DraftState ds;
   int chunk_max;                        // rows per prefill chunk
-  int32_t* chain_parent; float* chunk_taps; float* chunk_g;
+  float* chunk_taps; float* chunk_g;
   int rows1_max;                        // rows per sequence of a chain batch's forward 1
   ChainState cs_chain;
 
@@ -76,7 +81,7 @@ struct eagle3_ctx {
     const eagle3_config& c = cfg;
     Carver cv(base);
     const size_t k = c.hidden, I = c.intermediate, Hd = (size_t)c.n_heads * c.head_dim;
-    const size_t Rpad = (size_t)(Rall + 63) / 64 * 64;
+    const size_t Rpad = Rall;
     x = cv.take<float>((size_t)Rall * k);
     act_k = cv.take<char>(Rpad * 3 * k * act_size);
     act_attn = cv.take<char>(Rpad * Hd * act_size);
@@ -88,7 +93,7 @@ struct eagle3_ctx {
     mask = cv.take<uint32_t>((size_t)Rall * 4);
     slot = cv.take<int32_t>(Rall);
     cs = cv.take<float>((size_t)Rall * c.head_dim);
-    seq = cv.take<SeqInfo>(std::max(c.max_batch, 1));
+    seq = cv.take<SeqInfo>(std::max(c.max_batch, (chunk_max + 63) / 64));
     accept_stats = cv.take<float>(accept_scratch_floats(R_max, c.vocab));
     const int mb = std::max(c.max_batch, 1);
     z = cv.take<float>((size_t)std::max(Md_max, mb) * c.draft_vocab);
@@ -118,7 +123,6 @@ struct eagle3_ctx {
     ds.row_slot = cv.take<int32_t>(c.max_topk);
     ds.row_mask = cv.take<uint32_t>((size_t)c.max_topk * 4);
     ds.seq = cv.take<SeqInfo>(1);
-    chain_parent = cv.take<int32_t>(64);
     chunk_taps = cv.take<float>((size_t)3 * chunk_max * k);
     chunk_g = cv.take<float>((size_t)chunk_max * k);
     ws_need = cv.off;
@@ -216,15 +220,17 @@ int eagle3_create(const eagle3_config* cfg, eagle3_ctx** out) {
   ctx->act_size = ctx->bf16 ? 2 : 4;
   ctx->R_max = c.max_batch * c.max_nodes;
   ctx->Md_max = std::max(c.max_new, c.max_topk);
-  ctx->Rall = std::max(ctx->R_max, ctx->Md_max);
+  ctx->chunk_max = ctx->bf16 ? PREFILL_ROWS_BF16 : PREFILL_ROWS_FP32;
+  ctx->Rall = (std::max({ctx->R_max, ctx->Md_max, ctx->chunk_max}) + 63) / 64 * 64;
   ctx->a_rows = c.max_new + (c.max_depth - 1) * c.max_topk;
-  ctx->chunk_max = std::min(c.max_nodes, c.max_new);
   ctx->rows1_max = std::min(c.max_nodes, c.max_new);
   ctx->pool_max = 1 + c.max_topk + (c.max_depth - 1) * c.max_topk * c.max_topk;
   const size_t widest = std::max<size_t>({(size_t)(c.n_heads + 2 * c.n_kv_heads) * c.head_dim, (size_t)c.hidden,
                                           ctx->bf16 ? (size_t)0 : (size_t)2 * c.intermediate});
-  // split-K partial sums: up to 4 slices of the widest projection, 8 of a hidden-sized one
-  ctx->part_floats = std::max<size_t>({1024 * widest, 4 * (size_t)ctx->Rall * widest, 8 * (size_t)ctx->Rall * c.hidden});
+  // split-K partial sums: up to 4 slices of the widest projection, 8 of a hidden-sized one; 2 for a prefill chunk, whose
+  // many rows fill the chip without more
+  const size_t R_step = std::max(ctx->R_max, ctx->Md_max);
+  ctx->part_floats = std::max<size_t>({1024 * widest, 4 * R_step * widest, 8 * R_step * c.hidden, 2 * (size_t)ctx->chunk_max * widest});
   size_t af = 0;
   for (int b = 1; b <= c.max_batch; ++b) {
     const int s = attention_pick_splits(b, c.max_nodes, c.n_heads, c.n_kv_heads, 1 << 30);
@@ -232,6 +238,9 @@ int eagle3_create(const eagle3_config* cfg, eagle3_ctx** out) {
   }
   af = std::max(af, attention_scratch_floats(ctx->Md_max, c.n_heads, c.head_dim,
                                              attention_pick_splits(1, ctx->Md_max, c.n_heads, c.n_kv_heads, 1 << 30)));
+  for (int b = 1; 64 * b <= ctx->chunk_max; ++b)         // prefill: blocks of 64 rows
+    af = std::max(af, attention_scratch_floats(64 * b, c.n_heads, c.head_dim,
+                                               attention_pick_splits(b, 64, c.n_heads, c.n_kv_heads, 1 << 30)));
   ctx->attn_floats = ctx->bf16 ? af : 1;
   ctx->carve(nullptr);
   *out = ctx;
@@ -347,16 +356,17 @@ static int fuse_rows(eagle3_ctx* ctx, const float* low, const float* mid, const 
 // attention + output projection + MLP of one layer, shared by the target stack and the draft layer.
 // On entry: qkv partial sums are in `part` (S_qkv of them), x holds the residual rows.
 // On exit: `part` holds S_down partial sums of the MLP output (to be added to x by the caller).
-static int layer_tail(eagle3_ctx* ctx, const eagle3_layer_weights& w, int B, int rows_per_seq, int S_qkv,
+// R rows exist, B * rows_per_seq of them (and up to 63 more in a prefill chunk's last block) go through attention.
+static int layer_tail(eagle3_ctx* ctx, const eagle3_layer_weights& w, int B, int rows_per_seq, int R, int S_qkv,
                       const int32_t* slot, const float* cs, const uint32_t* mask, const SeqInfo* seq, void* kc, void* vc,
                       int max_len, int* S_down, hipStream_t st) {
   const eagle3_config& c = ctx->cfg;
-  const int R = B * rows_per_seq, k = c.hidden, H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim, I = c.intermediate;
+  const int k = c.hidden, H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim, I = c.intermediate;
   CK(launch_rope_kv_write(ctx->bf16, ctx->part, S_qkv, R, H, Hkv, d, cs, slot, ctx->q, kc, vc, st));
   int ns = 1;
   if (ctx->bf16) {
     ns = attention_pick_splits(B, rows_per_seq, H, Hkv, max_len);
-    while (ns > 1 && attention_scratch_floats(R, H, d, ns) > ctx->attn_floats) --ns;
+    while (ns > 1 && attention_scratch_floats(B * rows_per_seq, H, d, ns) > ctx->attn_floats) --ns;
   }
   CK(launch_tree_attention(ctx->bf16, ctx->q, kc, vc, seq, mask, B, rows_per_seq, H, Hkv, d, max_len, ns,
                            ctx->attn_scratch, ctx->act_attn, st));
@@ -371,23 +381,14 @@ static int layer_tail(eagle3_ctx* ctx, const eagle3_layer_weights& w, int B, int
   return EAGLE3_OK;
 }
 
-// Layers [l0, l1) of the target stack over the B*N node rows.  x_in == nullptr: start from the token
-// embeddings (requires l0 == 0).  logits != nullptr: finish with the final norm and the LM head (requires
-// l1 == n_layers).  x_out (optional) receives the residual stream after layer l1 - 1.
-static int verify_layers(eagle3_ctx* ctx, int B, int N, const int32_t* tree_tok, const int32_t* parent,
-                         const eagle3_kv* kv, const float* x_in, int l0, int l1, float* x_out, float* logits, float* taps,
-                         float* dbg_hidden, hipStream_t st) {
+// Layers [l0, l1) of the target stack over R rows, whose residual stream is in ctx->x and whose slots, masks and rotary
+// tables are prepared; attention sees them as B sequences of N rows.  logits != nullptr: finish with the final norm and the
+// LM head (requires l1 == n_layers).  x_out (optional) receives the residual stream after layer l1 - 1.
+static int run_layers(eagle3_ctx* ctx, int B, int N, int R, const eagle3_kv* kv, int max_len, int l0, int l1, float* x_out,
+                      float* logits, float* taps, float* dbg_hidden, hipStream_t st) {
   const eagle3_config& c = ctx->cfg;
-  const int R = B * N, k = c.hidden, H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim;
-  const int max_len = kv->max_prefix_len + N;
+  const int k = c.hidden, H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim;
   const size_t Rk = (size_t)R * k;
-
-  CK(launch_tree_prep(parent, kv->kv_indptr, kv->prefix_len, B, N, d, c.rope_theta, ctx->depth, ctx->mask, ctx->slot,
-                      ctx->cs, ctx->seq, st));
-  if (x_in)
-    CK(hipMemcpyAsync(ctx->x, x_in, Rk * sizeof(float), hipMemcpyDeviceToDevice, st));
-  else
-    CK(launch_embed_rows(ctx->bf16, ctx->tw.embed, tree_tok, R, k, c.vocab, ctx->x, st));
   int S_prev = 0;                                   // partial sums of the previous layer's MLP still to be added
   for (int l = l0; l <= l1; ++l) {
     // x becomes the output of layer l-1 here: record taps / debug copies, then norm for what follows
@@ -409,13 +410,28 @@ static int verify_layers(eagle3_ctx* ctx, int B, int N, const int32_t* tree_tok,
     GemmWeights Wqkv = {{w.wq, w.wk, w.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
     int S_qkv = 1;
     TRY(ctx->project(ctx->act_k, Wqkv, R, (H + 2 * Hkv) * d, k, GEMM_EPI_PARTIAL, &S_qkv, st));
-    TRY(layer_tail(ctx, w, B, N, S_qkv, ctx->slot, ctx->cs, ctx->mask, ctx->seq, kv->k[l], kv->v[l], max_len, &S_prev, st));
+    TRY(layer_tail(ctx, w, B, N, R, S_qkv, ctx->slot, ctx->cs, ctx->mask, ctx->seq, kv->k[l], kv->v[l], max_len, &S_prev, st));
   }
   if (l1 == c.n_layers && logits) {
     GemmWeights Wlm = {{ctx->tw.lm_head, nullptr, nullptr}, {c.vocab, 0, 0}, 1, 0};
     return ctx->project(ctx->act_k, Wlm, R, c.vocab, k, GEMM_EPI_PARTIAL, nullptr, st, logits);
   }
   return EAGLE3_OK;
+}
+
+// The same over the node rows of B trees, from the token embeddings (x_in == nullptr, requires l0 == 0) or from x_in.
+static int verify_layers(eagle3_ctx* ctx, int B, int N, const int32_t* tree_tok, const int32_t* parent,
+                         const eagle3_kv* kv, const float* x_in, int l0, int l1, float* x_out, float* logits, float* taps,
+                         float* dbg_hidden, hipStream_t st) {
+  const eagle3_config& c = ctx->cfg;
+  const int R = B * N;
+  CK(launch_tree_prep(parent, kv->kv_indptr, kv->prefix_len, B, N, c.head_dim, c.rope_theta, ctx->depth, ctx->mask, ctx->slot,
+                      ctx->cs, ctx->seq, st));
+  if (x_in)
+    CK(hipMemcpyAsync(ctx->x, x_in, (size_t)R * c.hidden * sizeof(float), hipMemcpyDeviceToDevice, st));
+  else
+    CK(launch_embed_rows(ctx->bf16, ctx->tw.embed, tree_tok, R, c.hidden, c.vocab, ctx->x, st));
+  return run_layers(ctx, B, N, R, kv, kv->max_prefix_len + N, l0, l1, x_out, logits, taps, dbg_hidden, st);
 }
 
 static int check_verify_args(eagle3_ctx* ctx, int B, int N, const int32_t* tree_tok, const int32_t* parent,
@@ -492,7 +508,7 @@ int eagle3_draft_expand(eagle3_ctx* ctx, const float* g_new, const int32_t* tok_
     GemmWeights Wqkv = {{w.wq, w.wk, w.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
     int S_qkv = 1, S_down = 1;
     TRY(ctx->project(ctx->act_k, Wqkv, M, (H + 2 * Hkv) * d, 2 * k, GEMM_EPI_PARTIAL, &S_qkv, st));
-    TRY(layer_tail(ctx, w, 1, M, S_qkv, slot, ctx->cs, mask, seq, kc, vc, max_len, &S_down, st));
+    TRY(layer_tail(ctx, w, 1, M, M, S_qkv, slot, ctx->cs, mask, seq, kc, vc, max_len, &S_down, st));
     // a = y1 + MLP(...): keep it for the children, and norm it for the LM head
     float* copies[4] = {ctx->a_buf + (size_t)a_row0 * k, nullptr, nullptr, nullptr};
     CK(launch_add_norm(ctx->bf16, ctx->x, ctx->part, S_down, M, k, ctx->dw.final_norm, c.rms_eps, ctx->act_k, copies, st));
@@ -562,7 +578,7 @@ int eagle3_draft_chain(eagle3_ctx* ctx, int32_t B, const float* g_new, const int
     GemmWeights Wqkv = {{w.wq, w.wk, w.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
     int S_qkv = 1, S_down = 1;
     TRY(ctx->project(ctx->act_k, Wqkv, M, (H + 2 * Hkv) * d, 2 * k, GEMM_EPI_PARTIAL, &S_qkv, st));
-    TRY(layer_tail(ctx, w, B, rps, S_qkv, slot, ctx->cs, mask, seq, kc, vc, max_len, &S_down, st));
+    TRY(layer_tail(ctx, w, B, rps, M, S_qkv, slot, ctx->cs, mask, seq, kc, vc, max_len, &S_down, st));
     if (level == 1 && rows1 > 1) {
       // a = y1 + MLP(...) for every row, then the row of each sequence's last real position moves to row b
       CK(launch_add_norm(ctx->bf16, ctx->x, ctx->part, S_down, M, k, nullptr, c.rms_eps, nullptr, nullptr, st));
@@ -593,19 +609,20 @@ int eagle3_prefill(eagle3_ctx* ctx, const int32_t* tokens, int32_t T, const eagl
   for (int l = 0; l < c.n_layers; ++l)
     if (!kv->k[l] || !kv->v[l]) return EAGLE3_E_NULL;
   hipStream_t st = (hipStream_t)stream;
-  const int k = c.hidden, H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim, C = ctx->chunk_max;
+  const int k = c.hidden, H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim;
   const eagle3_layer_weights& w = ctx->dw.layer;
-  CK(launch_chain_parent(ctx->chain_parent, std::min(C, 64), st));
-  int done_draft = 0;
+  // chunks of equal length (whole 64-row blocks): a short last chunk would stream all weights for a few rows
+  const int n_chunks = (T + ctx->chunk_max - 1) / ctx->chunk_max;
+  const int C = std::min(ctx->chunk_max, ((T + n_chunks - 1) / n_chunks + 63) / 64 * 64);
   for (int c0 = 0; c0 < T; c0 += C) {
-    const int n = std::min(C, T - c0);
+    const int n = std::min(C, T - c0), blocks = (n + 63) / 64;
     const bool last = c0 + n == T;
-    // target: the chunk as a chain on top of everything cached so far; features of every position recorded
-    eagle3_kv kvc = *kv;
-    kvc.max_prefix_len = kv->max_prefix_len + c0;
+    // target: the chunk on top of everything cached so far; features of every position recorded
     const size_t nk = (size_t)n * k;
-    TRY(verify_layers(ctx, 1, n, tokens + c0, ctx->chain_parent, &kvc, nullptr, 0, c.n_layers, nullptr, nullptr,
-                      ctx->chunk_taps, nullptr, st));
+    CK(launch_prefill_prep(kv->kv_indptr, kv->prefix_len, n, d, c.rope_theta, ctx->pos1, ctx->slot, ctx->mask, ctx->cs, ctx->seq, st));
+    CK(launch_embed_rows(ctx->bf16, ctx->tw.embed, tokens + c0, n, k, c.vocab, ctx->x, st));
+    TRY(run_layers(ctx, blocks, blocks == 1 ? n : 64, n, kv, kv->max_prefix_len + c0 + n, 0, c.n_layers, nullptr, nullptr,
+                   ctx->chunk_taps, nullptr, st));
     CK(launch_advance_lengths((int32_t*)kv->prefix_len, 1, n, st));
     if (last) {                                       // next-token logits of the last position only
       CK(launch_add_norm(ctx->bf16, ctx->x + (size_t)(n - 1) * k, nullptr, 0, 1, k, ctx->tw.final_norm, c.rms_eps, ctx->act_k,
@@ -618,7 +635,7 @@ int eagle3_prefill(eagle3_ctx* ctx, const int32_t* tokens, int32_t T, const eagl
     if (last) CK(hipMemcpyAsync(g_last, ctx->chunk_g + (size_t)(n - 1) * k, (size_t)k * sizeof(float), hipMemcpyDeviceToDevice, st));
     const int m = last ? n - 1 : n;
     if (m > 0) {
-      CK(launch_draft_prep1(dkv->kv_indptr, dkv->prefix_len, m, ctx->pos1, ctx->slot, ctx->mask, ctx->seq, st));
+      CK(launch_prefill_prep(dkv->kv_indptr, dkv->prefix_len, m, d, c.rope_theta, ctx->pos1, ctx->slot, ctx->mask, nullptr, ctx->seq, st));
       CK(launch_draft_input(ctx->bf16, ctx->tw.embed, c.vocab, tokens + c0 + 1, ctx->chunk_g, nullptr, m, k, ctx->dw.norm_embed,
                             ctx->dw.norm_feat, c.rms_eps, ctx->act_k, ctx->x, ctx->pos1, d, c.rope_theta, ctx->cs, st));
       GemmWeights Wqkv = {{w.wq, w.wk, w.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
@@ -626,10 +643,8 @@ int eagle3_prefill(eagle3_ctx* ctx, const int32_t* tokens, int32_t T, const eagl
       TRY(ctx->project(ctx->act_k, Wqkv, m, (H + 2 * Hkv) * d, 2 * k, GEMM_EPI_PARTIAL, &S_qkv, st));
       CK(launch_rope_kv_write(ctx->bf16, ctx->part, S_qkv, m, H, Hkv, d, ctx->cs, ctx->slot, ctx->q, dkv->k[0], dkv->v[0], st));
       CK(launch_advance_lengths((int32_t*)dkv->prefix_len, 1, m, st));
-      done_draft += m;
     }
   }
-  (void)done_draft;
   return EAGLE3_OK;
 }
 

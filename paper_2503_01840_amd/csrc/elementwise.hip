@@ -274,10 +274,34 @@ __global__ __launch_bounds__(64) void draft_prep1_kernel(const int32_t* __restri
   if (j == 0) { seq[0].kv_base = base; seq[0].n_prefix = P; seq[0].n_tail = n_new; seq[0].order = 0; }
 }
 
-// parent[i] = i - 1: a chain (ordinary causal decoding as a tree)
-__global__ __launch_bounds__(64) void chain_parent_kernel(int32_t* __restrict__ parent, int n) {
-  if ((int)threadIdx.x < n) parent[threadIdx.x] = (int)threadIdx.x - 1;
+// Rows of a prefill chunk, four per workgroup: row r continues the sequence at position P + r.  For attention the chunk is
+// cut into blocks of 64 rows: block b sees the context and every earlier block unconditionally (n_prefix = P + 64 b) and its
+// own rows causally through the row masks, so the tree kernels run a chunk of any length as a batch of "sequences" that
+// share one cache.  The last block has the most keys, so it is handed out first.
+__global__ __launch_bounds__(256) void prefill_prep_kernel(const int32_t* __restrict__ kv_indptr,
+                                                          const int32_t* __restrict__ prefix_len, int n, int d, float theta,
+                                                          int32_t* __restrict__ pos, int32_t* __restrict__ slot,
+                                                          uint32_t* __restrict__ mask, float* __restrict__ cs,
+                                                          SeqInfo* __restrict__ seq) {
+  const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (r >= n) return;
+  const int P = prefix_len[0], base = kv_indptr[0], j = r & 63, b = r >> 6;
+  if (lane < 4) {                                        // causal inside the block: bits 0..j
+    const int lo = 32 * lane;
+    mask[r * 4 + lane] = j < lo ? 0u : (j - lo >= 31 ? 0xFFFFFFFFu : ((2u << (j - lo)) - 1u));
+  }
+  if (lane == 0) {
+    pos[r] = P + r;
+    slot[r] = base + P + r;
+    if (j == 0) {
+      seq[b].kv_base = base; seq[b].n_prefix = P + r; seq[b].n_tail = min(64, n - r);
+      seq[b].order = (n + 63) / 64 - 1 - b;
+    }
+  }
+  if (cs)
+    for (int i = lane; i < d / 2; i += 64) rope_entry(cs, r, i, d, P + r, theta);
 }
+
 __global__ __launch_bounds__(64) void advance_lengths_kernel(int32_t* __restrict__ len, int B, int by) {
   const int b = blockIdx.x * 64 + threadIdx.x;
   if (b < B) len[b] += by;
@@ -285,9 +309,11 @@ __global__ __launch_bounds__(64) void advance_lengths_kernel(int32_t* __restrict
 
 }  // namespace
 
-hipError_t launch_chain_parent(int32_t* parent, int n, hipStream_t st) {
-  if (n > 64) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(chain_parent_kernel, dim3(1), dim3(64), 0, st, parent, n);
+hipError_t launch_prefill_prep(const int32_t* kv_indptr, const int32_t* prefix_len, int n, int head_dim, float theta,
+                               int32_t* pos, int32_t* slot, uint32_t* mask, float* cs, SeqInfo* seq, hipStream_t st) {
+  if (n < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(prefill_prep_kernel, dim3((n + 3) / 4), dim3(256), 0, st, kv_indptr, prefix_len, n, head_dim, theta, pos,
+                     slot, mask, cs, seq);
   return hipGetLastError();
 }
 hipError_t launch_advance_lengths(int32_t* len, int B, int by, hipStream_t st) {

@@ -73,7 +73,10 @@ hipError_t launch_draft_input(bool bf16, const void* embed, int vocab, const int
 hipError_t launch_draft_prep1(const int32_t* kv_indptr, const int32_t* prefix_len, int n_new, int32_t* pos, int32_t* slot,
                               uint32_t* mask, SeqInfo* seq, hipStream_t st);
 
-hipError_t launch_chain_parent(int32_t* parent, int n, hipStream_t st);                 // parent[i] = i - 1
+// Rows of a prefill chunk of n positions: positions, slots, causal masks inside blocks of 64 rows, one SeqInfo per block,
+// rotary tables (cs may be null).
+hipError_t launch_prefill_prep(const int32_t* kv_indptr, const int32_t* prefix_len, int n, int head_dim, float theta,
+                               int32_t* pos, int32_t* slot, uint32_t* mask, float* cs, SeqInfo* seq, hipStream_t st);
 hipError_t launch_advance_lengths(int32_t* len, int B, int by, hipStream_t st);          // len[b] += by
 
 // ---------------------------------------------------------------- attention (attention.hip)

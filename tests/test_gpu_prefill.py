@@ -1,0 +1,53 @@
+"""Prefill in chunks of many rows: prompt lengths at the edges of the 64-row attention blocks and of the chunks (256 rows in
+fp32, 2048 in bf16), every cache row, the fused feature and the logits of the last position against the oracle's prefill."""
+import numpy as np
+import pytest
+import torch
+
+import eagle3_synth as S
+from oracle import eagle3_oracle as O
+import pipeline as PL
+from test_gpu_edges import SMALL, _E
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("dtype,T", [("fp32", 64), ("fp32", 129), ("fp32", 256), ("fp32", 257),
+                                     ("bf16", 65), ("bf16", 192), ("bf16", 385), ("bf16", 2049)])
+def test_prefill_at_block_and_chunk_edges(dtype, T):
+    E = _E()
+    shape = S.get_shape("c1") if dtype == "fp32" else SMALL
+    rounding = "none" if dtype == "fp32" else "bf16"
+    # fp32: the exact path's 1e-4; bf16: the 2-layer bounds of the two-chunk test (one bf16 ulp of a rotated key at |k| < 8
+    # is 2^-5, of everything else below 2e-2)
+    tol_k, tol = (1e-4, 1e-4) if dtype == "fp32" else (4e-2, 2e-2)
+    model = PL.OracleModel(shape)
+    prompt = S.uniform_ints(S.SEED + T, S.TensorIds.PREFIX_TOK, (T,), 0, shape.vocab).numpy()
+    pre = O.prefill(shape, model.layer, model.globals(), prompt, rounding=rounding)
+    dw, emb = model.draft(), model.globals()["embed"]
+    g_all = O.fuse_features(dw["w_fc"], pre["taps"][0], pre["taps"][1], pre["taps"][2], rounding=rounding)
+    Kd = np.zeros((T - 1, shape.n_kv_heads, shape.head_dim)); Vd = np.zeros_like(Kd)
+    O.draft_forward(shape, dw, emb, g_all[:T - 1], prompt[1:], np.arange(T - 1), Kd, Vd, 0, 0,
+                    np.tril(np.ones((T - 1, T - 1), dtype=bool)), O._rounder(rounding))
+    ctx = E.Eagle3Context(shape, max_batch=1, max_nodes=8, max_depth=2, max_topk=2, max_new=4, device=DEV)
+    W = PL.device_weights(shape, device=DEV)
+    ctx.set_weights(W["target"], W["draft"])
+    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device=DEV)
+    z = lambda n: torch.full((n, shape.n_kv_heads, shape.head_dim), 7.0, dtype=ctx.storage_dtype, device=DEV)
+    ks, vs = [z(T + 3) for _ in range(shape.n_layers)], [z(T + 3) for _ in range(shape.n_layers)]
+    kv = E.KVCache(ks, vs, i32([0, T]), i32([0]), 0)
+    dkv = E.KVCache([z(T + 3)], [z(T + 3)], i32([0, T - 1]), i32([0]), 0)
+    g_last, logits = E.eagle3_prefill(ctx, i32(prompt), kv, dkv)
+    torch.cuda.synchronize()
+    f = lambda t: t.float().cpu().numpy()
+    assert int(kv.prefix_len[0]) == T and int(dkv.prefix_len[0]) == T - 1
+    for l in range(shape.n_layers):
+        assert np.max(np.abs(f(ks[l][:T]) - pre["k_new"][l])) < tol_k, l
+        assert np.max(np.abs(f(vs[l][:T]) - pre["v_new"][l])) < tol, l
+    assert np.max(np.abs(f(logits) - pre["logits"][-1])) < tol
+    assert np.max(np.abs(f(g_last) - g_all[-1])) < tol
+    assert np.max(np.abs(f(dkv.k_layers[0][:T - 1]) - Kd)) < tol_k
+    assert np.max(np.abs(f(dkv.v_layers[0][:T - 1]) - Vd)) < tol
+    for t, n in [(t, T) for t in ks + vs] + [(dkv.k_layers[0], T - 1), (dkv.v_layers[0], T - 1)]:
+        assert bool((t[n:] == 7.0).all()), "rows past the prompt were written"
