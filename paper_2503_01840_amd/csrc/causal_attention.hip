@@ -1,0 +1,565 @@
+// Causal attention of a run of consecutive positions (forward only): a prefill chunk against its sequence's cache, and the
+// draft layer's self-attention during a training-time-test step.
+//
+// Simulated step s over a training sequence of T positions: query i sees the ORIGINAL positions 0..i (ordinary
+// causal context) and, of every simulated step t = 1..s, only position i itself.  The causal part is a flash-style
+// pass over the original keys with the matrix cores; the s extra keys of a query are handled as the per-position
+// vector dot products they are (one key per query and step: a matrix product would compute T x T scores to keep T).
+//
+// bf16 kernel (head_dim 128).  A workgroup owns 128 query rows of one KV head: HG (1, 2 or 4) of the query heads that
+// share it x 128 / HG consecutive queries, so that every K/V tile it stages serves all of them.  8 wavefronts = 4 groups
+// of 32 rows x 2 halves of every 128-key tile; a wavefront takes its half in two blocks of 32 keys.
+//   * Tiles reach LDS by direct global-to-LDS loads, K one tile further ahead than V, swizzled per key; scores are
+//     produced transposed (S^T = K Q^T) so that a lane owns one query; the V^T operand comes from the transposing LDS
+//     read; exp(S) enters the value product as a bf16 head plus a bf16 tail.
+//   * One block is a matrix-unit time of 24 products (8 score + 16 value) against ~540 issue cycles of softmax.  Run
+//     one after the other they add up (all wavefronts pass the same barrier, so they stay in phase); here the softmax of
+//     block i runs between the score products of block i + 1 and the value products of block i - 1, none of which
+//     depend on it.
+//   * Only tiles that reach past a workgroup's first query need a mask.
+//   * The own keys of the simulated steps come last; their rows arrive while the last block is worked on.
+//   * Workgroups of later queries walk over more keys: they are handed out first, and the KV head is the fastest index,
+//     so that with 8 KV heads each XCD keeps one head's keys in its L2.
+// What bounds it: the chip's power.  At T = 2048, 32 heads over 8, the matrix units are busy 58 % of the cycles and the clock
+// drops to 1.86 GHz (1.53 GHz at T = 4096); 2.8 us per tile, 17 tiles per CU, plus 2.5 us before and 2.6 us after the walk
+// of each of a CU's two workgroups.  Measured against a kernel of one head x 64 queries per workgroup (4 wavefronts, scores,
+// softmax and values one after the other, own keys read from global memory by every lane for itself): T = 2048, s = 2:
+// 108 -> 65 us; T = 517, 64 heads, s = 5: 61 -> 28.5 us.
+// fp32 kernel: one workgroup per (query, head), exact arithmetic, for small checks.
+#include "common.hpp"
+#include "kernels.hpp"
+
+namespace {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef short short4v __attribute__((ext_vector_type(4)));
+typedef short short8v __attribute__((ext_vector_type(8)));
+constexpr int D = 128;
+constexpr int KT = 128;                       // keys per tile: two halves of two 32-key blocks
+constexpr int ROWB = D * 2;
+constexpr int TILE_BYTES = KT * ROWB;         // of K, and again of V
+constexpr int V_BASE = 2 * TILE_BYTES;        // two K slots, then three V slots: all of a CU's 160 KB
+constexpr int ROWS_WG = 128;
+constexpr int LDS_BYTES = 5 * TILE_BYTES;
+constexpr int Q_BASE = 4 * TILE_BYTES;        // the queries, staged in the third V slot before it is used
+constexpr int STAGE_BASE = 8 * 34 * 64 * 4;   // at the end: the exchange of the key halves, then 8 KB per wavefront
+
+constexpr int IPW = 4;                        // direct loads per wavefront per tile, for K and again for V
+constexpr float NEG = -1e30f;
+constexpr float MAX_SLACK = 8.f;
+
+struct CausalParams {
+  const bf16_t* q;        // [T, H, D]
+  const bf16_t* k;        // training: [s+1, T, Hkv, D]; prefill: the cache [slots, Hkv, D]
+  const bf16_t* v;
+  const SeqInfo* seq;     // prefill: kv_base and n_prefix of the sequence
+  int T, H, Hkv, s;
+  int hg, n_groups, n_qblocks;      // query heads per workgroup, KV heads x head groups, query blocks
+  float scale_log2;
+  void* out;              // training: fp32 [T, H, D]; prefill: fragment-major bf16 [T, H * D]
+};
+
+__device__ __forceinline__ void pair_values(float x, float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+
+// One wavefront-wide direct load: lane l's 16 bytes at base + lane_off land at LDS byte address lds_base + 16 l.  The
+// compiler does not see these as memory operations; the kernel counts them itself (s_waitcnt vmcnt).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void dma16(const void* base, uint32_t lane_off, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(lane_off), "s"(base)
+               : "memory", "m0");
+}
+#pragma clang diagnostic pop
+#define CAUSAL_PIN() __builtin_amdgcn_sched_barrier(0)
+#define CAUSAL_WAIT_LOADS(n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n) : "memory")
+
+__device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
+// LDS reads at a byte address
+__device__ __forceinline__ u32x4 read_lds(uint32_t a) { return *(const u32x4 __attribute__((address_space(3)))*)a; }
+__device__ __forceinline__ short4v read_tr(uint32_t a) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4v __attribute__((address_space(3)))*)a);
+}
+__device__ __forceinline__ floatx16 mfma(const u32x4& a, const u32x4& b, const floatx16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+#define INLINE_LAMBDA __attribute__((always_inline))
+
+template <bool V> struct Flag { static constexpr bool value = V; };
+
+// PREFILL: query i sits at position n_prefix + i of a sequence in the cache, whose earlier positions it sees as well.
+template <bool PREFILL>
+__global__ __launch_bounds__(512) void causal_attn_bf16_kernel(CausalParams p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rg = wave & 3, sb = wave >> 2;                   // row group, key half
+  const int kg = lane >> 5;
+  const int gh = blockIdx.x % p.n_groups;
+  const int qb = p.n_qblocks - 1 - (int)blockIdx.x / p.n_groups;
+  const int g = gh % p.Hkv, G = p.H / p.Hkv;
+  const int QB = ROWS_WG / p.hg;                             // queries per workgroup
+  const int head = g * G + (gh / p.Hkv) * p.hg + rg * 32 / QB;
+  const int q_first = qb * QB, q_wave = q_first + (rg * 32) % QB;
+  const int T = p.T;
+  const int pos0 = PREFILL ? p.seq[0].n_prefix : 0;          // position of query 0
+  const int pos_wave = pos0 + q_wave, pos = pos_wave + (lane & 31);
+  const int L = pos0 + min(T, q_first + QB);                 // original keys this workgroup walks over
+  const int n_tiles = (L + KT - 1) / KT;
+
+  const size_t row_stride = (size_t)p.Hkv * D;
+  const size_t first_key = (PREFILL ? (size_t)p.seq[0].kv_base * row_stride : 0) + (size_t)g * D;
+  const bf16_t* kbase = p.k + first_key;
+  const bf16_t* vbase = p.v + first_key;
+  // Instruction j (0..31) of a tile brings keys 4j .. 4j+3; lane l fetches, for key 4j + (l >> 4), the piece that belongs
+  // at position l & 15 of the swizzled row: K rows hold piece c at position c ^ (key & 15), V rows at c ^ ((key & 3) << 2).
+  // Keys past the end repeat the last one (masked later).
+  const int lkey = lane >> 4;
+  const uint32_t vpiece = ((lane & 15) ^ ((lkey & 3) << 2)) * 16;
+  uint32_t koff[IPW], voff[IPW];
+#pragma unroll
+  for (int i = 0; i < IPW; ++i) {
+    const int j = wave * IPW + i;
+    const uint32_t key_bytes = (uint32_t)(4 * j + lkey) * (uint32_t)(row_stride * 2);
+    koff[i] = key_bytes + (uint32_t)(((lane & 15) ^ (4 * (j & 3) + lkey)) * 16);
+    voff[i] = key_bytes + vpiece;
+  }
+  auto issue = [&](const bf16_t* base, const uint32_t (&off)[IPW], int t, uint32_t slot_base) INLINE_LAMBDA {   // slot at slot_base
+    const bf16_t* b0 = base + (size_t)t * KT * row_stride;
+    const uint32_t slot = lds0 + slot_base + wave * IPW * 1024;
+    if ((t + 1) * KT <= L) {
+#pragma unroll
+      for (int i = 0; i < IPW; ++i) dma16(b0, off[i], slot + i * 1024);
+    } else {
+      const int last = L - 1 - t * KT;
+#pragma unroll
+      for (int i = 0; i < IPW; ++i) {
+        const int key = 4 * (wave * IPW + i) + lkey;
+        dma16(b0, off[i] - (uint32_t)(key - min(key, last)) * (uint32_t)(row_stride * 2), slot + i * 1024);
+      }
+    }
+  };
+  // The simulated steps' own rows: up to hg steps x QB rows = 128 rows of K and of V at a time go through free tile
+  // slots as whole 256-byte rows, piece c of staged row i at position c ^ (i & 15), one copy for all heads and wavefronts.
+  // (Read by every lane for itself, 16 and 8 bytes per row and request, they were a third of the kernel: a request that
+  // touches 32 lines takes 32 times as long as one that touches one.)
+  auto issue_own = [&](int t0, uint32_t k_slot, uint32_t v_slot) INLINE_LAMBDA {
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) {
+      const int j = wave * IPW + i, r = (4 * j) % QB + lkey;             // staged rows 4j .. 4j+3: one step
+      const int t = min(t0 + 4 * j / QB, p.s);
+      const size_t base = ((size_t)t * T + q_first) * row_stride;
+      const uint32_t off = (uint32_t)(min(q_first + r, T - 1) - q_first) * (uint32_t)(row_stride * 2) +
+                           (uint32_t)(((lane & 15) ^ (4 * (j & 3) + lkey)) * 16);
+      dma16(kbase + base, off, lds0 + k_slot + j * 1024);
+      dma16(vbase + base, off, lds0 + v_slot + j * 1024);
+    }
+  };
+  // the workgroup's query rows, staged the same way (row group by row group) behind the tile slots
+#pragma unroll
+  for (int i = 0; i < IPW; ++i) {
+    const int j = wave * IPW + i, r = 4 * j + lkey, rgj = j >> 3;
+    const int h = g * G + (gh / p.Hkv) * p.hg + rgj * 32 / QB, qr = min(q_first + (rgj * 32) % QB + (r & 31), T - 1);
+    const uint32_t off = (uint32_t)(qr - q_first) * (uint32_t)(p.H * ROWB) + (uint32_t)(((lane & 15) ^ (r & 15)) * 16);
+    dma16(p.q + ((size_t)q_first * p.H + h) * D, off, lds0 + Q_BASE + j * 1024);
+  }
+  issue(kbase, koff, 0, 0);
+  issue(vbase, voff, 0, V_BASE);
+
+  uint32_t minus_lo = 0x0000BF80u, minus_hi = 0xBF800000u;   // bf16 pairs (-1, 0) and (0, -1), kept in registers
+  uint32_t ones = 0x3F803F80u;
+  asm volatile("" : "+v"(minus_lo), "+v"(minus_hi), "+v"(ones));
+
+  floatx16 o[4];
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+  float m_run = NEG, l_run = 0.f;              // l_run: this lane's share; its partner lane ^ 32 holds the rest
+
+  CAUSAL_WAIT_LOADS(0);                        // my part of tile 0 has landed; the barrier extends that to everyone's
+  __syncthreads();
+  u32x4 qf[8];
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks)
+    qf[ks] = *(const u32x4*)(smem + Q_BASE + (rg * 32 + (lane & 31)) * ROWB + (((2 * ks + kg) ^ (lane & 15)) * 16));
+
+  // LDS read addresses inside a tile slot.  K operand (32 keys x 16 k) of a block: lane (key = l & 31, pieces 2 ks + kg,
+  // whose swizzled offsets are the one of ks = 0 XOR 32 ks bytes).  V^T operand via transposing reads: call c of k-step m
+  // returns, for head-dim index db * 32 + (l & 31), keys 16 m + 8 c + 4 kg + 0..3 of the block; the lane hands in the
+  // address of 4 head-dim values of ONE of those keys: key + ((l & 15) >> 2), head-dim chunk 16 ((l >> 4) & 1) + 4 (l & 3)
+  // (offset of db: XOR 64 db bytes).
+  const uint32_t k_rd = lds0 + (uint32_t)((sb * 64 + (lane & 31)) * ROWB + ((kg ^ (lane & 15)) * 16));
+  const int vkey0 = sb * 64 + 4 * kg + ((lane & 15) >> 2);
+  const uint32_t v_rd = lds0 + (uint32_t)(V_BASE + vkey0 * ROWB + (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ ((vkey0 & 3) << 2)) * 16) +
+                                          (lane & 1) * 8);
+  constexpr uint32_t BLOCK = 32 * ROWB;
+
+  // Running max over a block of scores; returns the max in force from this block on.  It only moves when some row of the
+  // wavefront would raise its own by more than MAX_SLACK (log2 units): until then exp2 may exceed 1 by up to 2^MAX_SLACK,
+  // which the fp32 sums and the head/tail split carry without loss, and the output needs no rescaling.
+  auto new_max = [&](float mx) INLINE_LAMBDA -> float {
+    mx *= p.scale_log2;
+    float xa, xb;
+    pair_values(mx, xa, xb);
+    const float m_cand = fmaxf(m_run, fmaxf(xa, xb));
+    return __any(m_cand - m_run > MAX_SLACK) ? m_cand : m_run;
+  };
+  // An invisible score is -inf and the max is finite, so its weight is exactly zero.
+  auto weight = [&](float x, float m_new) INLINE_LAMBDA -> float {
+    return __builtin_amdgcn_exp2f(__builtin_fmaf(x, p.scale_log2, -m_new));
+  };
+  // Two weights as bf16 heads and tails (p = hi + lo, 16 significant bits): rounding them to a single bf16 would put a 2^-9
+  // relative error on the output.  The sum takes what the value products take, so that a rounded weight stays a weight: its
+  // error only reaches the output through the distance of its value from the mean.
+  auto split_pair = [&](float p0, float p1, uint32_t& h, uint32_t& l, float& sum) INLINE_LAMBDA {
+    h = pack_bf16x2(p0, p1);
+    // tail = p - head, one v_dot2c_f32_bf16 each: p + head.lo * -1 + head.hi * 0 (exact)
+    const float t0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, h), __builtin_bit_cast(bf16x2_t, minus_lo), p0, false);
+    const float t1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, h), __builtin_bit_cast(bf16x2_t, minus_hi), p1, false);
+    l = pack_bf16x2(t0, t1);
+    sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, h), __builtin_bit_cast(bf16x2_t, ones), sum, false);
+    sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, l), __builtin_bit_cast(bf16x2_t, ones), sum, false);
+  };
+  auto k_operand = [&](uint32_t at, int ks) INLINE_LAMBDA -> u32x4 { return read_lds(at ^ (32u * ks)); };
+  // operand n of a block of values: k-step n >> 2, head-dim block n & 3
+  auto v_operand = [&](uint32_t at, int n) INLINE_LAMBDA -> u32x4 {
+    const uint32_t a = (at ^ (64u * (n & 3))) + 16 * (n >> 2) * ROWB;
+    const short4v lo4 = read_tr(a), hi4 = read_tr(a + 8 * ROWB);
+    return __builtin_bit_cast(u32x4, __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  // weights of one block: entry i & 3 of operand i >> 2 of heads and tails
+  struct Weights { u32x4 h[2], l[2]; };
+  u32x4 va[4];                                 // value operands n of the block in work at n & 3
+
+  // Softmax of the block of scores in s (first key kb) among the products of its neighbours: values of the previous block
+  // (weights w; V at v_at, its first two operands already in va) and scores of the next one (K at k_at, into sn).  Leaves
+  // this block's weights in wn and its first two value operands (V at v_next) in va.  The order is written out and pinned:
+  // the compiler on its own puts the products first and the exponentials after them.
+  auto block = [&](auto has_prev, floatx16& s, floatx16& sn, const Weights& w, Weights& wn, int kb, uint32_t k_at, uint32_t v_at,
+                   uint32_t v_next) INLINE_LAMBDA {
+    constexpr bool PREV = decltype(has_prev)::value;
+    auto value = [&](int n, bool tail) INLINE_LAMBDA {
+      if constexpr (PREV) o[n & 3] = mfma(va[n & 3], tail ? w.l[n >> 2] : w.h[n >> 2], o[n & 3]);
+    };
+    auto fetch = [&](int n) INLINE_LAMBDA {
+      if constexpr (PREV) va[n & 3] = v_operand(v_at, n);
+    };
+    u32x4 kf[3];
+    fetch(2);
+    fetch(3);
+    kf[0] = k_operand(k_at, 0);
+    kf[1] = k_operand(k_at, 1);
+    if (kb + 31 > pos_wave) {                  // keys after the lane's query: key kb + i is visible iff kb + i <= pos
+      const int n_vis = pos - kb + 1;
+      const uint32_t vis = (n_vis >= 32 ? 0xFFFFFFFFu : n_vis <= 0 ? 0u : ((1u << n_vis) - 1u)) >> (4 * kg);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = ((vis >> (8 * (r >> 2) + (r & 3))) & 1u) ? s[r] : -INFINITY;
+    }
+    CAUSAL_PIN();
+    // first half: eight value products over the search for the max
+    value(0, false);
+    float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
+    CAUSAL_PIN();
+    value(1, false);
+    mx = fmaxf(fmaxf(mx, s[3]), s[4]); mx = fmaxf(fmaxf(mx, s[5]), s[6]);
+    CAUSAL_PIN();
+    value(0, true);
+    mx = fmaxf(fmaxf(mx, s[7]), s[8]); mx = fmaxf(fmaxf(mx, s[9]), s[10]);
+    CAUSAL_PIN();
+    value(1, true);
+    fetch(4);
+    mx = fmaxf(fmaxf(mx, s[11]), s[12]); mx = fmaxf(fmaxf(fmaxf(mx, s[13]), s[14]), s[15]);
+    CAUSAL_PIN();
+    value(2, false);
+    fetch(5);
+    const float m_new = new_max(mx);
+    CAUSAL_PIN();
+    value(3, false);
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    m_run = m_new;
+    CAUSAL_PIN();
+    value(2, true);
+    s[0] = weight(s[0], m_new);
+    CAUSAL_PIN();
+    value(3, true);
+    s[1] = weight(s[1], m_new);
+    CAUSAL_PIN();
+    // second half: eight score products and eight value products, one exponential each
+    float ls = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (j == 0) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sn[r] = 0.f;
+      }
+      sn = mfma(kf[j % 3], qf[j], sn);
+      if (j < 6) kf[(j + 2) % 3] = k_operand(k_at, j + 2);
+      if (j < 7) s[2 * j + 2] = weight(s[2 * j + 2], m_new);
+      CAUSAL_PIN();
+      value(4 + (j & 1) + 2 * (j >> 2), (j >> 1) & 1);
+      if (j == 1) fetch(6);
+      if (j == 2) fetch(7);
+      if (j == 6) va[0] = v_operand(v_next, 0);
+      if (j == 7) va[1] = v_operand(v_next, 1);
+      if (j < 7) s[2 * j + 3] = weight(s[2 * j + 3], m_new);
+      uint32_t h, l;
+      split_pair(s[2 * j], s[2 * j + 1], h, l, ls);
+      wn.h[j >> 2][j & 3] = h;
+      wn.l[j >> 2][j & 3] = l;
+      CAUSAL_PIN();
+    }
+    l_run = l_run * alpha + ls;
+#pragma unroll
+    for (int m = 0; m < 2; ++m) asm volatile("" : "+v"(wn.h[m]), "+v"(wn.l[m]));     // keeps the work above the branch below
+    if (__any(alpha != 1.0f)) {
+#pragma unroll
+      for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+    }
+  };
+
+  if (n_tiles > 1) {
+    issue(kbase, koff, 1, TILE_BYTES);
+    issue(vbase, voff, 1, V_BASE + TILE_BYTES);
+  }
+  floatx16 s0, s1;
+  Weights w0, w1;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s0[r] = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) s0 = mfma(k_operand(k_rd, ks), qf[ks], s0);
+  // Tile t in two blocks; one barrier between them.  It publishes K and V of tile t + 1, and frees the slots of K t and
+  // V t - 1 for K and V of tile t + 2.  So the second block can read K of t + 1, and V operands are in LDS early enough to
+  // be read a block ahead.
+  int kb = sb * 64;
+  uint32_t k_slot = 0, v_slot = 0;             // of tile t
+  uint32_t own_k = 0, own_v = 0;
+  block(Flag<false>(), s0, s1, w0, w0, kb, k_rd + BLOCK, v_rd, v_rd);
+#pragma unroll 1
+  for (int t = 0;; ++t) {
+    CAUSAL_WAIT_LOADS(0);
+    __syncthreads();
+    const uint32_t v_1 = v_slot == 2 * TILE_BYTES ? 0 : v_slot + TILE_BYTES;         // V slots of tiles t + 1, t + 2
+    if (t + 2 < n_tiles) {
+      const uint32_t v_2 = v_1 == 2 * TILE_BYTES ? 0 : v_1 + TILE_BYTES;
+      issue(kbase, koff, t + 2, k_slot);
+      issue(vbase, voff, t + 2, V_BASE + v_2);
+    }
+    const bool last = t + 1 == n_tiles;        // then the scores of a next block are formed from this tile and not read
+    const uint32_t k_1 = last ? k_slot : k_slot ^ TILE_BYTES;
+    if (last) {
+      own_k = k_slot ^ TILE_BYTES;
+      own_v = V_BASE + v_1;
+      if (!PREFILL && p.s > 0) issue_own(1, own_k, own_v);
+    }
+    block(Flag<true>(), s1, s0, w0, w1, kb + 32, k_rd + k_1, v_rd + v_slot, v_rd + v_slot + BLOCK);
+    if (last) break;
+    kb += KT;
+    block(Flag<true>(), s0, s1, w1, w0, kb, k_rd + k_1 + BLOCK, v_rd + v_slot + BLOCK, v_rd + v_1);
+    k_slot = k_1;
+    v_slot = v_1;
+  }
+#pragma unroll
+  for (int n = 0; n < 8; ++n) {
+    if (n > 1) va[n & 3] = v_operand(v_rd + v_slot + BLOCK, n);
+    o[n & 3] = mfma(va[n & 3], w1.h[n >> 2], o[n & 3]);
+    o[n & 3] = mfma(va[n & 3], w1.l[n >> 2], o[n & 3]);
+  }
+
+  // The query's own key of every simulated step: one dot product and one scaled row of values each, the two key halves
+  // taking alternate steps.  Last, as they are exact in fp32 against any max; taken first, their max would be in force for
+  // the first keys, whose largest weight is then no longer 1 but carried with 16 bits (twice the error in the first rows).  This lane holds the query's entries 16 ks + 8 kg + 0..7 (its partner lane ^ 32 the other
+  // half) and the output entries 32 db + 8 gq + 4 kg + 0..3.
+#pragma unroll 1
+  for (int t0 = 1; !PREFILL && t0 <= p.s; t0 += p.hg) {
+    if (t0 > 1) {
+      __syncthreads();
+      issue_own(t0, own_k, own_v);
+    }
+    CAUSAL_WAIT_LOADS(0);
+    __syncthreads();
+#pragma unroll 1
+    for (int t = t0 + ((t0 + sb + 1) & 1); t < t0 + p.hg && t <= p.s; t += 2) {
+      const int i = (t - t0) * QB + q_wave - q_first + (lane & 31);
+      const unsigned char* kr = smem + own_k + i * ROWB;
+      const unsigned char* vr = smem + own_v + i * ROWB + kg * 8;
+      float dot = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) {
+        const u32x4 kk = *(const u32x4*)(kr + (((2 * ks + kg) ^ (i & 15)) * 16));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          dot = fmaf(bf16_lo(qf[ks][e]), bf16_lo(kk[e]), dot);
+          dot = fmaf(bf16_hi(qf[ks][e]), bf16_hi(kk[e]), dot);
+        }
+      }
+      float xa, xb;
+      pair_values(dot, xa, xb);
+      const float sc = (xa + xb) * p.scale_log2;
+      const float m_new = fmaxf(m_run, sc);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new), pw = __builtin_amdgcn_exp2f(sc - m_new);
+      l_run = l_run * alpha + (kg == 0 ? pw : 0.f);
+      m_run = m_new;
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {
+        const uint2 vv = *(const uint2*)(vr + ((c ^ (i & 15)) * 16));
+        const int db = c >> 2, r = 4 * (c & 3);
+        o[db][r] = o[db][r] * alpha + pw * bf16_lo(vv.x);
+        o[db][r + 1] = o[db][r + 1] * alpha + pw * bf16_hi(vv.x);
+        o[db][r + 2] = o[db][r + 2] * alpha + pw * bf16_lo(vv.y);
+        o[db][r + 3] = o[db][r + 3] * alpha + pw * bf16_hi(vv.y);
+      }
+    }
+  }
+  CAUSAL_WAIT_LOADS(0);
+
+  // Merge the two key halves: each wavefront finishes the half of the head dimension (db = 2 sb, 2 sb + 1) and hands the
+  // other half, with its max and sum, to its partner through LDS.
+  __syncthreads();
+  float* xo = (float*)smem + (size_t)(rg * 2) * (34 * 64);
+  {
+    float* mine = xo + sb * (34 * 64);
+#pragma unroll
+    for (int d2 = 0; d2 < 2; ++d2)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mine[(d2 * 16 + r) * 64 + lane] = sb == 0 ? o[2 + d2][r] : o[d2][r];
+    mine[32 * 64 + lane] = m_run;
+    mine[33 * 64 + lane] = l_run;
+  }
+  __syncthreads();
+  const float* theirs = xo + (sb ^ 1) * (34 * 64);
+  const float m2 = theirs[32 * 64 + lane], l2 = theirs[33 * 64 + lane];
+  const float m_all = fmaxf(m_run, m2);
+  const float f1 = __builtin_amdgcn_exp2f(m_run - m_all), f2 = __builtin_amdgcn_exp2f(m2 - m_all);
+  float la, lb;
+  pair_values(l_run * f1 + l2 * f2, la, lb);
+  const float inv = 1.0f / (la + lb);
+  auto merged = [&](int d2, int gq) INLINE_LAMBDA -> floatx4 {         // values 32 d2 + 8 gq + 4 kg + 0..3 of this wavefront's half
+    floatx4 val;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = 4 * gq + e;
+      val[e] = ((sb == 0 ? o[d2][r] : o[2 + d2][r]) * f1 + theirs[(d2 * 16 + r) * 64 + lane] * f2) * inv;
+    }
+    return val;
+  };
+  if constexpr (PREFILL) {
+    if (q_wave + (lane & 31) >= T) return;
+#pragma unroll
+    for (int d2 = 0; d2 < 2; ++d2)
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq) {
+        const floatx4 val = merged(d2, gq);
+        Act<true>::store4((bf16_t*)p.out, q_wave + (lane & 31), head * D + sb * 64 + d2 * 32 + 8 * gq + 4 * kg, p.H * D, val[0], val[1],
+                          val[2], val[3]);
+      }
+  } else {
+    // The finished 32 rows x 64 values of this wavefront go through its own 8 KB of LDS, so that the stores are whole
+    // 256-byte runs: 16-byte piece c of row i at position c ^ (i & 15).
+    unsigned char* stage = smem + STAGE_BASE + wave * 8192;
+#pragma unroll
+    for (int d2 = 0; d2 < 2; ++d2)
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq)
+        *(floatx4*)(stage + (lane & 31) * 256 + (((d2 * 8 + 2 * gq + kg) ^ (lane & 15)) * 16)) = merged(d2, gq);
+    __builtin_amdgcn_wave_barrier();           // one wavefront's LDS operations complete in order
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int i = 4 * c + lkey;
+      const floatx4 val = *(const floatx4*)(stage + i * 256 + (((lane & 15) ^ (i & 15)) * 16));
+      if (q_wave + i < T) *(floatx4*)((float*)p.out + ((size_t)(q_wave + i) * p.H + head) * D + sb * 64 + (lane & 15) * 4) = val;
+    }
+  }
+}
+
+// fp32: one workgroup per (query, head); scores of the i + 1 + s visible keys in LDS
+__global__ __launch_bounds__(256) void ttt_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
+                                                          const float* __restrict__ v, int T, int H, int Hkv, int d, int s,
+                                                          float scale, float* __restrict__ out) {
+  extern __shared__ float sc[];
+  __shared__ float red[17];
+  const int i = blockIdx.x, h = blockIdx.y, g = h * Hkv / H, tid = threadIdx.x;
+  const int n = i + 1 + s;
+  const float* qr = q + ((size_t)i * H + h) * d;
+  auto key_row = [&](int j) { return j <= i ? (size_t)j : (size_t)(j - i) * T + i; };      // row of the [s+1, T] arrays
+  float mx = -INFINITY;
+  for (int j = tid; j < n; j += 256) {
+    const float* kr = k + (key_row(j) * Hkv + g) * d;
+    float acc = 0.f;
+    for (int e = 0; e < d; ++e) acc = fmaf(qr[e], kr[e], acc);
+    sc[j] = acc * scale;
+    mx = fmaxf(mx, sc[j]);
+  }
+  mx = block_max(mx, red);
+  float sum = 0.f;
+  for (int j = tid; j < n; j += 256) {
+    const float e = expf(sc[j] - mx);
+    sc[j] = e;
+    sum += e;
+  }
+  sum = block_sum(sum, red);
+  for (int e = tid; e < d; e += 256) {
+    float acc = 0.f;
+    for (int j = 0; j < n; ++j) acc = fmaf(sc[j], v[(key_row(j) * Hkv + g) * d + e], acc);
+    out[((size_t)i * H + h) * d + e] = acc / sum;
+  }
+}
+
+// 128 rows per workgroup: as many heads of one KV head as divide its group (4, 2 or 1) x the matching number of queries
+int heads_per_wg(int H, int Hkv) {
+  const int G = H / Hkv;
+  return G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1;
+}
+
+template <bool PREFILL>
+hipError_t launch_causal(CausalParams& p, hipStream_t st) {
+  auto kernel = causal_attn_bf16_kernel<PREFILL>;
+  static DeviceOnce configured;                  // the attribute belongs to the loaded code object of a device
+  hipError_t ce = configured.run([&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES); });
+  if (ce != hipSuccess) return ce;
+  p.hg = heads_per_wg(p.H, p.Hkv);
+  p.n_groups = p.H / p.hg;
+  p.n_qblocks = (p.T + ROWS_WG / p.hg - 1) / (ROWS_WG / p.hg);
+  p.scale_log2 = 1.4426950408889634f / sqrtf((float)D);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)p.n_groups * p.n_qblocks), dim3(512), LDS_BYTES, st, p);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_ttt_attention(bool bf16, const void* q, const void* k, const void* v, int T, int H, int Hkv, int d, int s,
+                                float* out, hipStream_t st) {
+  if (T < 1 || H < 1 || Hkv < 1 || H % Hkv || s < 0) return hipErrorInvalidValue;
+  if (!bf16) {
+    const size_t lds = (size_t)(T + s) * sizeof(float);
+    if (lds > 60 * 1024 || d > 1024) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(ttt_attn_f32_kernel, dim3(T, H), dim3(256), lds, st, (const float*)q, (const float*)k, (const float*)v,
+                       T, H, Hkv, d, s, 1.0f / sqrtf((float)d), out);
+    return hipGetLastError();
+  }
+  if (d != D) return hipErrorInvalidValue;
+  CausalParams p;
+  p.q = (const bf16_t*)q; p.k = (const bf16_t*)k; p.v = (const bf16_t*)v;
+  p.seq = nullptr;
+  p.T = T; p.H = H; p.Hkv = Hkv; p.s = s;
+  p.out = out;
+  return launch_causal<false>(p, st);
+}
+
+hipError_t launch_prefill_attention(const void* q, const void* kcache, const void* vcache, const SeqInfo* seq, int n, int H, int Hkv,
+                                    int d, void* out, hipStream_t st) {
+  if (n < 1 || H < 1 || Hkv < 1 || H % Hkv || d != D) return hipErrorInvalidValue;
+  CausalParams p;
+  p.q = (const bf16_t*)q; p.k = (const bf16_t*)kcache; p.v = (const bf16_t*)vcache;
+  p.seq = seq;
+  p.T = n; p.H = H; p.Hkv = Hkv; p.s = 0;
+  p.out = out;
+  return launch_causal<true>(p, st);
+}

@@ -156,7 +156,13 @@ hipError_t launch_commit(void* const* k_layers, void* const* v_layers, int n_lay
                          float* taps_new, int32_t* tok_new, int32_t* n_new, int32_t* draft_prefix_len, int draft_rows,
                          hipStream_t st);
 
-// ---------------------------------------------------------------- training-time-test attention (ttt_attention.hip)
+// ---------------------------------------------------------------- training-time-test attention (causal_attention.hip)
 // q [T,H,d], k / v [s+1,T,Hkv,d] (bf16 with d == 128, or fp32), out fp32 [T,H,d].
 hipError_t launch_ttt_attention(bool bf16, const void* q, const void* k, const void* v, int T, int H, int Hkv, int d, int s,
                                 float* out, hipStream_t st);
+// Causal attention of a prefill chunk (bf16, d == 128): rows 0..n-1 at positions seq[0].n_prefix + row of one sequence, whose
+// cache rows, the chunk's own included, are written.  q [n, H, d] bf16, out fragment-major bf16 [n, H * d].
+hipError_t launch_prefill_attention(const void* q, const void* kcache, const void* vcache, const SeqInfo* seq, int n, int H, int Hkv,
+                                    int d, void* out, hipStream_t st);
+// Whether that kernel, which does not split the keys, is the better one for n rows that see up to max_len keys.
+bool prefill_attention_fits(int n, int H, int Hkv, int max_len);
