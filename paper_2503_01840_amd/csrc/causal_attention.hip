@@ -553,6 +553,19 @@ hipError_t launch_ttt_attention(bool bf16, const void* q, const void* k, const v
   return launch_causal<false>(p, st);
 }
 
+// This kernel against the tree kernel, which cuts the keys into splits and merges them (us, 32 heads over 8 unless stated):
+//   enough workgroups for most CUs: 192 (768 rows) 22 against 38 with no context, 382 against 448 behind 16 k positions;
+//     512 (2048 rows) 70 against 112, 813 against 981; 128 (512 rows) 373 against 253 behind 16 k positions;
+//   walks so short that the merge costs more than the idle CUs: 1 tile 7.3 against 9.8-11.9, 4 tiles (512 rows) 16 against
+//     25, and with 8 heads over 2 (32 workgroups) 14.6 against 15.2; 8 tiles there (64 workgroups) 24.7 against 23.5;
+//   between the two the line runs near 10 workgroups per tile of walk: 64 and 6 tiles 20.3 against 21.5, 128 and 12 tiles 37
+//     against 42, but 64 and 10 tiles 30 against 26, 128 and 20 tiles 59 against 55.
+bool prefill_attention_fits(int n, int H, int Hkv, int max_len) {
+  const int hg = heads_per_wg(H, Hkv), qb = ROWS_WG / hg;
+  const int wgs = H / hg * ((n + qb - 1) / qb), tiles = (max_len + KT - 1) / KT;
+  return wgs >= 192 || tiles <= 4 || wgs >= 10 * tiles;
+}
+
 hipError_t launch_prefill_attention(const void* q, const void* kcache, const void* vcache, const SeqInfo* seq, int n, int H, int Hkv,
                                     int d, void* out, hipStream_t st) {
   if (n < 1 || H < 1 || Hkv < 1 || H % Hkv || d != D) return hipErrorInvalidValue;

@@ -357,19 +357,24 @@ static int fuse_rows(eagle3_ctx* ctx, const float* low, const float* mid, const 
 // On entry: qkv partial sums are in `part` (S_qkv of them), x holds the residual rows.
 // On exit: `part` holds S_down partial sums of the MLP output (to be added to x by the caller).
 // R rows exist, B * rows_per_seq of them (and up to 63 more in a prefill chunk's last block) go through attention.
-static int layer_tail(eagle3_ctx* ctx, const eagle3_layer_weights& w, int B, int rows_per_seq, int R, int S_qkv,
+// prefill: the rows are R consecutive positions of one sequence.
+static int layer_tail(eagle3_ctx* ctx, const eagle3_layer_weights& w, int B, int rows_per_seq, int R, bool prefill, int S_qkv,
                       const int32_t* slot, const float* cs, const uint32_t* mask, const SeqInfo* seq, void* kc, void* vc,
                       int max_len, int* S_down, hipStream_t st) {
   const eagle3_config& c = ctx->cfg;
   const int k = c.hidden, H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim, I = c.intermediate;
   CK(launch_rope_kv_write(ctx->bf16, ctx->part, S_qkv, R, H, Hkv, d, cs, slot, ctx->q, kc, vc, st));
-  int ns = 1;
-  if (ctx->bf16) {
-    ns = attention_pick_splits(B, rows_per_seq, H, Hkv, max_len);
-    while (ns > 1 && attention_scratch_floats(B * rows_per_seq, H, d, ns) > ctx->attn_floats) --ns;
+  if (prefill && ctx->bf16 && prefill_attention_fits(R, H, Hkv, max_len)) {
+    CK(launch_prefill_attention(ctx->q, kc, vc, seq, R, H, Hkv, d, ctx->act_attn, st));
+  } else {
+    int ns = 1;
+    if (ctx->bf16) {
+      ns = attention_pick_splits(B, rows_per_seq, H, Hkv, max_len);
+      while (ns > 1 && attention_scratch_floats(B * rows_per_seq, H, d, ns) > ctx->attn_floats) --ns;
+    }
+    CK(launch_tree_attention(ctx->bf16, ctx->q, kc, vc, seq, mask, B, rows_per_seq, H, Hkv, d, max_len, ns,
+                             ctx->attn_scratch, ctx->act_attn, st));
   }
-  CK(launch_tree_attention(ctx->bf16, ctx->q, kc, vc, seq, mask, B, rows_per_seq, H, Hkv, d, max_len, ns,
-                           ctx->attn_scratch, ctx->act_attn, st));
   int S_o = 1;
   GemmWeights Wo = {{w.wo, nullptr, nullptr}, {k, 0, 0}, 1, 0};
   TRY(ctx->project(ctx->act_attn, Wo, R, k, H * d, GEMM_EPI_PARTIAL, &S_o, st));
@@ -384,7 +389,7 @@ static int layer_tail(eagle3_ctx* ctx, const eagle3_layer_weights& w, int B, int
 // Layers [l0, l1) of the target stack over R rows, whose residual stream is in ctx->x and whose slots, masks and rotary
 // tables are prepared; attention sees them as B sequences of N rows.  logits != nullptr: finish with the final norm and the
 // LM head (requires l1 == n_layers).  x_out (optional) receives the residual stream after layer l1 - 1.
-static int run_layers(eagle3_ctx* ctx, int B, int N, int R, const eagle3_kv* kv, int max_len, int l0, int l1, float* x_out,
+static int run_layers(eagle3_ctx* ctx, int B, int N, int R, bool prefill, const eagle3_kv* kv, int max_len, int l0, int l1, float* x_out,
                       float* logits, float* taps, float* dbg_hidden, hipStream_t st) {
   const eagle3_config& c = ctx->cfg;
   const int k = c.hidden, H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim;
@@ -410,7 +415,7 @@ static int run_layers(eagle3_ctx* ctx, int B, int N, int R, const eagle3_kv* kv,
     GemmWeights Wqkv = {{w.wq, w.wk, w.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
     int S_qkv = 1;
     TRY(ctx->project(ctx->act_k, Wqkv, R, (H + 2 * Hkv) * d, k, GEMM_EPI_PARTIAL, &S_qkv, st));
-    TRY(layer_tail(ctx, w, B, N, R, S_qkv, ctx->slot, ctx->cs, ctx->mask, ctx->seq, kv->k[l], kv->v[l], max_len, &S_prev, st));
+    TRY(layer_tail(ctx, w, B, N, R, prefill, S_qkv, ctx->slot, ctx->cs, ctx->mask, ctx->seq, kv->k[l], kv->v[l], max_len, &S_prev, st));
   }
   if (l1 == c.n_layers && logits) {
     GemmWeights Wlm = {{ctx->tw.lm_head, nullptr, nullptr}, {c.vocab, 0, 0}, 1, 0};
@@ -431,7 +436,7 @@ static int verify_layers(eagle3_ctx* ctx, int B, int N, const int32_t* tree_tok,
     CK(hipMemcpyAsync(ctx->x, x_in, (size_t)R * c.hidden * sizeof(float), hipMemcpyDeviceToDevice, st));
   else
     CK(launch_embed_rows(ctx->bf16, ctx->tw.embed, tree_tok, R, c.hidden, c.vocab, ctx->x, st));
-  return run_layers(ctx, B, N, R, kv, kv->max_prefix_len + N, l0, l1, x_out, logits, taps, dbg_hidden, st);
+  return run_layers(ctx, B, N, R, false, kv, kv->max_prefix_len + N, l0, l1, x_out, logits, taps, dbg_hidden, st);
 }
 
 static int check_verify_args(eagle3_ctx* ctx, int B, int N, const int32_t* tree_tok, const int32_t* parent,
@@ -508,7 +513,7 @@ int eagle3_draft_expand(eagle3_ctx* ctx, const float* g_new, const int32_t* tok_
     GemmWeights Wqkv = {{w.wq, w.wk, w.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
     int S_qkv = 1, S_down = 1;
     TRY(ctx->project(ctx->act_k, Wqkv, M, (H + 2 * Hkv) * d, 2 * k, GEMM_EPI_PARTIAL, &S_qkv, st));
-    TRY(layer_tail(ctx, w, 1, M, M, S_qkv, slot, ctx->cs, mask, seq, kc, vc, max_len, &S_down, st));
+    TRY(layer_tail(ctx, w, 1, M, M, false, S_qkv, slot, ctx->cs, mask, seq, kc, vc, max_len, &S_down, st));
     // a = y1 + MLP(...): keep it for the children, and norm it for the LM head
     float* copies[4] = {ctx->a_buf + (size_t)a_row0 * k, nullptr, nullptr, nullptr};
     CK(launch_add_norm(ctx->bf16, ctx->x, ctx->part, S_down, M, k, ctx->dw.final_norm, c.rms_eps, ctx->act_k, copies, st));
@@ -578,7 +583,7 @@ int eagle3_draft_chain(eagle3_ctx* ctx, int32_t B, const float* g_new, const int
     GemmWeights Wqkv = {{w.wq, w.wk, w.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
     int S_qkv = 1, S_down = 1;
     TRY(ctx->project(ctx->act_k, Wqkv, M, (H + 2 * Hkv) * d, 2 * k, GEMM_EPI_PARTIAL, &S_qkv, st));
-    TRY(layer_tail(ctx, w, B, rps, M, S_qkv, slot, ctx->cs, mask, seq, kc, vc, max_len, &S_down, st));
+    TRY(layer_tail(ctx, w, B, rps, M, false, S_qkv, slot, ctx->cs, mask, seq, kc, vc, max_len, &S_down, st));
     if (level == 1 && rows1 > 1) {
       // a = y1 + MLP(...) for every row, then the row of each sequence's last real position moves to row b
       CK(launch_add_norm(ctx->bf16, ctx->x, ctx->part, S_down, M, k, nullptr, c.rms_eps, nullptr, nullptr, st));
@@ -621,7 +626,7 @@ int eagle3_prefill(eagle3_ctx* ctx, const int32_t* tokens, int32_t T, const eagl
     const size_t nk = (size_t)n * k;
     CK(launch_prefill_prep(kv->kv_indptr, kv->prefix_len, n, d, c.rope_theta, ctx->pos1, ctx->slot, ctx->mask, ctx->cs, ctx->seq, st));
     CK(launch_embed_rows(ctx->bf16, ctx->tw.embed, tokens + c0, n, k, c.vocab, ctx->x, st));
-    TRY(run_layers(ctx, blocks, blocks == 1 ? n : 64, n, kv, kv->max_prefix_len + c0 + n, 0, c.n_layers, nullptr, nullptr,
+    TRY(run_layers(ctx, blocks, blocks == 1 ? n : 64, n, true, kv, kv->max_prefix_len + c0 + n, 0, c.n_layers, nullptr, nullptr,
                    ctx->chunk_taps, nullptr, st));
     CK(launch_advance_lengths((int32_t*)kv->prefix_len, 1, n, st));
     if (last) {                                       // next-token logits of the last position only

@@ -25,3 +25,36 @@ def test_ttt_attention_at_tile_edges(T, H, Hkv, s, spread):
     # |values| < 5.  A score is a sum of 128 products whose absolute values add up to ~ 82 spread: fp32 leaves it ~ 1e-5 spread
     # off before the 1 / sqrt(128), the weights are carried with 16 bits: 5 * (2e-6 spread + 2^-16) at the very most, doubled
     assert np.max(np.abs(got - ref)) < 2 * 5 * (2e-6 * spread + 2.0 ** -16), (T, H, Hkv, s)
+
+
+# a prompt in two calls: P rows first, then n rows behind them, against the same prompt in one call.  n rows with P behind them
+# take the causal kernel (few tiles of keys) or the split one (long context, few rows)
+@pytest.mark.parametrize("P,n", [(1, 63), (64, 64), (77, 130), (127, 1), (200, 312), (700, 20), (1000, 500)])
+def test_prefill_continues_a_cached_prefix(P, n):
+    import pipeline as PL
+    from test_gpu_edges import SMALL, _E
+    E = _E()
+    shape = SMALL
+    ctx = E.Eagle3Context(shape, max_batch=1, max_nodes=8, max_depth=2, max_topk=2, max_new=4, device=DEV)
+    W = PL.device_weights(shape, device=DEV)
+    ctx.set_weights(W["target"], W["draft"])
+    T = P + n
+    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device=DEV)
+    tokens = S.uniform_ints(S.SEED + T, S.TensorIds.PREFIX_TOK, (T,), 0, shape.vocab).to(torch.int32).to(DEV)
+
+    def prefill(parts):
+        z = lambda: torch.zeros(T, shape.n_kv_heads, shape.head_dim, dtype=ctx.storage_dtype, device=DEV)
+        ks, vs = [z() for _ in range(shape.n_layers)], [z() for _ in range(shape.n_layers)]
+        kv = E.KVCache(ks, vs, i32([0, T]), i32([0]), 0)
+        dkv = E.KVCache([z()], [z()], i32([0, T]), i32([0]), 0)
+        at = 0
+        for m in parts:
+            g, logits = E.eagle3_prefill(ctx, tokens[at:at + m].contiguous(), kv, dkv)
+            at += m
+        torch.cuda.synchronize()
+        return torch.stack(ks + vs).float(), logits.float(), g.float()
+
+    for a, b in zip(prefill([T]), prefill([P, n])):
+        assert bool(torch.isfinite(b).all())
+        # same sums in another order, rounded to bf16 between the two layers: the two-layer bounds of the prefill tests
+        assert float((a - b).abs().max()) < 4e-2, (P, n)
