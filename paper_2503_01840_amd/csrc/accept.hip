@@ -1,13 +1,14 @@
 // Acceptance walk over the verified tree.
 //
-// Pass 1 (whole chip): per (row, chunk of ACCEPT_CHUNK vocabulary entries) the maximum, its first index and
-// the sum of exp(z - chunk max) of z = logits / T.  Pass 2: ONE wavefront per sequence walks from the root:
+// Pass 1 (whole chip): per (row, chunk of ACCEPT_CHUNK vocabulary entries) the maximum, its first index and (sampled
+// walk) the sum of exp(z - chunk max) of z = logits / T.  Pass 2: ONE wavefront per sequence walks from the root:
 //   greedy     follow the child whose token is the row argmax (ties -> smaller id), else stop with it;
 //   stochastic test the children in ascending node id against the running residual distribution, and on
 //              failure draw the bonus token by inverse CDF of the residual in vocabulary order.
 // The walk touches only the statistics of the visited rows plus, for the bonus draw, one chunk of logits.
 #include <limits.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "../../include/eagle3.h"
@@ -18,61 +19,86 @@ namespace {
 
 constexpr int CH = ACCEPT_CHUNK;
 
-// One workgroup per (row, chunk of 2048 logits): the chunk is read once (two 16-byte loads per thread), every
-// wavefront reduces its 512 entries to (max, first arg-max, sum of exp relative to that max) with shuffles, and the
-// four results are combined after a single barrier.
-__global__ __launch_bounds__(256) void accept_stats_kernel(const float* __restrict__ logits, int V, int n_chunks,
+// One wavefront per (row, chunk of 2048 logits): the chunk is read once (eight 16-byte loads per lane, all requested first)
+// as four pieces of 512 entries; each piece gives (max, first arg-max, sum of exp relative to that max), the four are
+// combined in order.  Bound: the stream of logits; what has to be kept out of its way is vector work, so the arg-max
+// is not carried through the reduction but found afterwards from the lanes that hold the max (compares and scalar bit
+// operations), and the greedy walk, which never looks at them, forms no sums.
+// 512 rows of 128256 logits (263 MB): 50.6 us as one workgroup per chunk with (value, index) reductions.
+template <bool SUMS>
+__global__ __launch_bounds__(256) void accept_stats_kernel(const float* __restrict__ logits, int V, int n_chunks, bool vec4,
                                                           float inv_t, float* __restrict__ stats) {
-  __shared__ float redv[4], reds[4];
-  __shared__ int redi[4];
-  const int c = blockIdx.x, r = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = blockIdx.x * 4 + (threadIdx.x >> 6), r = blockIdx.y, lane = threadIdx.x & 63;
+  if (c >= n_chunks) return;
   const float* z = logits + (size_t)r * V;
-  const int lo = c * CH + wave * 512;
-  float x[8];
-  int idx[8];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int v0 = lo + h * 256 + 4 * lane;
-    if (v0 + 3 < V && (V & 3) == 0) {
-      const float4 q = *(const float4*)(z + v0);
-      x[4 * h] = q.x; x[4 * h + 1] = q.y; x[4 * h + 2] = q.z; x[4 * h + 3] = q.w;
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) x[4 * h + j] = v0 + j < V ? z[v0 + j] : -INFINITY;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { x[4 * h + j] *= inv_t; idx[4 * h + j] = v0 + j; }
-  }
-  float mx = -INFINITY;
-  int am = INT_MAX;
-#pragma unroll
-  for (int j = 0; j < 8; ++j)
-    if (x[j] > mx) { mx = x[j]; am = idx[j]; }   // ascending index per thread: first maximum kept
-  wave_best_pair(mx, am);
-  float sum = 0.f;
-  if (mx > -INFINITY) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) sum += expf(x[j] - mx);   // exp(-inf) = 0 for the padding
-  }
-  sum = wave_sum_butterfly(sum);
-  if (lane == 0) { redv[wave] = mx; redi[wave] = am; reds[wave] = sum; }
-  __syncthreads();
-  if (tid == 0) {
-    float M = redv[0];
-    int A = redi[0];
-#pragma unroll
-    for (int w = 1; w < 4; ++w)
-      if (redv[w] > M || (redv[w] == M && redi[w] < A)) { M = redv[w]; A = redi[w]; }
-    float S = 0.f;
+  const int lo = c * CH;
+  float x[4][8];
+  if (vec4 && lo + CH <= V) {
 #pragma unroll
     for (int w = 0; w < 4; ++w)
-      if (redv[w] > -INFINITY) S += reds[w] * expf(redv[w] - M);
-    float* o = stats + ((size_t)r * n_chunks + c) * 4;
-    o[0] = M;
-    o[1] = __int_as_float(A);
-    o[2] = S;
-    o[3] = 0.f;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float4 q = *(const float4*)(z + lo + w * 512 + h * 256 + 4 * lane);
+        x[w][4 * h] = q.x; x[w][4 * h + 1] = q.y; x[w][4 * h + 2] = q.z; x[w][4 * h + 3] = q.w;
+      }
+  } else {
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int v = lo + w * 512 + (j >> 2) * 256 + 4 * lane + (j & 3);
+        x[w][j] = v < V ? z[v] : -INFINITY;
+      }
   }
+  float pm[4], ps[4];
+  int pi[4];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    float mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      x[w][j] *= inv_t;
+      mx = fmaxf(mx, x[w][j]);
+    }
+    mx = wave_max(mx);
+    pm[w] = mx;
+    // first entry equal to the max: entries run over h, then lanes, then e = j & 3
+    int first = INT_MAX;
+#pragma unroll
+    for (int h = 1; h >= 0; --h) {
+      unsigned long long eq[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) eq[e] = __ballot(x[w][4 * h + e] == mx);
+      const unsigned long long any = eq[0] | eq[1] | eq[2] | eq[3];
+      if (any) {
+        const int l = __ffsll((long long)any) - 1;
+        const int e = (eq[0] >> l) & 1 ? 0 : (eq[1] >> l) & 1 ? 1 : (eq[2] >> l) & 1 ? 2 : 3;
+        first = lo + w * 512 + h * 256 + 4 * l + e;
+      }
+    }
+    pi[w] = mx > -INFINITY ? first : INT_MAX;
+    ps[w] = 0.f;
+    if constexpr (SUMS) {
+      float sum = 0.f;
+      if (mx > -INFINITY) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sum += expf(x[w][j] - mx);   // exp(-inf) = 0 for the padding
+      }
+      ps[w] = wave_sum_butterfly(sum);
+    }
+  }
+  float M = pm[0];
+  int A = pi[0];
+#pragma unroll
+  for (int w = 1; w < 4; ++w)
+    if (pm[w] > M || (pm[w] == M && pi[w] < A)) { M = pm[w]; A = pi[w]; }
+  float S = 0.f;
+  if constexpr (SUMS) {
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      if (pm[w] > -INFINITY) S += ps[w] * expf(pm[w] - M);
+  }
+  if (lane == 0) *(float4*)(stats + ((size_t)r * n_chunks + c) * 4) = make_float4(M, __int_as_float(A), S, 0.f);
 }
 
 __device__ __forceinline__ float wave_incl_scan(float v, int lane) {
@@ -84,20 +110,44 @@ __device__ __forceinline__ float wave_incl_scan(float v, int lane) {
   return v;
 }
 
-__global__ __launch_bounds__(64) void accept_walk_kernel(const float* __restrict__ logits,
+// One workgroup per sequence.  Its wavefronts first reduce the chunk statistics of all N rows side by side (one memory
+// round trip instead of one per step of the walk); then the first wavefront walks on values in LDS, and only the bonus draw
+// goes back to memory.  Sampled walk over 64 8-node trees: 17.4 us when each step fetched its row's statistics.
+__global__ __launch_bounds__(1024) void accept_walk_kernel(const float* __restrict__ logits,
                                                         const int32_t* __restrict__ tree_tok,
-                                                        const int32_t* __restrict__ parent, int N, int V, int n_chunks,
+                                                        const int32_t* __restrict__ parent, int N, int V, int n_chunks, bool vec4,
                                                         float inv_t, bool greedy, const float* __restrict__ uniforms,
                                                         const float* __restrict__ stats, int32_t* __restrict__ accept_len,
                                                         int32_t* __restrict__ path, int32_t* __restrict__ bonus_tok) {
-  __shared__ int struck[64];
-  const int b = blockIdx.x, lane = threadIdx.x;
+  __shared__ float row_max[64], row_tot[64];
+  __shared__ int row_arg[64];
+  const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+  for (int r = wave; r < N; r += n_waves) {
+    const float* st = stats + (size_t)(b * N + r) * n_chunks * 4;
+    float mx = -INFINITY;
+    int am = INT_MAX;
+    for (int c = lane; c < n_chunks; c += 64) {
+      const float2 s = *(const float2*)(st + c * 4);
+      const int i = __float_as_int(s.y);
+      if (s.x > mx || (s.x == mx && i < am)) { mx = s.x; am = i; }
+    }
+    wave_best_pair(mx, am);
+    float tot = 0.f;
+    if (!greedy) {
+      for (int c = lane; c < n_chunks; c += 64) tot += st[c * 4 + 2] * expf(st[c * 4] - mx);
+      tot = wave_sum_butterfly(tot);
+    }
+    if (lane == 0) { row_max[r] = mx; row_arg[r] = am; row_tot[r] = tot; }
+  }
+  __syncthreads();
+  if (wave > 0) return;
   const int my_par = lane < N ? parent[b * N + lane] : INT_MIN;
   const int my_tok = lane < N ? tree_tok[b * N + lane] : -1;
   if (lane < N) path[b * N + lane] = lane == 0 ? 0 : -1;
   // what the child tests of the stochastic walk read, fetched for every node at once: the target's logit of the node's
   // own token at its parent's row, and the node's uniform (one memory round trip instead of one per tested child)
-  float my_z = 0.f, my_u = 0.f;
+  float my_z = 0.f, my_u = 0.f, my_bonus_u = 0.f;
+  if (!greedy && lane < N) my_bonus_u = uniforms[(size_t)b * 2 * N + 2 * lane + 1];
   if (!greedy && lane > 0 && lane < N && my_par >= 0 && my_par < lane) {
     my_z = logits[((size_t)b * N + my_par) * V + min(max(my_tok, 0), V - 1)];
     my_u = uniforms[(size_t)b * 2 * N + 2 * lane];
@@ -106,14 +156,8 @@ __global__ __launch_bounds__(64) void accept_walk_kernel(const float* __restrict
   for (int step = 0; step < N; ++step) {
     const int row = b * N + cur;
     const float* st = stats + (size_t)row * n_chunks * 4;
-    float mx = -INFINITY;
-    int am = INT_MAX;
-    for (int c = lane; c < n_chunks; c += 64) {
-      const float v = st[c * 4];
-      const int i = __float_as_int(st[c * 4 + 1]);
-      if (v > mx || (v == mx && i < am)) { mx = v; am = i; }
-    }
-    wave_best_pair(mx, am);
+    const float mx = row_max[cur];
+    const int am = row_arg[cur];
     const unsigned long long kids = __ballot(lane < N && lane > cur && my_par == cur);
     if (greedy) {
       const unsigned long long hit = __ballot(lane < N && lane > cur && my_par == cur && my_tok == am);
@@ -127,28 +171,24 @@ __global__ __launch_bounds__(64) void accept_walk_kernel(const float* __restrict
       break;
     }
     // ---- stochastic
-    float tot = 0.f;
-    for (int c = lane; c < n_chunks; c += 64) tot += st[c * 4 + 2] * expf(st[c * 4] - mx);
-    tot = wave_sum_butterfly(tot);
+    const float tot = row_tot[cur];
     const float* z = logits + (size_t)row * V;
     float rej = 0.f;
-    int n_struck = 0, accepted = -1;
+    int n_struck = 0, accepted = -1, struck = -1;      // lane j < n_struck holds the j-th rejected token
     unsigned long long rest = kids;
     while (rest) {
       const int c = __ffsll((long long)rest) - 1;
       rest &= rest - 1;
       const int t = min(max(__shfl(my_tok, c, 64), 0), V - 1);
-      bool is_struck = false;
-      for (int j = 0; j < n_struck; ++j) is_struck |= struck[j] == t;
+      const bool is_struck = __any(lane < n_struck && struck == t);
       const float pt = expf(__shfl(my_z, c, 64) * inv_t - mx) / tot;
       const float thr = is_struck ? 0.f : pt / (1.f - rej);
       const float u = __shfl(my_u, c, 64);
       if (u < thr) { accepted = c; break; }
       if (!is_struck) {
         rej += pt;
-        if (lane == 0) struck[n_struck] = t;
+        if (lane == n_struck) struck = t;
         ++n_struck;
-        __syncthreads();
       }
     }
     if (accepted >= 0) {
@@ -158,19 +198,18 @@ __global__ __launch_bounds__(64) void accept_walk_kernel(const float* __restrict
       continue;
     }
     // bonus token: first v (vocabulary order) whose residual CDF reaches u * (1 - rej), in un-normalised units
-    const float target = uniforms[(size_t)b * 2 * N + 2 * cur + 1] * (1.f - rej) * tot;
+    const float target = __shfl(my_bonus_u, cur, 64) * (1.f - rej) * tot;
     float carry = 0.f;
     int chunk = -1, last_pos_chunk = -1;
     float before = 0.f;
     for (int c0 = 0; c0 < n_chunks && chunk < 0; c0 += 64) {
       const int c = c0 + lane;
-      float sc = 0.f;
-      if (c < n_chunks) {
-        sc = st[c * 4 + 2] * expf(st[c * 4] - mx);
-        for (int j = 0; j < n_struck; ++j)
-          if (struck[j] / CH == c) sc -= expf(z[struck[j]] * inv_t - mx);
-        sc = fmaxf(sc, 0.f);
+      float sc = c < n_chunks ? st[c * 4 + 2] * expf(st[c * 4] - mx) : 0.f;
+      for (int j = 0; j < n_struck; ++j) {
+        const int t = __shfl(struck, j, 64);
+        if (t / CH == c) sc -= expf(z[t] * inv_t - mx);
       }
+      sc = fmaxf(sc, 0.f);
       const float incl = wave_incl_scan(sc, lane) + carry;
       const unsigned long long pos = __ballot(sc > 0.f);
       const unsigned long long cross = __ballot(sc > 0.f && incl >= target);
@@ -187,19 +226,27 @@ __global__ __launch_bounds__(64) void accept_walk_kernel(const float* __restrict
     // inside the chunk: 32 consecutive entries per lane
     const int v0 = chunk * CH + lane * (CH / 64);
     float e[CH / 64];
+    if (vec4 && (chunk + 1) * CH <= V) {
+#pragma unroll
+      for (int i = 0; i < CH / 64; i += 4) {
+        const float4 q = *(const float4*)(z + v0 + i);
+        e[i] = q.x; e[i + 1] = q.y; e[i + 2] = q.z; e[i + 3] = q.w;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < CH / 64; ++i) e[i] = v0 + i < V ? z[v0 + i] : -INFINITY;
+    }
     float ltot = 0.f;
 #pragma unroll
-    for (int i = 0; i < CH / 64; ++i) {
-      const int v = v0 + i;
-      float x = 0.f;
-      if (v < V) {
-        x = expf(z[v] * inv_t - mx);
-        for (int j = 0; j < n_struck; ++j)
-          if (struck[j] == v) x = 0.f;
-      }
-      e[i] = x;
-      ltot += x;
+    for (int i = 0; i < CH / 64; ++i) e[i] = v0 + i < V ? expf(e[i] * inv_t - mx) : 0.f;
+    for (int j = 0; j < n_struck; ++j) {
+      const int t = __shfl(struck, j, 64) - v0;
+#pragma unroll
+      for (int i = 0; i < CH / 64; ++i)
+        if (t == i) e[i] = 0.f;
     }
+#pragma unroll
+    for (int i = 0; i < CH / 64; ++i) ltot += e[i];
     const float lincl = wave_incl_scan(ltot, lane) + before;
     const unsigned long long lpos = __ballot(ltot > 0.f);
     unsigned long long lcross = take_last ? 0ull : __ballot(ltot > 0.f && lincl >= target);
@@ -240,10 +287,13 @@ hipError_t launch_accept(const float* logits, const int32_t* tree_tok, const int
   const int n_chunks = (V + CH - 1) / CH;
   const bool greedy = temperature <= 0.f;
   const float inv_t = greedy ? 1.f : 1.f / temperature;
-  hipLaunchKernelGGL(accept_stats_kernel, dim3(n_chunks, B * N), dim3(256), 0, st, logits, V, n_chunks, inv_t, scratch);
+  const bool vec4 = V % 4 == 0 && ((uintptr_t)logits & 15) == 0;       // whole 16-byte loads in every row
+  const dim3 grid((n_chunks + 3) / 4, B * N);
+  if (greedy) hipLaunchKernelGGL(accept_stats_kernel<false>, grid, dim3(256), 0, st, logits, V, n_chunks, vec4, inv_t, scratch);
+  else hipLaunchKernelGGL(accept_stats_kernel<true>, grid, dim3(256), 0, st, logits, V, n_chunks, vec4, inv_t, scratch);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(accept_walk_kernel, dim3(B), dim3(64), 0, st, logits, tree_tok, parent, N, V, n_chunks, inv_t, greedy,
+  hipLaunchKernelGGL(accept_walk_kernel, dim3(B), dim3(64 * std::min(N, 16)), 0, st, logits, tree_tok, parent, N, V, n_chunks, vec4, inv_t, greedy,
                      uniforms, scratch, accept_len, path, bonus);
   return hipGetLastError();
 }
