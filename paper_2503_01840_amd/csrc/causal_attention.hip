@@ -479,22 +479,23 @@ __global__ __launch_bounds__(512) void causal_attn_bf16_kernel(CausalParams p) {
   }
 }
 
-// fp32: one workgroup per (query, head); scores of the i + 1 + s visible keys in LDS
+// fp32: one workgroup per (query, head); scores of the i + 1 + s visible keys in LDS, the keys of the value sum dealt out to
+// 256 / d groups of threads
 __global__ __launch_bounds__(256) void ttt_attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
                                                           const float* __restrict__ v, int T, int H, int Hkv, int d, int s,
                                                           float scale, float* __restrict__ out) {
   extern __shared__ float sc[];
-  __shared__ float red[17];
+  __shared__ float red[17], qs[256], part[256];    // with 60 KB of scores still below the 64 KB of an ordinary launch
   const int i = blockIdx.x, h = blockIdx.y, g = h * Hkv / H, tid = threadIdx.x;
   const int n = i + 1 + s;
   const float* qr = q + ((size_t)i * H + h) * d;
+  if (tid < d) qs[tid] = qr[tid];
+  __syncthreads();
   auto key_row = [&](int j) { return j <= i ? (size_t)j : (size_t)(j - i) * T + i; };      // row of the [s+1, T] arrays
   float mx = -INFINITY;
   for (int j = tid; j < n; j += 256) {
     const float* kr = k + (key_row(j) * Hkv + g) * d;
-    float acc = 0.f;
-    for (int e = 0; e < d; ++e) acc = fmaf(qr[e], kr[e], acc);
-    sc[j] = acc * scale;
+    sc[j] = (d <= 256 ? dot_f32(qs, kr, d) : dot_f32(qr, kr, d)) * scale;
     mx = fmaxf(mx, sc[j]);
   }
   mx = block_max(mx, red);
@@ -504,11 +505,28 @@ __global__ __launch_bounds__(256) void ttt_attn_f32_kernel(const float* __restri
     sc[j] = e;
     sum += e;
   }
-  sum = block_sum(sum, red);
-  for (int e = tid; e < d; e += 256) {
-    float acc = 0.f;
-    for (int j = 0; j < n; ++j) acc = fmaf(sc[j], v[(key_row(j) * Hkv + g) * d + e], acc);
-    out[((size_t)i * H + h) * d + e] = acc / sum;
+  sum = block_sum(sum, red);                // also publishes sc
+  if (d > 128) {
+    for (int e = tid; e < d; e += 256) {
+      float acc = 0.f;
+#pragma unroll 8
+      for (int j = 0; j < n; ++j) acc = fmaf(sc[j], v[(key_row(j) * Hkv + g) * d + e], acc);
+      out[((size_t)i * H + h) * d + e] = acc / sum;
+    }
+    return;
+  }
+  const int groups = 256 / d, grp = tid / d, e = tid - grp * d;
+  float acc = 0.f;
+  if (grp < groups) {
+#pragma unroll 8
+    for (int j = grp; j < n; j += groups) acc = fmaf(sc[j], v[(key_row(j) * Hkv + g) * d + e], acc);
+  }
+  part[tid] = acc;
+  __syncthreads();
+  if (tid < d) {
+    acc = 0.f;
+    for (int j = 0; j < groups; ++j) acc += part[j * d + tid];
+    out[((size_t)i * H + h) * d + tid] = acc / sum;
   }
 }
 

@@ -137,6 +137,21 @@ __device__ __forceinline__ void wave_best_pair(float& v, int& i) {
   xlane_best_step<3>(v, i); xlane_best_step<4>(v, i); xlane_best_step<5>(v, i);
 }
 
+// Dot product of d entries of `a` and of row `b`, in order; 16-byte loads where b allows them.
+__device__ __forceinline__ float dot_f32(const float* a, const float* __restrict__ b, int d) {
+  float acc = 0.f;
+  if (d % 4 == 0 && ((uintptr_t)b & 15) == 0) {
+#pragma unroll 8
+    for (int i = 0; i < d; i += 4) {
+      const float4 v = *(const float4*)(b + i);
+      acc = fmaf(a[i + 3], v.w, fmaf(a[i + 2], v.z, fmaf(a[i + 1], v.y, fmaf(a[i], v.x, acc))));
+    }
+  } else {
+    for (int i = 0; i < d; ++i) acc = fmaf(a[i], b[i], acc);
+  }
+  return acc;
+}
+
 // Block-wide sum for blockDim.x a multiple of 64, <= 1024.  `red` is a __shared__ float[17].
 __device__ __forceinline__ float block_sum(float v, float* red) {
   v = wave_sum(v);

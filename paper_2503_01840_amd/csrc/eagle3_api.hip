@@ -157,14 +157,9 @@ struct eagle3_ctx {
       if (S_out) *S_out = S;
       return EAGLE3_OK;
     }
-    if ((size_t)M * N > part_floats && !direct_out) return EAGLE3_E_STATE;
-    float* out = direct_out ? direct_out : part;
-    int col = 0;
-    for (int i = 0; i < W.nmat; ++i) {
-      CK(launch_gemm_f32((const float*)act_in, (const float*)W.w[i], M, W.rows[i], K, out, N, col, st));
-      col += W.rows[i];
-    }
-    if (epi == GEMM_EPI_SWIGLU) CK(launch_swiglu_f32(part, M, N / 2, (float*)act_h, st));
+    if (epi == GEMM_EPI_PARTIAL && (size_t)M * N > part_floats && !direct_out) return EAGLE3_E_STATE;
+    float* out = epi == GEMM_EPI_SWIGLU ? (float*)act_h : direct_out ? direct_out : part;
+    CK(launch_gemm_f32((const float*)act_in, W, M, N, K, epi, out, st));
     if (S_out) *S_out = 1;
     return EAGLE3_OK;
   }

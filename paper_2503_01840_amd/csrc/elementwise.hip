@@ -1,5 +1,5 @@
 // Row-wise kernels between the GEMMs: embedding gather, residual add + RMSNorm, rotary embedding and
-// cache write, tree bookkeeping, SwiGLU (fp32 path), feature packing.  All are tiny next to the weight
+// cache write, tree bookkeeping, feature packing.  All are tiny next to the weight
 // streams; they exist to hand the next GEMM its operand in the layout it reads.
 #include <algorithm>
 
@@ -184,14 +184,6 @@ __global__ __launch_bounds__(1024) void rope_kv_write_kernel(const float* __rest
   }
 }
 
-__global__ __launch_bounds__(256) void swiglu_f32_kernel(const float* __restrict__ gu, int I, float* __restrict__ h) {
-  const int r = blockIdx.x;
-  for (int c = threadIdx.x; c < I; c += 256) {
-    const float g = gu[(size_t)r * 2 * I + c], u = gu[(size_t)r * 2 * I + I + c];
-    h[(size_t)r * I + c] = g / (1.f + expf(-g)) * u;
-  }
-}
-
 template <bool BF16>
 __global__ __launch_bounds__(256) void pack3_kernel(const float* __restrict__ a, const float* __restrict__ b,
                                                    const float* __restrict__ c, int k,
@@ -370,11 +362,6 @@ hipError_t launch_rope_kv_write(bool bf16, const float* qkv_partial, int S, int 
   else
     hipLaunchKernelGGL(rope_kv_write_kernel<false>, dim3(R), dim3(bd), 0, st, qkv_partial, S, R, H, Hkv, d, cs, slot,
                        (float*)q, (float*)kcache, (float*)vcache);
-  return hipGetLastError();
-}
-
-hipError_t launch_swiglu_f32(const float* gu, int R, int I, float* h, hipStream_t st) {
-  hipLaunchKernelGGL(swiglu_f32_kernel, dim3(R), dim3(256), 0, st, gu, I, h);
   return hipGetLastError();
 }
 

@@ -36,9 +36,8 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
                             size_t out_capacity_floats, int* S_out, hipStream_t st, hipEvent_t ev_start = nullptr,
                             hipEvent_t ev_stop = nullptr);
 
-// fp32 reference-quality GEMM: out[m, col0 + n] = sum_k x[m,k] w[n,k]; x [M,K], w [N,K], out row stride ld.
-hipError_t launch_gemm_f32(const float* x, const float* w, int M, int N, int K, float* out, int ld, int col0,
-                           hipStream_t st);
+// fp32 GEMM, exact arithmetic: x [M, K], weights [N, K] stacked.  epi PARTIAL: out [M, N]; SWIGLU (mode 1): out [M, N / 2].
+hipError_t launch_gemm_f32(const float* x, const GemmWeights& W, int M, int N, int K, int epi, float* out, hipStream_t st);
 
 // ---------------------------------------------------------------- elementwise (elementwise.hip)
 struct SeqInfo {           // one per sequence, device resident
@@ -60,7 +59,6 @@ hipError_t launch_tree_prep(const int32_t* parent, const int32_t* kv_indptr, con
 // Sums the q|k|v split-K partials, rotates q and k, writes q (activation type, [R,H,d]) and the cache rows.
 hipError_t launch_rope_kv_write(bool bf16, const float* qkv_partial, int S, int R, int H, int Hkv, int d, const float* cs,
                                 const int32_t* slot, void* q, void* kcache, void* vcache, hipStream_t st);
-hipError_t launch_swiglu_f32(const float* gu, int R, int I, float* h, hipStream_t st);
 hipError_t launch_pack3(bool bf16, const float* a, const float* b, const float* c, int M, int k, void* act, hipStream_t st);
 hipError_t launch_reduce_partials(const float* partial, int S, int M, int N, float* out, hipStream_t st);
 // Draft layer input: act[r] = [RMSNorm(E[tok[r]]; g_embed) ; RMSNorm(f_r; g_feat)], y[r] = f_r,
