@@ -73,9 +73,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   constexpr int A_SLOT = TM * (BK / 2) * 2, B_SLOT = TN * BK * 2;   // bytes
   constexpr int B_BASE = A_SLOTS * A_SLOT;
   // direct-to-LDS instructions (1 KiB each) per wavefront per activation / weight slot; a weight slot goes out in two halves
-  constexpr int A_DMA = A_SLOT / (1024 * NW), B_DMA = B_SLOT / (1024 * NW), BH = B_DMA / 2;
-  static_assert(A_DMA == 2 && (B_DMA == 2 || B_DMA == 4) && A_SLOT == A_DMA * 1024 * NW && B_SLOT == B_DMA * 1024 * NW,
-                "1 KiB pieces per wavefront");
+  // (192 rows over 8 wavefronts: 12 activation pieces; the last four wavefront-instructions repeat pieces, so that every
+  // wavefront has the same number of loads in flight)
+  constexpr int A_PIECES = A_SLOT / 1024, A_DMA = (A_PIECES + NW - 1) / NW, B_DMA = B_SLOT / (1024 * NW), BH = B_DMA / 2;
+  static_assert(A_DMA == 2 && (B_DMA == 2 || B_DMA == 4) && B_SLOT == B_DMA * 1024 * NW, "1 KiB pieces per wavefront");
   static_assert(TM % 64 == 0 && FN == 2, "whole 64-row activation tiles; one SwiGLU pair per wavefront");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
@@ -95,10 +96,13 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   // ---- this lane's global sources.  Piece q of an activation slot is (row tile q / 4, k-step (q / 2) % 2, row
   // half q % 2); piece q of a weight slot is rows 8 q .. 8 q + 7, eight lanes per row.
   const bf16_t* aptr[A_DMA];
+  int a_piece[A_DMA];                                  // where a repeated piece goes
   const bf16_t* bptr[B_DMA];
 #pragma unroll
   for (int i = 0; i < A_DMA; ++i) {
-    const int q = wave * A_DMA + i;
+    int q = wave * A_DMA + i;
+    if (A_PIECES < A_DMA * NW && q >= A_PIECES) q -= A_DMA * NW - A_PIECES;
+    if (A_PIECES < A_DMA * NW) a_piece[i] = q * 1024;
     const int rt = min(mblock * (TM / 64) + (q >> 2), MT - 1);
     aptr[i] = p.x + (((size_t)rt * (p.K >> 4) + (k_begin >> 4) + ((q >> 1) & 1)) * 2 + (q & 1)) * 512 + lane * 8;
   }
@@ -110,7 +114,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   // Loads past the end of the walk over K repeat the last (half-)stage into a slot nobody reads any more, which
   // keeps the number of loads in flight, and with it the waits below, the same in every iteration.
   auto issue_a = [&](int h, int i) {                   // piece i of half-stage h
-    dma16(aptr[i] + (size_t)min(h, 2 * KT - 1) * 2048, lds0 + (h % A_SLOTS) * A_SLOT + (wave * A_DMA + i) * 1024);
+    dma16(aptr[i] + (size_t)min(h, 2 * KT - 1) * 2048, lds0 + (h % A_SLOTS) * A_SLOT + (A_PIECES < A_DMA * NW ? a_piece[i] : (wave * A_DMA + i) * 1024));
   };
   auto issue_b = [&](int s, int i) {                   // piece i of weight stage s
     dma16(bptr[i] + (size_t)min(s, KT - 1) * BK, lds0 + B_BASE + (s % B_SLOTS) * B_SLOT + (wave * B_DMA + i) * 1024);
@@ -269,7 +273,8 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   // enough workgroups; 129..256 rows: ONE 256-row block x 128 weight rows per workgroup (8 wavefronts x 64 x 64), so that
   // every weight line enters exactly one CU and a stage takes in 48 KB instead of the 2 x 32 KB of two 128 x 128
   // workgroups (measured at 256 rows, 8B shapes: q/k/v 33.4 -> 26.6 us, down 54.3 -> 47.6, gate/up 86.0 -> 78.9);
-  // else 128 x 128 tiles, two workgroups per CU.
+  // else 128 x 128 tiles, two workgroups per CU (below 384 rows, and where few weight rows leave 256-row tiles short of
+  // workgroups).
   auto pick = [&](int TM, int TN, int want, int min_stages, int* S_pick) {
     const int wgs = ((N + TN - 1) / TN) * ((M + TM - 1) / TM);
     int S = 1;
@@ -290,8 +295,20 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
     cfg = 1;
     pick(128, 128, 384, 8, &S);
   }
+  // 192 instead of 256 rows per tile where that shortens the longest CU's share of the rows (rounds of 256 workgroups x rows
+  // per tile / K ranges) by more than the 10 % that the smaller tile costs, and for gate/up instead of the 128 x 128 tiles.
+  // Whole passes of the 8B shape, 6 layers, 256 (or 128) -> 192 rows: 300 rows 2.21 -> 2.02 ms, 520 rows 3.49 -> 3.02 (512
+  // rows fill one round of gate/up, 520 start a second), 700 rows 3.32 -> 2.96, 1100 rows 4.58 -> 4.12; where it is not taken:
+  // 2048 rows 6.52 against 6.79.
+  if (cfg == 0 || (cfg == 1 && epi == GEMM_EPI_SWIGLU && M > 256)) {
+    auto share = [&](int TM, int s) { return (((N + 255) / 256) * ((M + TM - 1) / TM) * s + 255) / 256 * TM / (double)s; };
+    int s192 = 1;
+    pick(192, 256, 160, 16, &s192);
+    if (cfg == 1 || 1.1 * share(192, s192) < share(256, S)) { cfg = 3; S = s192; }
+  }
   p.S = S;
   if (S_out) *S_out = S;
   if (cfg == 2) return launch_cfg<4, 2, 2, 2, 1>(p, S, st, ev_start, ev_stop);
+  if (cfg == 3) return launch_cfg<2, 4, 3, 2, 1>(p, S, st, ev_start, ev_stop);
   return cfg == 0 ? launch_cfg<2, 4, 4, 2, 1>(p, S, st, ev_start, ev_stop) : launch_cfg<2, 2, 2, 2, 2>(p, S, st, ev_start, ev_stop);
 }

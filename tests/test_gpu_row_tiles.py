@@ -1,0 +1,55 @@
+"""The many-row products at the edges of their 192-row tiles."""
+import numpy as np
+import pytest
+import torch
+
+import eagle3_synth as S
+from test_gpu_prefill import test_prefill_at_block_and_chunk_edges as _prefill_against_the_oracle
+from test_gpu_shapes import TOL, _E, _rms
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+# gate/up of the small model in 192-row tiles (257 rows and more): one row over a 64-row piece, over a tile, a full last tile
+@pytest.mark.parametrize("T", [257, 384, 386, 576, 577])
+def test_prefill_at_192_row_edges(T):
+    _prefill_against_the_oracle("bf16", T)
+
+
+# one layer of the 8B shape: 577..640 rows (192-row tiles, split and unsplit, of every projection but the LM head) against the same
+# sequences ten at a time (128- and 256-row tiles)
+@pytest.mark.parametrize("B,N", [(58, 10), (60, 10), (64, 10)])
+def test_rows_do_not_depend_on_the_batch(B, N):
+    E = _E()
+    full = S.get_shape("c3")
+    shape = full.with_(n_layers=1, taps=(0, 0, 0))
+    W = {k: v.to(DEV) for k, v in S.layer_weights(full, 3).items()}
+    tg = {k: v.to(DEV) for k, v in S.target_globals(full).items()}
+    ctx = E.Eagle3Context(shape, max_batch=B, max_nodes=N, max_depth=2, max_topk=2, max_new=4, device=DEV)
+    ctx.set_weights({"layers": [W], **tg}, None)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(B)
+    i32 = lambda v: torch.as_tensor(np.asarray(v), dtype=torch.int32, device=DEV)
+    x_in = 8.0 * torch.randn(B, N, full.hidden, device=DEV, generator=gen)
+    parent = i32(np.tile(np.arange(-1, N - 1), (B, 1)))
+    tok = torch.zeros(B, N, dtype=torch.int32, device=DEV)
+    P = 40
+    k0 = torch.randn(B * (P + N), full.n_kv_heads, full.head_dim, device=DEV, generator=gen).bfloat16()
+    v0 = torch.randn(B * (P + N), full.n_kv_heads, full.head_dim, device=DEV, generator=gen).bfloat16()
+
+    def run(b0, b1):
+        n = b1 - b0
+        k, v = k0[b0 * (P + N):b1 * (P + N)].clone(), v0[b0 * (P + N):b1 * (P + N)].clone()
+        kv = E.KVCache([k], [v], i32(np.arange(n + 1) * (P + N)), i32([P] * n), P)
+        x_out, _ = E.eagle3_tree_verify_layers(ctx, tok[b0:b1].contiguous(), parent[b0:b1].contiguous(), kv, x_in[b0:b1].contiguous(), 0, 1,
+                                               want_logits=True)
+        torch.cuda.synchronize()
+        return x_out.cpu().numpy(), k.float().cpu().numpy()
+
+    x, k = run(0, B)
+    for b0 in range(0, B, 10):
+        b1 = min(B, b0 + 10)
+        xr, kr = run(b0, b1)
+        assert np.max(np.abs(x[b0:b1] - xr)) < TOL * max(1.0, _rms(xr))
+        assert np.max(np.abs(k[b0 * (P + N):b1 * (P + N)] - kr)) < 4e-2
