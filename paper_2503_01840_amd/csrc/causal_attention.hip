@@ -441,25 +441,76 @@ __global__ __launch_bounds__(512) void causal_attn_bf16_kernel(CausalParams p) {
   float la, lb;
   pair_values(l_run * f1 + l2 * f2, la, lb);
   const float inv = 1.0f / (la + lb);
-  auto merged = [&](int d2, int gq) INLINE_LAMBDA -> floatx4 {         // values 32 d2 + 8 gq + 4 kg + 0..3 of this wavefront's half
-    floatx4 val;
+  floatx4 val[2][4];                           // values 32 d2 + 8 gq + 4 kg + 0..3 of this wavefront's half
+  float probe = 0.f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int r = 4 * gq + e;
-      val[e] = ((sb == 0 ? o[d2][r] : o[2 + d2][r]) * f1 + theirs[(d2 * 16 + r) * 64 + lane] * f2) * inv;
+  for (int d2 = 0; d2 < 2; ++d2)
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = 4 * gq + e;
+        const float x = ((sb == 0 ? o[d2][r] : o[2 + d2][r]) * f1 + theirs[(d2 * 16 + r) * 64 + lane] * f2) * inv;
+        val[d2][gq][e] = x;
+        probe = fmaf(x, 0.f, probe);           // stays 0 while every value is finite
+      }
+  if (__any(probe != 0.f)) {
+    // The value product multiplies keys that a query does not see with weights that are exactly zero, which keeps out everything but
+    // an infinity or NaN.  So rows that came out non-finite are formed again one key at a time over the keys they see: either the
+    // value at fault is one of those, or it does not count.
+    float m = NEG, l = 0.f;
+#pragma unroll
+    for (int d2 = 0; d2 < 2; ++d2)
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq) val[d2][gq] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    const int n_orig = min(pos_wave + 32, L);
+    const size_t own_row = min(q_wave + (lane & 31), T - 1);
+#pragma unroll 1
+    for (int j = 0; j < n_orig + (PREFILL ? 0 : p.s); ++j) {
+      const size_t at = (j < n_orig ? (size_t)j : (size_t)(j - n_orig + 1) * T + own_row) * row_stride;
+      float dot = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) {
+        const u32x4 kk = *(const u32x4*)(kbase + at + ks * 16 + kg * 8);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          dot = fmaf(bf16_lo(qf[ks][e]), bf16_lo(kk[e]), dot);
+          dot = fmaf(bf16_hi(qf[ks][e]), bf16_hi(kk[e]), dot);
+        }
+      }
+      float xa, xb;
+      pair_values(dot, xa, xb);
+      if (j < n_orig && j > pos) continue;
+      const float sc = (xa + xb) * p.scale_log2;
+      const float m_new = fmaxf(m, sc);
+      const float alpha = __builtin_amdgcn_exp2f(m - m_new), pw = __builtin_amdgcn_exp2f(sc - m_new);
+      l = l * alpha + pw;
+      m = m_new;
+#pragma unroll
+      for (int d2 = 0; d2 < 2; ++d2)
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {
+          const uint2 vv = *(const uint2*)(vbase + at + sb * 64 + d2 * 32 + 8 * gq + 4 * kg);
+          const floatx4 v = {bf16_lo(vv.x), bf16_hi(vv.x), bf16_lo(vv.y), bf16_hi(vv.y)};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) val[d2][gq][e] = val[d2][gq][e] * alpha + pw * v[e];
+        }
     }
-    return val;
-  };
+#pragma unroll
+    for (int d2 = 0; d2 < 2; ++d2)
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) val[d2][gq][e] /= l;
+  }
   if constexpr (PREFILL) {
     if (q_wave + (lane & 31) >= T) return;
 #pragma unroll
     for (int d2 = 0; d2 < 2; ++d2)
 #pragma unroll
-      for (int gq = 0; gq < 4; ++gq) {
-        const floatx4 val = merged(d2, gq);
-        Act<true>::store4((bf16_t*)p.out, q_wave + (lane & 31), head * D + sb * 64 + d2 * 32 + 8 * gq + 4 * kg, p.H * D, val[0], val[1],
-                          val[2], val[3]);
-      }
+      for (int gq = 0; gq < 4; ++gq)
+        Act<true>::store4((bf16_t*)p.out, q_wave + (lane & 31), head * D + sb * 64 + d2 * 32 + 8 * gq + 4 * kg, p.H * D, val[d2][gq][0],
+                          val[d2][gq][1], val[d2][gq][2], val[d2][gq][3]);
   } else {
     // The finished 32 rows x 64 values of this wavefront go through its own 8 KB of LDS, so that the stores are whole
     // 256-byte runs: 16-byte piece c of row i at position c ^ (i & 15).
@@ -468,13 +519,13 @@ __global__ __launch_bounds__(512) void causal_attn_bf16_kernel(CausalParams p) {
     for (int d2 = 0; d2 < 2; ++d2)
 #pragma unroll
       for (int gq = 0; gq < 4; ++gq)
-        *(floatx4*)(stage + (lane & 31) * 256 + (((d2 * 8 + 2 * gq + kg) ^ (lane & 15)) * 16)) = merged(d2, gq);
+        *(floatx4*)(stage + (lane & 31) * 256 + (((d2 * 8 + 2 * gq + kg) ^ (lane & 15)) * 16)) = val[d2][gq];
     __builtin_amdgcn_wave_barrier();           // one wavefront's LDS operations complete in order
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       const int i = 4 * c + lkey;
-      const floatx4 val = *(const floatx4*)(stage + i * 256 + (((lane & 15) ^ (i & 15)) * 16));
-      if (q_wave + i < T) *(floatx4*)((float*)p.out + ((size_t)(q_wave + i) * p.H + head) * D + sb * 64 + (lane & 15) * 4) = val;
+      const floatx4 v = *(const floatx4*)(stage + i * 256 + (((lane & 15) ^ (i & 15)) * 16));
+      if (q_wave + i < T) *(floatx4*)((float*)p.out + ((size_t)(q_wave + i) * p.H + head) * D + sb * 64 + (lane & 15) * 4) = v;
     }
   }
 }

@@ -1,0 +1,93 @@
+"""What a row may not see must not reach it, whatever its value: an infinity or NaN at one position leaves the results of every
+earlier position as they are (in a matrix product a weight of zero does not: 0 x Inf is NaN)."""
+import numpy as np
+import pytest
+import torch
+
+import eagle3_synth as S
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+INF, NAN = float("inf"), float("nan")
+
+
+def _reference(q, k, v):
+    """fp64, every query over exactly the keys it sees."""
+    T, H, d = q.shape
+    s, G = k.shape[0] - 1, k.shape[2]
+    q, k, v = q.double(), k.double(), v.double()
+    out = torch.empty(T, H, d, dtype=torch.float64)
+    for h in range(H):
+        g = h * G // H
+        for i in range(T):
+            kk = torch.cat([k[0, :i + 1, g], k[1:, i, g]])
+            vv = torch.cat([v[0, :i + 1, g], v[1:, i, g]])
+            w = ((kk * q[i, h]).sum(1) / d ** 0.5).softmax(0)
+            out[i, h] = (w[:, None] * vv).sum(0)
+    return out.numpy()
+
+
+# every number of query heads per workgroup (4, 2, 1); the bad position at the edges of 32-key blocks and of a workgroup's queries
+@pytest.mark.parametrize("H,Hkv", [(4, 1), (2, 1), (3, 1), (2, 2)])
+@pytest.mark.parametrize("T,at", [(1, 0), (40, 39), (130, 31), (130, 64), (200, 127), (200, 128), (200, 199)])
+@pytest.mark.parametrize("where,bad", [("v", INF), ("v", NAN), ("k", NAN), ("own v", -INF)])
+def test_ttt_attention_keeps_a_bad_position_to_the_rows_that_see_it(H, Hkv, T, at, where, bad):
+    import paper_2503_01840_amd as E
+    s = 2
+    q, k, v = (S.normal(S.SEED + T, i, dims, dtype=torch.bfloat16)
+               for i, dims in ((1, (T, H, 128)), (2, (s + 1, T, Hkv, 128)), (3, (s + 1, T, Hkv, 128))))
+    t = {"k": k[0], "v": v[0], "own v": v[1]}[where]
+    t[at, Hkv - 1, 3:70] = bad
+    got = E.eagle3_ttt_attention(q.to(DEV), k.to(DEV), v.to(DEV)).cpu().numpy()
+    ref = _reference(q, k, v)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+    ok = np.isfinite(ref)
+    assert np.array_equal(np.sign(got[~ok & ~np.isnan(ref)]), np.sign(ref[~ok & ~np.isnan(ref)]))
+    # the bound of the tile-edge tests: weights carried with 16 bits, |values| < 5
+    assert np.max(np.abs(got[ok] - ref[ok]), initial=0.0) < 2 * 5 * (2e-6 + 2.0 ** -16)
+
+
+def _prefill(E, shape, W, tokens, parts):
+    ctx = E.Eagle3Context(shape, max_batch=1, max_nodes=8, max_depth=2, max_topk=2, max_new=4, device=DEV)
+    ctx.set_weights(W["target"], W["draft"])
+    T = sum(parts)
+    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device=DEV)
+    z = lambda: torch.zeros(T, shape.n_kv_heads, shape.head_dim, dtype=ctx.storage_dtype, device=DEV)
+    ks, vs = [z() for _ in range(shape.n_layers)], [z() for _ in range(shape.n_layers)]
+    kv, dkv = E.KVCache(ks, vs, i32([0, T]), i32([0]), 0), E.KVCache([z()], [z()], i32([0, T]), i32([0]), 0)
+    at = 0
+    for n in parts:
+        E.eagle3_prefill(ctx, tokens[at:at + n].contiguous(), kv, dkv)
+        at += n
+    torch.cuda.synchronize()
+    return torch.stack(ks + vs).float().cpu(), torch.stack([dkv.k_layers[0], dkv.v_layers[0]]).float().cpu()
+
+
+# a token whose embedding row is NaN in the middle of a prompt; every number of query heads per workgroup
+@pytest.mark.parametrize("H,Hkv", [(4, 1), (2, 1), (3, 1), (2, 2)])
+@pytest.mark.parametrize("at", [31, 63, 127, 150])
+def test_prefill_keeps_a_bad_token_to_the_rows_that_see_it(H, Hkv, at):
+    _bad_token(_small(n_heads=H, n_kv_heads=Hkv), [200], at)
+
+
+def _small(**over):
+    from test_gpu_edges import SMALL
+    return SMALL.with_(**over)
+
+
+def _bad_token(shape, parts, at):
+    import paper_2503_01840_amd as E
+    import pipeline as PL
+    W = PL.device_weights(shape, device=DEV)
+    T = sum(parts)
+    tokens = S.uniform_ints(S.SEED + T, S.TensorIds.PREFIX_TOK, (T,), 0, shape.vocab - 1).to(torch.int32).to(DEV)
+    clean, clean_d = _prefill(E, shape, W, tokens, parts)
+    W["target"]["embed"] = W["target"]["embed"].clone()
+    W["target"]["embed"][shape.vocab - 1] = NAN
+    tokens[at] = shape.vocab - 1
+    got, got_d = _prefill(E, shape, W, tokens, parts)
+    # rows in the same kernels as before, their sums in another order where a row was formed again: the prefill tests' bounds
+    tol = 1e-4 if shape.dtype == "fp32" else 4e-2
+    assert bool(torch.isnan(got[:, at]).all())
+    for a, b in ((clean[:, :at], got[:, :at]), (clean_d[:, :at - 1], got_d[:, :at - 1])):
+        assert bool(torch.isfinite(b).all()) and float((a - b).abs().max()) < tol
