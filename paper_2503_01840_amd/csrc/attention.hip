@@ -370,10 +370,9 @@ __global__ __launch_bounds__(128 * CW, CW == 1 ? 1 : 2) void attn_tree_bf16_kern
 
 // one thread per (row, head, 4 consecutive head-dim entries); one pass over the splits in chunks of 8 whose
 // loads are all independent (online rescaling between chunks)
-__global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ o_part, const float* __restrict__ ml_part,
-                                                        int R, int N, int H, int n_splits, bf16_t* __restrict__ out) {
+__global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p, int R, bf16_t* __restrict__ out) {
   const int gid = blockIdx.x * 256 + threadIdx.x;
-  const int d4 = gid & 31, rh = gid >> 5;
+  const int d4 = gid & 31, rh = gid >> 5, H = p.H, N = p.N, n_splits = p.n_splits;
   if (rh >= R * H) return;
   const int h = rh % H, r = rh / H, b = r / N, node = r % N;
   const size_t base = (((size_t)b * H + h) * n_splits) * N + node;
@@ -385,8 +384,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const size_t pr = base + (size_t)min(s0 + j, n_splits - 1) * N;
-      ml[j] = *(const float2*)(ml_part + pr * 2);
-      o[j] = *(const float4*)(o_part + pr * D + 4 * d4);
+      ml[j] = *(const float2*)(p.ml_part + pr * 2);
+      o[j] = *(const float4*)(p.o_part + pr * D + 4 * d4);
     }
     float cm = M;
 #pragma unroll
@@ -403,7 +402,35 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
       }
     M = cm;
   }
-  const float inv = 1.0f / den;
+  float inv = 1.0f / den;
+  // The value product multiplies keys that a row does not see with weights that are exactly zero, which keeps out everything but an
+  // infinity or NaN.  So a row that came out non-finite is formed again by its 32 threads, one key at a time over the keys it sees.
+  // (Rows past the end of the sequence's own, which pad a batch, are never read.)
+  const float probe = fmaf(num.x * inv, 0.f, fmaf(num.y * inv, 0.f, fmaf(num.z * inv, 0.f, num.w * inv * 0.f)));
+  const unsigned long long bad = __ballot(probe != 0.f);                   // 0 or NaN
+  if ((uint32_t)(bad >> (threadIdx.x & 32)) != 0u && node < p.seq[b].n_tail) {
+    const SeqInfo si = p.seq[b];
+    const int g = h / (H / p.Hkv);
+    const float4 q = load4_f32(p.q, ((size_t)r * H + h) * D + 4 * d4);
+    float m = NEG;
+    den = 0.f;
+    num = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int j = 0; j < si.n_prefix + si.n_tail; ++j) {
+      const int off = j - si.n_prefix;
+      if (off >= 0 && !((p.mask[(size_t)r * 4 + ((off >> 5) & 3)] >> (off & 31)) & 1u)) continue;
+      const size_t at = ((size_t)(si.kv_base + j) * p.Hkv + g) * D + 4 * d4;
+      const float4 k = load4_f32(p.kc, at), v = load4_f32(p.vc, at);
+      float dot = fmaf(q.x, k.x, fmaf(q.y, k.y, fmaf(q.z, k.z, q.w * k.w)));
+#pragma unroll
+      for (int o = 16; o > 0; o >>= 1) dot += __shfl_xor(dot, o, 64);
+      const float sc = dot * p.scale_log2, m_new = fmaxf(m, sc);
+      const float a = __builtin_amdgcn_exp2f(m - m_new), w = __builtin_amdgcn_exp2f(sc - m_new);
+      num.x = num.x * a + w * v.x; num.y = num.y * a + w * v.y; num.z = num.z * a + w * v.z; num.w = num.w * a + w * v.w;
+      den = den * a + w;
+      m = m_new;
+    }
+    inv = 1.0f / den;
+  }
   Act<true>::store4(out, r, h * D + 4 * d4, H * D, num.x * inv, num.y * inv, num.z * inv, num.w * inv);
 }
 
@@ -422,13 +449,14 @@ __global__ __launch_bounds__(256) void attn_tree_f32_kernel(const float* __restr
   const int L = si.n_prefix + si.n_tail;
   for (int i = tid; i < d; i += 256) qs[i] = q[((size_t)r * H + h) * d + i];
   __syncthreads();
+  auto visible = [&](int kk) {
+    const int off = kk - si.n_prefix;
+    return off < 0 || ((mask[(size_t)r * 4 + ((off >> 5) & 3)] >> (off & 31)) & 1u);
+  };
   float mx = -INFINITY;
   for (int kk = tid; kk < L; kk += 256) {
-    const int off = kk - si.n_prefix;
-    bool vis = true;
-    if (off >= 0) vis = (mask[(size_t)r * 4 + ((off >> 5) & 3)] >> (off & 31)) & 1u;
     float s = -INFINITY;
-    if (vis) {
+    if (visible(kk)) {
       const float* kr = kc + ((size_t)(si.kv_base + kk) * Hkv + g) * d;
       s = dot_f32(qs, kr, d) * scale;
     }
@@ -438,9 +466,10 @@ __global__ __launch_bounds__(256) void attn_tree_f32_kernel(const float* __restr
   mx = block_max(mx, red);
   float sum = 0.f;
   for (int kk = tid; kk < L; kk += 256) {
-    const float e = expf(sc[kk] - mx);      // exp(-inf) = 0 for masked slots
-    sc[kk] = e;
-    sum += e;
+    const bool vis = visible(kk);
+    const float e = expf(sc[kk] - mx);
+    sc[kk] = vis ? e : -1.f;                // negative: leave the value out (a weight of zero would let an infinity through)
+    sum += vis ? e : 0.f;
   }
   sum = block_sum(sum, red);                // also publishes sc
   const int groups = 256 / d, grp = tid / d, i = tid - grp * d;
@@ -448,7 +477,10 @@ __global__ __launch_bounds__(256) void attn_tree_f32_kernel(const float* __restr
   if (grp < groups) {
     const float* v0 = vc + ((size_t)si.kv_base * Hkv + g) * d + i;
 #pragma unroll 8
-    for (int kk = grp; kk < L; kk += groups) acc = fmaf(sc[kk], v0[(size_t)kk * Hkv * d], acc);
+    for (int kk = grp; kk < L; kk += groups) {
+      const float w = sc[kk], v = v0[(size_t)kk * Hkv * d];
+      acc = w < 0.f ? acc : fmaf(w, v, acc);
+    }
   }
   part[tid] = acc;
   __syncthreads();
@@ -530,7 +562,6 @@ hipError_t launch_tree_attention(bool bf16, const void* q, const void* kcache, c
   const int grid = B * p.n_qblocks * n_splits * Hkv;
   hipError_t e = cw == 1 ? launch_attn_cw<1>(p, grid, st) : cw == 2 ? launch_attn_cw<2>(p, grid, st) : launch_attn_cw<4>(p, grid, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_merge_kernel, dim3((R * H * 32 + 255) / 256), dim3(256), 0, st, p.o_part, p.ml_part, R,
-                     rows_per_seq, H, n_splits, (bf16_t*)out);
+  hipLaunchKernelGGL(attn_merge_kernel, dim3((R * H * 32 + 255) / 256), dim3(256), 0, st, p, R, (bf16_t*)out);
   return hipGetLastError();
 }

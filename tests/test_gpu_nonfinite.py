@@ -70,6 +70,51 @@ def test_prefill_keeps_a_bad_token_to_the_rows_that_see_it(H, Hkv, at):
     _bad_token(_small(n_heads=H, n_kv_heads=Hkv), [200], at)
 
 
+# the same through the tree kernels: a chunk that the split kernel takes (few rows behind many keys), and the fp32 model
+@pytest.mark.parametrize("parts,at", [([700, 100], 730), ([700, 100], 763), ([700, 100], 799), ([1000, 20], 1001)])
+def test_prefill_behind_a_long_context_keeps_a_bad_token_to_the_rows_that_see_it(parts, at):
+    _bad_token(_small(), parts, at)
+
+
+@pytest.mark.parametrize("parts,at", [([130], 60), ([130], 100), ([40, 90], 100)])
+def test_prefill_fp32_keeps_a_bad_token_to_the_rows_that_see_it(parts, at):
+    _bad_token(S.get_shape("c1"), parts, at)
+
+
+# a bad node in a tree: nodes that do not descend from it keep their logits
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("P", [0, 5, 600])
+def test_verification_keeps_a_bad_node_to_its_descendants(dtype, P):
+    import paper_2503_01840_amd as E
+    import pipeline as PL
+    shape = S.get_shape("c1") if dtype == "fp32" else _small()
+    N = 30
+    parent = S.random_tree(S.SEED, 3, N, 6, 3)[0]
+    bad = 2
+    below = np.zeros(N, bool)
+    for i in range(N):
+        below[i] = i == bad or (i > 0 and below[parent[i]])
+    W = PL.device_weights(shape, device=DEV)
+    ctx = E.Eagle3Context(shape, max_batch=1, max_nodes=N, max_depth=2, max_topk=2, max_new=4, device=DEV)
+    i32 = lambda v: torch.tensor(np.asarray(v), dtype=torch.int32, device=DEV)
+    tok = S.uniform_ints(S.SEED, 5, (1, N), 0, shape.vocab - 1).to(torch.int32).to(DEV)
+
+    def logits():
+        ctx.set_weights(W["target"], W["draft"])
+        kv = [[S.normal(S.SEED + l, i, (P + N, shape.n_kv_heads, shape.head_dim)).to(ctx.storage_dtype).to(DEV)
+               for l in range(shape.n_layers)] for i in (1, 2)]
+        return E.eagle3_tree_verify(ctx, tok, i32(parent)[None], E.KVCache(*kv, i32([0, P + N]), i32([P]), P))[0][0].cpu()
+
+    clean = logits()
+    W["target"]["embed"] = W["target"]["embed"].clone()
+    W["target"]["embed"][shape.vocab - 1] = NAN
+    tok[0, bad] = shape.vocab - 1
+    got = logits()
+    assert bool(torch.isnan(got[below]).all()) and not below.all()
+    assert bool(torch.isfinite(got[~below]).all())
+    assert float((got[~below] - clean[~below]).abs().max()) < (1e-4 if dtype == "fp32" else 2e-2)
+
+
 def _small(**over):
     from test_gpu_edges import SMALL
     return SMALL.with_(**over)
@@ -89,5 +134,7 @@ def _bad_token(shape, parts, at):
     # rows in the same kernels as before, their sums in another order where a row was formed again: the prefill tests' bounds
     tol = 1e-4 if shape.dtype == "fp32" else 4e-2
     assert bool(torch.isnan(got[:, at]).all())
-    for a, b in ((clean[:, :at], got[:, :at]), (clean_d[:, :at - 1], got_d[:, :at - 1])):
+    # (the draft row of position i holds token i + 1; the last position of a call gets none)
+    n_draft = at - len(parts)
+    for a, b in ((clean[:, :at], got[:, :at]), (clean_d[:, :n_draft], got_d[:, :n_draft])):
         assert bool(torch.isfinite(b).all()) and float((a - b).abs().max()) < tol
