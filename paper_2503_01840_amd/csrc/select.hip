@@ -32,7 +32,7 @@ __global__ __launch_bounds__(256) void topk_spans_kernel(const float* __restrict
     v[j] = c < V ? zr[c] : -INFINITY;
     mx = fmaxf(mx, v[j]);
   }
-  mx = wave_max(mx);                                   // base < V, so at least one entry is finite
+  mx = wave_max(mx);
   float sum = 0.f;
 #pragma unroll
   for (int j = 0; j < 8; ++j) sum += expf(v[j] - mx);  // exp(-inf) = 0 for the padding
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void topk_spans_kernel(const float* __restrict
       const unsigned long long eq = __ballot(v[j] == mx);
       if (eq) at = j * 64 + __ffsll((long long)eq) - 1;
     }
-    if (!(mx > -INFINITY)) at = INT_MAX;               // fewer than K entries
+    if (!(mx > -INFINITY)) at = INT_MAX;               // fewer than K entries above -inf (a NaN is none): no candidate
 #pragma unroll
     for (int j = 0; j < 8; ++j)
       if (at == j * 64 + lane) v[j] = -INFINITY;
@@ -111,7 +111,8 @@ __global__ __launch_bounds__(64) void topk_merge64_kernel(const float* __restric
 // In the order (value desc, index asc) the K-th best of the spans' BEST candidates bounds the answer from below:
 // at least K candidates are not worse than it, so only candidates not worse than it can be among the top K, and
 // those come from exactly K spans (at most K * K survivors).  The survivors are ranked by counting, and rank r < K
-// is output r.
+// is output r.  Entries without a candidate (-inf or NaN) never survive; when fewer than K spans have one there is no
+// bound, and fewer than K * K survivors.  Ranks that are left over get index 0.
 __global__ __launch_bounds__(64) void topk_merge_kernel(const float* __restrict__ cand_val, const int32_t* __restrict__ cand_idx,
                                                        const float* __restrict__ span_stat, int n_spans, int K,
                                                        float* __restrict__ top_val, int32_t* __restrict__ top_idx) {
@@ -134,7 +135,7 @@ __global__ __launch_bounds__(64) void topk_merge_kernel(const float* __restrict_
   const float* cv = cand_val + (size_t)row * C;
   const int32_t* ci = cand_idx + (size_t)row * C;
   for (int i = lane; i < n_spans; i += 64) { head_v[i] = cv[i]; head_i[i] = ci[i]; }
-  if (lane == 0) { n_surv = 0; bound_v = -INFINITY; bound_i = INT_MAX; }      // fewer than K spans: everything survives
+  if (lane == 0) { n_surv = 0; bound_v = -INFINITY; bound_i = INT_MAX; }
   __syncthreads();
   const int kth = K - 1;
   for (int i = lane; i < n_spans; i += 64) {
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(64) void topk_merge_kernel(const float* __restrict_
     const int id = head_i[i];
     int rank = 0;
     for (int j = 0; j < n_spans; ++j) rank += better(head_v[j], head_i[j], v, id) ? 1 : 0;
-    if (rank == kth) { bound_v = v; bound_i = id; }
+    if (rank == kth && v > -INFINITY) { bound_v = v; bound_i = id; }
   }
   __syncthreads();
   const float bv = bound_v;
@@ -152,7 +153,7 @@ __global__ __launch_bounds__(64) void topk_merge_kernel(const float* __restrict_
     for (int r = 0; r < K; ++r) {
       const float v = cv[r * n_spans + i];
       const int id = ci[r * n_spans + i];
-      if (better(bv, bi, v, id)) break;                                        // a span's candidates are in order
+      if (!(v > -INFINITY) || better(bv, bi, v, id)) break;                    // a span's candidates are in order
       const int pos = atomicAdd(&n_surv, 1);
       surv_v[pos] = v;
       surv_i[pos] = id;
@@ -160,6 +161,10 @@ __global__ __launch_bounds__(64) void topk_merge_kernel(const float* __restrict_
   }
   __syncthreads();
   const int T = n_surv;
+  if (lane >= T && lane < K) {
+    top_val[row * K + lane] = -INFINITY - mx - lse;
+    top_idx[row * K + lane] = 0;
+  }
   for (int t = lane; t < T; t += 64) {
     const float v = surv_v[t];
     const int id = surv_i[t];

@@ -31,3 +31,40 @@ def test_draft_expand_over_draft_vocabularies(Vd, D, K, N):
     for key in ("tree_tok", "parent", "depth", "chosen"):
         assert np.array_equal(got[key], ref[key]), key
     assert np.max(np.abs(got["score"] - ref["score"])) < 1e-4          # fp32 logits and their log-sum-exp, up to D of them added
+
+
+# draft logits of which only a few are numbers: every id that comes out is one of the vocabulary, the numbers come first
+@pytest.mark.parametrize("Vd", [700, 32768, 32769, 70000])
+@pytest.mark.parametrize("n_good,K", [(0, 1), (0, 16), (3, 1), (3, 5), (5, 5), (17, 16)])
+def test_draft_expand_with_undefined_logits(Vd, n_good, K):
+    import paper_2503_01840_amd as E
+    shape = S.get_shape("c1").with_(name=f"n{Vd}", draft_vocab=Vd, vocab=Vd)
+    D, N = 3, 2 if K == 1 else 20
+    ctx = E.Eagle3Context(shape, max_batch=2, max_nodes=64, max_depth=4, max_topk=16, max_new=4, device=DEV)
+    W = PL.device_weights(shape, device=DEV)
+    good = np.sort(np.random.RandomState(Vd + K).choice(Vd, n_good, replace=False))
+    head = torch.full_like(W["draft"]["lm_head"], float("nan"))
+    head[good] = W["draft"]["lm_head"][good]
+    W["draft"]["lm_head"] = head
+    ctx.set_weights(W["target"], W["draft"])
+    inp = PL.synthetic_step_inputs(shape, n_new=2, prefix=42)
+    ks, vs, indptr, plen, P = PL.device_kv([inp["draft_kv"]], 2 + (D - 1) * K, DEV)
+    kv = E.KVCache(ks, vs, indptr, plen, P)
+    got = E.eagle3_draft_expand(ctx, inp["g_new"].to(DEV), inp["tok_new"].to(DEV), kv, D, K, N, debug=True)
+    torch.cuda.synchronize()
+    got = {k: v.cpu().numpy() for k, v in got.items()}
+    pool = got["pool_tok"][1:]
+    assert ((pool >= 0) & (pool < Vd)).all()
+    for c in range(0, len(pool), K):
+        first = pool[c:c + min(n_good, K)]
+        assert np.isin(first, good).all() and len(set(first)) == len(first)
+    assert (got["parent"][1:] >= 0).all() and (got["parent"][1:] < np.arange(1, N)).all()
+    assert (np.diff(got["chosen"]) > 0).all() and got["chosen"].min() >= 1
+    g = inp["g_new"].to(DEV)[None, :1].repeat(2, 1, 1).contiguous()
+    two = lambda v: torch.tensor([v, v], dtype=torch.int32, device=DEV)
+    kv2 = E.KVCache([torch.cat([ks[0], ks[0]])], [torch.cat([vs[0], vs[0]])], torch.tensor([0, len(ks[0]), 2 * len(ks[0])], dtype=torch.int32, device=DEV),
+                    two(P), P)
+    tok, _ = E.eagle3_draft_chain(ctx, g, two(1)[:, None].contiguous(), two(1), kv2, 2)
+    tok = tok.cpu().numpy()[:, 1:]
+    d2t = W["draft"]["d2t"].cpu().numpy()
+    assert np.isin(tok, d2t[good] if n_good else d2t[:1]).all()
