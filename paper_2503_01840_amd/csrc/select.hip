@@ -271,7 +271,8 @@ __global__ __launch_bounds__(1024) void draft_rerank_kernel(DraftState s, const 
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
       const int e = 64 * i + lane;
-      u[i] = e > 0 && e < pool ? (uint32_t)(rank_key(s.pool_score[e], e) >> 32) : 0u;   // 0: below every score
+      // 0 stands for no entry, below every score (the key of the one NaN with all bits set would be 0 as well)
+      u[i] = e > 0 && e < pool ? max((uint32_t)(rank_key(s.pool_score[e], e) >> 32), 1u) : 0u;
     }
     uint32_t thr = 0;
     for (int bit = 31; bit >= 0; --bit) {

@@ -36,14 +36,15 @@ def test_draft_expand_over_draft_vocabularies(Vd, D, K, N):
 # draft logits of which only a few are numbers: every id that comes out is one of the vocabulary, the numbers come first
 @pytest.mark.parametrize("Vd", [700, 32768, 32769, 70000])
 @pytest.mark.parametrize("n_good,K", [(0, 1), (0, 16), (3, 1), (3, 5), (5, 5), (17, 16)])
-def test_draft_expand_with_undefined_logits(Vd, n_good, K):
+@pytest.mark.parametrize("nan_bits", [0x7FC00000, -1])                 # -1: all bits set, as in memory filled with 0xFF
+def test_draft_expand_with_undefined_logits(Vd, n_good, K, nan_bits):
     import paper_2503_01840_amd as E
     shape = S.get_shape("c1").with_(name=f"n{Vd}", draft_vocab=Vd, vocab=Vd)
     D, N = 3, 2 if K == 1 else 20
     ctx = E.Eagle3Context(shape, max_batch=2, max_nodes=64, max_depth=4, max_topk=16, max_new=4, device=DEV)
     W = PL.device_weights(shape, device=DEV)
     good = np.sort(np.random.RandomState(Vd + K).choice(Vd, n_good, replace=False))
-    head = torch.full_like(W["draft"]["lm_head"], float("nan"))
+    head = torch.full_like(W["draft"]["lm_head"], nan_bits, dtype=torch.int32).view(torch.float32)
     head[good] = W["draft"]["lm_head"][good]
     W["draft"]["lm_head"] = head
     ctx.set_weights(W["target"], W["draft"])
