@@ -56,6 +56,7 @@ struct CausalParams {
   int T, H, Hkv, s;
   int hg, n_groups, n_qblocks;      // query heads per workgroup, KV heads x head groups, query blocks
   float scale_log2;
+  bool q_aligned;         // to 16 bytes
   void* out;              // training: fp32 [T, H, D]; prefill: fragment-major bf16 [T, H * D]
 };
 
@@ -160,13 +161,21 @@ __global__ __launch_bounds__(512) void causal_attn_bf16_kernel(CausalParams p) {
       dma16(vbase + base, off, lds0 + v_slot + j * 1024);
     }
   };
-  // the workgroup's query rows, staged the same way (row group by row group) behind the tile slots
+  // the workgroup's query rows, staged the same way (row group by row group) behind the tile slots; through registers where the
+  // caller's queries do not start at a multiple of 16 bytes
 #pragma unroll
   for (int i = 0; i < IPW; ++i) {
     const int j = wave * IPW + i, r = 4 * j + lkey, rgj = j >> 3;
     const int h = g * G + (gh / p.Hkv) * p.hg + rgj * 32 / QB, qr = min(q_first + (rgj * 32) % QB + (r & 31), T - 1);
     const uint32_t off = (uint32_t)(qr - q_first) * (uint32_t)(p.H * ROWB) + (uint32_t)(((lane & 15) ^ (r & 15)) * 16);
-    dma16(p.q + ((size_t)q_first * p.H + h) * D, off, lds0 + Q_BASE + j * 1024);
+    const bf16_t* src = p.q + ((size_t)q_first * p.H + h) * D;
+    if (__builtin_expect(p.q_aligned, 1)) {
+      dma16(src, off, lds0 + Q_BASE + j * 1024);
+    } else {
+      u32x4 piece;
+      __builtin_memcpy(&piece, (const char*)src + off, 16);
+      *(u32x4*)(smem + Q_BASE + j * 1024 + lane * 16) = piece;
+    }
   }
   issue(kbase, koff, 0, 0);
   issue(vbase, voff, 0, V_BASE);
@@ -454,7 +463,7 @@ __global__ __launch_bounds__(512) void causal_attn_bf16_kernel(CausalParams p) {
         val[d2][gq][e] = x;
         probe = fmaf(x, 0.f, probe);           // stays 0 while every value is finite
       }
-  if (__any(probe != 0.f)) {
+  if (__builtin_expect(__any(probe != 0.f), 0)) {
     // The value product multiplies keys that a query does not see with weights that are exactly zero, which keeps out everything but
     // an infinity or NaN.  So rows that came out non-finite are formed again one key at a time over the keys they see: either the
     // value at fault is one of those, or it does not count.
@@ -597,6 +606,7 @@ hipError_t launch_causal(CausalParams& p, hipStream_t st) {
   p.n_groups = p.H / p.hg;
   p.n_qblocks = (p.T + ROWS_WG / p.hg - 1) / (ROWS_WG / p.hg);
   p.scale_log2 = 1.4426950408889634f / sqrtf((float)D);
+  p.q_aligned = ((uintptr_t)p.q & 15) == 0;
   hipLaunchKernelGGL(kernel, dim3((unsigned)p.n_groups * p.n_qblocks), dim3(512), LDS_BYTES, st, p);
   return hipGetLastError();
 }

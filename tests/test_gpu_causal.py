@@ -27,6 +27,21 @@ def test_ttt_attention_at_tile_edges(T, H, Hkv, s, spread):
     assert np.max(np.abs(got - ref)) < 2 * 5 * (2e-6 * spread + 2.0 ** -16), (T, H, Hkv, s)
 
 
+# queries at any address; every number of query heads per workgroup
+@pytest.mark.parametrize("H,Hkv", [(4, 1), (4, 2), (3, 1)])
+@pytest.mark.parametrize("shift", [1, 2, 4, 8])
+@pytest.mark.parametrize("T", [33, 200])
+def test_ttt_attention_with_queries_at_any_address(H, Hkv, shift, T):
+    import paper_2503_01840_amd as E
+    q = S.normal(S.SEED + T, 1, (T, H, 128), dtype=torch.bfloat16)
+    k = S.normal(S.SEED + T, 2, (2, T, Hkv, 128), dtype=torch.bfloat16)
+    v = S.normal(S.SEED + T, 3, (2, T, Hkv, 128), dtype=torch.bfloat16)
+    flat = torch.zeros(q.numel() + 8, dtype=torch.bfloat16, device=DEV)
+    moved = flat[shift:shift + q.numel()].view(q.shape)
+    moved.copy_(q)
+    assert torch.equal(E.eagle3_ttt_attention(moved, k.to(DEV), v.to(DEV)), E.eagle3_ttt_attention(q.to(DEV), k.to(DEV), v.to(DEV)))
+
+
 # a prompt in two calls: P rows first, then n rows behind them, against the same prompt in one call.  n rows with P behind them
 # take the causal kernel (few tiles of keys) or the split one (long context, few rows)
 @pytest.mark.parametrize("P,n", [(1, 63), (64, 64), (77, 130), (127, 1), (200, 312), (700, 20), (1000, 500)])
