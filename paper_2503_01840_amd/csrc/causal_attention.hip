@@ -8,8 +8,10 @@
 //
 // bf16 kernel (head_dim 128).  A workgroup owns 128 query rows of one KV head: HG (1, 2 or 4) of the query heads that
 // share it x 128 / HG consecutive queries, so that every K/V tile it stages serves all of them.  8 wavefronts = 4 groups
-// of 32 rows x 2 halves of every 128-key tile; a wavefront takes its half in two blocks of 32 keys.
-//   * Tiles reach LDS by direct global-to-LDS loads, K one tile further ahead than V, swizzled per key; scores are
+// of 32 rows x 2 halves of every 128-key tile; a wavefront takes its half in two blocks of 32 keys.  (Where the chip would not be
+// full: 64 rows, 4 wavefronts.)
+//   * Tiles reach LDS by direct global-to-LDS loads, both K and V two tiles ahead, swizzled per key; K has two slots and V three,
+//     as its values are read one block later than its scores; scores are
 //     produced transposed (S^T = K Q^T) so that a lane owns one query; the V^T operand comes from the transposing LDS
 //     read; exp(S) enters the value product as a bf16 head plus a bf16 tail.
 //   * One block is a matrix-unit time of 24 products (8 score + 16 value) against ~540 issue cycles of softmax.  Run
@@ -26,6 +28,8 @@
 // softmax and values one after the other, own keys read from global memory by every lane for itself): T = 2048, s = 2:
 // 108 -> 65 us; T = 517, 64 heads, s = 5: 61 -> 28.5 us.
 // fp32 kernel: one workgroup per (query, head), exact arithmetic, for small checks.
+#include <algorithm>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -39,12 +43,10 @@ constexpr int KT = 128;                       // keys per tile: two halves of tw
 constexpr int ROWB = D * 2;
 constexpr int TILE_BYTES = KT * ROWB;         // of K, and again of V
 constexpr int V_BASE = 2 * TILE_BYTES;        // two K slots, then three V slots: all of a CU's 160 KB
-constexpr int ROWS_WG = 128;
 constexpr int LDS_BYTES = 5 * TILE_BYTES;
 constexpr int Q_BASE = 4 * TILE_BYTES;        // the queries, staged in the third V slot before it is used
 constexpr int STAGE_BASE = 8 * 34 * 64 * 4;   // at the end: the exchange of the key halves, then 8 KB per wavefront
 
-constexpr int IPW = 4;                        // direct loads per wavefront per tile, for K and again for V
 constexpr float NEG = -1e30f;
 constexpr float MAX_SLACK = 8.f;
 
@@ -94,12 +96,16 @@ __device__ __forceinline__ floatx16 mfma(const u32x4& a, const u32x4& b, const f
 template <bool V> struct Flag { static constexpr bool value = V; };
 
 // PREFILL: query i sits at position n_prefix + i of a sequence in the cache, whose earlier positions it sees as well.
-template <bool PREFILL>
-__global__ __launch_bounds__(512) void causal_attn_bf16_kernel(CausalParams p) {
+// RG: 32-row groups per workgroup.
+template <bool PREFILL, int RG>
+__global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rg = wave & 3, sb = wave >> 2;                   // row group, key half
+  constexpr int NW = 2 * RG, ROWS_WG = 32 * RG;
+  constexpr int IPW = 32 / NW;                               // direct loads per wavefront per tile, for K and again for V
+  constexpr int IPW_ROWS = ROWS_WG / 4 / NW;                 // and for one row of each of the workgroup's queries
+  const int rg = wave % RG, sb = wave / RG;                  // row group, key half
   const int kg = lane >> 5;
   const int gh = blockIdx.x % p.n_groups;
   const int qb = p.n_qblocks - 1 - (int)blockIdx.x / p.n_groups;
@@ -145,14 +151,14 @@ __global__ __launch_bounds__(512) void causal_attn_bf16_kernel(CausalParams p) {
       }
     }
   };
-  // The simulated steps' own rows: up to hg steps x QB rows = 128 rows of K and of V at a time go through free tile
+  // The simulated steps' own rows: up to hg steps x QB rows = ROWS_WG rows of K and of V at a time go through free tile
   // slots as whole 256-byte rows, piece c of staged row i at position c ^ (i & 15), one copy for all heads and wavefronts.
   // (Read by every lane for itself, 16 and 8 bytes per row and request, they were a third of the kernel: a request that
   // touches 32 lines takes 32 times as long as one that touches one.)
   auto issue_own = [&](int t0, uint32_t k_slot, uint32_t v_slot) INLINE_LAMBDA {
 #pragma unroll
-    for (int i = 0; i < IPW; ++i) {
-      const int j = wave * IPW + i, r = (4 * j) % QB + lkey;             // staged rows 4j .. 4j+3: one step
+    for (int i = 0; i < IPW_ROWS; ++i) {
+      const int j = wave * IPW_ROWS + i, r = (4 * j) % QB + lkey;             // staged rows 4j .. 4j+3: one step
       const int t = min(t0 + 4 * j / QB, p.s);
       const size_t base = ((size_t)t * T + q_first) * row_stride;
       const uint32_t off = (uint32_t)(min(q_first + r, T - 1) - q_first) * (uint32_t)(row_stride * 2) +
@@ -164,8 +170,8 @@ __global__ __launch_bounds__(512) void causal_attn_bf16_kernel(CausalParams p) {
   // the workgroup's query rows, staged the same way (row group by row group) behind the tile slots; through registers where the
   // caller's queries do not start at a multiple of 16 bytes
 #pragma unroll
-  for (int i = 0; i < IPW; ++i) {
-    const int j = wave * IPW + i, r = 4 * j + lkey, rgj = j >> 3;
+  for (int i = 0; i < IPW_ROWS; ++i) {
+    const int j = wave * IPW_ROWS + i, r = 4 * j + lkey, rgj = j >> 3;
     const int h = g * G + (gh / p.Hkv) * p.hg + rgj * 32 / QB, qr = min(q_first + (rgj * 32) % QB + (r & 31), T - 1);
     const uint32_t off = (uint32_t)(qr - q_first) * (uint32_t)(p.H * ROWB) + (uint32_t)(((lane & 15) ^ (r & 15)) * 16);
     const bf16_t* src = p.q + ((size_t)q_first * p.H + h) * D;
@@ -590,24 +596,46 @@ __global__ __launch_bounds__(256) void ttt_attn_f32_kernel(const float* __restri
   }
 }
 
-// 128 rows per workgroup: as many heads of one KV head as divide its group (4, 2 or 1) x the matching number of queries
-int heads_per_wg(int H, int Hkv) {
+// 32 RG rows per workgroup: as many heads of one KV head as divide its group (4, 2 or 1, and no more than RG) x the matching
+// number of queries
+int heads_per_wg(int H, int Hkv, int RG) {
   const int G = H / Hkv;
-  return G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1;
+  return G % 4 == 0 && RG >= 4 ? 4 : G % 2 == 0 ? 2 : 1;
+}
+int workgroups(int T, int H, int Hkv, int RG) {
+  const int hg = heads_per_wg(H, Hkv, RG), qb = 32 * RG / hg;
+  return H / hg * ((T + qb - 1) / qb);
 }
 
-template <bool PREFILL>
+// Workgroups of 64 rows instead of 128 where those leave CUs idle: one wavefront per SIMD then takes 1.95 us per tile instead of the
+// 2.45 us that two take side by side, and there are twice as many workgroups.  Up to 256 of them each has a CU to itself (64-row
+// form against 128-row form, us: 4 heads 4096 positions 66 / 82, 8 heads 2048 positions 37 / 45, 32 heads over 8 300
+// positions 11.5 / 13.6).  Up to 512, the shorter half of them (workgroup i of w walks over 1 - i / w of the tiles) starts on the CUs that are
+// done with the longer half's shorter ones, and pays the start, the own keys and the merge again: 8 heads 3000 positions 52 / 64,
+// 32 over 8 517 positions 15.7 / 18.7, but with 3 simulated steps over 32 KV heads 27.2 / 25.2, and 1000 positions of 32 over 8 27.9 / 27.6.
+// Beyond that the shared tiles win: 2048 positions 84 / 61.
+bool half_workgroups(int T, int H, int Hkv, int s) {
+  const int w = workgroups(T, H, Hkv, 2);
+  if (w <= 256) return true;
+  if (w > 512) return false;
+  const float tiles = (T + KT - 1) / KT;
+  auto fixed = [&](int RG, float batch) { const int hg = heads_per_wg(H, Hkv, RG); return 8.f + batch * ((s + hg - 1) / hg); };
+  const float start2 = fixed(2, 1.1f), two = 2.f * (1.95f * tiles * (1.f - 256.f / w) + start2);
+  return std::max(1.95f * tiles + start2, two) < 2.45f * tiles + fixed(4, 1.4f);
+}
+
+template <bool PREFILL, int RG>
 hipError_t launch_causal(CausalParams& p, hipStream_t st) {
-  auto kernel = causal_attn_bf16_kernel<PREFILL>;
+  auto kernel = causal_attn_bf16_kernel<PREFILL, RG>;
   static DeviceOnce configured;                  // the attribute belongs to the loaded code object of a device
   hipError_t ce = configured.run([&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES); });
   if (ce != hipSuccess) return ce;
-  p.hg = heads_per_wg(p.H, p.Hkv);
+  p.hg = heads_per_wg(p.H, p.Hkv, RG);
   p.n_groups = p.H / p.hg;
-  p.n_qblocks = (p.T + ROWS_WG / p.hg - 1) / (ROWS_WG / p.hg);
+  p.n_qblocks = workgroups(p.T, p.H, p.Hkv, RG) / p.n_groups;
   p.scale_log2 = 1.4426950408889634f / sqrtf((float)D);
   p.q_aligned = ((uintptr_t)p.q & 15) == 0;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)p.n_groups * p.n_qblocks), dim3(512), LDS_BYTES, st, p);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)p.n_groups * p.n_qblocks), dim3(128 * RG), LDS_BYTES, st, p);
   return hipGetLastError();
 }
 
@@ -629,7 +657,7 @@ hipError_t launch_ttt_attention(bool bf16, const void* q, const void* k, const v
   p.seq = nullptr;
   p.T = T; p.H = H; p.Hkv = Hkv; p.s = s;
   p.out = out;
-  return launch_causal<false>(p, st);
+  return half_workgroups(T, H, Hkv, s) ? launch_causal<false, 2>(p, st) : launch_causal<false, 4>(p, st);
 }
 
 // This kernel against the tree kernel, which cuts the keys into splits and merges them (us, 32 heads over 8 unless stated):
@@ -640,8 +668,7 @@ hipError_t launch_ttt_attention(bool bf16, const void* q, const void* k, const v
 //   between the two the line runs near 10 workgroups per tile of walk: 64 and 6 tiles 20.3 against 21.5, 128 and 12 tiles 37
 //     against 42, but 64 and 10 tiles 30 against 26, 128 and 20 tiles 59 against 55.
 bool prefill_attention_fits(int n, int H, int Hkv, int max_len) {
-  const int hg = heads_per_wg(H, Hkv), qb = ROWS_WG / hg;
-  const int wgs = H / hg * ((n + qb - 1) / qb), tiles = (max_len + KT - 1) / KT;
+  const int wgs = workgroups(n, H, Hkv, 4), tiles = (max_len + KT - 1) / KT;
   return wgs >= 192 || tiles <= 4 || wgs >= 10 * tiles;
 }
 
@@ -653,5 +680,5 @@ hipError_t launch_prefill_attention(const void* q, const void* kcache, const voi
   p.seq = seq;
   p.T = n; p.H = H; p.Hkv = Hkv; p.s = 0;
   p.out = out;
-  return launch_causal<true>(p, st);
+  return launch_causal<true, 4>(p, st);
 }

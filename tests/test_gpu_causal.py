@@ -27,6 +27,23 @@ def test_ttt_attention_at_tile_edges(T, H, Hkv, s, spread):
     assert np.max(np.abs(got - ref)) < 2 * 5 * (2e-6 * spread + 2.0 ** -16), (T, H, Hkv, s)
 
 
+# sizes around the lines between 64-row and 128-row workgroups (256 and 512 of the smaller ones)
+@pytest.mark.parametrize("T,H,Hkv,s", [(2048, 8, 8, 1), (2049, 8, 8, 0), (1025, 16, 16, 3), (513, 32, 8, 2), (1030, 32, 8, 0), (300, 64, 8, 2)])
+def test_ttt_attention_around_the_workgroup_sizes(T, H, Hkv, s):
+    import paper_2503_01840_amd as E
+    q = S.normal(S.SEED + T, 1, (T, H, 128), dtype=torch.bfloat16)
+    k = S.normal(S.SEED + T, 2, (s + 1, T, Hkv, 128), dtype=torch.bfloat16)
+    v = S.normal(S.SEED + T, 3, (s + 1, T, Hkv, 128), dtype=torch.bfloat16)
+    got = E.eagle3_ttt_attention(q.to(DEV), k.to(DEV), v.to(DEV)).cpu().numpy()
+    q64, K, V = O.as_f64(q), O.as_f64(k).reshape((s + 1) * T, Hkv, 128), O.as_f64(v).reshape((s + 1) * T, Hkv, 128)
+    sets = O.ttt_visible_sets(T, s)
+    rows = sorted({0, 31, 32, 63, 64, 127, 128, T // 2, T - 65, T - 64, T - 2, T - 1})
+    for i in rows:
+        ref = O.attention_explicit_sets(q64[i:i + 1], K, V, [sets[i]])
+        assert np.max(np.abs(got[i] - ref[0])) < 2 * 5 * (2e-6 + 2.0 ** -16), i          # the tile-edge bound
+    assert np.isfinite(got).all()
+
+
 # queries at any address; every number of query heads per workgroup
 @pytest.mark.parametrize("H,Hkv", [(4, 1), (4, 2), (3, 1)])
 @pytest.mark.parametrize("shift", [1, 2, 4, 8])
