@@ -5,7 +5,7 @@
 //   greedy     follow the child whose token is the row argmax (ties -> smaller id), else stop with it;
 //   stochastic test the children in ascending node id against the running residual distribution, and on
 //              failure draw the bonus token by inverse CDF of the residual in vocabulary order.
-// The walk touches only the statistics of the visited rows plus, for the bonus draw, one chunk of logits.
+// The walk's workgroup reduces the statistics of all rows of its tree first; the bonus draw reads one chunk of logits.
 #include <limits.h>
 
 #include <algorithm>
@@ -33,12 +33,14 @@ __global__ __launch_bounds__(256) void accept_stats_kernel(const float* __restri
   const float* z = logits + (size_t)r * V;
   const int lo = c * CH;
   float x[4][8];
-  if (vec4 && lo + CH <= V) {
+  if (vec4) {                                            // V % 4 == 0: a lane's four entries exist or do not
 #pragma unroll
     for (int w = 0; w < 4; ++w)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const float4 q = *(const float4*)(z + lo + w * 512 + h * 256 + 4 * lane);
+        const int v = lo + w * 512 + h * 256 + 4 * lane;
+        float4 q = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        if (v < V) q = *(const float4*)(z + v);
         x[w][4 * h] = q.x; x[w][4 * h + 1] = q.y; x[w][4 * h + 2] = q.z; x[w][4 * h + 3] = q.w;
       }
   } else {
@@ -101,6 +103,18 @@ __global__ __launch_bounds__(256) void accept_stats_kernel(const float* __restri
   if (lane == 0) *(float4*)(stats + ((size_t)r * n_chunks + c) * 4) = make_float4(M, __int_as_float(A), S, 0.f);
 }
 
+// Maxima over the wavefront of four values per lane: lanes 16 g .. 16 g + 15 end with that of a, c, b, d for g = 0..3.
+__device__ __forceinline__ float wave_max4(float a, float b, float c, float d) {
+  auto fold32 = [](float x, float y) {         // lanes 0..31: x over the two halves, lanes 32..63: y
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  };
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(fold32(a, b)), __float_as_uint(fold32(c, d)), false, false);
+  float m = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  m = xlane_max_step<0>(m); m = xlane_max_step<1>(m); m = xlane_max_step<2>(m); m = xlane_max_step<3>(m);
+  return m;
+}
+
 __device__ __forceinline__ float wave_incl_scan(float v, int lane) {
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
@@ -112,7 +126,11 @@ __device__ __forceinline__ float wave_incl_scan(float v, int lane) {
 
 // One workgroup per sequence.  Its wavefronts first reduce the chunk statistics of all N rows side by side (one memory
 // round trip instead of one per step of the walk); then the first wavefront walks on values in LDS, and only the bonus draw
-// goes back to memory.  Sampled walk over 64 8-node trees: 17.4 us when each step fetched its row's statistics.
+// goes back to memory.  Sampled walk over 64 8-node trees: 17.4 us when each step fetched its row's statistics, 9.6 us now.  A big
+// tree of which nothing is accepted uses one row of the 60: the loads of all rows and of the nodes are requested together, and
+// the maxima of a wavefront's four rows reduced together (60 nodes, 32000 logits, greedy, both kernels: 6.5 us with a fetch per
+// step, 8.2 us when each row was loaded and reduced by itself; some nodes accepted: 11.0, 9.4 and 7.0 us now).
+constexpr int ROWS_PER_WAVE = 4;               // up to 64 nodes on up to 16 wavefronts
 __global__ __launch_bounds__(1024) void accept_walk_kernel(const float* __restrict__ logits,
                                                         const int32_t* __restrict__ tree_tok,
                                                         const int32_t* __restrict__ parent, int N, int V, int n_chunks, bool vec4,
@@ -121,28 +139,62 @@ __global__ __launch_bounds__(1024) void accept_walk_kernel(const float* __restri
                                                         int32_t* __restrict__ path, int32_t* __restrict__ bonus_tok) {
   __shared__ float row_max[64], row_tot[64];
   __shared__ int row_arg[64];
-  const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
-  for (int r = wave; r < N; r += n_waves) {
-    const float* st = stats + (size_t)(b * N + r) * n_chunks * 4;
-    float mx = -INFINITY;
-    int am = INT_MAX;
-    for (int c = lane; c < n_chunks; c += 64) {
-      const float2 s = *(const float2*)(st + c * 4);
-      const int i = __float_as_int(s.y);
-      if (s.x > mx || (s.x == mx && i < am)) { mx = s.x; am = i; }
-    }
-    wave_best_pair(mx, am);
+  const int b = blockIdx.x, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
+  const int my_par = lane < N ? parent[b * N + lane] : INT_MIN;
+  const int my_tok = lane < N ? tree_tok[b * N + lane] : -1;
+  float4 first[ROWS_PER_WAVE];                 // this lane's first chunk of the wavefront's rows
+#pragma unroll
+  for (int j = 0; j < ROWS_PER_WAVE; ++j) {
+    const int r = wave + j * n_waves;
+    first[j] = make_float4(-INFINITY, __int_as_float(INT_MAX), 0.f, 0.f);
+    if (r < N && lane < n_chunks) first[j] = *(const float4*)(stats + ((size_t)(b * N + r) * n_chunks + lane) * 4);
+  }
+  auto arg_at = [&](int j, float mx) -> int {  // lane = chunk: the first lane that holds the max has the smallest index
+    const unsigned long long at = __ballot(first[j].x == mx);
+    return __builtin_amdgcn_readlane(__float_as_int(first[j].y), at ? __ffsll((long long)at) - 1 : 0);
+  };
+  auto finish = [&](int j, float mx, int am) {
+    const int r = wave + j * n_waves;
     float tot = 0.f;
     if (!greedy) {
-      for (int c = lane; c < n_chunks; c += 64) tot += st[c * 4 + 2] * expf(st[c * 4] - mx);
+      if (lane < n_chunks) tot = first[j].z * expf(first[j].x - mx);
+      for (int c = lane + 64; c < n_chunks; c += 64) {
+        const float* st = stats + ((size_t)(b * N + r) * n_chunks + c) * 4;
+        tot += st[2] * expf(st[0] - mx);
+      }
       tot = wave_sum_butterfly(tot);
     }
     if (lane == 0) { row_max[r] = mx; row_arg[r] = am; row_tot[r] = tot; }
+  };
+  if (n_chunks > 64) {
+#pragma unroll
+    for (int j = 0; j < ROWS_PER_WAVE; ++j)
+      if (wave + j * n_waves < N) {
+        const float* st = stats + (size_t)(b * N + wave + j * n_waves) * n_chunks * 4;
+        float mx = first[j].x;
+        int am = __float_as_int(first[j].y);
+        for (int c = lane + 64; c < n_chunks; c += 64) {
+          const float2 s = *(const float2*)(st + c * 4);
+          const int i = __float_as_int(s.y);
+          if (s.x > mx || (s.x == mx && i < am)) { mx = s.x; am = i; }
+        }
+        wave_best_pair(mx, am);
+        finish(j, mx, am);
+      }
+  } else if (wave + n_waves >= N) {
+    const float mx = wave_max(first[0].x);
+    if (wave < N) finish(0, mx, arg_at(0, mx));
+  } else {                                     // the maxima of four rows together: a quarter of the steps, which up to four
+    float mx = wave_max4(first[0].x, first[1].x, first[2].x, first[3].x);      // wavefronts share on each SIMD
+#pragma unroll
+    for (int j = 0; j < ROWS_PER_WAVE; ++j)
+      if (wave + j * n_waves < N) {
+        const float m = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(mx), 16 * ((j & 1) << 1 | j >> 1)));
+        finish(j, m, arg_at(j, m));
+      }
   }
   __syncthreads();
   if (wave > 0) return;
-  const int my_par = lane < N ? parent[b * N + lane] : INT_MIN;
-  const int my_tok = lane < N ? tree_tok[b * N + lane] : -1;
   if (lane < N) path[b * N + lane] = lane == 0 ? 0 : -1;
   // what the child tests of the stochastic walk read, fetched for every node at once: the target's logit of the node's
   // own token at its parent's row, and the node's uniform (one memory round trip instead of one per tested child)
@@ -293,7 +345,7 @@ hipError_t launch_accept(const float* logits, const int32_t* tree_tok, const int
   else hipLaunchKernelGGL(accept_stats_kernel<true>, grid, dim3(256), 0, st, logits, V, n_chunks, vec4, inv_t, scratch);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(accept_walk_kernel, dim3(B), dim3(64 * std::min(N, 16)), 0, st, logits, tree_tok, parent, N, V, n_chunks, vec4, inv_t, greedy,
+  hipLaunchKernelGGL(accept_walk_kernel, dim3(B), dim3(64 * std::min(N, 64 / ROWS_PER_WAVE)), 0, st, logits, tree_tok, parent, N, V, n_chunks, vec4, inv_t, greedy,
                      uniforms, scratch, accept_len, path, bonus);
   return hipGetLastError();
 }

@@ -45,3 +45,10 @@ def test_accept_matches_the_oracle(V, N, shift, temperature):
                 continue
         assert (int(n[b]), int(bonus[b])) == (want[0], want[2])
         assert path[b, :want[0] + 1].tolist() == list(want[1]) and (path[b, want[0] + 1:] == -1).all()
+
+
+# more chunks than lanes (131072 entries), and node counts around the rows of a wavefront (16, 32, 48)
+@pytest.mark.parametrize("V,N", [(131072, 33), (131073, 5), (133124, 17), (140000, 64), (2052, 31), (2052, 32), (2052, 33), (2052, 48), (2052, 49)])
+@pytest.mark.parametrize("temperature", [0.0, 0.7])
+def test_accept_over_many_chunks_and_rows(V, N, temperature):
+    test_accept_matches_the_oracle(V, N, 0, temperature)
