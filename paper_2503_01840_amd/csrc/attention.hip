@@ -466,10 +466,9 @@ __global__ __launch_bounds__(256) void attn_tree_f32_kernel(const float* __restr
   mx = block_max(mx, red);
   float sum = 0.f;
   for (int kk = tid; kk < L; kk += 256) {
-    const bool vis = visible(kk);
-    const float e = expf(sc[kk] - mx);
-    sc[kk] = vis ? e : -1.f;                // negative: leave the value out (a weight of zero would let an infinity through)
-    sum += vis ? e : 0.f;
+    const float e = expf(sc[kk] - mx);      // exp(-inf) = 0 for masked slots
+    sc[kk] = e;
+    sum += e;
   }
   sum = block_sum(sum, red);                // also publishes sc
   const int groups = 256 / d, grp = tid / d, i = tid - grp * d;
@@ -477,16 +476,18 @@ __global__ __launch_bounds__(256) void attn_tree_f32_kernel(const float* __restr
   if (grp < groups) {
     const float* v0 = vc + ((size_t)si.kv_base * Hkv + g) * d + i;
 #pragma unroll 8
-    for (int kk = grp; kk < L; kk += groups) {
-      const float w = sc[kk], v = v0[(size_t)kk * Hkv * d];
-      acc = w < 0.f ? acc : fmaf(w, v, acc);
-    }
+    for (int kk = grp; kk < L; kk += groups) acc = fmaf(sc[kk], v0[(size_t)kk * Hkv * d], acc);
   }
   part[tid] = acc;
   __syncthreads();
   if (tid < d) {
     acc = 0.f;
     for (int j = 0; j < groups; ++j) acc += part[j * d + tid];
+    if (fmaf(acc, 0.f, 0.f) != 0.f) {       // not finite: again without the slots that the row does not see (0 x Inf is NaN)
+      acc = 0.f;
+      for (int kk = 0; kk < L; ++kk)
+        if (visible(kk)) acc = fmaf(sc[kk], vc[((size_t)(si.kv_base + kk) * Hkv + g) * d + tid], acc);
+    }
     out[(size_t)r * H * d + h * d + tid] = acc / sum;
   }
 }
