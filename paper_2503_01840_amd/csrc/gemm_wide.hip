@@ -23,6 +23,7 @@
 //     as fragment-major bf16 (8-byte stores).
 #include "common.hpp"
 #include "kernels.hpp"
+#include "wide_tiles.hpp"
 
 namespace {
 
@@ -268,47 +269,10 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   p.nmat = W.nmat; p.mode = W.mode;
   p.M = M; p.N = N; p.K = K; p.epi = epi;
   p.out_f32 = (float*)out; p.out_xf = (bf16_t*)out;
-  const int KT = K / BK;
-  // 256 x 256 tiles when there are enough rows and, with at least 16 stages left per workgroup after split-K,
-  // enough workgroups; 129..256 rows: ONE 256-row block x 128 weight rows per workgroup (8 wavefronts x 64 x 64), so that
-  // every weight line enters exactly one CU and a stage takes in 48 KB instead of the 2 x 32 KB of two 128 x 128
-  // workgroups (measured at 256 rows, 8B shapes: q/k/v 33.4 -> 26.6 us, down 54.3 -> 47.6, gate/up 86.0 -> 78.9);
-  // else 128 x 128 tiles, two workgroups per CU (below 384 rows, and where few weight rows leave 256-row tiles short of
-  // workgroups).
-  auto pick = [&](int TM, int TN, int want, int min_stages, int* S_pick) {
-    const int wgs = ((N + TN - 1) / TN) * ((M + TM - 1) / TM);
-    int S = 1;
-    if (epi == GEMM_EPI_PARTIAL)
-      for (int s = 1; s <= 8 && wgs * S < want; ++s) {
-        if (KT % s) continue;
-        if (s > 1 && ((size_t)s * M * N > out_capacity_floats || KT / s < min_stages)) break;
-        S = s;
-      }
-    *S_pick = S;
-    return wgs * S;
-  };
-  int S = 1, cfg = 0;
-  if (M > 128 && M <= 256) {
-    cfg = 2;
-    pick(256, 128, 192, 8, &S);
-  } else if (M < 384 || (pick(256, 256, 160, 16, &S) < 160 && epi == GEMM_EPI_PARTIAL)) {
-    cfg = 1;
-    pick(128, 128, 384, 8, &S);
-  }
-  // 192 instead of 256 rows per tile where that shortens the longest CU's share of the rows (rounds of 256 workgroups x rows
-  // per tile / K ranges) by more than the 10 % that the smaller tile costs, and for gate/up instead of the 128 x 128 tiles.
-  // Whole passes of the 8B shape, 6 layers, 256 (or 128) -> 192 rows: 300 rows 2.21 -> 2.02 ms, 520 rows 3.49 -> 3.02 (512
-  // rows fill one round of gate/up, 520 start a second), 700 rows 3.32 -> 2.96, 1100 rows 4.58 -> 4.12; where it is not taken:
-  // 2048 rows 6.52 against 6.79.
-  if (cfg == 0 || (cfg == 1 && epi == GEMM_EPI_SWIGLU && M > 256)) {
-    auto share = [&](int TM, int s) { return (((N + 255) / 256) * ((M + TM - 1) / TM) * s + 255) / 256 * TM / (double)s; };
-    int s192 = 1;
-    pick(192, 256, 160, 16, &s192);
-    if (cfg == 1 || 1.1 * share(192, s192) < share(256, S)) { cfg = 3; S = s192; }
-  }
-  p.S = S;
-  if (S_out) *S_out = S;
-  if (cfg == 2) return launch_cfg<4, 2, 2, 2, 1>(p, S, st, ev_start, ev_stop);
-  if (cfg == 3) return launch_cfg<2, 4, 3, 2, 1>(p, S, st, ev_start, ev_stop);
-  return cfg == 0 ? launch_cfg<2, 4, 4, 2, 1>(p, S, st, ev_start, ev_stop) : launch_cfg<2, 2, 2, 2, 2>(p, S, st, ev_start, ev_stop);
+  const WideTiles t = wide_tiles(M, N, K, epi == GEMM_EPI_SWIGLU, out_capacity_floats);
+  p.S = t.S;
+  if (S_out) *S_out = t.S;
+  if (t.cols == 128)
+    return t.rows == 256 ? launch_cfg<4, 2, 2, 2, 1>(p, t.S, st, ev_start, ev_stop) : launch_cfg<2, 2, 2, 2, 2>(p, t.S, st, ev_start, ev_stop);
+  return t.rows == 256 ? launch_cfg<2, 4, 4, 2, 1>(p, t.S, st, ev_start, ev_stop) : launch_cfg<2, 4, 3, 2, 1>(p, t.S, st, ev_start, ev_stop);
 }

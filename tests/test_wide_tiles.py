@@ -1,0 +1,51 @@
+"""The tile rule of the many-row product (host code): it takes the 192-row tiles only where they were measured to be the faster ones.
+No GPU: the rule is compiled with the host compiler."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+BIG = 1 << 40
+
+# (rows M, outputs N, inputs K, SwiGLU): microseconds with the tile that the rule would take without 192-row tiles, with those
+MEASURED = [
+    ((300, 28672, 4096, 1), 120, 86), ((520, 28672, 4096, 1), 194, 160), ((1100, 28672, 4096, 1), 302, 257),      # 8B width
+    ((2048, 28672, 4096, 1), 423, 446), ((600, 6144, 4096, 0), 67, 47), ((1100, 4096, 14336, 0), 167, 133),
+    ((383, 57344, 8192, 1), 418, 355), ((600, 57344, 8192, 1), 648, 674),           # 70B width
+    ((300, 2048, 512, 1), 8.5, 16), ((300, 5632, 1024, 1), 12.6, 23), ((2048, 5632, 1024, 1), 32, 48),           # narrow models
+    ((300, 11264, 2048, 1), 30, 41), ((2048, 11264, 2048, 1), 109, 128), ((383, 16384, 3072, 1), 58, 62),
+    ((300, 37888, 3584, 1), 122, 143), ((400, 5120, 5120, 0), 40, 61), ((1024, 5120, 5120, 0), 65, 101),
+    ((2048, 5120, 13824, 0), 303, 474), ((2048, 2560, 2560, 0), 44, 60), ((900, 2560, 6912, 0), 55, 76),
+    ((1024, 5120, 3072, 0), 44, 68), ((900, 3072, 8192, 0), 65, 89), ((1100, 3072, 3072, 0), 38, 52),
+]
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    d = tmp_path_factory.mktemp("tiles")
+    (d / "m.cpp").write_text('#include <cstdio>\n#include "wide_tiles.hpp"\n'
+                             'int main() { int m, n, k, s; long long c; while (scanf("%d %d %d %d %lld", &m, &n, &k, &s, &c) == 5) {\n'
+                             '  WideTiles t = wide_tiles(m, n, k, s, c); printf("%d %d %d\\n", t.rows, t.cols, t.S); } }\n')
+    inc = os.path.join(ROOT, "paper_2503_01840_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(d / "m.cpp"), "-o", str(d / "m")], check=True)
+
+    def ask(queries):
+        text = "\n".join(" ".join(map(str, q)) for q in queries) + "\n"
+        out = subprocess.run([str(d / "m")], input=text, capture_output=True, text=True, check=True).stdout
+        return [tuple(map(int, line.split())) for line in out.splitlines()]
+    return ask
+
+
+def test_192_row_tiles_where_they_are_the_faster_ones(rule):
+    for (q, without, with192), (rows, cols, S) in zip(MEASURED, rule([q + (BIG,) for q, _, _ in MEASURED])):
+        assert (rows == 192) == (with192 < without), (q, rows, cols, S)
+
+
+def test_every_choice_can_be_launched(rule):
+    qs = [(M, N, K, s, cap) for M in (65, 128, 129, 256, 257, 383, 384, 520, 1000, 2048) for N in (256, 768, 5120, 28672)
+          for K in (128, 256, 2816, 4096, 14336) for s in (0, 1) for cap in (0, 2048 * 5120, BIG)]
+    tiles = {(256, 256), (192, 256), (256, 128), (128, 128)}
+    for (M, N, K, s, cap), (rows, cols, S) in zip(qs, rule(qs)):
+        assert (rows, cols) in tiles and 1 <= S <= 8 and (K // 64) % S == 0
+        assert S == 1 or (not s and S * M * N <= cap)
