@@ -107,8 +107,14 @@ typedef struct {
 /* ---- life cycle (host only; these may synchronise) ---------------------------------------------- */
 int eagle3_create(const eagle3_config* cfg, eagle3_ctx** out);
 int eagle3_destroy(eagle3_ctx* ctx);
+/* The workspace in which everything runs at full speed.  Most of it is for eagle3_prefill, which takes a prompt in chunks of
+ * up to 2048 positions (fp32: 256): 420 MiB for the 8B shape at batch 1, 781 MiB for 70B. */
 int eagle3_workspace_bytes(const eagle3_ctx* ctx, size_t* out);
-int eagle3_set_workspace(eagle3_ctx* ctx, void* dev, size_t bytes);      /* 256-byte aligned device memory */
+/* 256-byte aligned device memory.  Fewer bytes than eagle3_workspace_bytes are accepted as well, as long as the step calls fit
+ * (48 MiB, 71 MiB): eagle3_prefill then runs in the longest chunks that do, which changes its time (8B, 2048 tokens: 32 ms, 36 with
+ * half of the part that is for prefill, 43 with a quarter, 138 with none) and, as sums are formed in another order, its
+ * last bits.  EAGLE3_E_STATE, and the workspace set before stays, if even the step calls do not fit. */
+int eagle3_set_workspace(eagle3_ctx* ctx, void* dev, size_t bytes);
 int eagle3_set_weights(eagle3_ctx* ctx, const eagle3_target_weights* target /* may be NULL */,
                        const eagle3_draft_weights* draft /* may be NULL */);
 const char* eagle3_strerror(int code);
@@ -202,7 +208,7 @@ int eagle3_draft_chain(eagle3_ctx* ctx, int32_t B, const float* g_new, const int
 /* Section 3.1, first paragraph of the pipeline: during the prefill phase the target model runs over the prompt, the
  * low / mid / high feature sequences of its positions are recorded and fused, and the draft model's context is built
  * from them.  One sequence.  The T prompt tokens are run through every target layer in chunks of
- * up to 2048 positions (each on top of everything cached before it), their keys and
+ * up to 2048 positions (fp32: 256; fewer in a smaller workspace), each on top of everything cached before it, their keys and
  * values are appended to the target cache at slots prefix_len .. prefix_len + T - 1, and for every position i whose
  * following token is known (all but the last) the draft layer's key / value of the row (g_i, tokens[i+1]) is appended
  * to the draft cache (a draft row's key and value depend only on that row, so no draft attention runs here).

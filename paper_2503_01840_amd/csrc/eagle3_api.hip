@@ -30,9 +30,10 @@ int fail_hip(hipError_t e, const char* what) {
 
 size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 
-// Rows of a prefill chunk.  bf16: one pass over the weights serves the whole chunk, and from about 2048 rows on the products
-// run at the matrix cores' rate and more rows no longer help (an 8B-shaped prompt of 2048 tokens, 32 layers: 139.6 ms in chunks
-// of 64).  fp32 (small models, exact kernels): enough rows to amortise the launches.
+// Rows of a prefill chunk, as far as the workspace that the caller hands over holds them.  bf16: one pass over the weights serves
+// the whole chunk, and from about 2048 rows on the products run at the matrix cores' rate and more rows no longer help
+// (an 8B-shaped prompt of 2048 tokens, 32 layers: 139.6 ms in chunks of 64).  fp32 (small models, exact kernels): enough rows
+// to amortise the launches.
 constexpr int PREFILL_ROWS_BF16 = 2048, PREFILL_ROWS_FP32 = 256;
 
 struct Carver {          // first pass (base == nullptr) measures, second pass hands out pointers
@@ -57,7 +58,8 @@ struct eagle3_ctx {
   eagle3_draft_weights dw;
   bool has_target = false, has_draft = false;
   void* ws = nullptr;
-  size_t ws_bytes = 0, ws_need = 0;
+  size_t ws_bytes = 0, ws_full = 0;     // ws_full: with prefill chunks of full length
+  size_t ws_need = 0;                   // ws_need: of the present sizes (size_for)
 
   // optional per-launch timing of the GEMMs
   bool profiling = false;
@@ -65,23 +67,49 @@ struct eagle3_ctx {
   std::vector<Stamp> stamps;
   size_t stamps_used = 0;
 
-  int R_max, Md_max, Rall, a_rows, pool_max;     // Rall: rows of the widest launch, a multiple of 64
+  int R_max, Md_max, Rall, a_rows, pool_max;     // Rall: rows of the widest launch
   size_t part_floats, attn_floats;
   // workspace
   float* x; void* act_k; void* act_attn; void* act_h; void* q; float* part; float* attn_scratch;
   int32_t* depth; uint32_t* mask; int32_t* slot; float* cs; SeqInfo* seq;
   float* accept_stats;
   float* z; float* a_buf; int32_t* pos1; float* topk_scratch; DraftState ds;
-  int chunk_max;                        // rows per prefill chunk
+  int chunk_max;                        // rows per prefill chunk: a multiple of 64, or fewer than 64
   float* chunk_taps; float* chunk_g;
   int rows1_max;                        // rows per sequence of a chain batch's forward 1
   ChainState cs_chain;
+
+  int chunk_full() const { return bf16 ? PREFILL_ROWS_BF16 : PREFILL_ROWS_FP32; }
+  int chunk_least() const { return std::min(cfg.max_nodes, cfg.max_new); }      // prefill adds no rows to those of the step calls
+
+  // Sizes of everything when prefill runs in chunks of `chunk` rows.
+  void size_for(int chunk) {
+    const eagle3_config& c = cfg;
+    chunk_max = chunk;
+    const int R_step = std::max(R_max, Md_max);
+    Rall = std::max(R_step, chunk);
+    const size_t widest = std::max<size_t>((size_t)(c.n_heads + 2 * c.n_kv_heads) * c.head_dim, c.hidden);
+    // split-K partial sums: up to 4 slices of the widest projection, 8 of a hidden-sized one; 2 for a prefill chunk, whose
+    // many rows fill the chip without more
+    part_floats = std::max<size_t>({1024 * widest, 4 * (size_t)R_step * widest, 8 * (size_t)R_step * c.hidden, 2 * (size_t)chunk * widest});
+    size_t af = 0;
+    auto attention = [&](int batch, int rows) {
+      const int s = attention_pick_splits(batch, rows, c.n_heads, c.n_kv_heads, 1 << 30);
+      af = std::max(af, attention_scratch_floats(batch * rows, c.n_heads, c.head_dim, s));
+    };
+    for (int b = 1; b <= c.max_batch; ++b) attention(b, c.max_nodes);
+    attention(1, Md_max);
+    // prefill: blocks of 64 rows, as long as their number can be one that the unsplit kernel does not take at every length
+    for (int b = 1; 64 * b <= chunk && !prefill_attention_fits(64 * (b - 1) + 1, c.n_heads, c.n_kv_heads, 1 << 30); ++b) attention(b, 64);
+    attn_floats = bf16 ? af : 1;
+    carve(nullptr);
+  }
 
   void carve(void* base) {
     const eagle3_config& c = cfg;
     Carver cv(base);
     const size_t k = c.hidden, I = c.intermediate, Hd = (size_t)c.n_heads * c.head_dim;
-    const size_t Rpad = Rall;
+    const size_t Rpad = (size_t)(Rall + 63) / 64 * 64;
     x = cv.take<float>((size_t)Rall * k);
     act_k = cv.take<char>(Rpad * 3 * k * act_size);
     act_attn = cv.take<char>(Rpad * Hd * act_size);
@@ -215,29 +243,11 @@ int eagle3_create(const eagle3_config* cfg, eagle3_ctx** out) {
   ctx->act_size = ctx->bf16 ? 2 : 4;
   ctx->R_max = c.max_batch * c.max_nodes;
   ctx->Md_max = std::max(c.max_new, c.max_topk);
-  ctx->chunk_max = ctx->bf16 ? PREFILL_ROWS_BF16 : PREFILL_ROWS_FP32;
-  ctx->Rall = (std::max({ctx->R_max, ctx->Md_max, ctx->chunk_max}) + 63) / 64 * 64;
   ctx->a_rows = c.max_new + (c.max_depth - 1) * c.max_topk;
   ctx->rows1_max = std::min(c.max_nodes, c.max_new);
   ctx->pool_max = 1 + c.max_topk + (c.max_depth - 1) * c.max_topk * c.max_topk;
-  const size_t widest = std::max<size_t>({(size_t)(c.n_heads + 2 * c.n_kv_heads) * c.head_dim, (size_t)c.hidden,
-                                          ctx->bf16 ? (size_t)0 : (size_t)2 * c.intermediate});
-  // split-K partial sums: up to 4 slices of the widest projection, 8 of a hidden-sized one; 2 for a prefill chunk, whose
-  // many rows fill the chip without more
-  const size_t R_step = std::max(ctx->R_max, ctx->Md_max);
-  ctx->part_floats = std::max<size_t>({1024 * widest, 4 * R_step * widest, 8 * R_step * c.hidden, 2 * (size_t)ctx->chunk_max * widest});
-  size_t af = 0;
-  for (int b = 1; b <= c.max_batch; ++b) {
-    const int s = attention_pick_splits(b, c.max_nodes, c.n_heads, c.n_kv_heads, 1 << 30);
-    af = std::max(af, attention_scratch_floats(b * c.max_nodes, c.n_heads, c.head_dim, s));
-  }
-  af = std::max(af, attention_scratch_floats(ctx->Md_max, c.n_heads, c.head_dim,
-                                             attention_pick_splits(1, ctx->Md_max, c.n_heads, c.n_kv_heads, 1 << 30)));
-  for (int b = 1; 64 * b <= ctx->chunk_max; ++b)         // prefill: blocks of 64 rows
-    af = std::max(af, attention_scratch_floats(64 * b, c.n_heads, c.head_dim,
-                                               attention_pick_splits(b, 64, c.n_heads, c.n_kv_heads, 1 << 30)));
-  ctx->attn_floats = ctx->bf16 ? af : 1;
-  ctx->carve(nullptr);
+  ctx->size_for(ctx->chunk_full());
+  ctx->ws_full = ctx->ws_need;
   *out = ctx;
   return EAGLE3_OK;
 }
@@ -254,17 +264,26 @@ int eagle3_destroy(eagle3_ctx* ctx) {
 
 int eagle3_workspace_bytes(const eagle3_ctx* ctx, size_t* out) {
   if (!ctx || !out) return EAGLE3_E_NULL;
-  *out = ctx->ws_need;
+  *out = ctx->ws_full;
   return EAGLE3_OK;
 }
 
 int eagle3_set_workspace(eagle3_ctx* ctx, void* dev, size_t bytes) {
   if (!ctx || !dev) return EAGLE3_E_NULL;
-  if (bytes < ctx->ws_need || ((uintptr_t)dev & 255)) return EAGLE3_E_STATE;
-  ctx->ws = dev;
-  ctx->ws_bytes = bytes;
-  ctx->carve(dev);
-  return EAGLE3_OK;
+  if ((uintptr_t)dev & 255) return EAGLE3_E_STATE;
+  // the longest prefill chunks that fit
+  const int before = ctx->chunk_max, least = ctx->chunk_least();
+  for (int chunk = ctx->chunk_full(); chunk >= least; chunk = chunk > 64 ? chunk - 64 : chunk > least ? least : 0) {
+    ctx->size_for(chunk);
+    if (ctx->ws_need > bytes) continue;
+    ctx->ws = dev;
+    ctx->ws_bytes = bytes;
+    ctx->carve(dev);
+    return EAGLE3_OK;
+  }
+  ctx->size_for(before);
+  ctx->carve(ctx->ws);
+  return EAGLE3_E_STATE;
 }
 
 int eagle3_set_weights(eagle3_ctx* ctx, const eagle3_target_weights* t, const eagle3_draft_weights* d) {

@@ -145,3 +145,23 @@ def device_kv(pairs, extra_slots, device="cuda:0"):
     indptr = torch.tensor([0, P + extra_slots], dtype=torch.int32, device=device)
     plen = torch.tensor([P], dtype=torch.int32, device=device)
     return ks, vs, indptr, plen, P
+
+
+def shrink_workspace(ctx, part=0.0):
+    """Hands the context's workspace over again with fewer bytes: the least that the library accepts (prefill then runs in
+    chunks of min(max_nodes, max_new) rows) plus `part` of what is between that and the whole of it."""
+    from paper_2503_01840_amd import binding as Bd
+    L, at = Bd.lib(), ctx._ws.data_ptr() + (-ctx._ws.data_ptr()) % 256
+    lo, hi = 0, ctx.workspace_bytes
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if L.eagle3_set_workspace(ctx._h, at, mid) == 0 else (mid, hi)
+    n = hi + int(part * (ctx.workspace_bytes - hi))
+    assert L.eagle3_set_workspace(ctx._h, at, n) == 0
+    ctx._ws[n + at - ctx._ws.data_ptr():] = 171                  # what is not handed over stays as it is
+    return n
+
+
+def beyond_workspace(ctx, n):
+    """The bytes of the buffer after the first n of the workspace."""
+    return ctx._ws[n + (-ctx._ws.data_ptr()) % 256:]

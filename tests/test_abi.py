@@ -71,3 +71,36 @@ def test_bf16_configuration_limits(L):
         kw.update(bad)
         c = _cfg(**kw)
         assert L.eagle3_create(C.byref(c), C.byref(h)) == -2, bad
+
+
+# (configuration, bytes) that were enough when prefill ran in chunks of min(max_nodes, max_new) rows: 8B at batch 1 and 64, 70B,
+# one node only, a small bf16 model, tiny fp32 ones
+_B8 = dict(hidden=4096, n_heads=32, n_kv_heads=8, head_dim=128, intermediate=14336, vocab=128256, draft_vocab=32000, n_layers=32,
+           dtype=Bd.EAGLE3_BF16, max_depth=8, max_topk=10, max_nodes=60, max_new=8)
+_ENOUGH = [
+    (_B8, 49807360), (dict(_B8, hidden=8192, n_heads=64, intermediate=28672), 73793536),
+    (dict(_B8, max_batch=64, max_nodes=8, max_topk=2, max_new=64), 146159616),
+    (dict(_B8, max_nodes=1, max_depth=1, max_topk=1, max_new=1), 30407168),
+    (dict(dtype=Bd.EAGLE3_BF16, n_heads=2, n_kv_heads=1, head_dim=128, intermediate=256, max_batch=5, max_nodes=9, max_topk=3, max_new=10), 7852032),
+    (dict(), 6181632), (dict(max_batch=3, max_nodes=64, max_depth=8, max_topk=10, max_new=64), 8422144),
+]
+
+
+@pytest.mark.parametrize("over,enough", _ENOUGH)
+def test_a_workspace_below_the_full_one_is_accepted(L, over, enough):
+    h, full = C.c_void_p(), C.c_size_t()
+    c = _cfg(**over)
+    assert L.eagle3_create(C.byref(c), C.byref(h)) == 0
+    assert L.eagle3_workspace_bytes(h, C.byref(full)) == 0
+    at = C.c_void_p(4096)                                       # host arithmetic only: never dereferenced
+    assert L.eagle3_set_workspace(h, at, enough) == 0
+    assert L.eagle3_set_workspace(h, at, full.value) == 0
+    lo, hi = 0, full.value                                      # the least that is accepted
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if L.eagle3_set_workspace(h, at, mid) == 0 else (mid, hi)
+    assert 0 < hi <= enough
+    assert L.eagle3_set_workspace(h, at, hi - 1) == -3 and L.eagle3_set_workspace(h, C.c_void_p(4096 + 128), full.value) == -3
+    again = C.c_size_t()
+    assert L.eagle3_workspace_bytes(h, C.byref(again)) == 0 and again.value == full.value
+    L.eagle3_destroy(h)

@@ -148,7 +148,7 @@ def test_commit_moves_rows_in_every_layer_for_a_ragged_batch():
 @pytest.mark.parametrize("chunk", [64, 24])
 def test_prefill_builds_caches_features_and_the_draft_context(chunk):
     """eagle3_prefill against the oracle's prefill (tiny fp32 model, 64-token prompt; one chunk of 64, and chunks of
-    24 + 24 + 16): target cache of every layer, draft cache, fused feature and logits of the last position; then
+    24 + 24 + 16, in the least workspace): target cache of every layer, draft cache, fused feature and logits of the last position; then
     decoding continues from the GPU-built state and still equals plain greedy decoding."""
     import paper_2503_01840_amd as E
     shape = S.get_shape("c1")
@@ -157,6 +157,7 @@ def test_prefill_builds_caches_features_and_the_draft_context(chunk):
     inp = PL.real_prefill_inputs(shape, model)
     prompt, pre, P = inp["prefix_tok"], inp["prefill"], inp["P"]
     ctx = E.Eagle3Context(shape, max_batch=1, max_nodes=chunk, max_depth=D, max_topk=K, max_new=chunk, device=DEV)
+    PL.shrink_workspace(ctx)
     W = PL.device_weights(shape, device=DEV)
     ctx.set_weights(W["target"], W["draft"])
     cap = P + 8 * (D + 1) + 64
@@ -312,7 +313,7 @@ def test_batched_chain_decoding_equals_plain_greedy_decoding_per_sequence():
 
 
 def test_prefill_bf16_two_chunks_matches_the_oracle():
-    """bf16 storage: a 70-token prompt in chunks of 64 + 6 against the oracle's prefill in bf16 mode (2-layer model, so
+    """bf16 storage: a 70-token prompt in chunks of 64 + 6 (the least workspace) against the oracle's prefill in bf16 mode (2-layer model, so
     the single-layer tolerances apply): target cache, draft cache, fused feature and logits of the last position."""
     import paper_2503_01840_amd as E
     shape = S.get_shape("c2").with_(name="small", hidden=256, n_heads=4, n_kv_heads=2, intermediate=512, vocab=1024,
@@ -327,6 +328,7 @@ def test_prefill_bf16_two_chunks_matches_the_oracle():
     O.draft_forward(shape, dw, emb, g_all[:T - 1], prompt[1:], np.arange(T - 1), Kd, Vd, 0, 0,
                     np.tril(np.ones((T - 1, T - 1), dtype=bool)), O.bf16_round)
     ctx = E.Eagle3Context(shape, max_batch=1, max_nodes=64, max_depth=4, max_topk=4, max_new=64, device=DEV)
+    PL.shrink_workspace(ctx)
     W = PL.device_weights(shape, device=DEV)
     ctx.set_weights(W["target"], W["draft"])
     cap = T + 16

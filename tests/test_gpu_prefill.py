@@ -16,8 +16,18 @@ DEV = "cuda:0"
 @pytest.mark.parametrize("dtype,T", [("fp32", 64), ("fp32", 129), ("fp32", 256), ("fp32", 257),
                                      ("bf16", 65), ("bf16", 192), ("bf16", 385), ("bf16", 2049)])
 def test_prefill_at_block_and_chunk_edges(dtype, T):
+    _check(S.get_shape("c1") if dtype == "fp32" else SMALL, dtype, T)
+
+
+# three and more chunks: of 256 rows (fp32), and in workspaces of which 0, 2, 10 or 50 % of the part that prefill needs is there
+@pytest.mark.parametrize("dtype,T,part", [("fp32", 513, 1.0), ("fp32", 700, 1.0), ("fp32", 300, 0.0), ("fp32", 300, 0.5), ("bf16", 300, 0.0),
+                                          ("bf16", 700, 0.02), ("bf16", 700, 0.1), ("bf16", 2500, 0.5), ("bf16", 200, 0.0)])
+def test_prefill_in_several_chunks(dtype, T, part):
+    _check(S.get_shape("c1") if dtype == "fp32" else SMALL, dtype, T, part)
+
+
+def _check(shape, dtype, T, part=1.0):
     E = _E()
-    shape = S.get_shape("c1") if dtype == "fp32" else SMALL
     rounding = "none" if dtype == "fp32" else "bf16"
     # fp32: the exact path's 1e-4; bf16: the 2-layer bounds of the two-chunk test (one bf16 ulp of a rotated key at |k| < 8
     # is 2^-5, of everything else below 2e-2)
@@ -31,6 +41,7 @@ def test_prefill_at_block_and_chunk_edges(dtype, T):
     O.draft_forward(shape, dw, emb, g_all[:T - 1], prompt[1:], np.arange(T - 1), Kd, Vd, 0, 0,
                     np.tril(np.ones((T - 1, T - 1), dtype=bool)), O._rounder(rounding))
     ctx = E.Eagle3Context(shape, max_batch=1, max_nodes=8, max_depth=2, max_topk=2, max_new=4, device=DEV)
+    left = PL.shrink_workspace(ctx, part) if part < 1.0 else None
     W = PL.device_weights(shape, device=DEV)
     ctx.set_weights(W["target"], W["draft"])
     i32 = lambda v: torch.tensor(v, dtype=torch.int32, device=DEV)
@@ -49,5 +60,7 @@ def test_prefill_at_block_and_chunk_edges(dtype, T):
     assert np.max(np.abs(f(g_last) - g_all[-1])) < tol
     assert np.max(np.abs(f(dkv.k_layers[0][:T - 1]) - Kd)) < tol_k
     assert np.max(np.abs(f(dkv.v_layers[0][:T - 1]) - Vd)) < tol
+    if left is not None:
+        assert bool((PL.beyond_workspace(ctx, left) == 171).all()), "bytes past the workspace were written"
     for t, n in [(t, T) for t in ks + vs] + [(dkv.k_layers[0], T - 1), (dkv.v_layers[0], T - 1)]:
         assert bool((t[n:] == 7.0).all()), "rows past the prompt were written"

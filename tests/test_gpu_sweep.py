@@ -226,7 +226,7 @@ def test_ttt_attention_sweep():
 
 
 def test_prefill_sweep():
-    """6 random prompts (1..90 tokens) prefilled in chunks of 1..64 positions on the exact fp32 model: the target cache
+    """6 random prompts (1..90 tokens) prefilled in chunks of 1..64 positions (the least workspace) on the exact fp32 model: the target cache
     of every layer, the draft cache, the last position's logits and fused feature against the oracle's prefill."""
     E = _E()
     rs = np.random.RandomState(17 + 100 * SALT)
@@ -240,6 +240,7 @@ def test_prefill_sweep():
         inp = PL.real_prefill_inputs(shape, model, seed=S.SEED + 400 + 10 * SALT + i)
         prompt, pre = inp["prefix_tok"], inp["prefill"]
         ctx = E.Eagle3Context(shape, max_batch=1, max_nodes=chunk, max_depth=2, max_topk=2, max_new=chunk, device=DEV)
+        PL.shrink_workspace(ctx)
         ctx.set_weights(W["target"], W["draft"])
         cap = T + 8
         z = lambda: torch.zeros(cap, shape.n_kv_heads, shape.head_dim, dtype=torch.float32, device=DEV)
