@@ -26,7 +26,15 @@ def test_prefill_in_several_chunks(dtype, T, part):
     _check(S.get_shape("c1") if dtype == "fp32" else SMALL, dtype, T, part)
 
 
-def _check(shape, dtype, T, part=1.0):
+# every grouping of query heads in a workgroup of the causal kernel (four of a group, two such workgroups per KV head, two, one), with
+# the sequence behind others in a larger pool
+@pytest.mark.parametrize("H,Hkv", [(4, 1), (8, 1), (16, 2), (2, 1), (3, 1), (2, 2)])
+@pytest.mark.parametrize("T,base", [(129, 0), (300, 37)])
+def test_prefill_over_head_layouts_and_pool_offsets(H, Hkv, T, base):
+    _check(SMALL.with_(n_heads=H, n_kv_heads=Hkv), "bf16", T, base=base)
+
+
+def _check(shape, dtype, T, part=1.0, base=0):
     E = _E()
     rounding = "none" if dtype == "fp32" else "bf16"
     # fp32: the exact path's 1e-4; bf16: the 2-layer bounds of the two-chunk test (one bf16 ulp of a rotated key at |k| < 8
@@ -46,21 +54,21 @@ def _check(shape, dtype, T, part=1.0):
     ctx.set_weights(W["target"], W["draft"])
     i32 = lambda v: torch.tensor(v, dtype=torch.int32, device=DEV)
     z = lambda n: torch.full((n, shape.n_kv_heads, shape.head_dim), 7.0, dtype=ctx.storage_dtype, device=DEV)
-    ks, vs = [z(T + 3) for _ in range(shape.n_layers)], [z(T + 3) for _ in range(shape.n_layers)]
-    kv = E.KVCache(ks, vs, i32([0, T]), i32([0]), 0)
-    dkv = E.KVCache([z(T + 3)], [z(T + 3)], i32([0, T - 1]), i32([0]), 0)
+    ks, vs = [z(base + T + 3) for _ in range(shape.n_layers)], [z(base + T + 3) for _ in range(shape.n_layers)]
+    kv = E.KVCache(ks, vs, i32([base, base + T]), i32([0]), 0)
+    dkv = E.KVCache([z(base + T + 3)], [z(base + T + 3)], i32([base, base + T - 1]), i32([0]), 0)
     g_last, logits = E.eagle3_prefill(ctx, i32(prompt), kv, dkv)
     torch.cuda.synchronize()
-    f = lambda t: t.float().cpu().numpy()
+    for t, n in [(t, T) for t in ks + vs] + [(dkv.k_layers[0], T - 1), (dkv.v_layers[0], T - 1)]:
+        assert bool((t[:base] == 7.0).all()) and bool((t[base + n:] == 7.0).all()), "rows beside the prompt's were written"
+    f = lambda t: t[base:].float().cpu().numpy() if t.dim() == 3 else t.float().cpu().numpy()
     assert int(kv.prefix_len[0]) == T and int(dkv.prefix_len[0]) == T - 1
     for l in range(shape.n_layers):
-        assert np.max(np.abs(f(ks[l][:T]) - pre["k_new"][l])) < tol_k, l
-        assert np.max(np.abs(f(vs[l][:T]) - pre["v_new"][l])) < tol, l
+        assert np.max(np.abs(f(ks[l])[:T] - pre["k_new"][l])) < tol_k, l
+        assert np.max(np.abs(f(vs[l])[:T] - pre["v_new"][l])) < tol, l
     assert np.max(np.abs(f(logits) - pre["logits"][-1])) < tol
     assert np.max(np.abs(f(g_last) - g_all[-1])) < tol
-    assert np.max(np.abs(f(dkv.k_layers[0][:T - 1]) - Kd)) < tol_k
-    assert np.max(np.abs(f(dkv.v_layers[0][:T - 1]) - Vd)) < tol
+    assert np.max(np.abs(f(dkv.k_layers[0])[:T - 1] - Kd)) < tol_k
+    assert np.max(np.abs(f(dkv.v_layers[0])[:T - 1] - Vd)) < tol
     if left is not None:
         assert bool((PL.beyond_workspace(ctx, left) == 171).all()), "bytes past the workspace were written"
-    for t, n in [(t, T) for t in ks + vs] + [(dkv.k_layers[0], T - 1), (dkv.v_layers[0], T - 1)]:
-        assert bool((t[n:] == 7.0).all()), "rows past the prompt were written"

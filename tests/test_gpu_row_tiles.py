@@ -11,18 +11,29 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# gate/up of the small model in 192-row tiles (257 rows and more): one row over a 64-row piece, over a tile, a full last tile
+# gate/up of the small model in 192-row tiles (384 rows and more) and just above the 256-row line: one row over a 64-row piece, over
+# a tile, a full last tile
 @pytest.mark.parametrize("T", [257, 384, 386, 576, 577])
 def test_prefill_at_192_row_edges(T):
     _prefill_against_the_oracle("bf16", T)
 
 
 # one layer of the 8B shape: 577..640 rows (192-row tiles, split and unsplit, of every projection but the LM head) against the same
-# sequences ten at a time (128- and 256-row tiles)
+# sequences ten (128 x 128 tiles, the last few rows the few-row kernel) and 25 (256 x 128 tiles) at a time
 @pytest.mark.parametrize("B,N", [(58, 10), (60, 10), (64, 10)])
-def test_rows_do_not_depend_on_the_batch(B, N):
+@pytest.mark.parametrize("group", [10, 25])
+def test_rows_do_not_depend_on_the_batch(B, N, group):
+    _rows_alone_and_together(S.get_shape("c3"), B, N, group)
+
+
+# a gate/up of many weight rows in 192-row tiles from 257 rows on: the edges of a tile against at most 64 rows at a time
+@pytest.mark.parametrize("B,N,group", [(257, 1, 64), (64, 6, 10), (77, 5, 12), (64, 9, 7), (577, 1, 50)])
+def test_rows_at_192_row_edges(B, N, group):
+    _rows_alone_and_together(S.get_shape("c3").with_(name="flat", hidden=256, n_heads=4, n_kv_heads=2, vocab=1024), B, N, group)
+
+
+def _rows_alone_and_together(full, B, N, group):
     E = _E()
-    full = S.get_shape("c3")
     shape = full.with_(n_layers=1, taps=(0, 0, 0))
     W = {k: v.to(DEV) for k, v in S.layer_weights(full, 3).items()}
     tg = {k: v.to(DEV) for k, v in S.target_globals(full).items()}
@@ -48,8 +59,8 @@ def test_rows_do_not_depend_on_the_batch(B, N):
         return x_out.cpu().numpy(), k.float().cpu().numpy()
 
     x, k = run(0, B)
-    for b0 in range(0, B, 10):
-        b1 = min(B, b0 + 10)
+    for b0 in range(0, B, group):
+        b1 = min(B, b0 + group)
         xr, kr = run(b0, b1)
         assert np.max(np.abs(x[b0:b1] - xr)) < TOL * max(1.0, _rms(xr))
         assert np.max(np.abs(k[b0 * (P + N):b1 * (P + N)] - kr)) < 4e-2
