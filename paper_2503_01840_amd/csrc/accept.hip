@@ -129,7 +129,7 @@ __device__ __forceinline__ float wave_incl_scan(float v, int lane) {
 // goes back to memory.  Sampled walk over 64 8-node trees: 17.4 us when each step fetched its row's statistics, 9.6 us now.  A big
 // tree of which nothing is accepted uses one row of the 60: the loads of all rows and of the nodes are requested together, and
 // the maxima of a wavefront's four rows reduced together (60 nodes, 32000 logits, greedy, both kernels: 6.5 us with a fetch per
-// step, 8.2 us when each row was loaded and reduced by itself; some nodes accepted: 11.0, 9.4 and 7.0 us now).
+// step, 8.2 us when each row was loaded and reduced by itself, 6.0 us now; some nodes accepted: 11.0, 9.4 and 7.0 us).
 constexpr int ROWS_PER_WAVE = 4;               // up to 64 nodes on up to 16 wavefronts
 __global__ __launch_bounds__(1024) void accept_walk_kernel(const float* __restrict__ logits,
                                                         const int32_t* __restrict__ tree_tok,
