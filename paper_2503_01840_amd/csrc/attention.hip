@@ -416,6 +416,10 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p, int R, bf
     den = 0.f;
     num = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int j = 0; j < si.n_prefix + si.n_tail; ++j) {
+      if ((j & 31) == 31) {                    // a NaN stays one: the row is done when it has nothing else
+        const unsigned long long open = __ballot(num.x == num.x || num.y == num.y || num.z == num.z || num.w == num.w);
+        if ((uint32_t)(open >> (threadIdx.x & 32)) == 0u) break;
+      }
       const int off = j - si.n_prefix;
       if (off >= 0 && !((p.mask[(size_t)r * 4 + ((off >> 5) & 3)] >> (off & 31)) & 1u)) continue;
       const size_t at = ((size_t)(si.kv_base + j) * p.Hkv + g) * D + 4 * d4;
@@ -483,9 +487,9 @@ __global__ __launch_bounds__(256) void attn_tree_f32_kernel(const float* __restr
   if (tid < d) {
     acc = 0.f;
     for (int j = 0; j < groups; ++j) acc += part[j * d + tid];
-    if (fmaf(acc, 0.f, 0.f) != 0.f) {       // not finite: again without the slots that the row does not see (0 x Inf is NaN)
-      acc = 0.f;
-      for (int kk = 0; kk < L; ++kk)
+    if (fmaf(acc, 0.f, 0.f) != 0.f && r % N < si.n_tail) {       // not finite: again without the slots that the row does not see
+      acc = 0.f;                                                 // (0 x Inf is NaN; a NaN stays one)
+      for (int kk = 0; kk < L && acc == acc; ++kk)
         if (visible(kk)) acc = fmaf(sc[kk], vc[((size_t)(si.kv_base + kk) * Hkv + g) * d + tid], acc);
     }
     out[(size_t)r * H * d + h * d + tid] = acc / sum;

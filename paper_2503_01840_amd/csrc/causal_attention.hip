@@ -482,6 +482,16 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
     const size_t own_row = min(q_wave + (lane & 31), T - 1);
 #pragma unroll 1
     for (int j = 0; j < n_orig + (PREFILL ? 0 : p.s); ++j) {
+      if ((j & 31) == 31) {                    // a NaN stays one: nothing left to find out in a wavefront that has nothing else
+        bool open = false;
+#pragma unroll
+        for (int d2 = 0; d2 < 2; ++d2)
+#pragma unroll
+          for (int gq = 0; gq < 4; ++gq)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) open |= val[d2][gq][e] == val[d2][gq][e];
+        if (!__any(open)) break;
+      }
       const size_t at = (j < n_orig ? (size_t)j : (size_t)(j - n_orig + 1) * T + own_row) * row_stride;
       float dot = 0.f;
 #pragma unroll

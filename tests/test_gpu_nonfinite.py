@@ -47,6 +47,16 @@ def test_ttt_attention_keeps_a_bad_position_to_the_rows_that_see_it(H, Hkv, T, a
     assert np.max(np.abs(got[ok] - ref[ok]), initial=0.0) < 2 * 5 * (2e-6 + 2.0 ** -16)
 
 
+# everything NaN (a broken model): the same results, in time that does not grow with the number of keys
+@pytest.mark.parametrize("where", ["k", "v"])
+def test_ttt_attention_of_nothing_but_nan(where):
+    import paper_2503_01840_amd as E
+    T, H, Hkv = 3000, 8, 2
+    q, k, v = (torch.randn(*dims, dtype=torch.bfloat16, device=DEV) for dims in ((T, H, 128), (2, T, Hkv, 128), (2, T, Hkv, 128)))
+    {"k": k, "v": v}[where].fill_(NAN)
+    assert bool(torch.isnan(E.eagle3_ttt_attention(q, k, v)).all())
+
+
 def _prefill(E, shape, W, tokens, parts):
     ctx = E.Eagle3Context(shape, max_batch=1, max_nodes=8, max_depth=2, max_topk=2, max_new=4, device=DEV)
     ctx.set_weights(W["target"], W["draft"])
