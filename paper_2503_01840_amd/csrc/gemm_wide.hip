@@ -2,33 +2,39 @@
 // Y[M, N] = X[M, K] * W[N, K]^T, fp32 accumulate.  At this width the projections sit at the ridge between weight
 // streaming and the MFMA rate, so the kernel is organised around operand reuse and around keeping the loads, the
 // LDS reads and the MFMAs of a wavefront all in flight at once:
-//   * a workgroup owns a (32 FM WGM) x (32 FN WGN) output tile; its WGM x WGN wavefronts each hold FM x FN
-//     accumulators of v_mfma_f32_32x32x16_bf16 and there is no cross-wavefront reduction;
+//   * a workgroup owns a (32 FM WGM) x (32 FN WGN) output tile; its WGM x WGN wavefronts each hold 2 FM x 2 FN
+//     accumulators of v_mfma_f32_16x16x32_bf16 and there is no cross-wavefront reduction.  With many rows the chip is bound by
+//     power: products alone sustain 1.88 PFLOP/s as 32x32x16 and 2.14 as 16x16x32 (the sum over 32 k stays inside the matrix
+//     unit), with their operands read from LDS 1.64 and 1.86.  The sums come out bit for bit the same;
 //   * both operands reach LDS by direct global-to-LDS loads (global_load_lds_dwordx4: each wavefront
 //     instruction deposits 1 KiB contiguously, no staging registers).  A CU accepts roughly one cache line per
 //     four clocks whatever its size, so every request is a whole 128-byte line: activations come in 32-k slots
-//     (ring of 4; their fragment-major global layout already is the MFMA operand order, so the copy is verbatim
-//     and the LDS reads are linear), weights in 64-k slots (ring of 3; eight lanes per 128-byte row piece, and
-//     which 16 bytes a lane fetches is XOR-swizzled with the row index so that the MFMA operand reads, 32 rows x
-//     one piece, touch every bank once);
-//   * one barrier per 32-k half-stage.  The barrier of half-stage h also publishes the data of half-stage h + 1,
-//     so the first operand fragments of h + 1 are read into registers while the MFMAs of h still run and the
-//     matrix pipe does not idle after the next barrier; the four loads a wavefront issues per half-stage are
-//     spread between groups of MFMAs, so that a full load queue never holds up MFMA issue;
+//     (their fragment-major global layout holds every 16-row fragment in one 512-byte run per 16 k, so the copy is verbatim and
+//     the LDS reads are linear), weights in BK-wide slots, whole row pieces of 2 BK bytes, and
+//     which 16 bytes of its row a lane fetches is XOR-swizzled with the row index so that the MFMA operand reads, 16 rows x
+//     one piece, touch every bank once;
+//   * one barrier per 32 k.  The barrier of sub-stage h also publishes the data of sub-stage h + 1,
+//     so its operand fragments are read into a second set of registers while the products of h run; LDS reads and direct loads
+//     are dealt out between the products one by one, so that neither a full load queue nor a burst of reads holds up the matrix
+//     pipe (256 x 256 tiles: 2390 cycles per 64 k, of which 2048 are products; 2600 with them in bursts);
 //   * the workgroups that share a weight tile (one per 256 activation rows) are launched next to each other on
 //     the same XCD, so the tile leaves HBM once;
 //   * the weights are the MFMA's first operand: a lane then holds, for ONE activation row, runs of four
 //     consecutive output columns, which is what both epilogues store: fp32 split-K partials (16-byte stores), or
 //     SwiGLU (the tile interleaves gate and up rows so that both values of a pair sit in the same lane) written
 //     as fragment-major bf16 (8-byte stores).
+// 8B width, us, products as 32x32x16 with the reads and loads in bursts / now: 2048 rows gate/up 422 / 368 (1.31 PFLOP/s), down
+// 214 / 177, o 77 / 57, q/k/v 100 / 87; 512 rows gate/up 116 / 101, down 73 / 60, q/k/v 39 / 35; 256 rows gate/up 77 / 74.
+// Measured and not kept: 4 wavefronts of 128 x 128 each (a third fewer LDS reads: loop 4 % shorter, epilogue longer by the same);
+// K walks that start at different stages (0 to 8 % slower at 512 and 2048 rows).
+#include <utility>
+
 #include "common.hpp"
 #include "kernels.hpp"
 #include "wide_tiles.hpp"
 
 namespace {
 
-constexpr int BK = 64;                  // k per weight slot; the activation slots and the barriers are per BK / 2
-constexpr int A_SLOTS = 4, B_SLOTS = 3;
 
 struct WideParams {
   const bf16_t* x;
@@ -41,44 +47,63 @@ struct WideParams {
   bf16_t* out_xf;
 };
 
-// Global weight row behind row `row` of workgroup tile `tile` (TN rows per tile).
+// Global weight row behind row `row` of workgroup tile `tile` (TN rows per tile).  SwiGLU: every 64 rows of a tile are 32 gate
+// rows and the 32 up rows that belong to them.  Rows past the end repeat the last one.
 template <int TN>
-__device__ __forceinline__ const bf16_t* weight_row(const WideParams& p, int tile, int row) {
-  if (p.mode == 1) {                                   // TN/2 gate rows | TN/2 up rows
-    int r = tile * (TN / 2) + (row % (TN / 2));
-    r = min(r, p.rows[0] - 1);
-    return p.w[row / (TN / 2)] + (size_t)r * p.K;
+__device__ __forceinline__ const bf16_t* weight_row(const WideParams& p, int tile, int row, int& left) {
+  if (p.mode == 1) {
+    const int r = tile * (TN / 2) + (row >> 6) * 32 + (row & 31), last = p.rows[0] - 1;
+    left = max(last - r, 0);
+    return ((row & 32) ? p.w[1] : p.w[0]) + (size_t)min(r, last) * p.K;
   }
   int n = min(tile * TN + row, p.N - 1);
-  int m = 0;
-  while (m + 1 < p.nmat && n >= p.rows[m]) { n -= p.rows[m]; ++m; }
-  return p.w[m] + (size_t)n * p.K;
+  left = p.N - 1 - n;
+  const bf16_t* w = p.w[0];
+  if (p.nmat > 1 && n >= p.rows[0]) {
+    n -= p.rows[0]; w = p.w[1];
+    if (p.nmat > 2 && n >= p.rows[1]) { n -= p.rows[1]; w = p.w[2]; }
+  }
+  return w + (size_t)n * p.K;
 }
 
-// One wavefront-wide direct load: lane l's 16 bytes at `src` land at LDS byte address lds_base + 16 l.
-// The compiler does not see these as memory operations; the kernel counts them itself (s_waitcnt vmcnt).
+// One wavefront-wide direct load: lane l's 16 bytes at base + off land at LDS byte address lds_base + AT + 16 l; base is the
+// same for the whole wavefront.  The compiler does not see these as memory operations; the kernel counts them itself
+// (s_waitcnt vmcnt).
 // (m0 carries the LDS address; naming it as clobbered is what is meant, the compiler's remark about reserved
 // registers on a clobber list is switched off for this one statement.)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void dma16(const void* src, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(src) : "memory", "m0");
+template <int AT>
+__device__ __forceinline__ void dma16(const void* base, uint32_t off, uint32_t lds_base) {
+  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(off), "s"(base), "i"(AT)
+               : "memory", "m0", "scc");
 }
 #pragma clang diagnostic pop
-#define WIDE_WAIT_LOADS(n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n) : "memory")
+// f(0), f(1), ... f(N - 1) with the index as a constant
+template <int... I, typename F>
+__device__ __forceinline__ void unroll_seq(std::integer_sequence<int, I...>, F f) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F>
+__device__ __forceinline__ void unroll(F f) { unroll_seq(std::make_integer_sequence<int, N>{}, f); }
+// Own loads but the last n have landed, then everybody's.  No wait for LDS reads: those in flight at a barrier have until
+// the next one before their slot is written again, and are used before that.
+#define WIDE_WAIT_BARRIER(n) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(n) : "memory")
 #define WIDE_PIN() __builtin_amdgcn_sched_barrier(0)
 
-template <int WGM, int WGN, int FM, int FN, int OCC>
+template <int WGM, int WGN, int FM, int FN, int BK, int A_SLOTS, int B_SLOTS, int OCC>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WideParams p) {
   constexpr int TM = 32 * FM * WGM, TN = 32 * FN * WGN, NW = WGM * WGN;
-  constexpr int A_SLOT = TM * (BK / 2) * 2, B_SLOT = TN * BK * 2;   // bytes
+  constexpr int FA = 2 * FM, FB = 2 * FN;              // 16-row fragments of a wavefront's activation and weight rows
+  constexpr int SUB = BK / 32;                         // sub-stages of a weight stage
+  constexpr int A_SLOT = TM * 64, B_SLOT = TN * BK * 2;              // bytes
   constexpr int B_BASE = A_SLOTS * A_SLOT;
-  // direct-to-LDS instructions (1 KiB each) per wavefront per activation / weight slot; a weight slot goes out in two halves
+  constexpr int AA = A_SLOTS - 1, BA = B_SLOTS - 1;    // sub-stages and stages that the loads are ahead of the products
+  // direct-to-LDS instructions (1 KiB each) per wavefront per activation / weight slot; a weight slot goes out in SUB parts
   // (192 rows over 8 wavefronts: 12 activation pieces; the last four wavefront-instructions repeat pieces, so that every
   // wavefront has the same number of loads in flight)
-  constexpr int A_PIECES = A_SLOT / 1024, A_DMA = (A_PIECES + NW - 1) / NW, B_DMA = B_SLOT / (1024 * NW), BH = B_DMA / 2;
-  static_assert(A_DMA == 2 && (B_DMA == 2 || B_DMA == 4) && B_SLOT == B_DMA * 1024 * NW, "1 KiB pieces per wavefront");
-  static_assert(TM % 64 == 0 && FN == 2, "whole 64-row activation tiles; one SwiGLU pair per wavefront");
+  constexpr int A_PIECES = A_SLOT / 1024, A_DMA = (A_PIECES + NW - 1) / NW, B_DMA = B_SLOT / (1024 * NW), BP = B_DMA / SUB;
+  constexpr int B_LANES = BK / 8, B_ROWS = 64 / B_LANES;           // lanes to a row of a weight piece, rows of a piece
+  static_assert((BK == 64 || BK == 128) && B_DMA % SUB == 0 && B_SLOT == B_DMA * 1024 * NW, "1 KiB pieces per wavefront");
+  static_assert(TM % 64 == 0 && (WGM == 2 || FM == 2) && FN % 2 == 0, "whole 64-row activation tiles");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
@@ -91,148 +116,156 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
-  const int Kc = p.K / p.S, k_begin = split * Kc, KT = Kc / BK;   // KT weight stages = 2 KT half-stages
+  const int Kc = p.K / p.S, k_begin = split * Kc, KT = Kc / BK;   // KT weight stages = SUB KT sub-stages
   const int MT = (p.M + 63) >> 6;                      // 64-row activation tiles that exist
 
-  // ---- this lane's global sources.  Piece q of an activation slot is (row tile q / 4, k-step (q / 2) % 2, row
-  // half q % 2); piece q of a weight slot is rows 8 q .. 8 q + 7, eight lanes per row.
+  // ---- global sources: one address per piece for the wavefront, and the place in K as part of the lanes' offsets.  Piece q of
+  // an activation slot is (row tile q / 4, k-step (q / 2) % 2, row half q % 2); piece q of a weight slot is rows
+  // B_ROWS q .. B_ROWS (q + 1) - 1.
+  constexpr auto swizzle = [](int row) constexpr { return BK == 64 ? (row >> 1) & 7 : row & 15; };   // of the 16-byte pieces of a weight row
   const bf16_t* aptr[A_DMA];
-  int a_piece[A_DMA];                                  // where a repeated piece goes
   const bf16_t* bptr[B_DMA];
+  uint32_t a_off = lane * 16, b_off[B_DMA];
+  int a_first = wave * A_DMA;
+  if (A_PIECES < A_DMA * NW && a_first >= A_PIECES) a_first -= A_DMA * NW - A_PIECES;
 #pragma unroll
   for (int i = 0; i < A_DMA; ++i) {
-    int q = wave * A_DMA + i;
-    if (A_PIECES < A_DMA * NW && q >= A_PIECES) q -= A_DMA * NW - A_PIECES;
-    if (A_PIECES < A_DMA * NW) a_piece[i] = q * 1024;
-    const int rt = min(mblock * (TM / 64) + (q >> 2), MT - 1);
-    aptr[i] = p.x + (((size_t)rt * (p.K >> 4) + (k_begin >> 4) + ((q >> 1) & 1)) * 2 + (q & 1)) * 512 + lane * 8;
+    const int q = a_first + i, rt = min(mblock * (TM / 64) + (q >> 2), MT - 1);
+    aptr[i] = p.x + (((size_t)rt * (p.K >> 4) + (k_begin >> 4) + ((q >> 1) & 1)) * 2 + (q & 1)) * 512;
   }
 #pragma unroll
   for (int i = 0; i < B_DMA; ++i) {
-    const int row = 8 * (wave * B_DMA + i) + (lane >> 3), piece = (lane & 7) ^ ((row >> 1) & 7);
-    bptr[i] = weight_row<TN>(p, tile, row) + k_begin + piece * 8;
+    const int row = B_ROWS * (wave * B_DMA + i), r = lane / B_LANES;
+    int left;                                          // rows behind this one
+    bptr[i] = weight_row<TN>(p, tile, row, left) + k_begin;
+    b_off[i] = (uint32_t)min(r, left) * (uint32_t)p.K * 2 + (((lane % B_LANES) ^ swizzle(row + r)) * 16);
   }
-  // Loads past the end of the walk over K repeat the last (half-)stage into a slot nobody reads any more, which
-  // keeps the number of loads in flight, and with it the waits below, the same in every iteration.
-  auto issue_a = [&](int h, int i) {                   // piece i of half-stage h
-    dma16(aptr[i] + (size_t)min(h, 2 * KT - 1) * 2048, lds0 + (h % A_SLOTS) * A_SLOT + (A_PIECES < A_DMA * NW ? a_piece[i] : (wave * A_DMA + i) * 1024));
-  };
-  auto issue_b = [&](int s, int i) {                   // piece i of weight stage s
-    dma16(bptr[i] + (size_t)min(s, KT - 1) * BK, lds0 + B_BASE + (s % B_SLOTS) * B_SLOT + (wave * B_DMA + i) * 1024);
-  };
+  const uint32_t a_lds = lds0 + a_first * 1024, b_lds = lds0 + B_BASE + wave * B_DMA * 1024;
+  // Each piece of a (sub-)stage, then a step along K.  Past the end of the walk the last one is loaded again, into a
+  // slot nobody reads any more, which keeps the number of loads in flight, and with it the waits below, the same in every iteration.
+  auto load_a = [&](auto i, uint32_t slot) { dma16<i * 1024>(aptr[i], a_off, a_lds + slot); };
+  auto load_b = [&](auto i, uint32_t slot) { dma16<i * 1024>(bptr[i], b_off[i], b_lds + slot); };
+  auto step_a = [&](bool more) { a_off += more ? 4096u : 0u; };
+  auto step_b = [&](auto i, bool more) { b_off[i] += more ? 2u * BK : 0u; };
 
-  // ---- operand fragments of this wavefront inside their slots
-  int a_off[FM], b_off[FN][4];
+  // ---- operand fragments (16 rows x 32 k: lane l holds row l % 16, k 8 (l / 16) .. + 7) inside their slots.  The 32-row
+  // blocks of a wavefront: one of every pair (WGM = 2), so that their distances are constants, or two neighbours.
+  const int c = lane >> 4;
+  const int a_base = (c >> 1) * 2048 + (c & 1) * 512 + (lane & 15) * 16 + (WGM == 2 ? wm * 1024 : wm * 4096);
+  constexpr auto a_frag = [](int i) constexpr { return WGM == 2 ? (i >> 1) * 4096 + (i & 1) * 256 : (i >> 1) * 1024 + (i & 1) * 256; };
+  int b_base[SUB];
 #pragma unroll
-  for (int f = 0; f < FM; ++f) {
-    const int fa = wm * FM + f;                        // 32-row fragment of the tile
-    a_off[f] = (fa >> 1) * 4096 + (fa & 1) * 1024 + lane * 16;
-  }
-#pragma unroll
-  for (int f = 0; f < FN; ++f) {
-    const int nf = p.mode == 1 ? f * (TN / 64) + wn : wn * FN + f;
-    const int row = nf * 32 + (lane & 31);
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) b_off[f][ks] = B_BASE + row * (BK * 2) + (((2 * ks + (lane >> 5)) ^ ((row >> 1) & 7)) * 16);
-  }
-  auto a_slot_of = [&](int h) { return smem + (h % A_SLOTS) * A_SLOT; };
-  auto b_slot_of = [&](int s) { return smem + (s % B_SLOTS) * B_SLOT; };
-  auto load_frags = [&](bf16x8 (&a)[FM], bf16x8 (&b)[FN], const unsigned char* a_slot, const unsigned char* b_slot, int ks) {
-#pragma unroll
-    for (int f = 0; f < FM; ++f) a[f] = *(const bf16x8*)(a_slot + a_off[f] + (ks & 1) * 2048);
-#pragma unroll
-    for (int f = 0; f < FN; ++f) b[f] = *(const bf16x8*)(b_slot + b_off[f][ks]);
-  };
+  for (int q = 0; q < SUB; ++q) b_base[q] = B_BASE + (wn * 32 * FN + (lane & 15)) * (BK * 2) + (((4 * q + c) ^ swizzle(lane & 15)) * 16);
 
-  floatx16 acc[FM][FN];
+  floatx4 acc[FA][FB];
 #pragma unroll
-  for (int fm = 0; fm < FM; ++fm)
+  for (int i = 0; i < FA; ++i)
 #pragma unroll
-    for (int fn = 0; fn < FN; ++fn)
+    for (int f = 0; f < FB; ++f)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[fm][fn][r] = 0.f;
-  auto mfma_col = [&](const bf16x8 (&a)[FM], const bf16x8 (&b)[FN], int fn) {
-#pragma unroll
-    for (int fm = 0; fm < FM; ++fm) acc[fm][fn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[fn], a[fm], acc[fm][fn], 0, 0, 0);
-  };
+      for (int r = 0; r < 4; ++r) acc[i][f][r] = 0.f;
 
-  // Loads complete in issue order.  Per wavefront the order is
-  //   B0lo A0 B0hi A1 B1lo A2 B1hi | half-stage h = 2 s: A(h+3) B(s+2)lo | half-stage h = 2 s + 1: A(h+3) B(s+2)hi
-  // (A(h) = both pieces of activation half-stage h, B(s)lo / hi = the first / second half of the pieces of weight stage s).
-  auto issue_b_half = [&](int s, int half) {
+  // Loads complete in issue order.  Sub-stage v = SUB s + q issues every piece of activation sub-stage v + AA, then part q of the
+  // pieces of weight stage s + BA; the sub-stages before the first one issue what has begun by then.
+  constexpr int LEAD = ((AA > SUB * BA ? AA : SUB * BA) + SUB - 1) / SUB * SUB;
+  unroll<LEAD>([&](auto u) {
+    constexpr int v = u - LEAD, q = u % SUB, t = u / SUB - LEAD / SUB + BA;
+    if constexpr (v + AA >= 0) {
+      unroll<A_DMA>([&](auto i) { load_a(i, (v + AA) * A_SLOT); });
+      step_a(v + AA + 1 < SUB * KT);
+    }
+    if constexpr (t >= 0)
+      unroll<BP>([&](auto j) {
+        constexpr std::integral_constant<int, q * BP + j> i;
+        load_b(i, t * B_SLOT);
+        step_b(i, t + 1 < KT);
+      });
+  });
+  constexpr int PER = A_DMA + BP;                      // loads per sub-stage
+  constexpr auto least = [](int x, int y) constexpr { return x < y ? x : y; };
+  WIDE_WAIT_BARRIER(least(BP + (AA - 1) * PER, SUB * (BA - 1) * PER));   // A0 and B0 are in LDS
+  bf16x8 a0[FA], a1[FA], b0[FB], b1[FB];
 #pragma unroll
-    for (int i = 0; i < BH; ++i) issue_b(s, half * BH + i);
-  };
-  issue_b_half(0, 0); issue_a(0, 0); issue_a(0, 1); issue_b_half(0, 1);
-  issue_a(1, 0); issue_a(1, 1); issue_b_half(1, 0); issue_a(2, 0); issue_a(2, 1); issue_b_half(1, 1);
-  WIDE_WAIT_LOADS(2 * A_DMA + B_DMA);                  // A0 and B0 are in LDS ...
-  __syncthreads();                                     // ... for every wavefront
-  bf16x8 a0[FM], b0[FN], a1[FM], b1[FN];
-  load_frags(a0, b0, a_slot_of(0), b_slot_of(0), 0);
+  for (int i = 0; i < FA; ++i) a0[i] = *(const bf16x8*)(smem + a_base + a_frag(i));
+#pragma unroll
+  for (int f = 0; f < FB; ++f) b0[f] = *(const bf16x8*)(smem + b_base[0] + f * (32 * BK));
 
-  // One 32-k half-stage: a0 / b0 hold its first k-step on entry and the first k-step of the next one on exit.
-  auto half_stage = [&](int s, int half) {
-    const int h = 2 * s + half;
-    // everything up to A(h+1) (even h) / up to B(s+1)hi (odd h) has landed when only the loads issued after it
-    // are in flight: what the NEXT half-stage reads is in LDS, what THIS one reads was published a barrier ago
-    if (half == 0) WIDE_WAIT_LOADS(A_DMA + B_DMA); else WIDE_WAIT_LOADS(A_DMA + B_DMA / 2);
-    __syncthreads();                                   // ... for every wavefront; the slots of half-stage h - 1 are free
+  // One sub-stage: a and b hold its fragments; an and bn receive those of the next.  A fragment of weights stays the first
+  // operand of FA products in a row: with the operands the other way round the matrix units draw more power, which costs
+  // clock.  The direct loads and LDS reads are dealt out between the products, no two together, so that none of
+  // them keeps a product from being issued.
+  uint32_t b_slot = 0;                                 // of weight stage s
+  auto sub_stage = [&](int s, auto q, const bf16x8 (&a)[FA], const bf16x8 (&b)[FB], bf16x8 (&an)[FA], bf16x8 (&bn)[FB]) {
+    const int h = SUB * s + q;
+    // everything up to A(h+1) and, in the last sub-stage, B(s+1) has landed when only the loads issued after it are in
+    // flight: what the NEXT sub-stage reads is in LDS from here on, and the slots of sub-stage h - 1 are free
+    WIDE_WAIT_BARRIER(q < SUB - 1 ? BP + (AA - 2) * PER : least(BP + (AA - 2) * PER, (SUB * (BA - 1) - 1) * PER));
     WIDE_PIN();
-    issue_a(h + 3, 0);
-    load_frags(a1, b1, a_slot_of(h), b_slot_of(s), 2 * half + 1);
-    mfma_col(a0, b0, 0);
-    WIDE_PIN();
-    issue_a(h + 3, 1);
-    mfma_col(a0, b0, 1);
-    WIDE_PIN();
-    issue_b(s + 2, BH * half);
-    load_frags(a0, b0, a_slot_of(h + 1), b_slot_of(s + half), 2 * (1 - half));
-    mfma_col(a1, b1, 0);
-    WIDE_PIN();
-    if (BH == 2) issue_b(s + 2, BH * half + 1);
-    mfma_col(a1, b1, 1);
-    WIDE_PIN();
+    const uint32_t b_next = b_slot == BA * B_SLOT ? 0 : b_slot + B_SLOT, b_fill = b_slot == 0 ? BA * B_SLOT : b_slot - B_SLOT;   // of s + 1, s + BA
+    const uint32_t a_fill = (uint32_t)(h + AA) % A_SLOTS * A_SLOT;
+    const unsigned char* as = smem + (uint32_t)(h + 1) % A_SLOTS * A_SLOT + a_base;
+    const unsigned char* bs = smem + (q < SUB - 1 ? b_slot : b_next) + b_base[(q + 1) % SUB];
+    unroll<FA * FB>([&](auto x) {
+      constexpr int MF = FA * FB, NR = FA + FB;
+      constexpr int f = x / FA, i = x % FA;
+      acc[i][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[f], a[i], acc[i][f], 0, 0, 0);
+      // the reads in the order in which the next sub-stage needs them: b 0, every a, the rest of b
+      constexpr int r = (x * NR + MF - 1) / MF;        // read r goes behind product r MF / NR
+      if constexpr (r < NR && r * MF / NR == x) {
+        if constexpr (r == 0) bn[0] = *(const bf16x8*)bs;
+        else if constexpr (r <= FA) an[r - 1] = *(const bf16x8*)(as + a_frag(r - 1));
+        else bn[r - FA] = *(const bf16x8*)(bs + (r - FA) * (32 * BK));
+      }
+      constexpr int at = x - 1, d = (at * PER + MF - 1) / MF;  // load d behind product d MF / PER + 1
+      if constexpr (at >= 0 && d < PER && d * MF / PER == at) {
+        if constexpr (d < A_DMA) {
+          load_a(std::integral_constant<int, d>{}, a_fill);
+          if constexpr (d == A_DMA - 1) step_a(h + AA + 1 < SUB * KT);
+        } else {
+          constexpr std::integral_constant<int, q * BP + d - A_DMA> piece;
+          load_b(piece, b_fill);
+          step_b(piece, s + BA + 1 < KT);
+        }
+      }
+      WIDE_PIN();
+    });
+    if (q == SUB - 1) b_slot = b_next;
   };
-  for (int s = 0; s < KT; ++s) {
-    half_stage(s, 0);
-    half_stage(s, 1);
-  }
-  WIDE_WAIT_LOADS(0);                                  // nothing may still be writing LDS when the workgroup ends
+  for (int s = 0; s < KT; ++s)
+    unroll<SUB / 2>([&](auto q) {
+      sub_stage(s, std::integral_constant<int, 2 * q>{}, a0, b0, a1, b1);
+      sub_stage(s, std::integral_constant<int, 2 * q + 1>{}, a1, b1, a0, b0);
+    });
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // nothing may still be writing LDS when the workgroup ends
 
-  // ---- epilogue.  Accumulator r of lane l: activation row 32 fm + (l & 31) of the wavefront's rows, weight row
-  // 8 (r >> 2) + 4 (l >> 5) + (r & 3) of fragment fn.
-  const int m0 = mblock * TM + wm * (32 * FM) + (lane & 31);
-  const int nsub = 4 * (lane >> 5);
+  // ---- epilogue.  Accumulator r of lane l: activation row l % 16 of its fragment, weight row 4 (l / 16) + r of its own.
+  auto row_of = [&](int i) { return mblock * TM + (WGM == 2 ? (i >> 1) * 64 + wm * 32 : wm * 64 + (i >> 1) * 32) + (i & 1) * 16 + (lane & 15); };
   if (p.epi == GEMM_EPI_PARTIAL) {
     float* out = p.out_f32 + (size_t)split * p.M * p.N;
 #pragma unroll
-    for (int fm = 0; fm < FM; ++fm) {
-      const int m = m0 + 32 * fm;
+    for (int i = 0; i < FA; ++i) {
+      const int m = row_of(i);
       if (m >= p.M) continue;
 #pragma unroll
-      for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const int n = tile * TN + (wn * FN + fn) * 32 + 8 * c + nsub;
-          if (n < p.N)
-            *(float4*)(out + (size_t)m * p.N + n) =
-                make_float4(acc[fm][fn][4 * c], acc[fm][fn][4 * c + 1], acc[fm][fn][4 * c + 2], acc[fm][fn][4 * c + 3]);
-        }
+      for (int f = 0; f < FB; ++f) {
+        const int n = tile * TN + wn * 32 * FN + f * 16 + 4 * c;
+        if (n < p.N) *(floatx4*)(out + (size_t)m * p.N + n) = acc[i][f];
+      }
     }
   } else {
     const int I = p.N >> 1;
 #pragma unroll
-    for (int fm = 0; fm < FM; ++fm) {
-      const int m = m0 + 32 * fm;
+    for (int i = 0; i < FA; ++i) {
+      const int m = row_of(i);
       if (m >= p.M) continue;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int n = tile * (TN / 2) + wn * 32 + 8 * c + nsub;
+      for (int f = 0; f < FN; ++f) {                   // fragments of gate rows: two of every four
+        const int n = tile * (TN / 2) + wn * 16 * FN + f * 16 + 4 * c, gf = (f >> 1) * 4 + (f & 1);
         if (n >= I) continue;
         float h[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float g = acc[fm][0][4 * c + e], u = acc[fm][1][4 * c + e];
+          const float g = acc[i][gf][e], u = acc[i][gf + 2][e];
           h[e] = g / (1.f + expf(-g)) * u;
         }
         Act<true>::store4(p.out_xf, m, n, I, h[0], h[1], h[2], h[3]);
@@ -241,11 +274,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   }
 }
 
-template <int WGM, int WGN, int FM, int FN, int OCC>
+template <int WGM, int WGN, int FM, int FN, int BK, int A_SLOTS, int B_SLOTS, int OCC>
 hipError_t launch_cfg(WideParams& p, int S, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   constexpr int TM = 32 * FM * WGM, TN = 32 * FN * WGN;
-  constexpr int LDS = A_SLOTS * TM * (BK / 2) * 2 + B_SLOTS * TN * BK * 2;
-  auto kernel = gemm_wide_kernel<WGM, WGN, FM, FN, OCC>;
+  constexpr int LDS = A_SLOTS * TM * 64 + B_SLOTS * TN * BK * 2;
+  auto kernel = gemm_wide_kernel<WGM, WGN, FM, FN, BK, A_SLOTS, B_SLOTS, OCC>;
   static DeviceOnce configured;                        // the attribute belongs to the loaded code object of a device
   hipError_t ce = configured.run([&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS); });
   if (ce != hipSuccess) return ce;
@@ -261,8 +294,10 @@ hipError_t launch_cfg(WideParams& p, int S, hipStream_t st, hipEvent_t ev_start,
 // Picks the tile shape and the split-K factor, then launches.
 hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N, int K, int epi, void* out,
                             size_t out_capacity_floats, int* S_out, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  if (M <= 0 || N <= 0 || K <= 0 || K % BK || N % 4) return hipErrorInvalidValue;
+  if (M <= 0 || N <= 0 || K <= 0 || K % 64 || N % 4) return hipErrorInvalidValue;
   if (epi == GEMM_EPI_SWIGLU ? (W.mode != 1 || N % 8) : W.mode != 0) return hipErrorInvalidValue;
+  for (int i = 0; W.mode == 0 && i + 1 < W.nmat; ++i)
+    if (W.rows[i] % 8) return hipErrorInvalidValue;    // the rows of one direct load belong to one matrix
   WideParams p;
   p.x = x;
   for (int i = 0; i < 3; ++i) { p.w[i] = (const bf16_t*)W.w[i]; p.rows[i] = W.rows[i]; }
@@ -273,6 +308,6 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   p.S = t.S;
   if (S_out) *S_out = t.S;
   if (t.cols == 128)
-    return t.rows == 256 ? launch_cfg<4, 2, 2, 2, 1>(p, t.S, st, ev_start, ev_stop) : launch_cfg<2, 2, 2, 2, 2>(p, t.S, st, ev_start, ev_stop);
-  return t.rows == 256 ? launch_cfg<2, 4, 4, 2, 1>(p, t.S, st, ev_start, ev_stop) : launch_cfg<2, 4, 3, 2, 1>(p, t.S, st, ev_start, ev_stop);
+    return t.rows == 256 ? launch_cfg<4, 2, 2, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop) : launch_cfg<2, 2, 2, 2, 64, 4, 3, 2>(p, t.S, st, ev_start, ev_stop);
+  return t.rows == 256 ? launch_cfg<2, 4, 4, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop) : launch_cfg<2, 4, 3, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
 }
