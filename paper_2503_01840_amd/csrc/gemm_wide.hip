@@ -24,7 +24,8 @@
 //     SwiGLU (the tile interleaves gate and up rows so that both values of a pair sit in the same lane) written
 //     as fragment-major bf16 (8-byte stores).
 // 8B width, us, products as 32x32x16 with the reads and loads in bursts / now: 2048 rows gate/up 422 / 368 (1.31 PFLOP/s), down
-// 214 / 177, o 77 / 57, q/k/v 100 / 87; 512 rows gate/up 116 / 101, down 73 / 60, q/k/v 39 / 35; 256 rows gate/up 77 / 74.
+// 214 / 177, o 77 / 57, q/k/v 100 / 87; 512 rows gate/up 116 / 101, down 73 / 60, q/k/v 39 / 35; 256 rows gate/up 77 / 74 (69.5
+// with 128-k weight stages), 77 rows 60 / 59 (54.7).
 // Measured and not kept: 4 wavefronts of 128 x 128 each (a third fewer LDS reads: loop 4 % shorter, epilogue longer by the same);
 // K walks that start at different stages (0 to 8 % slower at 512 and 2048 rows).
 #include <utility>
@@ -307,7 +308,12 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   const WideTiles t = wide_tiles(M, N, K, epi == GEMM_EPI_SWIGLU, out_capacity_floats);
   p.S = t.S;
   if (S_out) *S_out = t.S;
+  if (t.cols == 128 && t.k == 128)
+    return t.rows == 256 ? launch_cfg<4, 2, 2, 2, 128, 4, 3, 1>(p, t.S, st, ev_start, ev_stop)
+                         : launch_cfg<2, 2, 2, 2, 128, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
   if (t.cols == 128)
-    return t.rows == 256 ? launch_cfg<4, 2, 2, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop) : launch_cfg<2, 2, 2, 2, 64, 4, 3, 2>(p, t.S, st, ev_start, ev_stop);
-  return t.rows == 256 ? launch_cfg<2, 4, 4, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop) : launch_cfg<2, 4, 3, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
+    return t.rows == 256 ? launch_cfg<4, 2, 2, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop)
+                         : launch_cfg<2, 2, 2, 2, 64, 4, 3, 2>(p, t.S, st, ev_start, ev_stop);
+  return t.rows == 256 ? launch_cfg<2, 4, 4, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop)
+                       : launch_cfg<2, 4, 3, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
 }

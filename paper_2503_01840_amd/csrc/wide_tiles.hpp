@@ -8,9 +8,10 @@
 struct WideTiles {
   int rows, cols;      // output tile of a workgroup
   int S;               // K ranges (split-K partial sums); 1 for SwiGLU
+  int k;               // width of a weight stage: 64, or 128 for tiles of 128 weight rows
 };
 
-inline WideTiles wide_tiles(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
+inline WideTiles wide_tiles_k64(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
   const int KT = K / 64;
   auto ceil_div = [](int a, int b) { return (a + b - 1) / b; };
   auto pick = [&](int rows, int cols, int want, int min_stages) -> WideTiles {
@@ -22,7 +23,7 @@ inline WideTiles wide_tiles(int M, int N, int K, bool swiglu, size_t out_capacit
         if (s > 1 && ((size_t)s * M * N > out_capacity_floats || KT / s < min_stages)) break;
         S = s;
       }
-    return {rows, cols, S};
+    return {rows, cols, S, 64};
   };
   // 129..256 rows: ONE 256-row block x 128 weight rows per workgroup (8 wavefronts x 64 x 64), so that every weight line enters
   // exactly one CU and a stage takes in 48 KB instead of the 2 x 32 KB of two 128 x 128 workgroups (measured at 256 rows, 8B
@@ -49,4 +50,19 @@ inline WideTiles wide_tiles(int M, int N, int K, bool swiglu, size_t out_capacit
     return (n / 64 * 0.6f + (rest == 0 ? 0.f : rest <= 32 ? 0.4f : 0.6f)) / w.S;
   };
   return cost(mid) < cost(t) ? mid : t;
+}
+
+// Tiles of 128 weight rows leave room in LDS for weight stages of 128 k, whose row pieces of 256 bytes HBM delivers faster than
+// pieces of 128, where one workgroup has a CU to itself.  256 x 128 always has; 128 x 128 runs two to a CU otherwise, and that
+// is the better way between 257 and 512 workgroups (one round of two against two of one), and beyond where row blocks share a weight tile.  A workgroup's walk has to be long
+// enough, as fewer and larger stages start later.  8B and 70B widths, us, 64 / 128: 77 rows gate/up (224 workgroups) 59.1 / 54.7, LM
+// head (1002) 256 / 242, down (256, 14 stages) 28.9 / 28.1, but o (256, 4 stages) 12.6 / 13.8, q/k/v (384) 18.6 / 22.4 and 70B gate/up
+// (448) 185 / 201; 300 rows LM head (3006) 457 / 530; 256 rows gate/up 71.8 / 69.5, q/k/v 24.2 / 23.6, but o (4 stages) 17.8 / 18.4.
+inline WideTiles wide_tiles(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
+  WideTiles t = wide_tiles_k64(M, N, K, swiglu, out_capacity_floats);
+  const int wgs = (N + t.cols - 1) / t.cols * ((M + t.rows - 1) / t.rows) * t.S, range = K / t.S;
+  if (t.cols == 128 && range % 128 == 0 && range >= (t.rows == 256 && t.S == 1 ? 256 : 1024) &&
+      (t.rows == 256 || wgs <= 256 || (wgs > 512 && M <= 128)))
+    t.k = 128;
+  return t;
 }

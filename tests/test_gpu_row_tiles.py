@@ -32,6 +32,13 @@ def test_rows_at_192_row_edges(B, N, group):
     _rows_alone_and_together(S.get_shape("c3").with_(name="flat", hidden=256, n_heads=4, n_kv_heads=2, vocab=1024), B, N, group)
 
 
+# 128-k weight stages: the first and last row count of 128 x 128 and of 256 x 128 tiles and one between, against at most 64 rows at a
+# time.  8B width: gate/up, down and the LM head take them, q/k/v and o from 129 rows on.
+@pytest.mark.parametrize("B,N,group", [(65, 1, 64), (43, 3, 21), (128, 1, 64), (129, 1, 64), (64, 3, 20), (64, 4, 16)])
+def test_rows_in_wide_weight_stages(B, N, group):
+    _rows_alone_and_together(S.get_shape("c3"), B, N, group)
+
+
 def _rows_alone_and_together(full, B, N, group):
     E = _E()
     shape = full.with_(n_layers=1, taps=(0, 0, 0))

@@ -49,3 +49,16 @@ def test_every_choice_can_be_launched(rule):
     for (M, N, K, s, cap), (rows, cols, S) in zip(qs, rule(qs)):
         assert (rows, cols) in tiles and 1 <= S <= 8 and (K // 64) % S == 0
         assert S == 1 or (not s and S * M * N <= cap)
+
+
+def test_weight_stages_divide_every_range_of_k(tmp_path):
+    (tmp_path / "m.cpp").write_text('#include <cstdio>\n#include <initializer_list>\n#include "wide_tiles.hpp"\n'
+                                    'int main() { for (int M : {65, 77, 128, 129, 200, 256, 257, 300, 383, 520, 2048})\n'
+                                    '  for (int N = 256; N <= 131072; N += N / 3) for (int K = 128; K <= 28672; K += 128) for (int s : {0, 1}) {\n'
+                                    '    const WideTiles t = wide_tiles(M, N, K, s, (size_t)1 << 40);\n'
+                                    '    if (K / t.S % t.k || (t.k != 64 && (t.k != 128 || t.cols != 128))) { printf("%d %d %d %d\\n", M, N, K, s); return 1; } }\n'
+                                    '  return 0; }\n')
+    inc = os.path.join(ROOT, "paper_2503_01840_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
+    r = subprocess.run([str(tmp_path / "m")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
