@@ -379,27 +379,37 @@ static int fuse_rows(eagle3_ctx* ctx, const float* low, const float* mid, const 
 // On exit: `part` holds S_down partial sums of the MLP output (to be added to x by the caller).
 // R rows exist, B * rows_per_seq of them (and up to 63 more in a prefill chunk's last block) go through attention.
 // prefill: the rows are R consecutive positions of one sequence.
+// last_row: of the rows only the last one goes on behind its keys and values (its residual row stays where it is).
 static int layer_tail(eagle3_ctx* ctx, const eagle3_layer_weights& w, int B, int rows_per_seq, int R, bool prefill, int S_qkv,
                       const int32_t* slot, const float* cs, const uint32_t* mask, const SeqInfo* seq, void* kc, void* vc,
-                      int max_len, int* S_down, hipStream_t st) {
+                      int max_len, int* S_down, hipStream_t st, bool last_row = false) {
   const eagle3_config& c = ctx->cfg;
   const int k = c.hidden, H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim, I = c.intermediate;
   CK(launch_rope_kv_write(ctx->bf16, ctx->part, S_qkv, R, H, Hkv, d, cs, slot, ctx->q, kc, vc, st));
-  if (prefill && ctx->bf16 && prefill_attention_fits(R, H, Hkv, max_len)) {
-    CK(launch_prefill_attention(ctx->q, kc, vc, seq, R, H, Hkv, d, ctx->act_attn, st));
+  const char* q = (const char*)ctx->q;
+  float* x = ctx->x;
+  if (last_row) {                                   // the block that row R - 1 is in, as a sequence of that row alone
+    q += (size_t)(R - 1) * H * d * ctx->act_size;
+    x += (size_t)(R - 1) * k;
+    seq += (R - 1) / 64;
+    mask += (size_t)(R - 1) * 4;
+    B = rows_per_seq = R = 1;
+  }
+  if (!last_row && prefill && ctx->bf16 && prefill_attention_fits(R, H, Hkv, max_len)) {
+    CK(launch_prefill_attention(q, kc, vc, seq, R, H, Hkv, d, ctx->act_attn, st));
   } else {
     int ns = 1;
     if (ctx->bf16) {
       ns = attention_pick_splits(B, rows_per_seq, H, Hkv, max_len);
       while (ns > 1 && attention_scratch_floats(B * rows_per_seq, H, d, ns) > ctx->attn_floats) --ns;
     }
-    CK(launch_tree_attention(ctx->bf16, ctx->q, kc, vc, seq, mask, B, rows_per_seq, H, Hkv, d, max_len, ns,
+    CK(launch_tree_attention(ctx->bf16, q, kc, vc, seq, mask, B, rows_per_seq, H, Hkv, d, max_len, ns,
                              ctx->attn_scratch, ctx->act_attn, st));
   }
   int S_o = 1;
   GemmWeights Wo = {{w.wo, nullptr, nullptr}, {k, 0, 0}, 1, 0};
   TRY(ctx->project(ctx->act_attn, Wo, R, k, H * d, GEMM_EPI_PARTIAL, &S_o, st));
-  CK(launch_add_norm(ctx->bf16, ctx->x, ctx->part, S_o, R, k, w.norm_mlp, c.rms_eps, ctx->act_k, nullptr, st));
+  CK(launch_add_norm(ctx->bf16, x, ctx->part, S_o, R, k, w.norm_mlp, c.rms_eps, ctx->act_k, nullptr, st));
   GemmWeights Wgu = {{w.w_gate, w.w_up, nullptr}, {I, I, 0}, 2, 1};
   TRY(ctx->project(ctx->act_k, Wgu, R, 2 * I, k, GEMM_EPI_SWIGLU, nullptr, st));
   GemmWeights Wd = {{w.w_down, nullptr, nullptr}, {k, 0, 0}, 1, 0};
@@ -409,9 +419,9 @@ static int layer_tail(eagle3_ctx* ctx, const eagle3_layer_weights& w, int B, int
 
 // Layers [l0, l1) of the target stack over R rows, whose residual stream is in ctx->x and whose slots, masks and rotary
 // tables are prepared; attention sees them as B sequences of N rows.  logits != nullptr: finish with the final norm and the
-// LM head (requires l1 == n_layers).  x_out (optional) receives the residual stream after layer l1 - 1.
+// LM head (requires l1 == n_layers).  norm_out: finish with the norm in front of layer l1.  x_out (optional) receives the residual stream after layer l1 - 1.
 static int run_layers(eagle3_ctx* ctx, int B, int N, int R, bool prefill, const eagle3_kv* kv, int max_len, int l0, int l1, float* x_out,
-                      float* logits, float* taps, float* dbg_hidden, hipStream_t st) {
+                      float* logits, float* taps, float* dbg_hidden, hipStream_t st, bool norm_out = false) {
   const eagle3_config& c = ctx->cfg;
   const int k = c.hidden, H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim;
   const size_t Rk = (size_t)R * k;
@@ -425,7 +435,7 @@ static int run_layers(eagle3_ctx* ctx, int B, int N, int R, bool prefill, const 
     if (dbg_hidden) copies[3] = dbg_hidden + (size_t)l * Rk;
     if (l == l1 && x_out) copies[3] = x_out;
     const bool head = l == c.n_layers;
-    if (l == l1 && !(head && logits)) {               // the range ends inside the stack: no norm needed
+    if (l == l1 && !(head && logits) && !norm_out) {  // the range ends inside the stack: no norm needed
       CK(launch_add_norm(ctx->bf16, ctx->x, ctx->part, S_prev, R, k, nullptr, c.rms_eps, nullptr, copies, st));
       break;
     }
@@ -637,6 +647,10 @@ int eagle3_prefill(eagle3_ctx* ctx, const int32_t* tokens, int32_t T, const eagl
   hipStream_t st = (hipStream_t)stream;
   const int k = c.hidden, H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim;
   const eagle3_layer_weights& w = ctx->dw.layer;
+  // Behind the last layer only the last position is read, unless that layer's output is one of the three features: the others need
+  // no more of it than their keys and values.  8B width, 32 layers: 2048 tokens 27.8 -> 27.2 ms.
+  bool tail_row = true;
+  for (int t = 0; t < 3; ++t) tail_row = tail_row && c.tap_layers[t] != c.n_layers - 1;
   // chunks of equal length (whole 64-row blocks): a short last chunk would stream all weights for a few rows
   const int n_chunks = (T + ctx->chunk_max - 1) / ctx->chunk_max;
   const int C = std::min(ctx->chunk_max, ((T + n_chunks - 1) / n_chunks + 63) / 64 * 64);
@@ -647,12 +661,23 @@ int eagle3_prefill(eagle3_ctx* ctx, const int32_t* tokens, int32_t T, const eagl
     const size_t nk = (size_t)n * k;
     CK(launch_prefill_prep(kv->kv_indptr, kv->prefix_len, n, d, c.rope_theta, ctx->pos1, ctx->slot, ctx->mask, ctx->cs, ctx->seq, st));
     CK(launch_embed_rows(ctx->bf16, ctx->tw.embed, tokens + c0, n, k, c.vocab, ctx->x, st));
-    TRY(run_layers(ctx, blocks, blocks == 1 ? n : 64, n, true, kv, kv->max_prefix_len + c0 + n, 0, c.n_layers, nullptr, nullptr,
-                   ctx->chunk_taps, nullptr, st));
+    const int max_len = kv->max_prefix_len + c0 + n, L = c.n_layers;
+    int S_tail = 0;
+    if (tail_row) {
+      TRY(run_layers(ctx, blocks, blocks == 1 ? n : 64, n, true, kv, max_len, 0, L - 1, nullptr, nullptr, ctx->chunk_taps, nullptr, st, true));
+      const eagle3_layer_weights& wl = ctx->layers[L - 1];
+      GemmWeights Wl = {{wl.wq, wl.wk, wl.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
+      int S_qkv = 1;
+      TRY(ctx->project(ctx->act_k, Wl, n, (H + 2 * Hkv) * d, k, GEMM_EPI_PARTIAL, &S_qkv, st));
+      if (last) TRY(layer_tail(ctx, wl, 1, 1, n, true, S_qkv, ctx->slot, ctx->cs, ctx->mask, ctx->seq, kv->k[L - 1], kv->v[L - 1], max_len, &S_tail, st, true));
+      else CK(launch_rope_kv_write(ctx->bf16, ctx->part, S_qkv, n, H, Hkv, d, ctx->cs, ctx->slot, ctx->q, kv->k[L - 1], kv->v[L - 1], st));
+    } else {
+      TRY(run_layers(ctx, blocks, blocks == 1 ? n : 64, n, true, kv, max_len, 0, L, nullptr, nullptr, ctx->chunk_taps, nullptr, st));
+    }
     CK(launch_advance_lengths((int32_t*)kv->prefix_len, 1, n, st));
     if (last) {                                       // next-token logits of the last position only
-      CK(launch_add_norm(ctx->bf16, ctx->x + (size_t)(n - 1) * k, nullptr, 0, 1, k, ctx->tw.final_norm, c.rms_eps, ctx->act_k,
-                         nullptr, st));
+      CK(launch_add_norm(ctx->bf16, ctx->x + (size_t)(n - 1) * k, S_tail ? ctx->part : nullptr, S_tail, 1, k, ctx->tw.final_norm, c.rms_eps,
+                         ctx->act_k, nullptr, st));
       GemmWeights Wlm = {{ctx->tw.lm_head, nullptr, nullptr}, {c.vocab, 0, 0}, 1, 0};
       TRY(ctx->project(ctx->act_k, Wlm, 1, c.vocab, k, GEMM_EPI_PARTIAL, nullptr, st, logits_last));
     }

@@ -34,6 +34,15 @@ def test_prefill_over_head_layouts_and_pool_offsets(H, Hkv, T, base):
     _check(SMALL.with_(n_heads=H, n_kv_heads=Hkv), "bf16", T, base=base)
 
 
+# no feature behind the last layer, so that only the last position goes through all of it: one position, the edges of the 64-row
+# blocks, a second chunk of one position, several chunks
+@pytest.mark.parametrize("dtype,T,part", [("fp32", 2, 1.0), ("fp32", 65, 1.0), ("fp32", 257, 1.0), ("fp32", 300, 0.0), ("bf16", 2, 1.0),
+                                          ("bf16", 64, 1.0), ("bf16", 65, 1.0), ("bf16", 577, 1.0), ("bf16", 2049, 1.0), ("bf16", 300, 0.0)])
+def test_prefill_without_a_feature_of_the_last_layer(dtype, T, part):
+    shape = S.get_shape("c1") if dtype == "fp32" else SMALL.with_(n_layers=3)
+    _check(shape.with_(taps=(0, 0, shape.n_layers - 2)), dtype, T, part)
+
+
 def _check(shape, dtype, T, part=1.0, base=0):
     E = _E()
     rounding = "none" if dtype == "fp32" else "bf16"
