@@ -158,7 +158,7 @@ struct eagle3_ctx {
   }
 
   // One projection Y = act W^T.  epi PARTIAL: result (S partial sums) in `part`; *S_out = S.
-  // epi SWIGLU: silu(gate)*up lands in act_h.
+  // epi SWIGLU: silu(gate)*up lands in act_h.  fp32: to direct_out only (a layer's products are fused with what follows them).
   int project(const void* act_in, const GemmWeights& W, int M, int N, int K, int epi, int* S_out, hipStream_t st,
               float* direct_out = nullptr) {
     if (bf16 && M > 64) {
@@ -192,9 +192,7 @@ struct eagle3_ctx {
       if (S_out) *S_out = S;
       return EAGLE3_OK;
     }
-    if (epi == GEMM_EPI_PARTIAL && (size_t)M * N > part_floats && !direct_out) return EAGLE3_E_STATE;
-    float* out = epi == GEMM_EPI_SWIGLU ? (float*)act_h : direct_out ? direct_out : part;
-    CK(launch_gemm_f32((const float*)act_in, W, M, N, K, epi, out, st));
+    CK(launch_gemm_f32((const float*)act_in, W, M, N, K, epi, direct_out, st));
     if (S_out) *S_out = 1;
     return EAGLE3_OK;
   }
@@ -374,18 +372,53 @@ static int fuse_rows(eagle3_ctx* ctx, const float* low, const float* mid, const 
   return ctx->project(ctx->act_k, W, M, k, 3 * k, GEMM_EPI_PARTIAL, nullptr, st, g_out);
 }
 
+// q/k/v projection of R rows, rotated, k and v in their cache slots.  in: the projection's operand, K wide; fp32 with a gain: the
+// rows whose RMSNorm is that operand.
+static int project_qkv(eagle3_ctx* ctx, const eagle3_layer_weights& w, const void* in, const void* gain, int K, int R, const int32_t* slot,
+                       const float* cs, void* kc, void* vc, hipStream_t st) {
+  const eagle3_config& c = ctx->cfg;
+  const int H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim;
+  GemmWeights Wqkv = {{w.wq, w.wk, w.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
+  if (!ctx->bf16) {
+    F32Fuse f;
+    f.gain = (const float*)gain; f.eps = c.rms_eps;
+    f.cs = cs; f.slot = slot; f.kc = (float*)kc; f.vc = (float*)vc; f.H = H; f.Hkv = Hkv; f.d = d;
+    CK(launch_gemm_f32((const float*)in, Wqkv, R, (H + 2 * Hkv) * d, K, GEMM_EPI_ROPE, (float*)ctx->q, st, f));
+    return EAGLE3_OK;
+  }
+  int S = 1;
+  TRY(ctx->project(in, Wqkv, R, (H + 2 * Hkv) * d, K, GEMM_EPI_PARTIAL, &S, st));
+  CK(launch_rope_kv_write(true, ctx->part, S, R, H, Hkv, d, cs, slot, ctx->q, kc, vc, st));
+  return EAGLE3_OK;
+}
+
+// RMSNorm and LM head of R rows, to which S partial sums in `part` are added first; copies: see launch_add_norm.
+static int norm_head(eagle3_ctx* ctx, float* x, int S, int R, const void* gain, float* const copies[4], const void* head, int V, float* out,
+                     hipStream_t st) {
+  const int k = ctx->cfg.hidden;
+  GemmWeights W = {{head, nullptr, nullptr}, {V, 0, 0}, 1, 0};
+  if (!ctx->bf16) {
+    F32Fuse f;
+    f.gain = (const float*)gain; f.eps = ctx->cfg.rms_eps;
+    CK(launch_gemm_f32(x, W, R, V, k, GEMM_EPI_PARTIAL, out, st, f));
+    return EAGLE3_OK;
+  }
+  CK(launch_add_norm(true, x, S ? ctx->part : nullptr, S, R, k, gain, ctx->cfg.rms_eps, ctx->act_k, copies, st));
+  return ctx->project(ctx->act_k, W, R, V, k, GEMM_EPI_PARTIAL, nullptr, st, out);
+}
+
 // attention + output projection + MLP of one layer, shared by the target stack and the draft layer.
-// On entry: qkv partial sums are in `part` (S_qkv of them), x holds the residual rows.
-// On exit: `part` holds S_down partial sums of the MLP output (to be added to x by the caller).
+// On entry: q, and the cache rows of k and v, are written (project_qkv); x holds the residual rows.
+// On exit: bf16: `part` holds S_down partial sums of the MLP output (to be added to x by the caller); fp32: x holds the layer's
+// output, and so does each non-null copy; S_down = 0.
 // R rows exist, B * rows_per_seq of them (and up to 63 more in a prefill chunk's last block) go through attention.
 // prefill: the rows are R consecutive positions of one sequence.
 // last_row: of the rows only the last one goes on behind its keys and values (its residual row stays where it is).
-static int layer_tail(eagle3_ctx* ctx, const eagle3_layer_weights& w, int B, int rows_per_seq, int R, bool prefill, int S_qkv,
-                      const int32_t* slot, const float* cs, const uint32_t* mask, const SeqInfo* seq, void* kc, void* vc,
-                      int max_len, int* S_down, hipStream_t st, bool last_row = false) {
+static int layer_tail(eagle3_ctx* ctx, const eagle3_layer_weights& w, int B, int rows_per_seq, int R, bool prefill, const uint32_t* mask,
+                      const SeqInfo* seq, void* kc, void* vc, int max_len, float* const copies[4], int* S_down, hipStream_t st,
+                      bool last_row = false) {
   const eagle3_config& c = ctx->cfg;
   const int k = c.hidden, H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim, I = c.intermediate;
-  CK(launch_rope_kv_write(ctx->bf16, ctx->part, S_qkv, R, H, Hkv, d, cs, slot, ctx->q, kc, vc, st));
   const char* q = (const char*)ctx->q;
   float* x = ctx->x;
   if (last_row) {                                   // the block that row R - 1 is in, as a sequence of that row alone
@@ -408,11 +441,21 @@ static int layer_tail(eagle3_ctx* ctx, const eagle3_layer_weights& w, int B, int
   }
   int S_o = 1;
   GemmWeights Wo = {{w.wo, nullptr, nullptr}, {k, 0, 0}, 1, 0};
-  TRY(ctx->project(ctx->act_attn, Wo, R, k, H * d, GEMM_EPI_PARTIAL, &S_o, st));
-  CK(launch_add_norm(ctx->bf16, x, ctx->part, S_o, R, k, w.norm_mlp, c.rms_eps, ctx->act_k, nullptr, st));
   GemmWeights Wgu = {{w.w_gate, w.w_up, nullptr}, {I, I, 0}, 2, 1};
-  TRY(ctx->project(ctx->act_k, Wgu, R, 2 * I, k, GEMM_EPI_SWIGLU, nullptr, st));
   GemmWeights Wd = {{w.w_down, nullptr, nullptr}, {k, 0, 0}, 1, 0};
+  if (!ctx->bf16) {
+    F32Fuse norm, out;
+    norm.gain = (const float*)w.norm_mlp; norm.eps = c.rms_eps;
+    for (int i = 0; copies && i < 4; ++i) out.copies[i] = copies[i];
+    CK(launch_gemm_f32((const float*)ctx->act_attn, Wo, R, k, H * d, GEMM_EPI_RESIDUAL, x, st));
+    CK(launch_gemm_f32(x, Wgu, R, 2 * I, k, GEMM_EPI_SWIGLU, (float*)ctx->act_h, st, norm));
+    CK(launch_gemm_f32((const float*)ctx->act_h, Wd, R, k, I, GEMM_EPI_RESIDUAL, x, st, out));
+    *S_down = 0;
+    return EAGLE3_OK;
+  }
+  TRY(ctx->project(ctx->act_attn, Wo, R, k, H * d, GEMM_EPI_PARTIAL, &S_o, st));
+  CK(launch_add_norm(true, x, ctx->part, S_o, R, k, w.norm_mlp, c.rms_eps, ctx->act_k, nullptr, st));
+  TRY(ctx->project(ctx->act_k, Wgu, R, 2 * I, k, GEMM_EPI_SWIGLU, nullptr, st));
   TRY(ctx->project(ctx->act_h, Wd, R, k, I, GEMM_EPI_PARTIAL, S_down, st));
   return EAGLE3_OK;
 }
@@ -423,34 +466,35 @@ static int layer_tail(eagle3_ctx* ctx, const eagle3_layer_weights& w, int B, int
 static int run_layers(eagle3_ctx* ctx, int B, int N, int R, bool prefill, const eagle3_kv* kv, int max_len, int l0, int l1, float* x_out,
                       float* logits, float* taps, float* dbg_hidden, hipStream_t st, bool norm_out = false) {
   const eagle3_config& c = ctx->cfg;
-  const int k = c.hidden, H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim;
+  const int k = c.hidden;
   const size_t Rk = (size_t)R * k;
-  int S_prev = 0;                                   // partial sums of the previous layer's MLP still to be added
-  for (int l = l0; l <= l1; ++l) {
-    // x becomes the output of layer l-1 here: record taps / debug copies, then norm for what follows
-    float* copies[4] = {nullptr, nullptr, nullptr, nullptr};
+  // what receives the residual stream in front of layer l, the output of layer l - 1
+  struct Copies { float* p[4]; };
+  auto copies_at = [&](int l) {
+    Copies co = {};
     if (l > 0 && taps)
       for (int t = 0; t < 3; ++t)
-        if (c.tap_layers[t] == l - 1) copies[t] = taps + (size_t)t * Rk;
-    if (dbg_hidden) copies[3] = dbg_hidden + (size_t)l * Rk;
-    if (l == l1 && x_out) copies[3] = x_out;
-    const bool head = l == c.n_layers;
-    if (l == l1 && !(head && logits) && !norm_out) {  // the range ends inside the stack: no norm needed
-      CK(launch_add_norm(ctx->bf16, ctx->x, ctx->part, S_prev, R, k, nullptr, c.rms_eps, nullptr, copies, st));
-      break;
-    }
-    const void* gain = head ? ctx->tw.final_norm : ctx->layers[l].norm_attn;
-    CK(launch_add_norm(ctx->bf16, ctx->x, ctx->part, S_prev, R, k, gain, c.rms_eps, ctx->act_k, copies, st));
+        if (c.tap_layers[t] == l - 1) co.p[t] = taps + (size_t)t * Rk;
+    if (dbg_hidden) co.p[3] = dbg_hidden + (size_t)l * Rk;
+    if (l == l1 && x_out) co.p[3] = x_out;
+    return co;
+  };
+  int S_prev = 0;                                   // bf16: partial sums of the previous layer's MLP still to be added
+  for (int l = l0; l <= l1; ++l) {
+    // bf16: x becomes the output of layer l-1 here, is copied, and normed for what follows.  fp32: x is complete, layer l-1 has
+    // made the copies, and the norm is part of the product that follows.
+    const Copies co = copies_at(l);
+    const bool any = co.p[0] || co.p[1] || co.p[2] || co.p[3], head = l == c.n_layers && l == l1 && logits;
+    if (head && ctx->bf16) return norm_head(ctx, ctx->x, S_prev, R, ctx->tw.final_norm, co.p, ctx->tw.lm_head, c.vocab, logits, st);
+    const bool norm = l < l1 || norm_out;
+    if (ctx->bf16) CK(launch_add_norm(true, ctx->x, ctx->part, S_prev, R, k, norm ? ctx->layers[l].norm_attn : nullptr, c.rms_eps, norm ? ctx->act_k : nullptr, co.p, st));
+    else if (l == l0 && any) CK(launch_add_norm(false, ctx->x, nullptr, 0, R, k, nullptr, c.rms_eps, nullptr, co.p, st));
+    if (head) return norm_head(ctx, ctx->x, 0, R, ctx->tw.final_norm, nullptr, ctx->tw.lm_head, c.vocab, logits, st);
     if (l == l1) break;
     const eagle3_layer_weights& w = ctx->layers[l];
-    GemmWeights Wqkv = {{w.wq, w.wk, w.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
-    int S_qkv = 1;
-    TRY(ctx->project(ctx->act_k, Wqkv, R, (H + 2 * Hkv) * d, k, GEMM_EPI_PARTIAL, &S_qkv, st));
-    TRY(layer_tail(ctx, w, B, N, R, prefill, S_qkv, ctx->slot, ctx->cs, ctx->mask, ctx->seq, kv->k[l], kv->v[l], max_len, &S_prev, st));
-  }
-  if (l1 == c.n_layers && logits) {
-    GemmWeights Wlm = {{ctx->tw.lm_head, nullptr, nullptr}, {c.vocab, 0, 0}, 1, 0};
-    return ctx->project(ctx->act_k, Wlm, R, c.vocab, k, GEMM_EPI_PARTIAL, nullptr, st, logits);
+    TRY(project_qkv(ctx, w, ctx->bf16 ? ctx->act_k : ctx->x, w.norm_attn, k, R, ctx->slot, ctx->cs, kv->k[l], kv->v[l], st));
+    const Copies next = copies_at(l + 1);
+    TRY(layer_tail(ctx, w, B, N, R, prefill, ctx->mask, ctx->seq, kv->k[l], kv->v[l], max_len, next.p, &S_prev, st));
   }
   return EAGLE3_OK;
 }
@@ -541,15 +585,12 @@ int eagle3_draft_expand(eagle3_ctx* ctx, const float* g_new, const int32_t* tok_
                             ctx->dw.norm_embed, ctx->dw.norm_feat, c.rms_eps, ctx->act_k, ctx->x, pos, d, c.rope_theta, ctx->cs,
                             st));
     }
-    GemmWeights Wqkv = {{w.wq, w.wk, w.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
-    int S_qkv = 1, S_down = 1;
-    TRY(ctx->project(ctx->act_k, Wqkv, M, (H + 2 * Hkv) * d, 2 * k, GEMM_EPI_PARTIAL, &S_qkv, st));
-    TRY(layer_tail(ctx, w, 1, M, M, false, S_qkv, slot, ctx->cs, mask, seq, kc, vc, max_len, &S_down, st));
+    TRY(project_qkv(ctx, w, ctx->act_k, nullptr, 2 * k, M, slot, ctx->cs, kc, vc, st));
     // a = y1 + MLP(...): keep it for the children, and norm it for the LM head
     float* copies[4] = {ctx->a_buf + (size_t)a_row0 * k, nullptr, nullptr, nullptr};
-    CK(launch_add_norm(ctx->bf16, ctx->x, ctx->part, S_down, M, k, ctx->dw.final_norm, c.rms_eps, ctx->act_k, copies, st));
-    GemmWeights Wlm = {{ctx->dw.lm_head, nullptr, nullptr}, {Vd, 0, 0}, 1, 0};
-    TRY(ctx->project(ctx->act_k, Wlm, M, Vd, k, GEMM_EPI_PARTIAL, nullptr, st, ctx->z));
+    int S_down = 1;
+    TRY(layer_tail(ctx, w, 1, M, M, false, mask, seq, kc, vc, max_len, copies, &S_down, st));
+    TRY(norm_head(ctx, ctx->x, S_down, M, ctx->dw.final_norm, copies, ctx->dw.lm_head, Vd, ctx->z, st));
     const int row0 = level == 1 ? n_new - 1 : 0, n_rows = level == 1 ? 1 : K;
     CK(launch_topk_rows(ctx->z, Vd, row0, n_rows, Vd, K, ctx->topk_scratch, ds.top_val, ds.top_idx, st));
     CK(launch_draft_select(ds, ctx->dw.d2t, dkv->kv_indptr, dkv->prefix_len, level, depth, K, n_new, 0, st));
@@ -611,22 +652,19 @@ int eagle3_draft_chain(eagle3_ctx* ctx, int32_t B, const float* g_new, const int
                             ctx->dw.norm_feat, c.rms_eps, ctx->act_k, ctx->x, pos, d, c.rope_theta, ctx->cs, st));
     }
     const int max_len = dkv->max_prefix_len + rows1 + level;
-    GemmWeights Wqkv = {{w.wq, w.wk, w.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
-    int S_qkv = 1, S_down = 1;
-    TRY(ctx->project(ctx->act_k, Wqkv, M, (H + 2 * Hkv) * d, 2 * k, GEMM_EPI_PARTIAL, &S_qkv, st));
-    TRY(layer_tail(ctx, w, B, rps, M, false, S_qkv, slot, ctx->cs, mask, seq, kc, vc, max_len, &S_down, st));
-    if (level == 1 && rows1 > 1) {
+    TRY(project_qkv(ctx, w, ctx->act_k, nullptr, 2 * k, M, slot, ctx->cs, kc, vc, st));
+    const bool gather = level == 1 && rows1 > 1;
+    float* copies[4] = {gather ? nullptr : ctx->a_buf, nullptr, nullptr, nullptr};
+    int S_down = 1;
+    TRY(layer_tail(ctx, w, B, rps, M, false, mask, seq, kc, vc, max_len, copies, &S_down, st));
+    if (gather) {
       // a = y1 + MLP(...) for every row, then the row of each sequence's last real position moves to row b
-      CK(launch_add_norm(ctx->bf16, ctx->x, ctx->part, S_down, M, k, nullptr, c.rms_eps, nullptr, nullptr, st));
+      if (ctx->bf16) CK(launch_add_norm(true, ctx->x, ctx->part, S_down, M, k, nullptr, c.rms_eps, nullptr, nullptr, st));
       CK(launch_chain_gather(ctx->x, n_new, B, rows1, k, ctx->a_buf, st));
       CK(hipMemcpyAsync(ctx->x, ctx->a_buf, (size_t)B * k * sizeof(float), hipMemcpyDeviceToDevice, st));
-      CK(launch_add_norm(ctx->bf16, ctx->x, nullptr, 0, B, k, ctx->dw.final_norm, c.rms_eps, ctx->act_k, nullptr, st));
-    } else {
-      float* copies[4] = {ctx->a_buf, nullptr, nullptr, nullptr};
-      CK(launch_add_norm(ctx->bf16, ctx->x, ctx->part, S_down, B, k, ctx->dw.final_norm, c.rms_eps, ctx->act_k, copies, st));
+      S_down = 0;
     }
-    GemmWeights Wlm = {{ctx->dw.lm_head, nullptr, nullptr}, {Vd, 0, 0}, 1, 0};
-    TRY(ctx->project(ctx->act_k, Wlm, B, Vd, k, GEMM_EPI_PARTIAL, nullptr, st, ctx->z));
+    TRY(norm_head(ctx, ctx->x, S_down, B, ctx->dw.final_norm, copies, ctx->dw.lm_head, Vd, ctx->z, st));
     CK(launch_topk_rows(ctx->z, Vd, 0, B, Vd, 1, ctx->topk_scratch, cs.top_val, cs.top_idx, st));
     CK(launch_chain_select(cs, ctx->dw.d2t, dkv->kv_indptr, dkv->prefix_len, n_new, tok_new, B, rows1, level, length,
                            chain_tok, chain_logp, st));
@@ -666,20 +704,14 @@ int eagle3_prefill(eagle3_ctx* ctx, const int32_t* tokens, int32_t T, const eagl
     if (tail_row) {
       TRY(run_layers(ctx, blocks, blocks == 1 ? n : 64, n, true, kv, max_len, 0, L - 1, nullptr, nullptr, ctx->chunk_taps, nullptr, st, true));
       const eagle3_layer_weights& wl = ctx->layers[L - 1];
-      GemmWeights Wl = {{wl.wq, wl.wk, wl.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
-      int S_qkv = 1;
-      TRY(ctx->project(ctx->act_k, Wl, n, (H + 2 * Hkv) * d, k, GEMM_EPI_PARTIAL, &S_qkv, st));
-      if (last) TRY(layer_tail(ctx, wl, 1, 1, n, true, S_qkv, ctx->slot, ctx->cs, ctx->mask, ctx->seq, kv->k[L - 1], kv->v[L - 1], max_len, &S_tail, st, true));
-      else CK(launch_rope_kv_write(ctx->bf16, ctx->part, S_qkv, n, H, Hkv, d, ctx->cs, ctx->slot, ctx->q, kv->k[L - 1], kv->v[L - 1], st));
+      TRY(project_qkv(ctx, wl, ctx->bf16 ? ctx->act_k : ctx->x, wl.norm_attn, k, n, ctx->slot, ctx->cs, kv->k[L - 1], kv->v[L - 1], st));
+      if (last) TRY(layer_tail(ctx, wl, 1, 1, n, true, ctx->mask, ctx->seq, kv->k[L - 1], kv->v[L - 1], max_len, nullptr, &S_tail, st, true));
     } else {
       TRY(run_layers(ctx, blocks, blocks == 1 ? n : 64, n, true, kv, max_len, 0, L, nullptr, nullptr, ctx->chunk_taps, nullptr, st));
     }
     CK(launch_advance_lengths((int32_t*)kv->prefix_len, 1, n, st));
     if (last) {                                       // next-token logits of the last position only
-      CK(launch_add_norm(ctx->bf16, ctx->x + (size_t)(n - 1) * k, S_tail ? ctx->part : nullptr, S_tail, 1, k, ctx->tw.final_norm, c.rms_eps,
-                         ctx->act_k, nullptr, st));
-      GemmWeights Wlm = {{ctx->tw.lm_head, nullptr, nullptr}, {c.vocab, 0, 0}, 1, 0};
-      TRY(ctx->project(ctx->act_k, Wlm, 1, c.vocab, k, GEMM_EPI_PARTIAL, nullptr, st, logits_last));
+      TRY(norm_head(ctx, ctx->x + (size_t)(n - 1) * k, S_tail, 1, ctx->tw.final_norm, nullptr, ctx->tw.lm_head, c.vocab, logits_last, st));
     }
     // fused features of the chunk's positions; the draft cache rows of those whose next token is known
     TRY(fuse_rows(ctx, ctx->chunk_taps, ctx->chunk_taps + nk, ctx->chunk_taps + 2 * nk, n, ctx->chunk_g, st));
@@ -689,10 +721,7 @@ int eagle3_prefill(eagle3_ctx* ctx, const int32_t* tokens, int32_t T, const eagl
       CK(launch_prefill_prep(dkv->kv_indptr, dkv->prefix_len, m, d, c.rope_theta, ctx->pos1, ctx->slot, ctx->mask, nullptr, ctx->seq, st));
       CK(launch_draft_input(ctx->bf16, ctx->tw.embed, c.vocab, tokens + c0 + 1, ctx->chunk_g, nullptr, m, k, ctx->dw.norm_embed,
                             ctx->dw.norm_feat, c.rms_eps, ctx->act_k, ctx->x, ctx->pos1, d, c.rope_theta, ctx->cs, st));
-      GemmWeights Wqkv = {{w.wq, w.wk, w.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
-      int S_qkv = 1;
-      TRY(ctx->project(ctx->act_k, Wqkv, m, (H + 2 * Hkv) * d, 2 * k, GEMM_EPI_PARTIAL, &S_qkv, st));
-      CK(launch_rope_kv_write(ctx->bf16, ctx->part, S_qkv, m, H, Hkv, d, ctx->cs, ctx->slot, ctx->q, dkv->k[0], dkv->v[0], st));
+      TRY(project_qkv(ctx, w, ctx->act_k, nullptr, 2 * k, m, ctx->slot, ctx->cs, dkv->k[0], dkv->v[0], st));
       CK(launch_advance_lengths((int32_t*)dkv->prefix_len, 1, m, st));
     }
   }

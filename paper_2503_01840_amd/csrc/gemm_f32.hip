@@ -1,11 +1,15 @@
 // fp32 GEMM for the exact-arithmetic (small model) configuration: out[m, n] = sum_k x[m, k] w[n, k] over up to three
-// stacked weight matrices, or h = silu(gate) * up of two.
+// stacked weight matrices, or h = silu(gate) * up of two.  What stands between two products of a layer is done by them, as a launch
+// of its own costs as much as a product does here: the RMSNorm of the input rows (every wavefront sums their squares along with
+// its own products; 3.1 us a launch saved), the rotation and cache write of q/k/v, and the residual sum.
 //
 // One wavefront per (weight row, group of 8 activation rows); the lanes stride over K, four consecutive k at a time.  At
 // these sizes (a few hundred rows of a few hundred k, all of it in L2) a launch is bound by its own latency: the loads of
 // an iteration are requested together, the eight sums of a wavefront are reduced together (two halving steps leave four
 // sums per register, then four DPP steps), and a stacked weight is one launch (16 rows of a 256 x 256 weight: 5.2 us with one
 // load per iteration and eight shuffle reductions one after the other, 3.7 us now).
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -18,7 +22,9 @@ struct F32Params {
   int rows[3];
   int nmat, M, N, K;
   float* out;
+  F32Fuse f;
 };
+enum { STORE, SWIGLU, RESIDUAL, ROPE };
 
 // acc[r] (r = 0..7) summed over the 64 lanes: on return lane 16 j + i holds row_of(j) of lo and 4 + row_of(j) of hi,
 // row_of = 0, 2, 1, 3.
@@ -39,23 +45,34 @@ __device__ __forceinline__ void sum8(const float (&acc)[RM], float& lo, float& h
   lo = xlane_sum_step<3>(lo); hi = xlane_sum_step<3>(hi);
 }
 
-// NW weight rows per wavefront (2: gate and up); VEC: 16-byte loads
-template <int NW, bool VEC>
-__device__ __forceinline__ void dot_rows(const F32Params& p, const float* const (&wr)[NW], int m0, int lane, float (&acc)[NW][RM]) {
+// NW weight rows per wavefront (2: gate and up, or the two of a rotary pair); VEC: 16-byte loads.  NORM: acc sums gain * x * w, and
+// ss the squares of x.
+template <int NW, bool NORM, bool VEC>
+__device__ __forceinline__ void dot_rows(const F32Params& p, const float* const (&wr)[NW], int m0, int lane, float (&acc)[NW][RM],
+                                         float (&ss)[RM]) {
   const float* xr[RM];
 #pragma unroll
   for (int r = 0; r < RM; ++r) xr[r] = p.x + (size_t)min(m0 + r, p.M - 1) * p.K;
 #pragma unroll
-  for (int i = 0; i < NW; ++i)
+  for (int r = 0; r < RM; ++r) {
+    ss[r] = 0.f;
 #pragma unroll
-    for (int r = 0; r < RM; ++r) acc[i][r] = 0.f;
+    for (int i = 0; i < NW; ++i) acc[i][r] = 0.f;
+  }
   if constexpr (VEC) {
     for (int k = 4 * lane; k < p.K; k += 256) {
-      float4 w[NW], x[RM];
+      float4 w[NW], x[RM], g;
 #pragma unroll
       for (int i = 0; i < NW; ++i) w[i] = *(const float4*)(wr[i] + k);
 #pragma unroll
       for (int r = 0; r < RM; ++r) x[r] = *(const float4*)(xr[r] + k);
+      if constexpr (NORM) {
+        g = *(const float4*)(p.f.gain + k);
+#pragma unroll
+        for (int r = 0; r < RM; ++r) ss[r] = fmaf(x[r].w, x[r].w, fmaf(x[r].z, x[r].z, fmaf(x[r].y, x[r].y, fmaf(x[r].x, x[r].x, ss[r]))));
+#pragma unroll
+        for (int i = 0; i < NW; ++i) w[i] = make_float4(w[i].x * g.x, w[i].y * g.y, w[i].z * g.z, w[i].w * g.w);
+      }
 #pragma unroll
       for (int i = 0; i < NW; ++i)
 #pragma unroll
@@ -63,60 +80,108 @@ __device__ __forceinline__ void dot_rows(const F32Params& p, const float* const 
           acc[i][r] = fmaf(x[r].w, w[i].w, fmaf(x[r].z, w[i].z, fmaf(x[r].y, w[i].y, fmaf(x[r].x, w[i].x, acc[i][r]))));
     }
   } else {
-    for (int k = lane; k < p.K; k += 64)
+    for (int k = lane; k < p.K; k += 64) {
+      const float g = NORM ? p.f.gain[k] : 1.f;
 #pragma unroll
-      for (int i = 0; i < NW; ++i) {
-        const float w = wr[i][k];
+      for (int r = 0; r < RM; ++r) {
+        const float x = xr[r][k];
+        if constexpr (NORM) ss[r] = fmaf(x, x, ss[r]);
 #pragma unroll
-        for (int r = 0; r < RM; ++r) acc[i][r] = fmaf(xr[r][k], w, acc[i][r]);
+        for (int i = 0; i < NW; ++i) acc[i][r] = fmaf(x, wr[i][k] * g, acc[i][r]);
       }
+    }
   }
 }
 
-template <bool SWIGLU, bool VEC>
+template <int EPI, bool NORM, bool VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Params p) {
-  constexpr int NW = SWIGLU ? 2 : 1;
+  constexpr int NW = EPI == SWIGLU || EPI == ROPE ? 2 : 1;
   const int lane = threadIdx.x & 63, n = blockIdx.x * 4 + (threadIdx.x >> 6), m0 = blockIdx.y * RM;
   if (n >= p.N) return;
   const float* wr[NW];
-  if constexpr (SWIGLU) {
+  const int half = p.f.d / 2;
+  if constexpr (EPI == SWIGLU) {
     wr[0] = p.w[0] + (size_t)n * p.K;
     wr[1] = p.w[1] + (size_t)n * p.K;
   } else {
-    int i = 0, row = n;
+    int i = 0, row = EPI == ROPE ? n / half * p.f.d + n % half : n;              // ROPE: pair n % half of head n / half
     while (i + 1 < p.nmat && row >= p.rows[i]) { row -= p.rows[i]; ++i; }
     wr[0] = p.w[i] + (size_t)row * p.K;
+    if constexpr (EPI == ROPE) wr[1] = wr[0] + (size_t)half * p.K;
   }
-  float acc[NW][RM], lo[NW], hi[NW];
-  dot_rows<NW, VEC>(p, wr, m0, lane, acc);
+  float acc[NW][RM], ss[RM], lo[NW], hi[NW];
+  dot_rows<NW, NORM, VEC>(p, wr, m0, lane, acc, ss);
 #pragma unroll
   for (int i = 0; i < NW; ++i) sum8(acc[i], lo[i], hi[i]);
+  if constexpr (NORM) {
+    float s_lo, s_hi;
+    sum8(ss, s_lo, s_hi);
+    const float i_lo = 1.0f / sqrtf(s_lo / (float)p.K + p.f.eps), i_hi = 1.0f / sqrtf(s_hi / (float)p.K + p.f.eps);
+#pragma unroll
+    for (int i = 0; i < NW; ++i) { lo[i] *= i_lo; hi[i] *= i_hi; }
+  }
   const int j = lane >> 4, m = m0 + ((j & 1) << 1 | j >> 1);
   if (lane & 15) return;
-  auto value = [](const float (&v)[NW]) {
-    if constexpr (SWIGLU) return v[0] / (1.f + expf(-v[0])) * v[1];
-    else return v[0];
+  auto put = [&](int m, const float (&v)[NW]) {
+    if (m >= p.M) return;
+    const size_t at = (size_t)m * p.N + n;
+    if constexpr (EPI == STORE) p.out[at] = v[0];
+    if constexpr (EPI == SWIGLU) p.out[at] = v[0] / (1.f + expf(-v[0])) * v[1];
+    if constexpr (EPI == RESIDUAL) {
+      const float x = p.out[at] + v[0];
+      p.out[at] = x;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (p.f.copies[i]) p.f.copies[i][at] = x;
+    }
+    if constexpr (EPI == ROPE) {
+      const F32Fuse& f = p.f;
+      const int h = n / half, i = n % half;
+      float a = v[0], b = v[1];
+      if (h < f.H + f.Hkv) {
+        const float c = f.cs[(size_t)m * f.d + i], s = f.cs[(size_t)m * f.d + half + i];
+        a = v[0] * c - v[1] * s;
+        b = v[1] * c + v[0] * s;
+      }
+      float* dst = h < f.H ? p.out + ((size_t)m * f.H + h) * f.d
+                           : (h < f.H + f.Hkv ? f.kc + ((size_t)f.slot[m] * f.Hkv + h - f.H) * f.d
+                                              : f.vc + ((size_t)f.slot[m] * f.Hkv + h - f.H - f.Hkv) * f.d);
+      dst[i] = a;
+      dst[half + i] = b;
+    }
   };
-  if (m < p.M) p.out[(size_t)m * p.N + n] = value(lo);
-  if (m + 4 < p.M) p.out[(size_t)(m + 4) * p.N + n] = value(hi);
+  put(m, lo);
+  put(m + 4, hi);
 }
 }  // namespace
 
-hipError_t launch_gemm_f32(const float* x, const GemmWeights& W, int M, int N, int K, int epi, float* out, hipStream_t st) {
+hipError_t launch_gemm_f32(const float* x, const GemmWeights& W, int M, int N, int K, int epi, float* out, hipStream_t st,
+                           const F32Fuse& fuse) {
   if (M <= 0 || N <= 0 || K <= 0) return hipErrorInvalidValue;
   if (epi == GEMM_EPI_SWIGLU && (W.mode != 1 || N % 2)) return hipErrorInvalidValue;
+  if (epi == GEMM_EPI_ROPE && (fuse.d < 8 || fuse.d % 8 || N != (fuse.H + 2 * fuse.Hkv) * fuse.d)) return hipErrorInvalidValue;
+  if (fuse.gain && (K % 4 || K > 8192)) return hipErrorInvalidValue;
   F32Params p;
   p.x = x;
-  bool vec = K % 4 == 0 && ((uintptr_t)x & 15) == 0;         // 16-byte loads in every row
+  bool vec = K % 4 == 0 && (((uintptr_t)x | (uintptr_t)fuse.gain) & 15) == 0;        // 16-byte loads in every row
   for (int i = 0; i < 3; ++i) {
     p.w[i] = (const float*)W.w[i];
     p.rows[i] = W.rows[i];
     if (i < W.nmat) vec = vec && ((uintptr_t)W.w[i] & 15) == 0;
   }
-  p.nmat = W.nmat; p.M = M; p.N = epi == GEMM_EPI_SWIGLU ? N / 2 : N; p.K = K;
+  p.nmat = W.nmat; p.M = M; p.N = epi == GEMM_EPI_SWIGLU || epi == GEMM_EPI_ROPE ? N / 2 : N; p.K = K;
   p.out = out;
-  auto kernel = epi == GEMM_EPI_SWIGLU ? (vec ? gemm_f32_kernel<true, true> : gemm_f32_kernel<true, false>)
-                                       : (vec ? gemm_f32_kernel<false, true> : gemm_f32_kernel<false, false>);
-  hipLaunchKernelGGL(kernel, dim3((p.N + 3) / 4, (M + RM - 1) / RM), dim3(256), 0, st, p);
+  p.f = fuse;
+  const dim3 grid((p.N + 3) / 4, (M + RM - 1) / RM);
+  auto run = [&](auto e) {
+    constexpr int E = decltype(e)::value;
+    auto kernel = fuse.gain ? (vec ? gemm_f32_kernel<E, true, true> : gemm_f32_kernel<E, true, false>)
+                            : (vec ? gemm_f32_kernel<E, false, true> : gemm_f32_kernel<E, false, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, p);
+  };
+  if (epi == GEMM_EPI_SWIGLU) run(std::integral_constant<int, SWIGLU>());
+  else if (epi == GEMM_EPI_RESIDUAL) run(std::integral_constant<int, RESIDUAL>());
+  else if (epi == GEMM_EPI_ROPE) run(std::integral_constant<int, ROPE>());
+  else run(std::integral_constant<int, STORE>());
   return hipGetLastError();
 }

@@ -16,7 +16,7 @@ struct GemmWeights {
   int nmat;
   int mode;
 };
-enum { GEMM_EPI_PARTIAL = 0, GEMM_EPI_SWIGLU = 1 };
+enum { GEMM_EPI_PARTIAL = 0, GEMM_EPI_SWIGLU = 1, GEMM_EPI_RESIDUAL = 2, GEMM_EPI_ROPE = 3 };   // the last two: fp32 only
 
 // Y = X W^T for few rows (M <= a few hundred) streaming the weights once: bf16 inputs, fp32 accumulate.
 //   x      fragment-major bf16 [ceil64(M), K] (see xf_offset)
@@ -36,8 +36,21 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
                             size_t out_capacity_floats, int* S_out, hipStream_t st, hipEvent_t ev_start = nullptr,
                             hipEvent_t ev_stop = nullptr);
 
-// fp32 GEMM, exact arithmetic: x [M, K], weights [N, K] stacked.  epi PARTIAL: out [M, N]; SWIGLU (mode 1): out [M, N / 2].
-hipError_t launch_gemm_f32(const float* x, const GemmWeights& W, int M, int N, int K, int epi, float* out, hipStream_t st);
+// fp32 GEMM, exact arithmetic: x [M, K], weights [N, K] stacked.  epi PARTIAL: out [M, N]; SWIGLU (mode 1): out [M, N / 2];
+// RESIDUAL: out [M, N] += , and copies of the sum to each non-null copies[i]; ROPE: the rows are q|k|v heads, out = q [M, H, d]
+// rotated, k rotated and v to the cache rows slot[m].
+struct F32Fuse {
+  const float* gain = nullptr;          // x is the RMSNorm of the rows given, with this gain
+  float eps = 0.f;
+  float* copies[4] = {nullptr, nullptr, nullptr, nullptr};
+  const float* cs = nullptr;            // rotary table [M, d]
+  const int32_t* slot = nullptr;
+  float* kc = nullptr;
+  float* vc = nullptr;
+  int H = 0, Hkv = 0, d = 0;
+};
+hipError_t launch_gemm_f32(const float* x, const GemmWeights& W, int M, int N, int K, int epi, float* out, hipStream_t st,
+                           const F32Fuse& fuse = F32Fuse());
 
 // ---------------------------------------------------------------- elementwise (elementwise.hip)
 struct SeqInfo {           // one per sequence, device resident
