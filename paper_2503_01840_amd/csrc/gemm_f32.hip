@@ -99,59 +99,70 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Params p) {
   const int lane = threadIdx.x & 63, n = blockIdx.x * 4 + (threadIdx.x >> 6), m0 = blockIdx.y * RM;
   if (n >= p.N) return;
   const float* wr[NW];
-  const int half = p.f.d / 2;
+  const F32Fuse& f = p.f;
+  const int half = f.d / 2;
+  const int head = EPI == ROPE ? n / half : 0, pair = EPI == ROPE ? n - head * half : 0;
   if constexpr (EPI == SWIGLU) {
     wr[0] = p.w[0] + (size_t)n * p.K;
     wr[1] = p.w[1] + (size_t)n * p.K;
   } else {
-    int i = 0, row = EPI == ROPE ? n / half * p.f.d + n % half : n;              // ROPE: pair n % half of head n / half
+    int i = 0, row = EPI == ROPE ? head * f.d + pair : n;
     while (i + 1 < p.nmat && row >= p.rows[i]) { row -= p.rows[i]; ++i; }
     wr[0] = p.w[i] + (size_t)row * p.K;
     if constexpr (EPI == ROPE) wr[1] = wr[0] + (size_t)half * p.K;
   }
-  float acc[NW][RM], ss[RM], lo[NW], hi[NW];
+  // what the epilogue reads of rows m and m + 4, requested before the products
+  const int j = lane >> 4, m = m0 + ((j & 1) << 1 | j >> 1), mc[2] = {min(m, p.M - 1), min(m + 4, p.M - 1)};
+  float before[2], cosine[2] = {1.f, 1.f}, sine[2] = {0.f, 0.f};
+  int slot[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    if constexpr (EPI == RESIDUAL) before[i] = p.out[(size_t)mc[i] * p.N + n];
+    if constexpr (EPI == ROPE) {
+      if (head < f.H + f.Hkv) { cosine[i] = f.cs[(size_t)mc[i] * f.d + pair]; sine[i] = f.cs[(size_t)mc[i] * f.d + half + pair]; }
+      slot[i] = f.slot[mc[i]];
+    }
+  }
+  float acc[NW][RM], ss[RM], sum[2][NW];
   dot_rows<NW, NORM, VEC>(p, wr, m0, lane, acc, ss);
 #pragma unroll
-  for (int i = 0; i < NW; ++i) sum8(acc[i], lo[i], hi[i]);
+  for (int i = 0; i < NW; ++i) sum8(acc[i], sum[0][i], sum[1][i]);
   if constexpr (NORM) {
-    float s_lo, s_hi;
-    sum8(ss, s_lo, s_hi);
-    const float i_lo = 1.0f / sqrtf(s_lo / (float)p.K + p.f.eps), i_hi = 1.0f / sqrtf(s_hi / (float)p.K + p.f.eps);
+    float sq[2];
+    sum8(ss, sq[0], sq[1]);
 #pragma unroll
-    for (int i = 0; i < NW; ++i) { lo[i] *= i_lo; hi[i] *= i_hi; }
+    for (int i = 0; i < 2; ++i) {
+      const float inv = 1.0f / sqrtf(sq[i] / (float)p.K + f.eps);
+#pragma unroll
+      for (int w = 0; w < NW; ++w) sum[i][w] *= inv;
+    }
   }
-  const int j = lane >> 4, m = m0 + ((j & 1) << 1 | j >> 1);
   if (lane & 15) return;
-  auto put = [&](int m, const float (&v)[NW]) {
-    if (m >= p.M) return;
-    const size_t at = (size_t)m * p.N + n;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = m + 4 * i;
+    if (row >= p.M) break;
+    const float (&v)[NW] = sum[i];
+    const size_t at = (size_t)row * p.N + n;
     if constexpr (EPI == STORE) p.out[at] = v[0];
     if constexpr (EPI == SWIGLU) p.out[at] = v[0] / (1.f + expf(-v[0])) * v[1];
     if constexpr (EPI == RESIDUAL) {
-      const float x = p.out[at] + v[0];
+      const float x = before[i] + v[0];
       p.out[at] = x;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (p.f.copies[i]) p.f.copies[i][at] = x;
+      for (int t = 0; t < 4; ++t)
+        if (f.copies[t]) f.copies[t][at] = x;
     }
     if constexpr (EPI == ROPE) {
-      const F32Fuse& f = p.f;
-      const int h = n / half, i = n % half;
       float a = v[0], b = v[1];
-      if (h < f.H + f.Hkv) {
-        const float c = f.cs[(size_t)m * f.d + i], s = f.cs[(size_t)m * f.d + half + i];
-        a = v[0] * c - v[1] * s;
-        b = v[1] * c + v[0] * s;
-      }
-      float* dst = h < f.H ? p.out + ((size_t)m * f.H + h) * f.d
-                           : (h < f.H + f.Hkv ? f.kc + ((size_t)f.slot[m] * f.Hkv + h - f.H) * f.d
-                                              : f.vc + ((size_t)f.slot[m] * f.Hkv + h - f.H - f.Hkv) * f.d);
-      dst[i] = a;
-      dst[half + i] = b;
+      if (head < f.H + f.Hkv) { a = v[0] * cosine[i] - v[1] * sine[i]; b = v[1] * cosine[i] + v[0] * sine[i]; }
+      float* dst = head < f.H ? p.out + ((size_t)row * f.H + head) * f.d
+                              : (head < f.H + f.Hkv ? f.kc + ((size_t)slot[i] * f.Hkv + head - f.H) * f.d
+                                                    : f.vc + ((size_t)slot[i] * f.Hkv + head - f.H - f.Hkv) * f.d);
+      dst[pair] = a;
+      dst[half + pair] = b;
     }
-  };
-  put(m, lo);
-  put(m + 4, hi);
+  }
 }
 }  // namespace
 

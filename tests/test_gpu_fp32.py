@@ -48,3 +48,10 @@ def test_small_models_fp32(hidden, heads, kv_heads, d, inter, N):
     logits, taps = E.eagle3_tree_verify(ctx, i32(tok)[None], i32(parent)[None], kv)
     assert np.max(np.abs(logits[0].cpu().numpy() - ref["logits"])) < 1e-4
     assert np.max(np.abs(taps[:, 0].cpu().numpy() - ref["taps"])) < 1e-4
+
+
+# heads of 64 and 128: lane groups that share a key; 21 + N keys around a full batch of them (80 and 40), fewer keys than groups
+@pytest.mark.parametrize("heads,kv_heads,d", [(4, 2, 64), (3, 1, 128)])
+@pytest.mark.parametrize("N", [1, 18, 19, 20, 58, 59, 60, 64])
+def test_small_models_fp32_with_wide_heads(heads, kv_heads, d, N):
+    test_small_models_fp32(64, heads, kv_heads, d, 100, N)
