@@ -4,6 +4,7 @@
 // and that XCD has ceil(weight tiles / 8) of them for every row block and K range.
 #pragma once
 #include <cstddef>
+#include <initializer_list>
 
 struct WideTiles {
   int rows, cols;      // output tile of a workgroup
@@ -29,27 +30,29 @@ inline WideTiles wide_tiles_k64(int M, int N, int K, bool swiglu, size_t out_cap
   // exactly one CU and a stage takes in 48 KB instead of the 2 x 32 KB of two 128 x 128 workgroups (measured at 256 rows, 8B
   // shapes: q/k/v 33.4 -> 26.6 us, down 54.3 -> 47.6, gate/up 86.0 -> 78.9)
   if (M > 128 && M <= 256) return pick(256, 128, 192, 8);
-  // 256 x 256 tiles when there are enough rows and, with at least 16 stages left per workgroup after split-K, enough workgroups;
-  // else 128 x 128 tiles, two workgroups per CU
-  const WideTiles big = pick(256, 256, 160, 16);
-  const bool few = M < 384 || (ceil_div(N, 256) * ceil_div(M, 256) * big.S < 160 && !swiglu);
-  const WideTiles t = few ? pick(128, 128, 384, 8) : big;
-  if (few && !(swiglu && M > 256)) return t;
-  // 192 x 256 tiles where the fullest XCD gets done sooner with them.  Unit: a 256 x 256 workgroup's walk over all of K; 192 rows
-  // take 0.8 of it, two 128 x 128 workgroups on one CU 0.6, one alone 0.4.  Over eleven model widths from 256 to 8192, 257..2048
-  // rows, no product becomes slower by this rule (more than 2.5 %), and of those that would gain two are missed.  8B width, 256
-  // (or 128) -> 192 rows, us: gate/up 300 rows 120 -> 86, 520 rows 194 -> 160, 1100 rows 302 -> 257; q/k/v 600 rows 67 -> 47; down
-  // 1100 rows 167 -> 133.  Not taken: gate/up 2048 rows 423 / 446; hidden 5120, o at 400 rows 40 / 61 (36 instead of 24
-  // workgroups on an XCD: a second round); hidden 2048, gate/up at 300 rows 30 / 41 (one 128 x 128 workgroup per CU).
-  const WideTiles mid = pick(192, 256, 160, 16);
-  auto per_xcd = [&](const WideTiles& w) { return ceil_div(ceil_div(N, w.cols), 8) * ceil_div(M, w.rows) * w.S; };
+  if (M <= 128) return pick(128, 128, 384, 8);
+  // More rows: the tile whose launch is over first by this estimate, in microseconds.  A workgroup takes a start and an end, and a
+  // time per 64 k; the fullest XCD runs its workgroups in rounds of 32, of 64 for 128 x 128 tiles (two on a CU side by side, one
+  // alone where there are no more than 32 left); the consumer then reads the partial sums (5 TB/s).  The ten numbers are a fit to 17 products
+  // of the 8B, 70B and two narrower widths at 16 row counts from 257 to 2048, each with all four tiles: what the estimate picks is 0.3 %
+  // slower than the best of the four on average (15 % at worst: gate/up of hidden 2048, 576 and 1300 rows), and 6 % faster than
+  // picking by workgroup counts.  8B width, product and reading, us, 256 x 256 / 192 x 256 / 256 x 128 / 128 x 128: q/k/v 300 rows
+  // 38 / 35 / 36 / 44, 512 rows 44 / 64 / 40 / 50; down 300 rows 63 / 58 / 60 / 69, 512 rows 73 / 80 / 67 / 83; o 1024 rows 49 / 49 / 42 / 50;
+  // gate/up 300 rows 101 / 88 / 117 / 119, 1024 rows 197 / 235 / 231 / 274, 2048 rows 384 / 395 / 426 / 507; hidden 2048, gate/up 450 rows
+  // 47 / 41 / 32 / 41.
   auto cost = [&](const WideTiles& w) -> float {
-    const int n = per_xcd(w);
-    if (w.cols == 256) return ceil_div(n, 32) * (w.rows == 256 ? 1.f : 0.8f) / w.S;
+    const int n = ceil_div(ceil_div(N, w.cols), 8) * ceil_div(M, w.rows) * w.S;
+    const float stages = (float)KT / w.S, read = swiglu ? 0.f : (float)w.S * M * N * (4.f / 5e6f);
+    if (w.cols == 256) return ceil_div(n, 32) * (w.rows == 256 ? 8.72f + 1.43f * stages : 8.0f + 1.14f * stages) + read;
+    if (w.rows == 256) return ceil_div(n, 32) * (6.74f + 0.85f * stages) + read;
+    const float two = 8.4f + 1.13f * stages, one = 4.66f + 0.79f * stages;
     const int rest = n % 64;
-    return (n / 64 * 0.6f + (rest == 0 ? 0.f : rest <= 32 ? 0.4f : 0.6f)) / w.S;
+    return n / 64 * two + (rest == 0 ? 0.f : rest <= 32 ? one : two) + read;
   };
-  return cost(mid) < cost(t) ? mid : t;
+  WideTiles best = pick(256, 256, 160, 16);
+  for (const WideTiles& t : {pick(192, 256, 160, 16), pick(256, 128, 192, 16), pick(128, 128, 384, 8)})
+    if (cost(t) < cost(best)) best = t;
+  return best;
 }
 
 // Tiles of 128 weight rows leave room in LDS for weight stages of 128 k, whose row pieces of 256 bytes HBM delivers faster than
