@@ -8,13 +8,14 @@
 //
 // bf16 kernel (head_dim 128).  A workgroup owns 128 query rows of one KV head: HG (1, 2 or 4) of the query heads that
 // share it x 128 / HG consecutive queries, so that every K/V tile it stages serves all of them.  8 wavefronts = 4 groups
-// of 32 rows x 2 halves of every 128-key tile; a wavefront takes its half in two blocks of 32 keys.  (Where the chip would not be
+// of 32 rows x 2 halves of every 128-key tile; a wavefront takes the first and third or the second and fourth of the tile's
+// 32-key blocks, so that both are done early where the last tile ends after 64 keys.  (Where the chip would not be
 // full: 64 rows, 4 wavefronts.)
 //   * Tiles reach LDS by direct global-to-LDS loads, both K and V two tiles ahead, swizzled per key; K has two slots and V three,
 //     as its values are read one block later than its scores; scores are
 //     produced transposed (S^T = K Q^T) so that a lane owns one query; the V^T operand comes from the transposing LDS
 //     read; exp(S) enters the value product as a bf16 head plus a bf16 tail.
-//   * One block is a matrix-unit time of 24 products (8 score + 16 value) against ~540 issue cycles of softmax.  Run
+//   * One block is a matrix-unit time of 24 products (8 score + 16 value, 768 cycles) against ~450 issue cycles of softmax.  Run
 //     one after the other they add up (all wavefronts pass the same barrier, so they stay in phase); here the softmax of
 //     block i runs between the score products of block i + 1 and the value products of block i - 1, none of which
 //     depend on it.
@@ -22,11 +23,13 @@
 //   * The own keys of the simulated steps come last; their rows arrive while the last block is worked on.
 //   * Workgroups of later queries walk over more keys: they are handed out first, and the KV head is the fastest index,
 //     so that with 8 KV heads each XCD keeps one head's keys in its L2.
-// What bounds it: the chip's power.  At T = 2048, 32 heads over 8, the matrix units are busy 58 % of the cycles and the clock
-// drops to 1.86 GHz (1.53 GHz at T = 4096); 2.8 us per tile, 17 tiles per CU, plus 2.5 us before and 2.6 us after the walk
-// of each of a CU's two workgroups.  Measured against a kernel of one head x 64 queries per workgroup (4 wavefronts, scores,
+// What bounds it: the chip's power where every CU has two workgroups and more (at T = 2048, 32 heads over 8, the clock drops to 1.86 GHz, at
+// T = 4096 to 1.53), and the walk of the longest workgroup with its start, own keys and merge where there are fewer.  The softmax
+// must stay in the gaps it is written into: with the sum of the weights formed behind the block, copies between registers, a last
+// tile taken whole and the output rescaled at every own key it was 29.0 instead of 22.6 us (T = 517, 64 heads, s = 5), 72 instead
+// of 67 (T = 2048, 32 heads over 8, s = 5) and 36.0 instead of 32.6 (T = 2048, 8 heads, s = 0).  Measured against a kernel of one head x 64 queries per workgroup (4 wavefronts, scores,
 // softmax and values one after the other, own keys read from global memory by every lane for itself): T = 2048, s = 2:
-// 108 -> 65 us; T = 517, 64 heads, s = 5: 61 -> 28.5 us.
+// 108 -> 65 us; T = 517, 64 heads, s = 5: 61 -> 22.6 us.
 // fp32 kernel: one workgroup per (query, head), exact arithmetic, for small checks.
 #include <algorithm>
 
@@ -185,6 +188,10 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
   }
   issue(kbase, koff, 0, 0);
   issue(vbase, voff, 0, V_BASE);
+  if (n_tiles > 1) {
+    issue(kbase, koff, 1, TILE_BYTES);
+    issue(vbase, voff, 1, V_BASE + TILE_BYTES);
+  }
 
   uint32_t minus_lo = 0x0000BF80u, minus_hi = 0xBF800000u;   // bf16 pairs (-1, 0) and (0, -1), kept in registers
   uint32_t ones = 0x3F803F80u;
@@ -197,7 +204,9 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
     for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
   float m_run = NEG, l_run = 0.f;              // l_run: this lane's share; its partner lane ^ 32 holds the rest
 
-  CAUSAL_WAIT_LOADS(0);                        // my part of tile 0 has landed; the barrier extends that to everyone's
+  // my part of the queries and of tile 0 has landed (loads complete in order); the barrier extends that to everyone's
+  if (n_tiles > 1) CAUSAL_WAIT_LOADS(2 * IPW);
+  else CAUSAL_WAIT_LOADS(0);
   __syncthreads();
   u32x4 qf[8];
 #pragma unroll
@@ -209,21 +218,22 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
   // returns, for head-dim index db * 32 + (l & 31), keys 16 m + 8 c + 4 kg + 0..3 of the block; the lane hands in the
   // address of 4 head-dim values of ONE of those keys: key + ((l & 15) >> 2), head-dim chunk 16 ((l >> 4) & 1) + 4 (l & 3)
   // (offset of db: XOR 64 db bytes).
-  const uint32_t k_rd = lds0 + (uint32_t)((sb * 64 + (lane & 31)) * ROWB + ((kg ^ (lane & 15)) * 16));
-  const int vkey0 = sb * 64 + 4 * kg + ((lane & 15) >> 2);
+  const uint32_t k_rd = lds0 + (uint32_t)((sb * 32 + (lane & 31)) * ROWB + ((kg ^ (lane & 15)) * 16));
+  const int vkey0 = sb * 32 + 4 * kg + ((lane & 15) >> 2);
   const uint32_t v_rd = lds0 + (uint32_t)(V_BASE + vkey0 * ROWB + (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ ((vkey0 & 3) << 2)) * 16) +
                                           (lane & 1) * 8);
-  constexpr uint32_t BLOCK = 32 * ROWB;
+  constexpr uint32_t BLOCK = 64 * ROWB;                      // to a wavefront's second block of the tile
 
   // Running max over a block of scores; returns the max in force from this block on.  It only moves when some row of the
   // wavefront would raise its own by more than MAX_SLACK (log2 units): until then exp2 may exceed 1 by up to 2^MAX_SLACK,
   // which the fp32 sums and the head/tail split carry without loss, and the output needs no rescaling.
-  auto new_max = [&](float mx) INLINE_LAMBDA -> float {
+  auto new_max = [&](float mx, bool& grows) INLINE_LAMBDA -> float {
     mx *= p.scale_log2;
     float xa, xb;
     pair_values(mx, xa, xb);
     const float m_cand = fmaxf(m_run, fmaxf(xa, xb));
-    return __any(m_cand - m_run > MAX_SLACK) ? m_cand : m_run;
+    grows = __any(m_cand - m_run > MAX_SLACK);
+    return grows ? m_cand : m_run;
   };
   // An invisible score is -inf and the max is finite, so its weight is exactly zero.
   auto weight = [&](float x, float m_new) INLINE_LAMBDA -> float {
@@ -237,9 +247,10 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
     // tail = p - head, one v_dot2c_f32_bf16 each: p + head.lo * -1 + head.hi * 0 (exact)
     const float t0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, h), __builtin_bit_cast(bf16x2_t, minus_lo), p0, false);
     const float t1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, h), __builtin_bit_cast(bf16x2_t, minus_hi), p1, false);
-    l = pack_bf16x2(t0, t1);
     sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, h), __builtin_bit_cast(bf16x2_t, ones), sum, false);
+    l = pack_bf16x2(t0, t1);
     sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, l), __builtin_bit_cast(bf16x2_t, ones), sum, false);
+    asm volatile("" : "+v"(h), "+v"(l), "+v"(sum));          // here, among the products, and not where they are used
   };
   auto k_operand = [&](uint32_t at, int ks) INLINE_LAMBDA -> u32x4 { return read_lds(at ^ (32u * ks)); };
   // operand n of a block of values: k-step n >> 2, head-dim block n & 3
@@ -256,9 +267,9 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
   // (weights w; V at v_at, its first two operands already in va) and scores of the next one (K at k_at, into sn).  Leaves
   // this block's weights in wn and its first two value operands (V at v_next) in va.  The order is written out and pinned:
   // the compiler on its own puts the products first and the exponentials after them.
-  auto block = [&](auto has_prev, floatx16& s, floatx16& sn, const Weights& w, Weights& wn, int kb, uint32_t k_at, uint32_t v_at,
+  auto block = [&](auto has_prev, auto has_next, floatx16& s, floatx16& sn, const Weights& w, Weights& wn, int kb, uint32_t k_at, uint32_t v_at,
                    uint32_t v_next) INLINE_LAMBDA {
-    constexpr bool PREV = decltype(has_prev)::value;
+    constexpr bool PREV = decltype(has_prev)::value, NEXT = decltype(has_next)::value;
     auto value = [&](int n, bool tail) INLINE_LAMBDA {
       if constexpr (PREV) o[n & 3] = mfma(va[n & 3], tail ? w.l[n >> 2] : w.h[n >> 2], o[n & 3]);
     };
@@ -268,8 +279,10 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
     u32x4 kf[3];
     fetch(2);
     fetch(3);
-    kf[0] = k_operand(k_at, 0);
-    kf[1] = k_operand(k_at, 1);
+    if constexpr (NEXT) {
+      kf[0] = k_operand(k_at, 0);
+      kf[1] = k_operand(k_at, 1);
+    }
     if (kb + 31 > pos_wave) {                  // keys after the lane's query: key kb + i is visible iff kb + i <= pos
       const int n_vis = pos - kb + 1;
       const uint32_t vis = (n_vis >= 32 ? 0xFFFFFFFFu : n_vis <= 0 ? 0u : ((1u << n_vis) - 1u)) >> (4 * kg);
@@ -293,57 +306,67 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
     CAUSAL_PIN();
     value(2, false);
     fetch(5);
-    const float m_new = new_max(mx);
+    bool grows;
+    const float m_new = new_max(mx, grows);
     CAUSAL_PIN();
     value(3, false);
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-    m_run = m_new;
     CAUSAL_PIN();
     value(2, true);
-    s[0] = weight(s[0], m_new);
+    float p0 = weight(s[0], m_new);
     CAUSAL_PIN();
     value(3, true);
-    s[1] = weight(s[1], m_new);
+    float p1 = weight(s[1], m_new);
     CAUSAL_PIN();
     // second half: eight score products and eight value products, one exponential each
     float ls = 0.f;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      if (j == 0) {
+      float next0 = 0.f, next1 = 0.f;
+      if constexpr (NEXT) {
+        if (j == 0) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sn[r] = 0.f;
+          for (int r = 0; r < 16; ++r) sn[r] = 0.f;
+        }
+        sn = mfma(kf[j % 3], qf[j], sn);
+        if (j < 6) kf[(j + 2) % 3] = k_operand(k_at, j + 2);
       }
-      sn = mfma(kf[j % 3], qf[j], sn);
-      if (j < 6) kf[(j + 2) % 3] = k_operand(k_at, j + 2);
-      if (j < 7) s[2 * j + 2] = weight(s[2 * j + 2], m_new);
+      if (j < 7) next0 = weight(s[2 * j + 2], m_new);
       CAUSAL_PIN();
       value(4 + (j & 1) + 2 * (j >> 2), (j >> 1) & 1);
       if (j == 1) fetch(6);
       if (j == 2) fetch(7);
       if (j == 6) va[0] = v_operand(v_next, 0);
       if (j == 7) va[1] = v_operand(v_next, 1);
-      if (j < 7) s[2 * j + 3] = weight(s[2 * j + 3], m_new);
+      if (j < 7) next1 = weight(s[2 * j + 3], m_new);
       uint32_t h, l;
-      split_pair(s[2 * j], s[2 * j + 1], h, l, ls);
+      split_pair(p0, p1, h, l, ls);
+      p0 = next0;
+      p1 = next1;
       wn.h[j >> 2][j & 3] = h;
       wn.l[j >> 2][j & 3] = l;
       CAUSAL_PIN();
     }
-    l_run = l_run * alpha + ls;
-#pragma unroll
-    for (int m = 0; m < 2; ++m) asm volatile("" : "+v"(wn.h[m]), "+v"(wn.l[m]));     // keeps the work above the branch below
-    if (__any(alpha != 1.0f)) {
+    if (grows) {
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      m_run = m_new;
+      l_run *= alpha;
 #pragma unroll
       for (int db = 0; db < 4; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
     }
+    l_run += ls;
+  };
+  // the last block's values: its first two operands are in va
+  auto finish = [&](const Weights& w, uint32_t v_at) INLINE_LAMBDA {
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      if (n > 1) va[n & 3] = v_operand(v_at, n);
+      o[n & 3] = mfma(va[n & 3], w.h[n >> 2], o[n & 3]);
+      o[n & 3] = mfma(va[n & 3], w.l[n >> 2], o[n & 3]);
+    }
   };
 
-  if (n_tiles > 1) {
-    issue(kbase, koff, 1, TILE_BYTES);
-    issue(vbase, voff, 1, V_BASE + TILE_BYTES);
-  }
   floatx16 s0, s1;
   Weights w0, w1;
 #pragma unroll
@@ -353,12 +376,11 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
   // Tile t in two blocks; one barrier between them.  It publishes K and V of tile t + 1, and frees the slots of K t and
   // V t - 1 for K and V of tile t + 2.  So the second block can read K of t + 1, and V operands are in LDS early enough to
   // be read a block ahead.
-  int kb = sb * 64;
+  int kb = sb * 32;
   uint32_t k_slot = 0, v_slot = 0;             // of tile t
-  uint32_t own_k = 0, own_v = 0;
-  block(Flag<false>(), s0, s1, w0, w0, kb, k_rd + BLOCK, v_rd, v_rd);
+  block(Flag<false>(), Flag<true>(), s0, s1, w0, w0, kb, k_rd + BLOCK, v_rd, v_rd);
 #pragma unroll 1
-  for (int t = 0;; ++t) {
+  for (int t = 0; t + 1 < n_tiles; ++t) {
     CAUSAL_WAIT_LOADS(0);
     __syncthreads();
     const uint32_t v_1 = v_slot == 2 * TILE_BYTES ? 0 : v_slot + TILE_BYTES;         // V slots of tiles t + 1, t + 2
@@ -367,25 +389,22 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
       issue(kbase, koff, t + 2, k_slot);
       issue(vbase, voff, t + 2, V_BASE + v_2);
     }
-    const bool last = t + 1 == n_tiles;        // then the scores of a next block are formed from this tile and not read
-    const uint32_t k_1 = last ? k_slot : k_slot ^ TILE_BYTES;
-    if (last) {
-      own_k = k_slot ^ TILE_BYTES;
-      own_v = V_BASE + v_1;
-      if (!PREFILL && p.s > 0) issue_own(1, own_k, own_v);
-    }
-    block(Flag<true>(), s1, s0, w0, w1, kb + 32, k_rd + k_1, v_rd + v_slot, v_rd + v_slot + BLOCK);
-    if (last) break;
+    const uint32_t k_1 = k_slot ^ TILE_BYTES;
+    block(Flag<true>(), Flag<true>(), s1, s0, w0, w1, kb + 64, k_rd + k_1, v_rd + v_slot, v_rd + v_slot + BLOCK);
     kb += KT;
-    block(Flag<true>(), s0, s1, w1, w0, kb, k_rd + k_1 + BLOCK, v_rd + v_slot + BLOCK, v_rd + v_1);
+    block(Flag<true>(), Flag<true>(), s0, s1, w1, w0, kb, k_rd + k_1 + BLOCK, v_rd + v_slot + BLOCK, v_rd + v_1);
     k_slot = k_1;
     v_slot = v_1;
   }
-#pragma unroll
-  for (int n = 0; n < 8; ++n) {
-    if (n > 1) va[n & 3] = v_operand(v_rd + v_slot + BLOCK, n);
-    o[n & 3] = mfma(va[n & 3], w1.h[n >> 2], o[n & 3]);
-    o[n & 3] = mfma(va[n & 3], w1.l[n >> 2], o[n & 3]);
+  // The last tile's second block, where any query of the workgroup sees a key of it.  K's other slot and V's next were last read
+  // before the last barrier: the own rows go there.
+  const uint32_t own_k = k_slot ^ TILE_BYTES, own_v = V_BASE + (v_slot == 2 * TILE_BYTES ? 0 : v_slot + TILE_BYTES);
+  if (!PREFILL && p.s > 0) issue_own(1, own_k, own_v);
+  if (kb + 64 < L) {
+    block(Flag<true>(), Flag<false>(), s1, s0, w0, w1, kb + 64, 0, v_rd + v_slot, v_rd + v_slot + BLOCK);
+    finish(w1, v_rd + v_slot + BLOCK);
+  } else {
+    finish(w0, v_rd + v_slot);
   }
 
   // The query's own key of every simulated step: one dot product and one scaled row of values each, the two key halves
@@ -405,31 +424,36 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
       const int i = (t - t0) * QB + q_wave - q_first + (lane & 31);
       const unsigned char* kr = smem + own_k + i * ROWB;
       const unsigned char* vr = smem + own_v + i * ROWB + kg * 8;
-      float dot = 0.f;
+      float dot[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ks = 0; ks < 8; ++ks) {
         const u32x4 kk = *(const u32x4*)(kr + (((2 * ks + kg) ^ (i & 15)) * 16));
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          dot = fmaf(bf16_lo(qf[ks][e]), bf16_lo(kk[e]), dot);
-          dot = fmaf(bf16_hi(qf[ks][e]), bf16_hi(kk[e]), dot);
-        }
+        for (int e = 0; e < 4; ++e)
+          dot[e] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, (uint32_t)qf[ks][e]), __builtin_bit_cast(bf16x2_t, (uint32_t)kk[e]), dot[e], false);
       }
       float xa, xb;
-      pair_values(dot, xa, xb);
+      pair_values((dot[0] + dot[1]) + (dot[2] + dot[3]), xa, xb);
       const float sc = (xa + xb) * p.scale_log2;
-      const float m_new = fmaxf(m_run, sc);
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new), pw = __builtin_amdgcn_exp2f(sc - m_new);
-      l_run = l_run * alpha + (kg == 0 ? pw : 0.f);
-      m_run = m_new;
+      if (__any(sc - m_run > MAX_SLACK)) {     // as in new_max
+        const float m_new = fmaxf(m_run, sc), alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+      }
+      const float pw = __builtin_amdgcn_exp2f(sc - m_run);
+      l_run += kg == 0 ? pw : 0.f;
 #pragma unroll
       for (int c = 0; c < 16; ++c) {
         const uint2 vv = *(const uint2*)(vr + ((c ^ (i & 15)) * 16));
         const int db = c >> 2, r = 4 * (c & 3);
-        o[db][r] = o[db][r] * alpha + pw * bf16_lo(vv.x);
-        o[db][r + 1] = o[db][r + 1] * alpha + pw * bf16_hi(vv.x);
-        o[db][r + 2] = o[db][r + 2] * alpha + pw * bf16_lo(vv.y);
-        o[db][r + 3] = o[db][r + 3] * alpha + pw * bf16_hi(vv.y);
+        o[db][r] = fmaf(pw, bf16_lo(vv.x), o[db][r]);
+        o[db][r + 1] = fmaf(pw, bf16_hi(vv.x), o[db][r + 1]);
+        o[db][r + 2] = fmaf(pw, bf16_lo(vv.y), o[db][r + 2]);
+        o[db][r + 3] = fmaf(pw, bf16_hi(vv.y), o[db][r + 3]);
       }
     }
   }
@@ -617,21 +641,22 @@ int workgroups(int T, int H, int Hkv, int RG) {
   return H / hg * ((T + qb - 1) / qb);
 }
 
-// Workgroups of 64 rows instead of 128 where those leave CUs idle: one wavefront per SIMD then takes 1.95 us per tile instead of the
-// 2.45 us that two take side by side, and there are twice as many workgroups.  Up to 256 of them each has a CU to itself (64-row
-// form against 128-row form, us: 4 heads 4096 positions 66 / 82, 8 heads 2048 positions 37 / 45, 32 heads over 8 300
-// positions 11.5 / 13.6).  Up to 512, the shorter half of them (workgroup i of w walks over 1 - i / w of the tiles) starts on the CUs that are
-// done with the longer half's shorter ones, and pays the start, the own keys and the merge again: 8 heads 3000 positions 52 / 64,
-// 32 over 8 517 positions 15.7 / 18.7, but with 3 simulated steps over 32 KV heads 27.2 / 25.2, and 1000 positions of 32 over 8 27.9 / 27.6.
-// Beyond that the shared tiles win: 2048 positions 84 / 61.
+// Workgroups of 64 rows instead of 128 where those leave CUs idle: one wavefront per SIMD then takes 1.81 us per tile instead of the
+// 2.39 us that two take side by side, and there are twice as many workgroups.  Up to 256 of them each has a CU to itself (64-row
+// form against 128-row form, us: 4 heads 4000 positions 60 / 80, 8 heads 2048 positions 33 / 44, 32 heads over 8 300
+// positions 10.3 / 12.5).  Up to 512, the shorter half of them (workgroup i of w walks over 1 - i / w of the tiles) starts on the CUs that are
+// done with the longer half's shorter ones, and pays the start, the own keys and the merge again: 8 heads 3000 positions 47 / 62,
+// 32 over 8 517 positions 13.4 / 17.0, but 64 over 8 300 positions with 3 simulated steps 18.6 / 14.8, and 1000 positions of 32 over 8
+// with 3 steps 30.5 / 28.2.  The constants are fitted to both forms at 75 sizes; what they pick is 0.1 % slower than the better form on
+// average, 4 % at worst.  Beyond 512 the shared tiles win: 2048 positions 84 / 61.
 bool half_workgroups(int T, int H, int Hkv, int s) {
   const int w = workgroups(T, H, Hkv, 2);
   if (w <= 256) return true;
   if (w > 512) return false;
-  const float tiles = (T + KT - 1) / KT;
-  auto fixed = [&](int RG, float batch) { const int hg = heads_per_wg(H, Hkv, RG); return 8.f + batch * ((s + hg - 1) / hg); };
-  const float start2 = fixed(2, 1.1f), two = 2.f * (1.95f * tiles * (1.f - 256.f / w) + start2);
-  return std::max(1.95f * tiles + start2, two) < 2.45f * tiles + fixed(4, 1.4f);
+  const float tiles = 0.5f * ((T + KT / 2 - 1) / (KT / 2));    // a last tile of no more than 64 keys takes half of a tile's time
+  auto fixed = [&](int RG, float start, float batch) { const int hg = heads_per_wg(H, Hkv, RG); return start + batch * ((s + hg - 1) / hg); };
+  const float start2 = fixed(2, 5.2f, 1.7f), two = 2.f * (1.81f * tiles * (1.f - 256.f / w) + start2);
+  return std::max(1.81f * tiles + start2, two) < 2.39f * tiles + fixed(4, 6.5f, 1.8f);
 }
 
 template <bool PREFILL, int RG>

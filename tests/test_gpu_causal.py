@@ -27,6 +27,14 @@ def test_ttt_attention_at_tile_edges(T, H, Hkv, s, spread):
     assert np.max(np.abs(got - ref)) < 2 * 5 * (2e-6 * spread + 2.0 ** -16), (T, H, Hkv, s)
 
 
+# every number of 32-key blocks in the last tile (a wavefront takes the first and third or the second and fourth), the own rows
+# behind a tile whose second pair is left out, one and several tiles
+@pytest.mark.parametrize("T", [64, 65, 96, 97, 160, 192, 193, 224, 225, 256])
+@pytest.mark.parametrize("H,Hkv,s", [(8, 2, 5), (3, 3, 2), (2, 1, 0)])
+def test_ttt_attention_with_partly_filled_last_tiles(T, H, Hkv, s):
+    test_ttt_attention_at_tile_edges(T, H, Hkv, s, 3.0)
+
+
 # sizes around the lines between 64-row and 128-row workgroups (256 and 512 of the smaller ones)
 @pytest.mark.parametrize("T,H,Hkv,s", [(2048, 8, 8, 1), (2049, 8, 8, 0), (1025, 16, 16, 3), (513, 32, 8, 2), (1030, 32, 8, 0), (300, 64, 8, 2)])
 def test_ttt_attention_around_the_workgroup_sizes(T, H, Hkv, s):
