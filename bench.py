@@ -144,7 +144,7 @@ def main():
     del flush
 
     # per-launch kernel durations of the weight-streaming GEMMs (HIP events attached to every dispatch on the stream
-    # in use), by kernel: 64-weight-row workgroups (q/k/v, o, down), 128-weight-row ones (gate/up, LM head), draft GEMMs
+    # in use), by kernel: workgroups of 64 weight rows, of 128 or 256, draft GEMMs
     ctx.profile_begin()
     step()
     torch.cuda.synchronize()
@@ -161,8 +161,8 @@ def main():
                 "bytes_per_launch": by / n, "achieved": by / ms / 1e6, "unit": "GB/s", "frac": by / ms / 1e6 / HBM_PEAK_GBPS,
                 "ms_per_step": ms}
 
-    kernels = [k for k in (kernel_line("gemm_skinny_kernel<2>", "q/k/v, o, down at 60 activation rows", t64),
-                           kernel_line("gemm_skinny128_kernel", "gate/up, LM head at 60 activation rows", t128),
+    kernels = [k for k in (kernel_line("gemm_skinny_kernel<2>", "60 activation rows, 64 weight rows to a workgroup", t64),
+                           kernel_line("gemm_wide_kernel", "60 activation rows, 128 or 256 weight rows to a workgroup", t128),
                            kernel_line("gemm_skinny_kernel<1>", "every projection of the draft (<= 10 rows), feature fusion", few))
                if k]
     ab = algorithmic_bytes(shape, n_new)

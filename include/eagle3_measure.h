@@ -17,8 +17,8 @@ extern "C" {
  * synchronises, then reports the summed kernel duration, the number of launches and the weight bytes those launches
  * read, for one kind of launch:
  *   EAGLE3_GEMM_FEW_ROWS   at most 32 activation rows (the draft's GEMMs, feature fusion)
- *   EAGLE3_GEMM_TILE64     33..64 rows, 64-weight-row workgroups with split-K (q/k/v, o, down at verification width)
- *   EAGLE3_GEMM_TILE128    33..64 rows, 128-weight-row workgroups (gate/up, LM head at verification width)
+ *   EAGLE3_GEMM_TILE64     33..64 rows, workgroups of 64 weight rows (smaller matrices)
+ *   EAGLE3_GEMM_TILE128    33..64 rows, workgroups of 128 or 256 weight rows
  *   EAGLE3_GEMM_MANY_ROWS  more than 64 rows (batched verification)
  * The counters are reset by eagle3_profile_begin. */
 enum { EAGLE3_GEMM_FEW_ROWS = 0, EAGLE3_GEMM_TILE64 = 1, EAGLE3_GEMM_TILE128 = 2, EAGLE3_GEMM_MANY_ROWS = 3 };

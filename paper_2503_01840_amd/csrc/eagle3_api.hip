@@ -178,16 +178,23 @@ struct eagle3_ctx {
       return EAGLE3_OK;
     }
     if (bf16) {
-      int S = epi == GEMM_EPI_SWIGLU ? 1 : gemm_skinny_pick_splits(N, K, M);
-      while (S > 1 && ((size_t)S * M * N > part_floats || (K / 128) % S != 0)) --S;   // the next smaller divisor of the stage count
+      // what the direct loads and 16-byte stores of the wider tiles need
+      bool wide_ok = W.mode == 1 ? N % 8 == 0 : N % 4 == 0;
+      for (int i = 0; i < W.nmat; ++i) wide_ok = wide_ok && (uintptr_t)W.w[i] % 16 == 0 && (W.nmat == 1 || W.rows[i] % 8 == 0);
+      wide_ok = wide_ok && (uintptr_t)direct_out % 16 == 0;
+      const FewRows t = few_rows(M, N, K, epi == GEMM_EPI_SWIGLU, direct_out != nullptr, part_floats, wide_ok);
+      const int S = t.S;
       if (epi == GEMM_EPI_PARTIAL && direct_out == nullptr && (size_t)S * M * N > part_floats) return EAGLE3_E_STATE;
       void* out = epi == GEMM_EPI_SWIGLU ? act_h : (direct_out && S == 1 ? (void*)direct_out : (void*)part);
       Stamp* sp = profiling && stamps_used < stamps.size() ? &stamps[stamps_used++] : nullptr;
       if (sp) {
         sp->bytes = 2.0 * N * K;
-        sp->kind = M <= 32 ? EAGLE3_GEMM_FEW_ROWS : gemm_skinny_uses_tile128(W, M, N, S) ? EAGLE3_GEMM_TILE128 : EAGLE3_GEMM_TILE64;
+        sp->kind = M <= 32 ? EAGLE3_GEMM_FEW_ROWS : t.cols == 64 ? EAGLE3_GEMM_TILE64 : EAGLE3_GEMM_TILE128;
       }
-      CK(launch_gemm_skinny((const bf16_t*)act_in, W, M, N, K, S, epi, out, st, sp ? sp->a : nullptr, sp ? sp->b : nullptr));
+      if (t.cols == 64)
+        CK(launch_gemm_skinny((const bf16_t*)act_in, W, M, N, K, S, epi, out, st, sp ? sp->a : nullptr, sp ? sp->b : nullptr));
+      else
+        CK(launch_gemm_wide64((const bf16_t*)act_in, W, M, N, K, t.cols, S, epi, out, st, sp ? sp->a : nullptr, sp ? sp->b : nullptr));
       if (direct_out && S > 1) CK(launch_reduce_partials(part, S, M, N, direct_out, st));
       if (S_out) *S_out = S;
       return EAGLE3_OK;

@@ -1,4 +1,5 @@
-// bf16 GEMM for MANY activation rows (batched verification: 64 sequences x 8 nodes = 512 rows):
+// bf16 GEMM for MANY activation rows (batched verification: 64 sequences x 8 nodes = 512 rows), and for 33..64 rows where its tiles
+// fill the chip:
 // Y[M, N] = X[M, K] * W[N, K]^T, fp32 accumulate.  At this width the projections sit at the ridge between weight
 // streaming and the MFMA rate, so the kernel is organised around operand reuse and around keeping the loads, the
 // LDS reads and the MFMAs of a wavefront all in flight at once:
@@ -28,6 +29,15 @@
 // with 128-k weight stages), 77 rows 60 / 59 (54.7).
 // Measured and not kept: 4 wavefronts of 128 x 128 each (a third fewer LDS reads: loop 4 % shorter, epilogue longer by the same);
 // K walks that start at different stages (0 to 8 % slower at 512 and 2048 rows).
+//
+// 33..64 rows stream weights, and of the CU's in-order slots for outstanding lines every activation line takes one like a weight line
+// does: tiles of 64 x 128 and 64 x 256 have half and a quarter of an activation line per weight line, where the 64 x 64 tiles of
+// gemm_skinny.hip have one.  A workgroup then streams 32 KB of weights in 0.92 us, and 256 of them in 1.44 (5.8 TB/s).
+// STAGGER, for them: with a K range of a multiple of 4 KB all workgroups that walk in step ask the same few memory channels, so each
+// starts at a stage of its own and goes round.  60 rows, us, 64 x 64 tiles (or 64 x 128 through registers) / in step / staggered:
+// gate/up 28672 x 4096 46.4 / 49.5 / 45.9, 57344 x 8192 176 / 176 / 161 (64 x 256), LM head 128256 x 4096 208 / 255 / 194 (64 x 256),
+// q/k/v 10240 x 8192 42.9 / 41.6 / 38.6, 5120 x 5120 18.9 / 14.5 / 14.7; but ranges of 7168 and 1024 k: down 8192 x 28672 97.8 / 86.9 /
+// 97.9, 12288 x 4096 26.4 / 23.6 / 26.3.
 #include <utility>
 
 #include "common.hpp"
@@ -90,7 +100,7 @@ __device__ __forceinline__ void unroll(F f) { unroll_seq(std::make_integer_seque
 #define WIDE_WAIT_BARRIER(n) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(n) : "memory")
 #define WIDE_PIN() __builtin_amdgcn_sched_barrier(0)
 
-template <int WGM, int WGN, int FM, int FN, int BK, int A_SLOTS, int B_SLOTS, int OCC>
+template <int WGM, int WGN, int FM, int FN, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WideParams p) {
   constexpr int TM = 32 * FM * WGM, TN = 32 * FN * WGN, NW = WGM * WGN;
   constexpr int FA = 2 * FM, FB = 2 * FN;              // 16-row fragments of a wavefront's activation and weight rows
@@ -146,8 +156,15 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   // slot nobody reads any more, which keeps the number of loads in flight, and with it the waits below, the same in every iteration.
   auto load_a = [&](auto i, uint32_t slot) { dma16<i * 1024>(aptr[i], a_off, a_lds + slot); };
   auto load_b = [&](auto i, uint32_t slot) { dma16<i * 1024>(bptr[i], b_off[i], b_lds + slot); };
-  auto step_a = [&](bool more) { a_off += more ? 4096u : 0u; };
-  auto step_b = [&](auto i, bool more) { b_off[i] += more ? 2u * BK : 0u; };
+  const int rot = STAGGER ? (tile * 5 + split) % KT : 0;
+  if (STAGGER) {
+    a_off += rot * SUB * 4096u;
+#pragma unroll
+    for (int i = 0; i < B_DMA; ++i) b_off[i] += rot * (2u * BK);
+  }
+  // to sub-stage v (stage t) of the walk, from the one before it
+  auto step_a = [&](int v) { a_off += v >= SUB * KT ? 0u : STAGGER && v == SUB * (KT - rot) ? 4096u - SUB * KT * 4096u : 4096u; };
+  auto step_b = [&](auto i, int t) { b_off[i] += t >= KT ? 0u : STAGGER && t == KT - rot ? 2u * BK - KT * 2u * BK : 2u * BK; };
 
   // ---- operand fragments (16 rows x 32 k: lane l holds row l % 16, k 8 (l / 16) .. + 7) inside their slots.  The 32-row
   // blocks of a wavefront: one of every pair (WGM = 2), so that their distances are constants, or two neighbours.
@@ -173,13 +190,13 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
     constexpr int v = u - LEAD, q = u % SUB, t = u / SUB - LEAD / SUB + BA;
     if constexpr (v + AA >= 0) {
       unroll<A_DMA>([&](auto i) { load_a(i, (v + AA) * A_SLOT); });
-      step_a(v + AA + 1 < SUB * KT);
+      step_a(v + AA + 1);
     }
     if constexpr (t >= 0)
       unroll<BP>([&](auto j) {
         constexpr std::integral_constant<int, q * BP + j> i;
         load_b(i, t * B_SLOT);
-        step_b(i, t + 1 < KT);
+        step_b(i, t + 1);
       });
   });
   constexpr int PER = A_DMA + BP;                      // loads per sub-stage
@@ -221,11 +238,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
       if constexpr (at >= 0 && d < PER && d * MF / PER == at) {
         if constexpr (d < A_DMA) {
           load_a(std::integral_constant<int, d>{}, a_fill);
-          if constexpr (d == A_DMA - 1) step_a(h + AA + 1 < SUB * KT);
+          if constexpr (d == A_DMA - 1) step_a(h + AA + 1);
         } else {
           constexpr std::integral_constant<int, q * BP + d - A_DMA> piece;
           load_b(piece, b_fill);
-          step_b(piece, s + BA + 1 < KT);
+          step_b(piece, s + BA + 1);
         }
       }
       WIDE_PIN();
@@ -275,11 +292,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   }
 }
 
-template <int WGM, int WGN, int FM, int FN, int BK, int A_SLOTS, int B_SLOTS, int OCC>
+template <int WGM, int WGN, int FM, int FN, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER = false>
 hipError_t launch_cfg(WideParams& p, int S, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   constexpr int TM = 32 * FM * WGM, TN = 32 * FN * WGN;
   constexpr int LDS = A_SLOTS * TM * 64 + B_SLOTS * TN * BK * 2;
-  auto kernel = gemm_wide_kernel<WGM, WGN, FM, FN, BK, A_SLOTS, B_SLOTS, OCC>;
+  auto kernel = gemm_wide_kernel<WGM, WGN, FM, FN, BK, A_SLOTS, B_SLOTS, OCC, STAGGER>;
   static DeviceOnce configured;                        // the attribute belongs to the loaded code object of a device
   hipError_t ce = configured.run([&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS); });
   if (ce != hipSuccess) return ce;
@@ -292,19 +309,28 @@ hipError_t launch_cfg(WideParams& p, int S, hipStream_t st, hipEvent_t ev_start,
 
 }  // namespace
 
-// Picks the tile shape and the split-K factor, then launches.
-hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N, int K, int epi, void* out,
-                            size_t out_capacity_floats, int* S_out, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+namespace {
+
+hipError_t fill_params(WideParams& p, const bf16_t* x, const GemmWeights& W, int M, int N, int K, int epi, void* out) {
   if (M <= 0 || N <= 0 || K <= 0 || K % 64 || N % 4) return hipErrorInvalidValue;
   if (epi == GEMM_EPI_SWIGLU ? (W.mode != 1 || N % 8) : W.mode != 0) return hipErrorInvalidValue;
   for (int i = 0; W.mode == 0 && i + 1 < W.nmat; ++i)
     if (W.rows[i] % 8) return hipErrorInvalidValue;    // the rows of one direct load belong to one matrix
-  WideParams p;
   p.x = x;
   for (int i = 0; i < 3; ++i) { p.w[i] = (const bf16_t*)W.w[i]; p.rows[i] = W.rows[i]; }
   p.nmat = W.nmat; p.mode = W.mode;
   p.M = M; p.N = N; p.K = K; p.epi = epi;
   p.out_f32 = (float*)out; p.out_xf = (bf16_t*)out;
+  return hipSuccess;
+}
+
+}  // namespace
+
+// Picks the tile shape and the split-K factor, then launches.
+hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N, int K, int epi, void* out,
+                            size_t out_capacity_floats, int* S_out, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  WideParams p;
+  if (hipError_t e = fill_params(p, x, W, M, N, K, epi, out)) return e;
   const WideTiles t = wide_tiles(M, N, K, epi == GEMM_EPI_SWIGLU, out_capacity_floats);
   p.S = t.S;
   if (S_out) *S_out = t.S;
@@ -316,4 +342,20 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
                          : launch_cfg<2, 2, 2, 2, 64, 4, 3, 2>(p, t.S, st, ev_start, ev_stop);
   return t.rows == 256 ? launch_cfg<2, 4, 4, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop)
                        : launch_cfg<2, 4, 3, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
+}
+
+// At most 64 rows, in tiles of 64 x cols.
+hipError_t launch_gemm_wide64(const bf16_t* x, const GemmWeights& W, int M, int N, int K, int cols, int S, int epi, void* out,
+                              hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  WideParams p;
+  if (hipError_t e = fill_params(p, x, W, M, N, K, epi, out)) return e;
+  if (M > 64 || S < 1 || (cols != 128 && cols != 256) || K % (S * (cols == 128 ? 128 : 64)) || (epi == GEMM_EPI_SWIGLU && S != 1))
+    return hipErrorInvalidValue;
+  p.S = S;
+  const bool stagger = K / S % 2048 == 0;
+  if (cols == 128)
+    return stagger ? launch_cfg<2, 2, 1, 2, 128, 5, 3, 1, true>(p, S, st, ev_start, ev_stop)
+                   : launch_cfg<2, 2, 1, 2, 128, 5, 3, 1>(p, S, st, ev_start, ev_stop);
+  return stagger ? launch_cfg<2, 4, 1, 2, 64, 8, 4, 1, true>(p, S, st, ev_start, ev_stop)
+                 : launch_cfg<2, 4, 1, 2, 64, 8, 4, 1>(p, S, st, ev_start, ev_stop);
 }

@@ -25,16 +25,16 @@ enum { GEMM_EPI_PARTIAL = 0, GEMM_EPI_SWIGLU = 1, GEMM_EPI_RESIDUAL = 2, GEMM_EP
 // Requires K % (128*S) == 0.  N = total weight rows.  ev_start / ev_stop (optional): events attached to the dispatch.
 hipError_t launch_gemm_skinny(const bf16_t* x, const GemmWeights& W, int M, int N, int K, int S, int epi,
                               void* out, hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
-// Whether launch_gemm_skinny takes the 128-weight-row workgroups for this shape.
-bool gemm_skinny_uses_tile128(const GemmWeights& W, int M, int N, int S);
-// Chooses the split-K factor for a [N, K] weight so that about two workgroups per CU are resident.
-int gemm_skinny_pick_splits(int N, int K, int M);
 
 // The same product for many rows (M > 64): MFMA-bound tiling, see gemm_wide.hip.  Chooses tile shape and split-K
 // itself (S <= what fits into out_capacity_floats; 0 forces S = 1) and reports S.
 hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N, int K, int epi, void* out,
                             size_t out_capacity_floats, int* S_out, hipStream_t st, hipEvent_t ev_start = nullptr,
                             hipEvent_t ev_stop = nullptr);
+
+// The same for at most 64 rows in tiles of 64 x cols (128 or 256), in S ranges of K.  Weights and out at multiples of 16 bytes.
+hipError_t launch_gemm_wide64(const bf16_t* x, const GemmWeights& W, int M, int N, int K, int cols, int S, int epi, void* out,
+                              hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 
 // fp32 GEMM, exact arithmetic: x [M, K], weights [N, K] stacked.  epi PARTIAL: out [M, N]; SWIGLU (mode 1): out [M, N / 2];
 // RESIDUAL: out [M, N] += , and copies of the sum to each non-null copies[i]; ROPE: the rows are q|k|v heads, out = q [M, H, d]

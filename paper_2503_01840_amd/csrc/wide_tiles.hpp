@@ -69,3 +69,65 @@ inline WideTiles wide_tiles(int M, int N, int K, bool swiglu, size_t out_capacit
     t.k = 128;
   return t;
 }
+
+// ---- at most 64 rows
+//
+// Split-K factor of the 64-weight-row workgroups of gemm_skinny.hip, from measurements on MI355X (two of them fit a CU):
+//   * 192-256 workgroups already stream a [4096..6144, 4096] weight at its best rate, and every extra split adds an
+//     fp32 partial tile the consumer has to read back: take the smallest divisor of the stage count that reaches 192;
+//   * between 256 and ~450 workgroups some CUs get two and the others one, and the launch takes as long as with
+//     512 (320 workgroups on a [10240, 8192] weight: 46.7 us, 160 or 640: 43.5 us): skip those;
+//   * a K range left longer than 64 stages is cut further (a [8192, 28672] weight streams 22 % faster as 512
+//     workgroups of 56 stages than as 256 of 112).
+inline int skinny_splits(int N, int K) {
+  const int tiles = (N + 63) / 64, KT = K / 128;
+  int best = 1;
+  for (int S = 1; S <= 16; ++S) {
+    if (KT % S) continue;
+    if (S > 1 && KT / S < 4) break;
+    const int wgs = tiles * S;
+    if (S > 1 && wgs > 256 && wgs < 450) continue;
+    best = S;
+    if (wgs >= 192 && (KT / S <= 64 || wgs >= 512)) break;
+  }
+  return best;
+}
+
+struct FewRows {
+  int cols;            // weight rows of a workgroup: 64 (gemm_skinny.hip), or 128 or 256 (64-row tiles of gemm_wide.hip)
+  int S;
+};
+
+// 33..64 rows: the tile whose launch is over first by this estimate, in microseconds.  A workgroup of any kind takes 4.9 for start and
+// end.  128 and 256 weight rows: one to a CU; a stage of 32 KB of weights takes 0.92 us where few CUs are busy and 1.44 where all are,
+// in rounds of 32 workgroups of the fullest XCD.  64 weight rows: two to a CU; a stage of 16 KB takes 0.73 alone, 1.59 where each CU
+// has two.  Every partial sum costs its reader 0.15, and a result that goes straight to its place a launch of 5 more if it is split.
+// The numbers are a fit to 35 products (K 2048..28672, N 2048..151936), each with 3 to 20 tiles and splits: what the estimate picks is
+// 0.6 % slower than the best of them on average and 5 % at worst, and it is 6 % faster than 64 weight rows (128 through registers for the large
+// ones) on average.  us, what it takes / 64 weight rows: 8B q/k/v 14.4 / 15.8, gate/up 45.9 / 46.4, LM head 194 / 208, draft q/k/v 22.9 / 26.3;
+// 70B q/k/v 38.6 / 42.9, gate/up 161 / 176, down 86.9 / 97.8; 5120 x 5120 14.5 / 18.9, 22016 x 4096 39.4 / 47.1; it leaves 8B o and down,
+// 2560 x 9728 (18.0, 22.8 with 128 weight rows) and 16384 x 2048 (15.8, 19.8) to 64 weight rows.
+// Up to 32 rows the 64-row workgroups, with half a tile of activations, are at 5.4 TB/s and stay.
+// wide_ok: types and alignment are what gemm_wide.hip can take.  capacity: floats for partial sums.
+inline FewRows few_rows(int M, int N, int K, bool swiglu, bool direct, size_t capacity, bool wide_ok) {
+  auto fits = [&](int S) { return S == 1 || (size_t)S * M * N <= capacity; };
+  FewRows best = {64, swiglu ? 1 : skinny_splits(N, K)};
+  while (best.S > 1 && (!fits(best.S) || (K / 128) % best.S != 0)) --best.S;   // the next smaller divisor of the stage count
+  if (M <= 32 || !wide_ok) return best;
+  auto extra = [&](int S) { return S == 1 ? 0.f : 0.15f * S + (direct ? 5.f : 0.f); };
+  const int wgs = (N + 63) / 64 * best.S, rest = wgs % 512;
+  const float range = (float)K / best.S / 128;
+  float least = extra(best.S) + wgs / 512 * (4.9f + 1.59f * range);
+  if (rest) least += 4.9f + range * (rest <= 256 ? 0.73f : rest <= 440 ? 1.37f : 1.59f * rest / 512);
+  for (int cols : {128, 256})
+    for (int S = 1; S <= (swiglu ? 1 : 16); ++S) {
+      const int bk = cols == 128 ? 128 : 64, KT = K / bk;
+      if (KT % S || K / S < 512 || !fits(S)) continue;
+      const int n = ((N + cols - 1) / cols + 7) / 8 * S, last = n % 32;
+      const float stages = (float)KT / S;
+      float t = extra(S) + n / 32 * (4.9f + 1.44f * stages);
+      if (last) t += 4.9f + stages * (last <= 20 ? 0.92f : 1.44f * last / 32);
+      if (t < least) { least = t; best = {cols, S}; }
+    }
+  return best;
+}

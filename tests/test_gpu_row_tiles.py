@@ -39,7 +39,21 @@ def test_rows_in_wide_weight_stages(B, N, group):
     _rows_alone_and_together(S.get_shape("c3"), B, N, group)
 
 
-def _rows_alone_and_together(full, B, N, group):
+# 33..64 rows, logits included, against at most 32 rows at a time (the few-row kernel).  8B width: q/k/v in 64 x 128 tiles in step,
+# gate/up staggered, LM head 64 x 256 staggered.  "wide": gate/up and a LM head that ends within a tile in 64 x 256 tiles in step.
+# "deep": o in five ranges, down in six, a LM head of a few rows more than whole 64 x 128 tiles.
+FEW = {"8b": S.get_shape("c3"),
+       "wide": S.get_shape("c3").with_(name="wide", hidden=3584, n_heads=28, n_kv_heads=4, intermediate=18944, vocab=33004),
+       "deep": S.get_shape("c3").with_(name="deep", hidden=5120, n_heads=40, n_kv_heads=8, intermediate=13824, vocab=20484)}
+
+
+@pytest.mark.parametrize("name", list(FEW))
+@pytest.mark.parametrize("B,N,group", [(33, 1, 32), (12, 4, 8), (63, 1, 32), (64, 1, 32), (1, 64, 1)])
+def test_rows_of_64_row_tiles(name, B, N, group):
+    _rows_alone_and_together(FEW[name], B, N, group, logits=True)
+
+
+def _rows_alone_and_together(full, B, N, group, logits=False):
     E = _E()
     shape = full.with_(n_layers=1, taps=(0, 0, 0))
     W = {k: v.to(DEV) for k, v in S.layer_weights(full, 3).items()}
@@ -60,14 +74,16 @@ def _rows_alone_and_together(full, B, N, group):
         n = b1 - b0
         k, v = k0[b0 * (P + N):b1 * (P + N)].clone(), v0[b0 * (P + N):b1 * (P + N)].clone()
         kv = E.KVCache([k], [v], i32(np.arange(n + 1) * (P + N)), i32([P] * n), P)
-        x_out, _ = E.eagle3_tree_verify_layers(ctx, tok[b0:b1].contiguous(), parent[b0:b1].contiguous(), kv, x_in[b0:b1].contiguous(), 0, 1,
+        x_out, lg = E.eagle3_tree_verify_layers(ctx, tok[b0:b1].contiguous(), parent[b0:b1].contiguous(), kv, x_in[b0:b1].contiguous(), 0, 1,
                                                want_logits=True)
         torch.cuda.synchronize()
-        return x_out.cpu().numpy(), k.float().cpu().numpy()
+        return x_out.cpu().numpy(), k.float().cpu().numpy(), lg.float().cpu().numpy() if logits else None
 
-    x, k = run(0, B)
+    x, k, lg = run(0, B)
     for b0 in range(0, B, group):
         b1 = min(B, b0 + group)
-        xr, kr = run(b0, b1)
+        xr, kr, lr = run(b0, b1)
         assert np.max(np.abs(x[b0:b1] - xr)) < TOL * max(1.0, _rms(xr))
         assert np.max(np.abs(k[b0 * (P + N):b1 * (P + N)] - kr)) < 4e-2
+        if logits:
+            assert np.max(np.abs(lg[b0:b1] - lr)) < TOL * max(1.0, _rms(lr))

@@ -62,3 +62,20 @@ def test_weight_stages_divide_every_range_of_k(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
     r = subprocess.run([str(tmp_path / "m")], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+def test_few_rows_choices_can_be_launched(tmp_path):
+    (tmp_path / "m.cpp").write_text('#include <cstdio>\n#include <initializer_list>\n#include "wide_tiles.hpp"\n'
+                                    'int main() { long seen[3] = {0, 0, 0};\n'
+                                    '  for (int M : {1, 32, 33, 60, 64}) for (int N = 4; N <= 160000; N += 4 + N / 3) for (int K = 128; K <= 28672; K += 128)\n'
+                                    '    for (int s : {0, 1}) for (int direct : {0, 1}) for (int ok : {0, 1}) for (long cap : {0l, 4l * M * N, 1l << 40}) {\n'
+                                    '      const FewRows t = few_rows(M, N, K, s, direct, cap, ok);\n'
+                                    '      ++seen[t.cols / 128];\n'
+                                    '      const bool good = (t.cols == 64 || (M > 32 && ok && (t.cols == 128 || t.cols == 256))) && t.S >= 1 && t.S <= 16 &&\n'
+                                    '        K / (t.cols == 256 ? 64 : 128) % t.S == 0 && (t.S == 1 || (!s && (long)t.S * M * N <= cap));\n'
+                                    '      if (!good) { printf("%d %d %d %d %d %ld: %d %d\\n", M, N, K, s, direct, cap, t.cols, t.S); return 1; } }\n'
+                                    '  return !(seen[0] && seen[1] && seen[2]); }\n')
+    inc = os.path.join(ROOT, "paper_2503_01840_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
+    r = subprocess.run([str(tmp_path / "m")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
