@@ -368,13 +368,14 @@ __global__ __launch_bounds__(128 * CW, CW == 1 ? 1 : 2) void attn_tree_bf16_kern
   }
 }
 
-// one thread per (row, head, 4 consecutive head-dim entries); one pass over the splits in chunks of 8 whose
+// one thread per (row, head, 4 consecutive head-dim entries), a workgroup takes eight rows of one head, whose pieces make up whole lines
+// of the fragment-major output; one pass over the splits in chunks of 8 whose
 // loads are all independent (online rescaling between chunks)
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p, int R, bf16_t* __restrict__ out) {
-  const int gid = blockIdx.x * 256 + threadIdx.x;
-  const int d4 = gid & 31, rh = gid >> 5, H = p.H, N = p.N, n_splits = p.n_splits;
-  if (rh >= R * H) return;
-  const int h = rh % H, r = rh / H, b = r / N, node = r % N;
+  const int H = p.H, N = p.N, n_splits = p.n_splits;
+  const int d4 = threadIdx.x & 31, h = blockIdx.x % H, r = blockIdx.x / H * 8 + (threadIdx.x >> 5);
+  if (r >= R) return;
+  const int b = r / N, node = r % N;
   const size_t base = (((size_t)b * H + h) * n_splits) * N + node;
   float M = NEG, den = 0.f;
   float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -642,6 +643,6 @@ hipError_t launch_tree_attention(bool bf16, const void* q, const void* kcache, c
   const int grid = B * p.n_qblocks * n_splits * Hkv;
   hipError_t e = cw == 1 ? launch_attn_cw<1>(p, grid, st) : cw == 2 ? launch_attn_cw<2>(p, grid, st) : launch_attn_cw<4>(p, grid, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_merge_kernel, dim3((R * H * 32 + 255) / 256), dim3(256), 0, st, p, R, (bf16_t*)out);
+  hipLaunchKernelGGL(attn_merge_kernel, dim3((R + 7) / 8 * H), dim3(256), 0, st, p, R, (bf16_t*)out);
   return hipGetLastError();
 }

@@ -21,6 +21,14 @@ __global__ __launch_bounds__(256) void embed_rows_kernel(const TW* __restrict__ 
 
 struct CopyOut { float* p[4]; };
 
+// Row of workgroup x where a workgroup takes one row (or a part of one) and writes it as an activation.  bf16: a 128-byte line of the
+// fragment-major layout holds pieces of eight rows, and workgroups go to the XCDs in turn; eight consecutive rows go to one XCD, whose L2
+// then puts the line together.  The grid is a multiple of 64 wide (rows_grid); rows past the end do nothing.  Against rows dealt out one by one:
+// verification of 64 trees 11.14 -> 10.93 ms, 2048 tokens 26.8 -> 26.5, an 8B step 6.26 -> 6.19 (with the same in the attention merge).
+template <bool BF16>
+__device__ __forceinline__ int row_of_workgroup(int x) { return BF16 ? (x >> 6) * 64 + (x & 7) * 8 + ((x >> 3) & 7) : x; }
+int rows_grid(int R) { return (R + 63) / 64 * 64; }
+
 // One workgroup per row, four consecutive columns per thread (two such groups when k > 4096): the row stays
 // in registers between the partial-sum reduction and the normalised store.
 template <bool BF16>
@@ -28,7 +36,8 @@ __global__ __launch_bounds__(1024) void add_norm_kernel(float* __restrict__ x, c
                                                        int R, int k, const typename Act<BF16>::type* __restrict__ gain,
                                                        float eps, typename Act<BF16>::type* __restrict__ act, CopyOut co) {
   __shared__ float red[17];
-  const int r = blockIdx.x, nvec = k >> 2, bd = blockDim.x;
+  const int r = row_of_workgroup<BF16>(blockIdx.x), nvec = k >> 2, bd = blockDim.x;
+  if (r >= R) return;
   constexpr int VPT = 2;
   float4 val[VPT];
   float ss = 0.f;
@@ -192,10 +201,10 @@ __global__ __launch_bounds__(1024) void rope_kv_write_kernel(const float* __rest
 // bf16 stores are 2 bytes each).
 template <bool BF16, bool VEC>
 __global__ __launch_bounds__(256) void pack3_kernel(const float* __restrict__ a, const float* __restrict__ b,
-                                                   const float* __restrict__ c, int k,
+                                                   const float* __restrict__ c, int M, int k,
                                                    typename Act<BF16>::type* __restrict__ act) {
-  const int r = blockIdx.x, col = (VEC ? 4 : 1) * (blockIdx.y * 256 + threadIdx.x);
-  if (col >= 3 * k) return;
+  const int r = row_of_workgroup<BF16>(blockIdx.x), col = (VEC ? 4 : 1) * (blockIdx.y * 256 + threadIdx.x);
+  if (r >= M || col >= 3 * k) return;
   const int part = col / k;
   const float* src = (part == 0 ? a : part == 1 ? b : c) + (size_t)r * k + col - part * k;
   if constexpr (VEC) {
@@ -220,14 +229,15 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
 template <bool BF16>
 __global__ __launch_bounds__(1024) void draft_input_kernel(const typename Act<BF16>::type* __restrict__ embed, int vocab,
                                                           const int32_t* __restrict__ tok, const float* __restrict__ feat,
-                                                          const int32_t* __restrict__ src_row, int k,
+                                                          const int32_t* __restrict__ src_row, int M, int k,
                                                           const typename Act<BF16>::type* __restrict__ g_embed,
                                                           const typename Act<BF16>::type* __restrict__ g_feat, float eps,
                                                           typename Act<BF16>::type* __restrict__ act,
                                                           float* __restrict__ y, const int32_t* __restrict__ pos,
                                                           int head_dim, float theta, float* __restrict__ cs) {
   __shared__ float red_e[17], red_f[17];
-  const int r = blockIdx.x;
+  const int r = row_of_workgroup<BF16>(blockIdx.x);
+  if (r >= M) return;
   const int t = min(max(tok[r], 0), vocab - 1);
   const float* f = feat + (size_t)(src_row ? src_row[r] : r) * k;
   float4 e[4], v[4];
@@ -350,7 +360,7 @@ hipError_t launch_add_norm(bool bf16, float* x, const float* partial, int S, int
   if (k % 4 || k > 8192) return hipErrorInvalidValue;
   const int bd = std::min(1024, (k / 4 + 63) / 64 * 64);
   if (bf16)
-    hipLaunchKernelGGL(add_norm_kernel<true>, dim3(R), dim3(bd), 0, st, x, partial, S, R, k, (const bf16_t*)gain, eps,
+    hipLaunchKernelGGL(add_norm_kernel<true>, dim3(rows_grid(R)), dim3(bd), 0, st, x, partial, S, R, k, (const bf16_t*)gain, eps,
                        (bf16_t*)act, co);
   else
     hipLaunchKernelGGL(add_norm_kernel<false>, dim3(R), dim3(bd), 0, st, x, partial, S, R, k, (const float*)gain, eps,
@@ -385,13 +395,13 @@ hipError_t launch_rope_kv_write(bool bf16, const float* qkv_partial, int S, int 
 hipError_t launch_pack3(bool bf16, const float* a, const float* b, const float* c, int M, int k, void* act, hipStream_t st) {
   const bool vec = k % 4 == 0 && (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) & 15) == 0;
   const int cols = vec ? 3 * k / 4 : 3 * k;
-  const dim3 grid(M, (cols + 255) / 256);
+  const dim3 grid(bf16 ? rows_grid(M) : M, (cols + 255) / 256);
   if (bf16) {
     auto kernel = vec ? pack3_kernel<true, true> : pack3_kernel<true, false>;
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, a, b, c, k, (bf16_t*)act);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, a, b, c, M, k, (bf16_t*)act);
   } else {
     auto kernel = vec ? pack3_kernel<false, true> : pack3_kernel<false, false>;
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, a, b, c, k, (float*)act);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, a, b, c, M, k, (float*)act);
   }
   return hipGetLastError();
 }
@@ -409,11 +419,11 @@ hipError_t launch_draft_input(bool bf16, const void* embed, int vocab, const int
   if (k % 4 || k > 16384) return hipErrorInvalidValue;
   const int threads = std::min(1024, ((k / 4 + 63) / 64) * 64);
   if (bf16)
-    hipLaunchKernelGGL(draft_input_kernel<true>, dim3(M), dim3(threads), 0, st, (const bf16_t*)embed, vocab, tok, feat,
-                       src_row, k, (const bf16_t*)g_embed, (const bf16_t*)g_feat, eps, (bf16_t*)act, y, pos, head_dim, theta, cs);
+    hipLaunchKernelGGL(draft_input_kernel<true>, dim3(rows_grid(M)), dim3(threads), 0, st, (const bf16_t*)embed, vocab, tok, feat,
+                       src_row, M, k, (const bf16_t*)g_embed, (const bf16_t*)g_feat, eps, (bf16_t*)act, y, pos, head_dim, theta, cs);
   else
     hipLaunchKernelGGL(draft_input_kernel<false>, dim3(M), dim3(threads), 0, st, (const float*)embed, vocab, tok, feat,
-                       src_row, k, (const float*)g_embed, (const float*)g_feat, eps, (float*)act, y, pos, head_dim, theta, cs);
+                       src_row, M, k, (const float*)g_embed, (const float*)g_feat, eps, (float*)act, y, pos, head_dim, theta, cs);
   return hipGetLastError();
 }
 
