@@ -28,7 +28,6 @@
 // 214 / 177, o 77 / 57, q/k/v 100 / 87; 512 rows gate/up 116 / 101, down 73 / 60, q/k/v 39 / 35; 256 rows gate/up 77 / 74 (69.5
 // with 128-k weight stages), 77 rows 60 / 59 (54.7).
 // Measured and not kept: 4 wavefronts of 128 x 128 each (a third fewer LDS reads: loop 4 % shorter, epilogue longer by the same);
-// K walks that start at different stages (0 to 8 % slower at 512 and 2048 rows).
 //
 // 33..64 rows stream weights, and of the CU's in-order slots for outstanding lines every activation line takes one like a weight line
 // does: tiles of 64 x 128 and 64 x 256 have half and a quarter of an activation line per weight line, where the 64 x 64 tiles of
@@ -334,12 +333,23 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   const WideTiles t = wide_tiles(M, N, K, epi == GEMM_EPI_SWIGLU, out_capacity_floats);
   p.S = t.S;
   if (S_out) *S_out = t.S;
-  if (t.cols == 128 && t.k == 128)
-    return t.rows == 256 ? launch_cfg<4, 2, 2, 2, 128, 4, 3, 1>(p, t.S, st, ev_start, ev_stop)
-                         : launch_cfg<2, 2, 2, 2, 128, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
-  if (t.cols == 128)
-    return t.rows == 256 ? launch_cfg<4, 2, 2, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop)
-                         : launch_cfg<2, 2, 2, 2, 64, 4, 3, 2>(p, t.S, st, ev_start, ev_stop);
+  // Staggered walks (see above) also up to 256 rows, where the K range is not split.  us, in step / staggered: gate/up 28672 x 4096 77 rows
+  // 55.4 / 51.6, 256 rows 75.6 / 72.8, 57344 x 8192 77 rows 199 / 191, LM head 128256 x 4096 77 rows 252 / 227, 256 rows 329 / 302; but
+  // split 77 rows q/k/v 20.7 / 21.1, 8192 x 8192 32.0 / 34.7, 256 rows 10240 x 8192 76.5 / 74.5, 8192 x 8192 48.9 / 49.3, and 0 to 8 % slower
+  // at 512 and 2048 rows.
+  const bool stagger = M <= 256 && t.S == 1 && K % 2048 == 0;
+  if (t.cols == 128 && t.k == 128) {
+    if (t.rows == 256)
+      return stagger ? launch_cfg<4, 2, 2, 2, 128, 4, 3, 1, true>(p, t.S, st, ev_start, ev_stop)
+                     : launch_cfg<4, 2, 2, 2, 128, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
+    return stagger ? launch_cfg<2, 2, 2, 2, 128, 4, 3, 1, true>(p, t.S, st, ev_start, ev_stop)
+                   : launch_cfg<2, 2, 2, 2, 128, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
+  }
+  if (t.cols == 128) {
+    if (t.rows == 256) return launch_cfg<4, 2, 2, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
+    return stagger ? launch_cfg<2, 2, 2, 2, 64, 4, 3, 2, true>(p, t.S, st, ev_start, ev_stop)
+                   : launch_cfg<2, 2, 2, 2, 64, 4, 3, 2>(p, t.S, st, ev_start, ev_stop);
+  }
   return t.rows == 256 ? launch_cfg<2, 4, 4, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop)
                        : launch_cfg<2, 4, 3, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
 }
