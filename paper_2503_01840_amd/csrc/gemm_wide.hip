@@ -333,11 +333,10 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   const WideTiles t = wide_tiles(M, N, K, epi == GEMM_EPI_SWIGLU, out_capacity_floats);
   p.S = t.S;
   if (S_out) *S_out = t.S;
-  // Staggered walks (see above) also up to 256 rows, where the K range is not split.  us, in step / staggered: gate/up 28672 x 4096 77 rows
-  // 55.4 / 51.6, 256 rows 75.6 / 72.8, 57344 x 8192 77 rows 199 / 191, LM head 128256 x 4096 77 rows 252 / 227, 256 rows 329 / 302; but
-  // split 77 rows q/k/v 20.7 / 21.1, 8192 x 8192 32.0 / 34.7, 256 rows 10240 x 8192 76.5 / 74.5, 8192 x 8192 48.9 / 49.3, and 0 to 8 % slower
-  // at 512 and 2048 rows.
-  const bool stagger = M <= 256 && t.S == 1 && K % 2048 == 0;
+  // Staggered walks (see above) also up to 256 rows.  us, in step / staggered: gate/up 28672 x 4096 77 rows 55.4 / 51.6, 256 rows 75.6 / 72.8,
+  // LM head 128256 x 4096 77 rows 252 / 227, 256 rows 329 / 302, 8192 x 8192 in four ranges 77 rows 35.0 / 30.6, 256 rows 48.9 / 49.3; stages of
+  // 64 k, LM head 252 / 210, but 8192 x 28672 in seven ranges 115 / 132; and 0 to 8 % slower at 512 and 2048 rows.
+  const bool stagger = M <= 256 && K / t.S % 2048 == 0 && (t.k == 128 || t.S == 1);
   if (t.cols == 128 && t.k == 128) {
     if (t.rows == 256)
       return stagger ? launch_cfg<4, 2, 2, 2, 128, 4, 3, 1, true>(p, t.S, st, ev_start, ev_stop)

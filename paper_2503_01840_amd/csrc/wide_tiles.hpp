@@ -12,6 +12,41 @@ struct WideTiles {
   int k;               // width of a weight stage: 64, or 128 for tiles of 128 weight rows
 };
 
+// 65..256 rows: 128 weight rows to a workgroup, so that every weight line enters one CU, and one block of 128
+// or 256 activation rows.  Stages of 128 k, whose row pieces of 256 bytes HBM delivers faster than pieces of 128, take all of a CU's LDS;
+// with stages of 64 k two 128 x 128 workgroups run side by side.  The kind and the split whose launch is over first by this estimate,
+// in microseconds: a start and an end, a time per stage that grows with the workgroups that stream at once, in rounds of 32 workgroups
+// of the fullest XCD (64 side by side), and the reading of the partial sums (5 TB/s).  The numbers are a fit to 29 products (K 2048..28672,
+// N 2048..151936) at 77, 128 and 200 rows, each with every split; what the estimate picks is 0.5 % slower than the best on average, 7 % at
+// worst, where picking by workgroup counts (384 and 192 of them) was 6.5 %, 32 % at worst.  77 rows, us, by counts / by the estimate:
+// q/k/v 6144 x 4096 18.8 / 18.5 with half the partial sums, 5120 x 5120 21.1 / 17.7, 5120 x 13824 42.8 / 32.8, 8192 x 28672 115 / 103;
+// 128 rows 8192 x 8192 36.5 / 33.9.  (Worst: 77 rows LM head 128256 x 4096, 226 where stages of 64 k take 210.)
+inline WideTiles wide_tiles_256(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
+  const int rows = M <= 128 ? 128 : 256, per_xcd = ((N + 127) / 128 + 7) / 8;
+  const float slower = 1.f + 0.0026f * (M - 77);                       // up to 128 rows
+  const float start = M <= 128 ? 6.6f : 8.4f, alone = M <= 128 ? 1.28f * slower : 1.79f, full = M <= 128 ? 1.39f * slower : 1.99f;
+  WideTiles best = {rows, 128, 1, 64};
+  float least = 0.f;
+  for (int k : {128, 64})
+    for (int S = 1; S <= (swiglu ? 1 : 8); ++S) {
+      const int range = K / S, n = per_xcd * S;
+      if (K % (k * S) || range < 512 || (S > 1 && (size_t)S * M * N > out_capacity_floats)) continue;
+      if (k == 64 && M > 128 && K % 128 == 0) continue;                // for ranges that 128 does not divide
+      const float stages = (float)range / k;
+      float t = swiglu ? 0.f : (float)S * M * N * (4.f / 5e6f);
+      if (k == 128 || M > 128) {
+        const float f = k == 128 ? 1.f : 0.55f;                        // of a stage of 128 k
+        t += n / 32 * (start + full * f * stages);
+        if (n % 32) t += start + stages * f * (full * (n % 32) / 32 > alone ? full * (n % 32) / 32 : alone);
+      } else {
+        t += n / 64 * (4.7f + 1.66f * stages);
+        if (n % 64) t += 4.7f + stages * (n % 64 <= 32 ? 0.87f : 1.66f);
+      }
+      if (least == 0.f || t < least) { least = t; best = {rows, 128, S, k}; }
+    }
+  return best;
+}
+
 inline WideTiles wide_tiles_k64(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
   const int KT = K / 64;
   auto ceil_div = [](int a, int b) { return (a + b - 1) / b; };
@@ -26,12 +61,7 @@ inline WideTiles wide_tiles_k64(int M, int N, int K, bool swiglu, size_t out_cap
       }
     return {rows, cols, S, 64};
   };
-  // 129..256 rows: ONE 256-row block x 128 weight rows per workgroup (8 wavefronts x 64 x 64), so that every weight line enters
-  // exactly one CU and a stage takes in 48 KB instead of the 2 x 32 KB of two 128 x 128 workgroups (measured at 256 rows, 8B
-  // shapes: q/k/v 33.4 -> 26.6 us, down 54.3 -> 47.6, gate/up 86.0 -> 78.9)
-  if (M > 128 && M <= 256) return pick(256, 128, 192, 8);
-  if (M <= 128) return pick(128, 128, 384, 8);
-  // More rows: the tile whose launch is over first by this estimate, in microseconds.  A workgroup takes a start and an end, and a
+  // The tile whose launch is over first by this estimate, in microseconds.  A workgroup takes a start and an end, and a
   // time per 64 k; the fullest XCD runs its workgroups in rounds of 32, of 64 for 128 x 128 tiles (two on a CU side by side, one
   // alone where there are no more than 32 left); the consumer then reads the partial sums (5 TB/s).  The ten numbers are a fit to 17 products
   // of the 8B, 70B and two narrower widths at 16 row counts from 257 to 2048, each with all four tiles: what the estimate picks is 0.3 %
@@ -55,18 +85,13 @@ inline WideTiles wide_tiles_k64(int M, int N, int K, bool swiglu, size_t out_cap
   return best;
 }
 
-// Tiles of 128 weight rows leave room in LDS for weight stages of 128 k, whose row pieces of 256 bytes HBM delivers faster than
-// pieces of 128, where one workgroup has a CU to itself.  256 x 128 always has; 128 x 128 runs two to a CU otherwise, and that
-// is the better way between 257 and 512 workgroups (one round of two against two of one), and beyond where row blocks share a weight tile.  A workgroup's walk has to be long
-// enough, as fewer and larger stages start later.  8B and 70B widths, us, 64 / 128: 77 rows gate/up (224 workgroups) 59.1 / 54.7, LM
-// head (1002) 256 / 242, down (256, 14 stages) 28.9 / 28.1, but o (256, 4 stages) 12.6 / 13.8, q/k/v (384) 18.6 / 22.4 and 70B gate/up
-// (448) 185 / 201; 300 rows LM head (3006) 457 / 530; 256 rows gate/up 71.8 / 69.5, q/k/v 24.2 / 23.6, but o (4 stages) 17.8 / 18.4.
+// Stages of 128 k beyond 256 rows: where one workgroup has a CU to itself, 256 x 128 always, 128 x 128 up to 256 workgroups (300 rows LM
+// head, 3006 workgroups: 457 us with 64, 530 with 128).  A workgroup's walk has to be long enough, as fewer and larger stages start later.
 inline WideTiles wide_tiles(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
+  if (M <= 256) return wide_tiles_256(M, N, K, swiglu, out_capacity_floats);
   WideTiles t = wide_tiles_k64(M, N, K, swiglu, out_capacity_floats);
   const int wgs = (N + t.cols - 1) / t.cols * ((M + t.rows - 1) / t.rows) * t.S, range = K / t.S;
-  if (t.cols == 128 && range % 128 == 0 && range >= (t.rows == 256 && t.S == 1 ? 256 : 1024) &&
-      (t.rows == 256 || wgs <= 256 || (wgs > 512 && M <= 128)))
-    t.k = 128;
+  if (t.cols == 128 && range % 128 == 0 && range >= (t.rows == 256 && t.S == 1 ? 256 : 1024) && (t.rows == 256 || wgs <= 256)) t.k = 128;
   return t;
 }
 
