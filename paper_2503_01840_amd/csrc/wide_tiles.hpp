@@ -20,7 +20,8 @@ struct WideTiles {
 // N 2048..151936) at 77, 128 and 200 rows, each with every split; what the estimate picks is 0.5 % slower than the best on average, 7 % at
 // worst, where picking by workgroup counts (384 and 192 of them) was 6.5 %, 32 % at worst.  77 rows, us, by counts / by the estimate:
 // q/k/v 6144 x 4096 18.8 / 18.5 with half the partial sums, 5120 x 5120 21.1 / 17.7, 5120 x 13824 42.8 / 32.8, 8192 x 28672 115 / 103;
-// 128 rows 8192 x 8192 36.5 / 33.9.  (Worst: 77 rows LM head 128256 x 4096, 226 where stages of 64 k take 210.)
+// 128 rows 8192 x 8192 36.5 / 33.9.  Stages of 64 k are left for splits whose ranges 128 does not divide: 4096 x 11008 in four of 2752,
+// 200 rows 54 us, in two of 5504 80; 3584 x 18944 in eight of 2368 53, in four 74.  (Worst: 77 rows LM head 128256 x 4096, 226 where stages of 64 k take 210.)
 inline WideTiles wide_tiles_256(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
   const int rows = M <= 128 ? 128 : 256, per_xcd = ((N + 127) / 128 + 7) / 8;
   const float slower = 1.f + 0.0026f * (M - 77);                       // up to 128 rows
@@ -31,7 +32,7 @@ inline WideTiles wide_tiles_256(int M, int N, int K, bool swiglu, size_t out_cap
     for (int S = 1; S <= (swiglu ? 1 : 8); ++S) {
       const int range = K / S, n = per_xcd * S;
       if (K % (k * S) || range < 512 || (S > 1 && (size_t)S * M * N > out_capacity_floats)) continue;
-      if (k == 64 && M > 128 && K % 128 == 0) continue;                // for ranges that 128 does not divide
+      if (k == 64 && M > 128 && range % 128 == 0) continue;            // for ranges that 128 does not divide
       const float stages = (float)range / k;
       float t = swiglu ? 0.f : (float)S * M * N * (4.f / 5e6f);
       if (k == 128 || M > 128) {

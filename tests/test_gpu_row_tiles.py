@@ -39,6 +39,12 @@ def test_rows_in_wide_weight_stages(B, N, group):
     _rows_alone_and_together(S.get_shape("c3"), B, N, group)
 
 
+# 64-k weight stages in split products of 129..256 rows: down in four ranges of 2752
+@pytest.mark.parametrize("B,N,group", [(129, 1, 64), (64, 3, 20), (64, 4, 16)])
+def test_rows_in_ranges_that_wide_weight_stages_do_not_divide(B, N, group):
+    _rows_alone_and_together(S.get_shape("c3").with_(name="mha", n_kv_heads=32, intermediate=11008, vocab=1024), B, N, group)
+
+
 # 33..64 rows, logits included, against at most 32 rows at a time (the few-row kernel).  8B width: q/k/v in 64 x 128 tiles in step,
 # gate/up staggered, LM head 64 x 256 staggered.  "wide": gate/up and a LM head that ends within a tile in 64 x 256 tiles in step.
 # "deep": o in five ranges, down in six, a LM head of a few rows more than whole 64 x 128 tiles.

@@ -51,6 +51,12 @@ def test_every_choice_can_be_launched(rule):
         assert S == 1 or (not s and S * M * N <= cap)
 
 
+# K a multiple of 128, and of the ranges only those of a split that 128 does not divide fill the chip: the split comes before wide stages
+@pytest.mark.parametrize("N,K,S", [(512, 1408, 2), (1024, 2816, 4), (2048, 5632, 8), (3584, 18944, 8), (4096, 11008, 4)])
+def test_splits_whose_ranges_128_does_not_divide(rule, N, K, S):
+    assert rule([(M, N, K, 0, BIG) for M in (129, 160, 200, 256)]) == [(256, 128, S)] * 4
+
+
 def test_weight_stages_divide_every_range_of_k(tmp_path):
     (tmp_path / "m.cpp").write_text('#include <cstdio>\n#include <initializer_list>\n#include "wide_tiles.hpp"\n'
                                     'int main() { for (int M : {65, 77, 128, 129, 200, 256, 257, 300, 383, 520, 2048})\n'
