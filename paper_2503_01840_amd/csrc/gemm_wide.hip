@@ -336,7 +336,7 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   // Staggered walks (see above) also up to 256 rows.  us, in step / staggered: gate/up 28672 x 4096 77 rows 55.4 / 51.6, 256 rows 75.6 / 72.8,
   // LM head 128256 x 4096 77 rows 252 / 227, 256 rows 329 / 302, 8192 x 8192 in four ranges 77 rows 35.0 / 30.6, 256 rows 48.9 / 49.3; stages of
   // 64 k, LM head 252 / 210, but 8192 x 28672 in seven ranges 115 / 132; and 0 to 8 % slower at 512 and 2048 rows.
-  const bool stagger = M <= 256 && K / t.S % 2048 == 0 && (t.k == 128 || t.S == 1);
+  const bool stagger = wide_stagger(M, K, t);
   if (t.cols == 128 && t.k == 128) {
     if (t.rows == 256)
       return stagger ? launch_cfg<4, 2, 2, 2, 128, 4, 3, 1, true>(p, t.S, st, ev_start, ev_stop)

@@ -12,36 +12,43 @@ struct WideTiles {
   int k;               // width of a weight stage: 64, or 128 for tiles of 128 weight rows
 };
 
+// Whether the K walks of a launch of 65..256 rows start at a stage of each workgroup's own (gemm_wide.hip has the figures).
+inline bool wide_stagger(int M, int K, const WideTiles& t) { return M <= 256 && K / t.S % 2048 == 0 && (t.k == 128 || t.S == 1); }
+
 // 65..256 rows: 128 weight rows to a workgroup, so that every weight line enters one CU, and one block of 128
 // or 256 activation rows.  Stages of 128 k, whose row pieces of 256 bytes HBM delivers faster than pieces of 128, take all of a CU's LDS;
 // with stages of 64 k two 128 x 128 workgroups run side by side.  The kind and the split whose launch is over first by this estimate,
 // in microseconds: a start and an end, a time per stage that grows with the workgroups that stream at once, in rounds of 32 workgroups
-// of the fullest XCD (64 side by side), and the reading of the partial sums (5 TB/s).  The numbers are a fit to 29 products (K 2048..28672,
-// N 2048..151936) at 77, 128 and 200 rows, each with every split; what the estimate picks is 0.5 % slower than the best on average, 7 % at
-// worst, where picking by workgroup counts (384 and 192 of them) was 6.5 %, 32 % at worst.  77 rows, us, by counts / by the estimate:
-// q/k/v 6144 x 4096 18.8 / 18.5 with half the partial sums, 5120 x 5120 21.1 / 17.7, 5120 x 13824 42.8 / 32.8, 8192 x 28672 115 / 103;
-// 128 rows 8192 x 8192 36.5 / 33.9.  Stages of 64 k are left for splits whose ranges 128 does not divide: 4096 x 11008 in four of 2752,
-// 200 rows 54 us, in two of 5504 80; 3584 x 18944 in eight of 2368 53, in four 74.  (Worst: 77 rows LM head 128256 x 4096, 226 where stages of 64 k take 210.)
+// of the fullest XCD (64 side by side), and the writing and reading of the partial sums.  The numbers are fits to 150 products of 34 model
+// shapes (K 512..28672, N 512..151936), each with every split and the kernel that reads the sums.  65, 77, 100 and 128 rows: what the estimate
+// picks is 0.1 % slower than the best on average, 9 % at worst (151936 x 3584), and nowhere more than 2 % slower than stages of 64 k split by
+// workgroup counts.  Before, walks of 64 k were charged too much, and large unsplit products took wide stages: us, wide / 64 k, gate/up
+// 57344 x 8192 100 rows 201 / 189, 37888 x 3584 65 rows 84 / 79, LM head 128256 x 4096 65 rows 234 / 212, 64000 x 7168 100 rows 214 / 192;
+// but gate/up 28672 x 4096 77 rows 53 / 57, LM head 151936 x 3584 77 rows 248 / 267.
+// 129, 160, 200 and 256 rows: 0.3 % and 9 %.  Stages of 64 k are left there for splits whose ranges 128 does not divide: 4096 x 11008
+// in four of 2752, 200 rows 54 us, in two of 5504 80; 3584 x 18944 in eight of 2368 53, in four 74.
 inline WideTiles wide_tiles_256(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
-  const int rows = M <= 128 ? 128 : 256, per_xcd = ((N + 127) / 128 + 7) / 8;
-  const float slower = 1.f + 0.0026f * (M - 77);                       // up to 128 rows
-  const float start = M <= 128 ? 6.6f : 8.4f, alone = M <= 128 ? 1.28f * slower : 1.79f, full = M <= 128 ? 1.39f * slower : 1.99f;
+  const bool few = M <= 128;
+  const int rows = few ? 128 : 256, per_xcd = ((N + 127) / 128 + 7) / 8;
+  const float slower = 1.f + 0.0008f * (M - 77);                       // up to 128 rows
+  const float start = few ? 6.4f : 8.4f, alone = few ? 1.37f * slower : 1.79f, full = few ? 1.41f * slower : 1.99f;
   WideTiles best = {rows, 128, 1, 64};
   float least = 0.f;
   for (int k : {128, 64})
     for (int S = 1; S <= (swiglu ? 1 : 8); ++S) {
       const int range = K / S, n = per_xcd * S;
       if (K % (k * S) || range < 512 || (S > 1 && (size_t)S * M * N > out_capacity_floats)) continue;
-      if (k == 64 && M > 128 && range % 128 == 0) continue;            // for ranges that 128 does not divide
+      if (k == 64 && !few && range % 128 == 0) continue;               // for ranges that 128 does not divide
       const float stages = (float)range / k;
-      float t = swiglu ? 0.f : (float)S * M * N * (4.f / 5e6f);
-      if (k == 128 || M > 128) {
+      float t = swiglu ? 0.f : (float)S * M * N * (few ? 2.3e-6f : 0.8e-6f);
+      if (k == 128 || !few) {
         const float f = k == 128 ? 1.f : 0.55f;                        // of a stage of 128 k
         t += n / 32 * (start + full * f * stages);
         if (n % 32) t += start + stages * f * (full * (n % 32) / 32 > alone ? full * (n % 32) / 32 : alone);
       } else {
-        t += n / 64 * (4.7f + 1.66f * stages);
-        if (n % 64) t += 4.7f + stages * (n % 64 <= 32 ? 0.87f : 1.66f);
+        const float last = n % 64 / 64.f;
+        t += n / 64 * (3.9f + 1.47f * stages);
+        if (last > 0.f) t += 3.9f + stages * (last <= 0.5f ? 0.93f : 1.47f * last > 1.44f ? 1.47f * last : 1.44f);
       }
       if (least == 0.f || t < least) { least = t; best = {rows, 128, S, k}; }
     }

@@ -21,12 +21,21 @@ MEASURED = [
 ]
 
 
+# at most 128 rows, unsplit: microseconds with stages of 128 k, of 64 k
+MEASURED_STAGES = [
+    ((100, 57344, 8192, 1), 201, 189), ((65, 37888, 3584, 1), 84, 79), ((65, 128256, 4096, 0), 234, 212), ((128, 128256, 4096, 0), 234, 224),
+    ((128, 100000, 6144, 0), 315, 295), ((77, 128256, 2048, 0), 131, 125), ((77, 128256, 3072, 0), 182, 177), ((77, 28672, 4096, 1), 53, 57),
+    ((128, 32768, 6144, 1), 83, 90), ((100, 27648, 5120, 1), 64, 71), ((77, 32000, 4096, 0), 57, 60), ((65, 16384, 3072, 1), 37, 41),
+]
+
+
 @pytest.fixture(scope="module")
-def rule(tmp_path_factory):
+def whole_rule(tmp_path_factory):
+    """(M, N, K, SwiGLU, capacity) -> (rows, cols, S, k of a stage, staggered)"""
     d = tmp_path_factory.mktemp("tiles")
     (d / "m.cpp").write_text('#include <cstdio>\n#include "wide_tiles.hpp"\n'
                              'int main() { int m, n, k, s; long long c; while (scanf("%d %d %d %d %lld", &m, &n, &k, &s, &c) == 5) {\n'
-                             '  WideTiles t = wide_tiles(m, n, k, s, c); printf("%d %d %d\\n", t.rows, t.cols, t.S); } }\n')
+                             '  WideTiles t = wide_tiles(m, n, k, s, c); printf("%d %d %d %d %d\\n", t.rows, t.cols, t.S, t.k, wide_stagger(m, k, t)); } }\n')
     inc = os.path.join(ROOT, "paper_2503_01840_amd", "csrc")
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(d / "m.cpp"), "-o", str(d / "m")], check=True)
 
@@ -35,6 +44,11 @@ def rule(tmp_path_factory):
         out = subprocess.run([str(d / "m")], input=text, capture_output=True, text=True, check=True).stdout
         return [tuple(map(int, line.split())) for line in out.splitlines()]
     return ask
+
+
+@pytest.fixture(scope="module")
+def rule(whole_rule):
+    return lambda queries: [t[:3] for t in whole_rule(queries)]
 
 
 def test_192_row_tiles_where_they_are_the_faster_ones(rule):
@@ -55,6 +69,11 @@ def test_every_choice_can_be_launched(rule):
 @pytest.mark.parametrize("N,K,S", [(512, 1408, 2), (1024, 2816, 4), (2048, 5632, 8), (3584, 18944, 8), (4096, 11008, 4)])
 def test_splits_whose_ranges_128_does_not_divide(rule, N, K, S):
     assert rule([(M, N, K, 0, BIG) for M in (129, 160, 200, 256)]) == [(256, 128, S)] * 4
+
+
+def test_weight_stages_where_they_are_the_faster_ones(whole_rule):
+    for (q, wide, narrow), (rows, cols, S, k, _) in zip(MEASURED_STAGES, whole_rule([q + (0,) for q, _, _ in MEASURED_STAGES])):
+        assert (rows, cols, S) == (128, 128, 1) and (k == 128) == (wide < narrow), (q, k)
 
 
 def test_weight_stages_divide_every_range_of_k(tmp_path):
