@@ -71,21 +71,22 @@ inline WideTiles wide_tiles_k64(int M, int N, int K, bool swiglu, size_t out_cap
   };
   // The tile whose launch is over first by this estimate, in microseconds.  A workgroup takes a start and an end, and a
   // time per 64 k; the fullest XCD runs its workgroups in rounds of 32, of 64 for 128 x 128 tiles (two on a CU side by side, one
-  // alone where there are no more than 32 left); the consumer then reads the partial sums (5 TB/s).  The ten numbers are a fit to 17 products
-  // of the 8B, 70B and two narrower widths at 16 row counts from 257 to 2048, each with all four tiles: what the estimate picks is 0.3 %
-  // slower than the best of the four on average (15 % at worst: gate/up of hidden 2048, 576 and 1300 rows), and 6 % faster than
-  // picking by workgroup counts.  8B width, product and reading, us, 256 x 256 / 192 x 256 / 256 x 128 / 128 x 128: q/k/v 300 rows
-  // 38 / 35 / 36 / 44, 512 rows 44 / 64 / 40 / 50; down 300 rows 63 / 58 / 60 / 69, 512 rows 73 / 80 / 67 / 83; o 1024 rows 49 / 49 / 42 / 50;
-  // gate/up 300 rows 101 / 88 / 117 / 119, 1024 rows 197 / 235 / 231 / 274, 2048 rows 384 / 395 / 426 / 507; hidden 2048, gate/up 450 rows
-  // 47 / 41 / 32 / 41.
+  // alone where there are no more than 32 left); writing and reading the partial sums comes on top.  The eleven numbers are a fit to 150 products
+  // of 34 model shapes at 13 row counts from 257 to 2048, each with all four tiles and the kernel that reads the sums: what the estimate picks
+  // is 0.2 % slower than the best of the four on average (13 % at worst: 2304 x 9216 at 1500 rows), and 12 % faster than picking by workgroup
+  // counts.  Fitted to 17 products, it had charged 128 x 128 tiles too much: us, then / now, down 4352 x 17024 300 rows 114 / 100, gate/up
+  // 18432 x 2304 257 rows 48 / 43, o 5120 x 5120 300 rows 43 / 40.  8B width, product and reading, us, 256 x 256 / 192 x 256 /
+  // 256 x 128 / 128 x 128: q/k/v 300 rows 38 / 35 / 36 / 44, 512 rows 44 / 64 / 40 / 50, 600 rows 73 / 52 / 71 / 50; down 300 rows
+  // 63 / 58 / 60 / 69, 512 rows 73 / 80 / 67 / 83; o 1024 rows 49 / 49 / 42 / 50; gate/up 300 rows 101 / 87 / 116 / 121, 1024 rows
+  // 197 / 235 / 231 / 274, 2048 rows 382 / 392 / 406 / 509; hidden 2048, gate/up 300 rows 45 / 41 / 31 / 30.
   auto cost = [&](const WideTiles& w) -> float {
     const int n = ceil_div(ceil_div(N, w.cols), 8) * ceil_div(M, w.rows) * w.S;
-    const float stages = (float)KT / w.S, read = swiglu ? 0.f : (float)w.S * M * N * (4.f / 5e6f);
-    if (w.cols == 256) return ceil_div(n, 32) * (w.rows == 256 ? 8.72f + 1.43f * stages : 8.0f + 1.14f * stages) + read;
-    if (w.rows == 256) return ceil_div(n, 32) * (6.74f + 0.85f * stages) + read;
-    const float two = 8.4f + 1.13f * stages, one = 4.66f + 0.79f * stages;
+    const float stages = (float)KT / w.S, sums = swiglu ? 0.f : (float)w.S * M * N * 1.2e-6f;
+    if (w.cols == 256) return ceil_div(n, 32) * (w.rows == 256 ? 7.4f + 1.36f * stages : 8.2f + 1.1f * stages) + sums;
+    if (w.rows == 256) return ceil_div(n, 32) * (8.f + 0.81f * stages) + sums;
+    const float two = 7.3f + 1.085f * stages, one = 7.4f + 0.595f * stages;
     const int rest = n % 64;
-    return n / 64 * two + (rest == 0 ? 0.f : rest <= 32 ? one : two) + read;
+    return n / 64 * two + (rest == 0 ? 0.f : rest <= 32 ? one : two) + sums;
   };
   WideTiles best = pick(256, 256, 160, 16);
   for (const WideTiles& t : {pick(192, 256, 160, 16), pick(256, 128, 192, 16), pick(128, 128, 384, 8)})

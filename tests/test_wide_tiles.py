@@ -8,18 +8,19 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 BIG = 1 << 40
 
-# (rows M, outputs N, inputs K, SwiGLU): microseconds with the tile that the rule would take without 192-row tiles, with those
+# (rows M, outputs N, inputs K, SwiGLU): microseconds of the product and the kernel that reads it with the fastest of the other tiles, with
+# 192-row tiles
 MEASURED = [
-    ((300, 28672, 4096, 1), 120, 86), ((520, 28672, 4096, 1), 194, 160), ((1100, 28672, 4096, 1), 302, 257),      # 8B width
-    ((2048, 28672, 4096, 1), 423, 446), ((600, 6144, 4096, 0), 67, 47), ((1100, 4096, 14336, 0), 167, 133),
-    ((383, 57344, 8192, 1), 418, 355), ((600, 57344, 8192, 1), 648, 674),           # 70B width
-    ((300, 2048, 512, 1), 8.5, 16), ((300, 5632, 1024, 1), 12.6, 23), ((2048, 5632, 1024, 1), 32, 48),           # narrow models
-    ((300, 11264, 2048, 1), 30, 41), ((2048, 11264, 2048, 1), 109, 128), ((383, 16384, 3072, 1), 58, 62),
-    ((300, 37888, 3584, 1), 122, 143), ((400, 5120, 5120, 0), 40, 61), ((1024, 5120, 5120, 0), 65, 101),
-    ((2048, 5120, 13824, 0), 303, 474), ((2048, 2560, 2560, 0), 44, 60), ((900, 2560, 6912, 0), 55, 76),
-    ((1024, 5120, 3072, 0), 44, 68), ((900, 3072, 8192, 0), 65, 89), ((1100, 3072, 3072, 0), 38, 52),
+    ((300, 28672, 4096, 1), 101, 87), ((520, 28672, 4096, 1), 161, 153), ((1100, 28672, 4096, 1), 263, 234),      # 8B width
+    ((2048, 28672, 4096, 1), 382, 392), ((600, 6144, 4096, 0), 50, 52), ((768, 6144, 4096, 0), 75, 55), ((1100, 4096, 14336, 0), 154, 148),
+    ((383, 57344, 8192, 1), 382, 325), ((600, 57344, 8192, 1), 546, 589), ((300, 10240, 5120, 0), 59, 65),          # 70B and 13B widths
+    ((300, 2048, 512, 1), 8.6, 15), ((300, 5632, 1024, 1), 15, 24), ((2048, 5632, 1024, 1), 30, 44),                # narrow models
+    ((300, 11264, 2048, 1), 30, 41), ((576, 11264, 2048, 1), 36, 42), ((2048, 11264, 2048, 1), 95, 115), ((383, 16384, 3072, 1), 47, 62),
+    ((257, 18432, 2304, 1), 43, 48), ((300, 17920, 1536, 1), 31, 35), ((300, 4352, 17024, 0), 100, 114), ((300, 5120, 5120, 0), 40, 43),
+    ((300, 37888, 3584, 1), 119, 135), ((400, 5120, 5120, 0), 48, 68), ((1024, 5120, 5120, 0), 78, 107),
+    ((2048, 5120, 13824, 0), 286, 453), ((2048, 2560, 2560, 0), 59, 80), ((900, 2560, 6912, 0), 61, 87),
+    ((1024, 5120, 3072, 0), 60, 79), ((900, 3072, 8192, 0), 70, 99), ((1100, 3072, 3072, 0), 43, 64),
 ]
-
 
 # at most 128 rows, unsplit: microseconds with stages of 128 k, of 64 k
 MEASURED_STAGES = [
