@@ -135,10 +135,13 @@ struct FewRows {
 // 33..64 rows: the tile whose launch is over first by this estimate, in microseconds.  A workgroup of any kind takes 4.9 for start and
 // end.  128 and 256 weight rows: one to a CU; a stage of 32 KB of weights takes 0.92 us where few CUs are busy and 1.44 where all are,
 // in rounds of 32 workgroups of the fullest XCD.  64 weight rows: two to a CU; a stage of 16 KB takes 0.73 alone, 1.59 where each CU
-// has two.  Every partial sum costs its reader 0.15, and a result that goes straight to its place a launch of 5 more if it is split.
+// has two.  Every partial sum costs its reader 0.15, and a result that goes straight to its place a launch of 5 more if it is split, and
+// 0.4 per million partial sums (LM head 65780 x 4352, 60 rows: 150 us in two ranges, 138 unsplit).
 // The numbers are a fit to 35 products (K 2048..28672, N 2048..151936), each with 3 to 20 tiles and splits: what the estimate picks is
-// 0.6 % slower than the best of them on average and 5 % at worst, and it is 6 % faster than 64 weight rows (128 through registers for the large
-// ones) on average.  us, what it takes / 64 weight rows: 8B q/k/v 14.4 / 15.8, gate/up 45.9 / 46.4, LM head 194 / 208, draft q/k/v 22.9 / 26.3;
+// 0.6 % slower than the best of them on average, over 900 products of 40 shapes too (15 % at worst: 7168 x 21504 in three ranges, 70 us, 60
+// in four), and 5 % faster than 64 weight rows (128 through registers for the large ones) on average; of the 900, 14 are slower than those,
+// by 3 to 8 % and 0.6 to 3.5 us (3072 x 3072 33 rows 14.6 / 14.0, fusion 8192 x 24576 88 / 84.5).  us, what it takes / 64 weight rows:
+// 8B q/k/v 14.4 / 15.8, gate/up 45.9 / 46.4, LM head 194 / 208, draft q/k/v 22.9 / 26.3;
 // 70B q/k/v 38.6 / 42.9, gate/up 161 / 176, down 86.9 / 97.8; 5120 x 5120 14.5 / 18.9, 22016 x 4096 39.4 / 47.1; it leaves 8B o and down,
 // 2560 x 9728 (18.0, 22.8 with 128 weight rows) and 16384 x 2048 (15.8, 19.8) to 64 weight rows.
 // Up to 32 rows the 64-row workgroups, with half a tile of activations, are at 5.4 TB/s and stay.
@@ -148,7 +151,7 @@ inline FewRows few_rows(int M, int N, int K, bool swiglu, bool direct, size_t ca
   FewRows best = {64, swiglu ? 1 : skinny_splits(N, K)};
   while (best.S > 1 && (!fits(best.S) || (K / 128) % best.S != 0)) --best.S;   // the next smaller divisor of the stage count
   if (M <= 32 || !wide_ok) return best;
-  auto extra = [&](int S) { return S == 1 ? 0.f : 0.15f * S + (direct ? 5.f : 0.f); };
+  auto extra = [&](int S) { return S == 1 ? 0.f : 0.15f * S + (direct ? 5.f + 0.4e-6f * S * M * N : 0.f); };
   const int wgs = (N + 63) / 64 * best.S, rest = wgs % 512;
   const float range = (float)K / best.S / 128;
   float least = extra(best.S) + wgs / 512 * (4.9f + 1.59f * range);

@@ -105,3 +105,16 @@ def test_few_rows_choices_can_be_launched(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
     r = subprocess.run([str(tmp_path / "m")], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+# 33..64 rows, LM heads whose partial sums cost more than the fuller rounds of a split give: unsplit; features' fusion: split
+def test_few_rows_splits_of_results_that_go_to_their_place(tmp_path):
+    (tmp_path / "m.cpp").write_text('#include <cstdio>\n#include "wide_tiles.hpp"\n'
+                                    'int main() { const int q[][4] = {{60, 65780, 4352, 0}, {33, 65780, 4352, 0}, {64, 65780, 4608, 0}, {64, 4096, 12288, 1}, {33, 5120, 15360, 1}};\n'
+                                    '  for (auto& c : q) { const FewRows t = few_rows(c[0], c[1], c[2], false, true, (size_t)1 << 40, true);\n'
+                                    '    if ((t.S > 1) != c[3]) { printf("%d %d %d: %d\\n", c[0], c[1], c[2], t.S); return 1; } }\n'
+                                    '  return 0; }\n')
+    inc = os.path.join(ROOT, "paper_2503_01840_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
+    r = subprocess.run([str(tmp_path / "m")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
