@@ -178,10 +178,9 @@ struct eagle3_ctx {
       return EAGLE3_OK;
     }
     if (bf16) {
-      // what the direct loads and 16-byte stores of the wider tiles need
-      bool wide_ok = W.mode == 1 ? N % 8 == 0 : N % 4 == 0;
+      // what the direct loads of the wider tiles need
+      bool wide_ok = W.mode == 0 || N % 8 == 0;
       for (int i = 0; i < W.nmat; ++i) wide_ok = wide_ok && (uintptr_t)W.w[i] % 16 == 0 && (W.nmat == 1 || W.rows[i] % 8 == 0);
-      wide_ok = wide_ok && (uintptr_t)direct_out % 16 == 0;
       const FewRows t = few_rows(M, N, K, epi == GEMM_EPI_SWIGLU, direct_out != nullptr, part_floats, wide_ok);
       const int S = t.S;
       if (epi == GEMM_EPI_PARTIAL && direct_out == nullptr && (size_t)S * M * N > part_floats) return EAGLE3_E_STATE;

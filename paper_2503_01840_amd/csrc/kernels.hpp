@@ -32,7 +32,7 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
                             size_t out_capacity_floats, int* S_out, hipStream_t st, hipEvent_t ev_start = nullptr,
                             hipEvent_t ev_stop = nullptr);
 
-// The same for at most 64 rows in tiles of 64 x cols (128 or 256), in S ranges of K.  Weights and out at multiples of 16 bytes.
+// The same for at most 64 rows in tiles of 64 x cols (128 or 256), in S ranges of K.  Weights at multiples of 16 bytes.
 hipError_t launch_gemm_wide64(const bf16_t* x, const GemmWeights& W, int M, int N, int K, int cols, int S, int epi, void* out,
                               hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 

@@ -55,6 +55,14 @@ FEW = {"8b": S.get_shape("c3"),
        "deep": S.get_shape("c3").with_(name="deep", hidden=5120, n_heads=40, n_kv_heads=8, intermediate=13824, vocab=20484)}
 
 
+# LM heads that do not end at a multiple of four, so that the rows of logits start anywhere: unsplit and in ranges, ending within a tile
+@pytest.mark.parametrize("hidden,heads,vocab", [(1024, 8, 30001), (3584, 28, 33002), (2048, 16, 8197), (2048, 16, 131)])
+@pytest.mark.parametrize("B", [33, 64])
+def test_rows_of_an_odd_vocabulary(hidden, heads, vocab, B):
+    _rows_alone_and_together(S.get_shape("c3").with_(name=f"odd{hidden}", hidden=hidden, n_heads=heads, n_kv_heads=4, intermediate=1024, vocab=vocab,
+                                                     draft_vocab=64), B, 1, 32, logits=True)
+
+
 @pytest.mark.parametrize("name", list(FEW))
 @pytest.mark.parametrize("B,N,group", [(33, 1, 32), (12, 4, 8), (63, 1, 32), (64, 1, 32), (1, 64, 1)])
 def test_rows_of_64_row_tiles(name, B, N, group):
@@ -66,7 +74,7 @@ def _rows_alone_and_together(full, B, N, group, logits=False):
     shape = full.with_(n_layers=1, taps=(0, 0, 0))
     W = {k: v.to(DEV) for k, v in S.layer_weights(full, 3).items()}
     tg = {k: v.to(DEV) for k, v in S.target_globals(full).items()}
-    ctx = E.Eagle3Context(shape, max_batch=B, max_nodes=N, max_depth=2, max_topk=2, max_new=4, device=DEV)
+    ctx = E.Eagle3Context(shape, max_batch=B, max_nodes=N, max_depth=2, max_topk=2, max_new=1 if full.vocab % 4 else 4, device=DEV)
     ctx.set_weights({"layers": [W], **tg}, None)
     gen = torch.Generator(device=DEV)
     gen.manual_seed(B)
