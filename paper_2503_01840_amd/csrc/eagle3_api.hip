@@ -378,18 +378,32 @@ static int fuse_rows(eagle3_ctx* ctx, const float* low, const float* mid, const 
   return ctx->project(ctx->act_k, W, M, k, 3 * k, GEMM_EPI_PARTIAL, nullptr, st, g_out);
 }
 
+// fp32: the operand of the product over N weight rows (pairs: see f32_norm_inside) that takes the RMSNorm of R rows of x: the rows
+// themselves, with the gain in f, or the normed ones.
+static int norm_operand(eagle3_ctx* ctx, float* x, const void* gain, int R, int N, int K, bool pairs, F32Fuse& f, const float** in,
+                        hipStream_t st) {
+  f.gain = (const float*)gain; f.eps = ctx->cfg.rms_eps;
+  *in = x;
+  if (!gain || f32_norm_inside(R, N, K, pairs)) return EAGLE3_OK;
+  CK(launch_add_norm(false, x, nullptr, 0, R, K, gain, f.eps, ctx->act_k, nullptr, st));
+  f.gain = nullptr;
+  *in = (const float*)ctx->act_k;
+  return EAGLE3_OK;
+}
+
 // q/k/v projection of R rows, rotated, k and v in their cache slots.  in: the projection's operand, K wide; fp32 with a gain: the
 // rows whose RMSNorm is that operand.
-static int project_qkv(eagle3_ctx* ctx, const eagle3_layer_weights& w, const void* in, const void* gain, int K, int R, const int32_t* slot,
+static int project_qkv(eagle3_ctx* ctx, const eagle3_layer_weights& w, void* in, const void* gain, int K, int R, const int32_t* slot,
                        const float* cs, void* kc, void* vc, hipStream_t st) {
   const eagle3_config& c = ctx->cfg;
   const int H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim;
   GemmWeights Wqkv = {{w.wq, w.wk, w.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
   if (!ctx->bf16) {
     F32Fuse f;
-    f.gain = (const float*)gain; f.eps = c.rms_eps;
+    const float* rows;
+    TRY(norm_operand(ctx, (float*)in, gain, R, (H + 2 * Hkv) * d, K, true, f, &rows, st));
     f.cs = cs; f.slot = slot; f.kc = (float*)kc; f.vc = (float*)vc; f.H = H; f.Hkv = Hkv; f.d = d;
-    CK(launch_gemm_f32((const float*)in, Wqkv, R, (H + 2 * Hkv) * d, K, GEMM_EPI_ROPE, (float*)ctx->q, st, f));
+    CK(launch_gemm_f32(rows, Wqkv, R, (H + 2 * Hkv) * d, K, GEMM_EPI_ROPE, (float*)ctx->q, st, f));
     return EAGLE3_OK;
   }
   int S = 1;
@@ -405,8 +419,9 @@ static int norm_head(eagle3_ctx* ctx, float* x, int S, int R, const void* gain, 
   GemmWeights W = {{head, nullptr, nullptr}, {V, 0, 0}, 1, 0};
   if (!ctx->bf16) {
     F32Fuse f;
-    f.gain = (const float*)gain; f.eps = ctx->cfg.rms_eps;
-    CK(launch_gemm_f32(x, W, R, V, k, GEMM_EPI_PARTIAL, out, st, f));
+    const float* rows;
+    TRY(norm_operand(ctx, x, gain, R, V, k, false, f, &rows, st));
+    CK(launch_gemm_f32(rows, W, R, V, k, GEMM_EPI_PARTIAL, out, st, f));
     return EAGLE3_OK;
   }
   CK(launch_add_norm(true, x, S ? ctx->part : nullptr, S, R, k, gain, ctx->cfg.rms_eps, ctx->act_k, copies, st));
@@ -451,10 +466,11 @@ static int layer_tail(eagle3_ctx* ctx, const eagle3_layer_weights& w, int B, int
   GemmWeights Wd = {{w.w_down, nullptr, nullptr}, {k, 0, 0}, 1, 0};
   if (!ctx->bf16) {
     F32Fuse norm, out;
-    norm.gain = (const float*)w.norm_mlp; norm.eps = c.rms_eps;
+    const float* rows;
     for (int i = 0; copies && i < 4; ++i) out.copies[i] = copies[i];
     CK(launch_gemm_f32((const float*)ctx->act_attn, Wo, R, k, H * d, GEMM_EPI_RESIDUAL, x, st));
-    CK(launch_gemm_f32(x, Wgu, R, 2 * I, k, GEMM_EPI_SWIGLU, (float*)ctx->act_h, st, norm));
+    TRY(norm_operand(ctx, x, w.norm_mlp, R, 2 * I, k, true, norm, &rows, st));
+    CK(launch_gemm_f32(rows, Wgu, R, 2 * I, k, GEMM_EPI_SWIGLU, (float*)ctx->act_h, st, norm));
     CK(launch_gemm_f32((const float*)ctx->act_h, Wd, R, k, I, GEMM_EPI_RESIDUAL, x, st, out));
     *S_down = 0;
     return EAGLE3_OK;

@@ -1,7 +1,7 @@
 // fp32 GEMM for the exact-arithmetic (small model) configuration: out[m, n] = sum_k x[m, k] w[n, k] over up to three
 // stacked weight matrices, or h = silu(gate) * up of two.  What stands between two products of a layer is done by them, as a launch
 // of its own costs as much as a product does here: the RMSNorm of the input rows (every wavefront sums their squares along with
-// its own products; 3.1 us a launch saved), the rotation and cache write of q/k/v, and the residual sum.
+// its own products; 3.1 us a launch saved, as long as there are few wavefronts: f32_norm_inside), the rotation and cache write of q/k/v, and the residual sum.
 //
 // One wavefront per (weight row, group of 8 activation rows); the lanes stride over K, four consecutive k at a time.  At
 // these sizes (a few hundred rows of a few hundred k, all of it in L2) a launch is bound by its own latency: the loads of

@@ -168,3 +168,15 @@ inline FewRows few_rows(int M, int N, int K, bool swiglu, bool direct, size_t ca
     }
   return best;
 }
+
+// ---- fp32
+//
+// Whether the RMSNorm of M rows of K is formed inside the fp32 product that reads them (gemm_f32.hip).  There every wavefront, of which
+// there is one to each group of 8 rows and each weight row (or pair: gate and up, the two of a rotary pair), sums the squares again: 0.05 to
+// 0.2 ns a wavefront, and 0.2 to 1 where K is more than 1024, against 3 us for a launch of its own.  us, inside / own launch: LM head 2048 x 512
+// 64 rows 12.9 / 14.3, 256 rows 43.7 / 41.8; 32000 x 2048 64 rows 675 / 600; q/k/v 3072 x 1024 64 rows 21.2 / 22.1, 256 rows 73.5 / 67.6; gate/up
+// 1376 x 256 128 rows 8.8 / 9.8, 512 rows 24.7 / 20.0; 11008 x 2048 16 rows 36.9 / 34.9, 64 rows 136 / 118.
+inline bool f32_norm_inside(int M, int N, int K, bool pairs) {
+  const long wavefronts = (long)((M + 7) / 8) * (pairs ? N / 2 : N);
+  return wavefronts <= (K > 1024 ? 8192 : pairs ? 16384 : 24576);
+}

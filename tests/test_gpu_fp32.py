@@ -55,3 +55,31 @@ def test_small_models_fp32(hidden, heads, kv_heads, d, inter, N):
 @pytest.mark.parametrize("N", [1, 18, 19, 20, 58, 59, 60, 64])
 def test_small_models_fp32_with_wide_heads(heads, kv_heads, d, N):
     test_small_models_fp32(64, heads, kv_heads, d, 100, N)
+
+
+# the norm inside the products (one sequence) and as a launch of its own (all of them): LM head from 97 rows on, gate/up from 185, q/k/v from
+# 337; rows that are no multiple of 8, and a second layer's norm behind the first one's residual sums
+@pytest.mark.parametrize("B,N", [(7, 13), (8, 13), (14, 13), (16, 13), (27, 13), (64, 16)])
+def test_rows_alone_and_together(B, N):
+    import paper_2503_01840_amd as E
+    shape = S.get_shape("c1").with_(n_layers=2, taps=(0, 1, 1))
+    P = 9
+    ctx = E.Eagle3Context(shape, max_batch=B, max_nodes=N, max_depth=2, max_topk=2, max_new=4, device=DEV)
+    W = PL.device_weights(shape, device=DEV)
+    ctx.set_weights(W["target"], W["draft"])
+    i32 = lambda v: torch.tensor(np.asarray(v), dtype=torch.int32, device=DEV)
+    tok = S.uniform_ints(S.SEED + N, 77, (B, N), 0, shape.vocab).to(torch.int32).to(DEV)
+    parent = i32(np.tile(np.asarray(S.random_tree(5, N, N, 6, 3)[0]), (B, 1)))
+    pool = S.normal(S.SEED, 3, (4, B * (P + N), shape.n_kv_heads, shape.head_dim)).float().to(DEV)
+
+    def run(b0, b1):
+        t = pool[:, b0 * (P + N):b1 * (P + N)].clone()
+        kv = E.KVCache([t[0], t[1]], [t[2], t[3]], i32(np.arange(b1 - b0 + 1) * (P + N)), i32([P] * (b1 - b0)), P)
+        logits, taps = E.eagle3_tree_verify(ctx, tok[b0:b1].contiguous(), parent[b0:b1].contiguous(), kv)
+        return logits.cpu().numpy(), taps.cpu().numpy(), t.cpu().numpy()
+
+    logits, taps, cache = run(0, B)
+    for b in sorted({0, B // 2, B - 1}):
+        lg, tp, c = run(b, b + 1)
+        assert np.max(np.abs(logits[b] - lg[0])) < 1e-4 and np.max(np.abs(taps[:, b] - tp[:, 0])) < 1e-4
+        assert np.max(np.abs(cache[:, b * (P + N):(b + 1) * (P + N)] - c)) < 1e-4

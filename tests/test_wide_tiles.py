@@ -118,3 +118,23 @@ def test_few_rows_splits_of_results_that_go_to_their_place(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
     r = subprocess.run([str(tmp_path / "m")], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+# fp32 (rows, weight rows, K, pairs): microseconds with the norm inside the product, as a launch of its own
+MEASURED_NORM = [
+    ((16, 2048, 256, 0), 3.7, 6.8), ((64, 2048, 512, 0), 12.9, 14.3), ((256, 2048, 512, 0), 43.7, 41.8), ((64, 32000, 2048, 0), 675, 600),
+    ((64, 8000, 512, 0), 42.6, 40.5), ((16, 8000, 512, 0), 12.7, 14.0), ((64, 3072, 1024, 1), 21.2, 22.1), ((256, 3072, 1024, 1), 73.5, 67.6),
+    ((128, 1376, 256, 1), 8.8, 9.8), ((512, 1376, 256, 1), 24.7, 20.0), ((64, 11008, 2048, 1), 136, 118), ((8, 6144, 2048, 1), 12.7, 14.4),
+]
+
+
+def test_fp32_norm_inside_the_product_where_it_is_the_faster_way(tmp_path):
+    rows = ", ".join("{%d, %d, %d, %d, %d}" % (*q, inside < own) for q, inside, own in MEASURED_NORM)
+    (tmp_path / "m.cpp").write_text('#include <cstdio>\n#include "wide_tiles.hpp"\n'
+                                    'int main() { const int q[][5] = {' + rows + '};\n'
+                                    '  for (auto& c : q) if (f32_norm_inside(c[0], c[1], c[2], c[3]) != c[4]) { printf("%d %d %d\\n", c[0], c[1], c[2]); return 1; }\n'
+                                    '  return 0; }\n')
+    inc = os.path.join(ROOT, "paper_2503_01840_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
+    r = subprocess.run([str(tmp_path / "m")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
