@@ -103,7 +103,7 @@ __device__ __forceinline__ void unroll(F f) { unroll_seq(std::make_integer_seque
 #define WIDE_WAIT_BARRIER(n) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(n) : "memory")
 #define WIDE_PIN() __builtin_amdgcn_sched_barrier(0)
 
-template <int WGM, int WGN, int FM, int FN, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER>
+template <int WGM, int WGN, int FM, int FN, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER, int SETS>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WideParams p) {
   constexpr int TM = 32 * FM * WGM, TN = 32 * FN * WGN, NW = WGM * WGN;
   constexpr int FA = 2 * FM, FB = 2 * FN;              // 16-row fragments of a wavefront's activation and weight rows
@@ -178,13 +178,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
 #pragma unroll
   for (int q = 0; q < SUB; ++q) b_base[q] = B_BASE + (wn * 32 * FN + (lane & 15)) * (BK * 2) + (((4 * q + c) ^ swizzle(lane & 15)) * 16);
 
-  floatx4 acc[FA][FB];
-#pragma unroll
-  for (int i = 0; i < FA; ++i)
-#pragma unroll
-    for (int f = 0; f < FB; ++f)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[i][f][r] = 0.f;
+  floatx4 sums[SETS][FA][FB];                          // sub-stage v adds to set v % SETS
+  floatx4(&acc)[FA][FB] = sums[0];
 
   // Loads complete in issue order.  Sub-stage v = SUB s + q issues every piece of activation sub-stage v + AA, then part q of the
   // pieces of weight stage s + BA; the sub-stages before the first one issue what has begun by then.
@@ -202,6 +197,14 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
         step_b(i, t + 1);
       });
   });
+#pragma unroll
+  for (int j = 0; j < SETS; ++j)
+#pragma unroll
+    for (int i = 0; i < FA; ++i)
+#pragma unroll
+      for (int f = 0; f < FB; ++f)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sums[j][i][f][r] = 0.f;
   constexpr int PER = A_DMA + BP;                      // loads per sub-stage
   constexpr auto least = [](int x, int y) constexpr { return x < y ? x : y; };
   WIDE_WAIT_BARRIER(least(BP + (AA - 1) * PER, SUB * (BA - 1) * PER));   // A0 and B0 are in LDS
@@ -216,7 +219,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   // clock.  The direct loads and LDS reads are dealt out between the products, no two together, so that none of
   // them keeps a product from being issued.
   uint32_t b_slot = 0;                                 // of weight stage s
-  auto sub_stage = [&](int s, auto q, const bf16x8 (&a)[FA], const bf16x8 (&b)[FB], bf16x8 (&an)[FA], bf16x8 (&bn)[FB]) {
+  auto sub_stage = [&](int s, auto q, auto set, const bf16x8 (&a)[FA], const bf16x8 (&b)[FB], bf16x8 (&an)[FA], bf16x8 (&bn)[FB]) {
     const int h = SUB * s + q;
     // everything up to A(h+1) and, in the last sub-stage, B(s+1) has landed when only the loads issued after it are in
     // flight: what the NEXT sub-stage reads is in LDS from here on, and the slots of sub-stage h - 1 are free
@@ -229,7 +232,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
     unroll<FA * FB>([&](auto x) {
       constexpr int MF = FA * FB, NR = FA + FB;
       constexpr int f = x / FA, i = x % FA;
-      acc[i][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[f], a[i], acc[i][f], 0, 0, 0);
+      sums[set][i][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[f], a[i], sums[set][i][f], 0, 0, 0);
       // the reads in the order in which the next sub-stage needs them: b 0, every a, the rest of b
       constexpr int r = (x * NR + MF - 1) / MF;        // read r goes behind product r MF / NR
       if constexpr (r < NR && r * MF / NR == x) {
@@ -252,12 +255,28 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
     });
     if (q == SUB - 1) b_slot = b_next;
   };
-  for (int s = 0; s < KT; ++s)
+  auto stage = [&](int s, auto first) {                // first: the set of its first sub-stage
     unroll<SUB / 2>([&](auto q) {
-      sub_stage(s, std::integral_constant<int, 2 * q>{}, a0, b0, a1, b1);
-      sub_stage(s, std::integral_constant<int, 2 * q + 1>{}, a1, b1, a0, b0);
+      sub_stage(s, std::integral_constant<int, 2 * q>{}, std::integral_constant<int, (first + 2 * q) % SETS>{}, a0, b0, a1, b1);
+      sub_stage(s, std::integral_constant<int, 2 * q + 1>{}, std::integral_constant<int, (first + 2 * q + 1) % SETS>{}, a1, b1, a0, b0);
     });
+  };
+  constexpr int STEP = SETS > SUB ? SETS / SUB : 1;    // stages until the sets come round
+  int s = 0;
+  for (; s + STEP <= KT; s += STEP) unroll<STEP>([&](auto t) { stage(s + t, std::integral_constant<int, t * SUB>{}); });
+  unroll<STEP - 1>([&](auto t) {
+    if (s + t < KT) stage(s + t, std::integral_constant<int, t * SUB>{});
+  });
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // nothing may still be writing LDS when the workgroup ends
+  unroll<SETS == 1 ? 0 : SETS == 2 ? 1 : 2>([&](auto n) {               // 4 sets: 0 + 2 and 1 + 3, then both
+    constexpr int half = SETS >> (n + 1);
+    unroll<half>([&](auto j) {
+#pragma unroll
+      for (int i = 0; i < FA; ++i)
+#pragma unroll
+        for (int f = 0; f < FB; ++f) sums[j][i][f] += sums[j + half][i][f];
+    });
+  });
 
   // ---- epilogue.  Accumulator r of lane l: activation row l % 16 of its fragment, weight row 4 (l / 16) + r of its own.
   auto row_of = [&](int i) { return mblock * TM + (WGM == 2 ? (i >> 1) * 64 + wm * 32 : wm * 64 + (i >> 1) * 32) + (i & 1) * 16 + (lane & 15); };
@@ -300,11 +319,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   }
 }
 
-template <int WGM, int WGN, int FM, int FN, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER = false>
+template <int WGM, int WGN, int FM, int FN, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER = false, int SETS = 1>
 hipError_t launch_cfg(WideParams& p, int S, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   constexpr int TM = 32 * FM * WGM, TN = 32 * FN * WGN;
   constexpr int LDS = A_SLOTS * TM * 64 + B_SLOTS * TN * BK * 2;
-  auto kernel = gemm_wide_kernel<WGM, WGN, FM, FN, BK, A_SLOTS, B_SLOTS, OCC, STAGGER>;
+  auto kernel = gemm_wide_kernel<WGM, WGN, FM, FN, BK, A_SLOTS, B_SLOTS, OCC, STAGGER, SETS>;
   static DeviceOnce configured;                        // the attribute belongs to the loaded code object of a device
   hipError_t ce = configured.run([&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS); });
   if (ce != hipSuccess) return ce;
@@ -373,8 +392,8 @@ hipError_t launch_gemm_wide64(const bf16_t* x, const GemmWeights& W, int M, int 
   p.S = S;
   const bool stagger = K / S % 2048 == 0;
   if (cols == 128)
-    return stagger ? launch_cfg<2, 2, 1, 2, 128, 5, 3, 1, true>(p, S, st, ev_start, ev_stop)
-                   : launch_cfg<2, 2, 1, 2, 128, 5, 3, 1>(p, S, st, ev_start, ev_stop);
-  return stagger ? launch_cfg<2, 4, 1, 2, 64, 8, 4, 1, true>(p, S, st, ev_start, ev_stop)
-                 : launch_cfg<2, 4, 1, 2, 64, 8, 4, 1>(p, S, st, ev_start, ev_stop);
+    return stagger ? launch_cfg<2, 2, 1, 2, 128, 5, 3, 2, true, 4>(p, S, st, ev_start, ev_stop)
+                   : launch_cfg<2, 2, 1, 2, 128, 5, 3, 2, false, 4>(p, S, st, ev_start, ev_stop);
+  return stagger ? launch_cfg<2, 4, 1, 2, 64, 8, 4, 1, true, 4>(p, S, st, ev_start, ev_stop)
+                 : launch_cfg<2, 4, 1, 2, 64, 8, 4, 1, false, 4>(p, S, st, ev_start, ev_stop);
 }
