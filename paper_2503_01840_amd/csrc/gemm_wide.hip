@@ -29,6 +29,9 @@
 // with 128-k weight stages), 77 rows 60 / 59 (54.7).
 // Measured and not kept: 4 wavefronts of 128 x 128 each (a third fewer LDS reads: loop 4 % shorter, epilogue longer by the same);
 //
+// SETS: sub-stages add to so many sets of accumulators in turn, so that the sums of a long range of K are as far from 64 bits as with as many
+// ranges (28672 x 4096 at 60 rows: 3.95e-7 with one set, 1.88e-7 with four, as in gemm_skinny.hip; 0.1 us a launch).
+//
 // 33..64 rows stream weights, and of the CU's in-order slots for outstanding lines every activation line takes one like a weight line
 // does: tiles of 64 x 128 and 64 x 256 have half and a quarter of an activation line per weight line, where the 64 x 64 tiles of
 // gemm_skinny.hip have one.  A workgroup then streams 32 KB of weights in 0.92 us, and 256 of them in 1.44 (5.8 TB/s).
@@ -366,12 +369,16 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   // LM head 128256 x 4096 77 rows 252 / 227, 256 rows 329 / 302, 8192 x 8192 in four ranges 77 rows 35.0 / 30.6, 256 rows 48.9 / 49.3; stages of
   // 64 k, LM head 252 / 210, but 8192 x 28672 in seven ranges 115 / 132; and 0 to 8 % slower at 512 and 2048 rows.
   const bool stagger = wide_stagger(M, K, t);
+  // Two chains of sums where a range of K is longer than the one that the same rows had before these tiles: 128 x 128 with 128-k stages (q/k/v
+  // 6144 x 4096 at 116 rows four ranges instead of eight: error 1.37e-7, 1.89e-7 with one chain; and 2 to 3 % faster, in 198 registers
+  // instead of 176 and 88 accumulators), and 256 x 128 above 256 rows (512 rows two ranges instead of four: 1.88e-7, 2.72e-7 with one; 1 % slower).
   if (t.cols == 128 && t.k == 128) {
+    if (t.rows == 256 && M > 256) return launch_cfg<4, 2, 2, 2, 128, 4, 3, 1, false, 2>(p, t.S, st, ev_start, ev_stop);
     if (t.rows == 256)
       return stagger ? launch_cfg<4, 2, 2, 2, 128, 4, 3, 1, true>(p, t.S, st, ev_start, ev_stop)
                      : launch_cfg<4, 2, 2, 2, 128, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
-    return stagger ? launch_cfg<2, 2, 2, 2, 128, 4, 3, 1, true>(p, t.S, st, ev_start, ev_stop)
-                   : launch_cfg<2, 2, 2, 2, 128, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
+    return stagger ? launch_cfg<2, 2, 2, 2, 128, 4, 3, 2, true, 2>(p, t.S, st, ev_start, ev_stop)
+                   : launch_cfg<2, 2, 2, 2, 128, 4, 3, 2, false, 2>(p, t.S, st, ev_start, ev_stop);
   }
   if (t.cols == 128) {
     if (t.rows == 256) return launch_cfg<4, 2, 2, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
