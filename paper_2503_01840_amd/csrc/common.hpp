@@ -69,10 +69,7 @@ __device__ __forceinline__ float4 load4_f32(const bf16_t* p, size_t i) {
   return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
                      __uint_as_float(v.y & 0xFFFF0000u));
 }
-// four consecutive values stored in the plain (row-major) storage type
-__device__ __forceinline__ void store4_plain(float* p, size_t i, float a, float b, float c, float d) {
-  *(float4*)(p + i) = make_float4(a, b, c, d);
-}
+// four consecutive values stored row-major
 __device__ __forceinline__ void store4_plain(bf16_t* p, size_t i, float a, float b, float c, float d) {
   uint2 v;
   v.x = pack_bf16x2(a, b);

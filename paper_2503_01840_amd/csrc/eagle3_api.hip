@@ -92,7 +92,7 @@ struct eagle3_ctx {
     const size_t widest = std::max<size_t>((size_t)(c.n_heads + 2 * c.n_kv_heads) * c.head_dim, c.hidden);
     // split-K partial sums: up to 4 slices of the widest projection, 8 of a hidden-sized one; 2 for a prefill chunk, whose
     // many rows fill the chip without more
-    part_floats = std::max<size_t>({1024 * widest, 4 * (size_t)R_step * widest, 8 * (size_t)R_step * c.hidden, 2 * (size_t)chunk * widest});
+    part_floats = bf16 ? std::max<size_t>({1024 * widest, 4 * (size_t)R_step * widest, 8 * (size_t)R_step * c.hidden, 2 * (size_t)chunk * widest}) : 1;
     size_t af = 0;
     auto attention = [&](int batch, int rows) {
       const int s = attention_pick_splits(batch, rows, c.n_heads, c.n_kv_heads, 1 << 30);
@@ -408,7 +408,7 @@ static int project_qkv(eagle3_ctx* ctx, const eagle3_layer_weights& w, void* in,
   }
   int S = 1;
   TRY(ctx->project(in, Wqkv, R, (H + 2 * Hkv) * d, K, GEMM_EPI_PARTIAL, &S, st));
-  CK(launch_rope_kv_write(true, ctx->part, S, R, H, Hkv, d, cs, slot, ctx->q, kc, vc, st));
+  CK(launch_rope_kv_write(ctx->part, S, R, H, Hkv, d, cs, slot, ctx->q, kc, vc, st));
   return EAGLE3_OK;
 }
 
@@ -504,7 +504,7 @@ static int run_layers(eagle3_ctx* ctx, int B, int N, int R, bool prefill, const 
   int S_prev = 0;                                   // bf16: partial sums of the previous layer's MLP still to be added
   for (int l = l0; l <= l1; ++l) {
     // bf16: x becomes the output of layer l-1 here, is copied, and normed for what follows.  fp32: x is complete, layer l-1 has
-    // made the copies, and the norm is part of the product that follows.
+    // made the copies, and the norm comes with the product that follows (norm_operand).
     const Copies co = copies_at(l);
     const bool any = co.p[0] || co.p[1] || co.p[2] || co.p[3], head = l == c.n_layers && l == l1 && logits;
     if (head && ctx->bf16) return norm_head(ctx, ctx->x, S_prev, R, ctx->tw.final_norm, co.p, ctx->tw.lm_head, c.vocab, logits, st);

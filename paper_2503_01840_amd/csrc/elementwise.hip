@@ -150,15 +150,11 @@ __global__ __launch_bounds__(256) void tree_prep_kernel(const int32_t* __restric
   }
 }
 
-// One workgroup per row; a thread handles four consecutive rotary pairs (i..i+3, i+d/2..i+d/2+3) of one head.
-template <bool BF16>
+// One workgroup per row; a thread handles four consecutive rotary pairs (i..i+3, i+d/2..i+d/2+3) of one head.  (fp32: gemm_f32.hip.)
 __global__ __launch_bounds__(1024) void rope_kv_write_kernel(const float* __restrict__ qkv, int S, int R, int H, int Hkv,
                                                             int d, const float* __restrict__ cs,
-                                                            const int32_t* __restrict__ slot,
-                                                            typename Act<BF16>::type* __restrict__ q,
-                                                            typename Act<BF16>::type* __restrict__ kc,
-                                                            typename Act<BF16>::type* __restrict__ vc) {
-  typedef typename Act<BF16>::type T;
+                                                            const int32_t* __restrict__ slot, bf16_t* __restrict__ q,
+                                                            bf16_t* __restrict__ kc, bf16_t* __restrict__ vc) {
   const int r = blockIdx.x, half = d / 2, NT = (H + 2 * Hkv) * d, q4 = half / 4;
   const size_t sl = (size_t)slot[r];
   for (int e = threadIdx.x; e < (H + 2 * Hkv) * q4; e += blockDim.x) {
@@ -179,7 +175,7 @@ __global__ __launch_bounds__(1024) void rope_kv_write_kernel(const float* __rest
           x2.x += b[j].x; x2.y += b[j].y; x2.z += b[j].z; x2.w += b[j].w;
         }
     }
-    T* dst;
+    bf16_t* dst;
     if (h < H + Hkv) {
       const float4 c = *(const float4*)(cs + (size_t)r * d + i), sn = *(const float4*)(cs + (size_t)r * d + half + i);
       const float4 o1 = make_float4(x1.x * c.x - x2.x * sn.x, x1.y * c.y - x2.y * sn.y, x1.z * c.z - x2.z * sn.z,
@@ -379,16 +375,12 @@ hipError_t launch_tree_prep(const int32_t* parent, const int32_t* kv_indptr, con
   return hipGetLastError();
 }
 
-hipError_t launch_rope_kv_write(bool bf16, const float* qkv_partial, int S, int R, int H, int Hkv, int d, const float* cs,
-                                const int32_t* slot, void* q, void* kcache, void* vcache, hipStream_t st) {
+hipError_t launch_rope_kv_write(const float* qkv_partial, int S, int R, int H, int Hkv, int d, const float* cs, const int32_t* slot,
+                                void* q, void* kcache, void* vcache, hipStream_t st) {
   if (d % 8) return hipErrorInvalidValue;
   const int bd = std::min(1024, ((H + 2 * Hkv) * d / 8 + 63) / 64 * 64);
-  if (bf16)
-    hipLaunchKernelGGL(rope_kv_write_kernel<true>, dim3(R), dim3(bd), 0, st, qkv_partial, S, R, H, Hkv, d, cs, slot,
-                       (bf16_t*)q, (bf16_t*)kcache, (bf16_t*)vcache);
-  else
-    hipLaunchKernelGGL(rope_kv_write_kernel<false>, dim3(R), dim3(bd), 0, st, qkv_partial, S, R, H, Hkv, d, cs, slot,
-                       (float*)q, (float*)kcache, (float*)vcache);
+  hipLaunchKernelGGL(rope_kv_write_kernel, dim3(R), dim3(bd), 0, st, qkv_partial, S, R, H, Hkv, d, cs, slot, (bf16_t*)q,
+                     (bf16_t*)kcache, (bf16_t*)vcache);
   return hipGetLastError();
 }
 

@@ -69,9 +69,9 @@ hipError_t launch_add_norm(bool bf16, float* x, const float* partial, int S, int
 hipError_t launch_tree_prep(const int32_t* parent, const int32_t* kv_indptr, const int32_t* prefix_len, int B, int N,
                             int head_dim, float theta, int32_t* depth, uint32_t* mask, int32_t* slot, float* cs,
                             SeqInfo* seq, hipStream_t st);
-// Sums the q|k|v split-K partials, rotates q and k, writes q (activation type, [R,H,d]) and the cache rows.
-hipError_t launch_rope_kv_write(bool bf16, const float* qkv_partial, int S, int R, int H, int Hkv, int d, const float* cs,
-                                const int32_t* slot, void* q, void* kcache, void* vcache, hipStream_t st);
+// bf16: sums the q|k|v split-K partials, rotates q and k, writes q [R,H,d] and the cache rows.
+hipError_t launch_rope_kv_write(const float* qkv_partial, int S, int R, int H, int Hkv, int d, const float* cs, const int32_t* slot,
+                                void* q, void* kcache, void* vcache, hipStream_t st);
 hipError_t launch_pack3(bool bf16, const float* a, const float* b, const float* c, int M, int k, void* act, hipStream_t st);
 hipError_t launch_reduce_partials(const float* partial, int S, int M, int N, float* out, hipStream_t st);
 // Draft layer input: act[r] = [RMSNorm(E[tok[r]]; g_embed) ; RMSNorm(f_r; g_feat)], y[r] = f_r,
