@@ -397,7 +397,7 @@ hipError_t launch_gemm_wide64(const bf16_t* x, const GemmWeights& W, int M, int 
   if (M > 64 || S < 1 || (cols != 128 && cols != 256) || K % (S * (cols == 128 ? 128 : 64)) || (epi == GEMM_EPI_SWIGLU && S != 1))
     return hipErrorInvalidValue;
   p.S = S;
-  const bool stagger = K / S % 2048 == 0;
+  const bool stagger = few_rows_stagger(K, S);
   if (cols == 128)
     return stagger ? launch_cfg<2, 2, 1, 2, 128, 5, 3, 2, true, 4>(p, S, st, ev_start, ev_stop)
                    : launch_cfg<2, 2, 1, 2, 128, 5, 3, 2, false, 4>(p, S, st, ev_start, ev_stop);

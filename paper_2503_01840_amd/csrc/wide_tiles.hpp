@@ -132,6 +132,9 @@ struct FewRows {
   int S;
 };
 
+// Whether the K walks of the 64-row tiles start at a stage of each workgroup's own (gemm_wide.hip has the figures).
+inline bool few_rows_stagger(int K, int S) { return K / S % 2048 == 0; }
+
 // 33..64 rows: the tile whose launch is over first by this estimate, in microseconds.  A workgroup of any kind takes 4.9 for start and
 // end.  128 and 256 weight rows: one to a CU; a stage of 32 KB of weights takes 0.92 us where few CUs are busy and 1.44 where all are,
 // in rounds of 32 workgroups of the fullest XCD.  64 weight rows: two to a CU; a stage of 16 KB takes 0.73 alone, 1.59 where each CU

@@ -86,9 +86,41 @@ def test_prefill_behind_a_long_context_keeps_a_bad_token_to_the_rows_that_see_it
     _bad_token(_small(), parts, at)
 
 
+# (heads of 64 and 128 and heads of other sizes have a kernel each)
+@pytest.mark.parametrize("d", [64, 128, 32, 72])
 @pytest.mark.parametrize("parts,at", [([130], 60), ([130], 100), ([40, 90], 100)])
-def test_prefill_fp32_keeps_a_bad_token_to_the_rows_that_see_it(parts, at):
-    _bad_token(S.get_shape("c1"), parts, at)
+def test_prefill_fp32_keeps_a_bad_token_to_the_rows_that_see_it(parts, at, d):
+    _bad_token(S.get_shape("c1").with_(head_dim=d), parts, at)
+
+
+# an infinity and a NaN among the values of tree slots that other rows do not see, in every kernel of the fp32 attention
+@pytest.mark.parametrize("d", [64, 128, 32, 72])
+@pytest.mark.parametrize("bad", [INF, NAN])
+def test_verification_fp32_keeps_bad_values_to_the_nodes_that_see_them(d, bad):
+    import paper_2503_01840_amd as E
+    import pipeline as PL
+    shape = S.get_shape("c1").with_(head_dim=d, n_layers=1, taps=(0, 0, 0))
+    N, P, at = 30, 40, 3
+    parent = S.random_tree(S.SEED, 3, N, 6, 3)[0]
+    below = np.zeros(N, bool)
+    for i in range(N):
+        below[i] = i == at or (i > 0 and below[parent[i]])
+    W = PL.device_weights(shape, device=DEV)
+    ctx = E.Eagle3Context(shape, max_batch=1, max_nodes=N, max_depth=2, max_topk=2, max_new=4, device=DEV)
+    ctx.set_weights(W["target"], W["draft"])
+    i32 = lambda v: torch.tensor(np.asarray(v), dtype=torch.int32, device=DEV)
+    tok = S.uniform_ints(S.SEED, 5, (1, N), 0, shape.vocab).to(torch.int32).to(DEV)
+
+    def stream(x_in):
+        k, v = (S.normal(S.SEED, i, (P + N, shape.n_kv_heads, d)).float().to(DEV) for i in (1, 2))
+        return E.eagle3_tree_verify_layers(ctx, tok, i32(parent)[None], E.KVCache([k], [v], i32([0, P + N]), i32([P]), P), x_in, 0, 1)[0][0].cpu()
+
+    x_in = S.normal(S.SEED, 9, (1, N, shape.hidden)).float().to(DEV)
+    clean = stream(x_in)
+    x_in[0, at, 5] = bad                                          # its row of keys and values is NaN throughout
+    got = stream(x_in)
+    assert bool(torch.isnan(got[below]).any(1).all()) and not below.all()
+    assert bool(torch.isfinite(got[~below]).all()) and float((got[~below] - clean[~below]).abs().max()) < 1e-4
 
 
 # a bad node in a tree: nodes that do not descend from it keep their logits

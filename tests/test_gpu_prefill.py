@@ -43,6 +43,12 @@ def test_prefill_without_a_feature_of_the_last_layer(dtype, T, part):
     _check(shape.with_(taps=(0, 0, shape.n_layers - 2)), dtype, T, part)
 
 
+# hidden 512 and 768: the fusion of the features in three and four ranges of K, summed by a launch of its own; 64 rows: the few-row product
+@pytest.mark.parametrize("hidden,T", [(512, 64), (512, 65), (512, 130), (512, 300), (768, 77), (768, 200), (768, 513)])
+def test_prefill_with_a_split_fusion(hidden, T):
+    _check(SMALL.with_(name=f"h{hidden}", hidden=hidden), "bf16", T)
+
+
 def _check(shape, dtype, T, part=1.0, base=0):
     E = _E()
     rounding = "none" if dtype == "fp32" else "bf16"

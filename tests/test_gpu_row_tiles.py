@@ -1,4 +1,5 @@
-"""The many-row products at the edges of their 192-row tiles."""
+"""The products of more than 32 rows at the edges of their tiles: the same rows in few and in many, and prompts against the oracle.  Which
+tile each of them takes is pinned in test_wide_tiles.py."""
 import numpy as np
 import pytest
 import torch
@@ -11,14 +12,13 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# gate/up of the small model in 192-row tiles (384 rows and more) and just above the 256-row line: one row over a 64-row piece, over
-# a tile, a full last tile
+# the small model in 128 x 128 tiles just above the 256-row line, one row over a 64-row piece, over a tile, a full last tile
 @pytest.mark.parametrize("T", [257, 384, 386, 576, 577])
 def test_prefill_at_192_row_edges(T):
     _prefill_against_the_oracle("bf16", T)
 
 
-# one layer of the 8B shape: 577..640 rows (192-row tiles, split and unsplit, of every projection but the LM head) against the same
+# one layer of the 8B shape: 577..640 rows (o and down in split, gate/up in unsplit 192-row tiles, q/k/v in 128 x 128 tiles side by side) against the same
 # sequences ten (128 x 128 tiles, the last few rows the few-row kernel) and 25 (256 x 128 tiles) at a time
 @pytest.mark.parametrize("B,N", [(58, 10), (60, 10), (64, 10)])
 @pytest.mark.parametrize("group", [10, 25])
@@ -26,7 +26,8 @@ def test_rows_do_not_depend_on_the_batch(B, N, group):
     _rows_alone_and_together(S.get_shape("c3"), B, N, group)
 
 
-# a gate/up of many weight rows in 192-row tiles from 257 rows on: the edges of a tile against at most 64 rows at a time
+# a gate/up of many weight rows in 192-row tiles at 257, 384, 576 and 577 rows (256-row ones at 385): the edges of a tile against at most 64 rows
+# at a time
 @pytest.mark.parametrize("B,N,group", [(257, 1, 64), (64, 6, 10), (77, 5, 12), (64, 9, 7), (577, 1, 50)])
 def test_rows_at_192_row_edges(B, N, group):
     _rows_alone_and_together(S.get_shape("c3").with_(name="flat", hidden=256, n_heads=4, n_kv_heads=2, vocab=1024), B, N, group)
@@ -70,6 +71,7 @@ def test_rows_of_64_row_tiles(name, B, N, group):
 
 
 def _rows_alone_and_together(full, B, N, group, logits=False):
+    """All B sequences of N rows at once against `group` of them at a time; one sequence: against its first 32 rows."""
     E = _E()
     shape = full.with_(n_layers=1, taps=(0, 0, 0))
     W = {k: v.to(DEV) for k, v in S.layer_weights(full, 3).items()}
@@ -86,20 +88,21 @@ def _rows_alone_and_together(full, B, N, group, logits=False):
     k0 = torch.randn(B * (P + N), full.n_kv_heads, full.head_dim, device=DEV, generator=gen).bfloat16()
     v0 = torch.randn(B * (P + N), full.n_kv_heads, full.head_dim, device=DEV, generator=gen).bfloat16()
 
-    def run(b0, b1):
-        n = b1 - b0
-        k, v = k0[b0 * (P + N):b1 * (P + N)].clone(), v0[b0 * (P + N):b1 * (P + N)].clone()
-        kv = E.KVCache([k], [v], i32(np.arange(n + 1) * (P + N)), i32([P] * n), P)
-        x_out, lg = E.eagle3_tree_verify_layers(ctx, tok[b0:b1].contiguous(), parent[b0:b1].contiguous(), kv, x_in[b0:b1].contiguous(), 0, 1,
-                                               want_logits=True)
+    def run(b0, b1, n_rows=N):
+        n, at = b1 - b0, slice(b0 * (P + N), (b1 - 1) * (P + N) + P + n_rows)
+        k, v = k0[at].clone(), v0[at].clone()
+        kv = E.KVCache([k], [v], i32(np.append(np.arange(n) * (P + N), k.shape[0])), i32([P] * n), P)
+        x_out, lg = E.eagle3_tree_verify_layers(ctx, tok[b0:b1, :n_rows].contiguous(), parent[b0:b1, :n_rows].contiguous(), kv,
+                                               x_in[b0:b1, :n_rows].contiguous(), 0, 1, want_logits=True)
         torch.cuda.synchronize()
         return x_out.cpu().numpy(), k.float().cpu().numpy(), lg.float().cpu().numpy() if logits else None
 
     x, k, lg = run(0, B)
+    rows = N if B > 1 else 32
     for b0 in range(0, B, group):
         b1 = min(B, b0 + group)
-        xr, kr, lr = run(b0, b1)
-        assert np.max(np.abs(x[b0:b1] - xr)) < TOL * max(1.0, _rms(xr))
-        assert np.max(np.abs(k[b0 * (P + N):b1 * (P + N)] - kr)) < 4e-2
+        xr, kr, lr = run(b0, b1, rows)
+        assert np.max(np.abs(x[b0:b1, :rows] - xr)) < TOL * max(1.0, _rms(xr))
+        assert np.max(np.abs(k[b0 * (P + N):b0 * (P + N) + len(kr)] - kr)) < 4e-2
         if logits:
-            assert np.max(np.abs(lg[b0:b1] - lr)) < TOL * max(1.0, _rms(lr))
+            assert np.max(np.abs(lg[b0:b1, :rows] - lr)) < TOL * max(1.0, _rms(lr))

@@ -1,5 +1,5 @@
-"""The tile rule of the many-row product (host code): it takes the 192-row tiles only where they were measured to be the faster ones.
-No GPU: the rule is compiled with the host compiler."""
+"""The rules by which products take their tiles, splits, weight stages and walks (host code, compiled with the host compiler; no GPU): against
+what was measured, and which of them the GPU tests of test_gpu_row_tiles.py run."""
 import os
 import subprocess
 
@@ -138,3 +138,50 @@ def test_fp32_norm_inside_the_product_where_it_is_the_faster_way(tmp_path):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
     r = subprocess.run([str(tmp_path / "m")], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+# hidden, q heads, kv heads, intermediate, vocabulary of the models of test_gpu_row_tiles.py
+MODELS = {"8b": (4096, 32, 8, 14336, 128256), "wide": (3584, 28, 4, 18944, 33004), "deep": (5120, 40, 8, 13824, 20484), "mha": (4096, 32, 32, 11008, 1024),
+          "flat": (256, 4, 2, 14336, 1024)}
+
+
+def _products(model, M):
+    """(outputs, inputs, SwiGLU, straight to its place, floats for partial sums) of q/k/v, o, gate/up, down and the LM head"""
+    k, H, G, I, V = MODELS[model]
+    widest = max((H + 2 * G) * 128, k)
+    cap = max(1024 * widest, 4 * M * widest, 8 * M * k, 2 * 2048 * widest)
+    return [((H + 2 * G) * 128, k, 0, 0, cap), (k, H * 128, 0, 0, cap), (2 * I, k, 1, 0, cap), (k, I, 0, 0, cap), (V, k, 0, 1, 0)]
+
+
+# what the comments there say that they cover: (rows, cols, S, k, staggered) of the products listed
+@pytest.mark.parametrize("model,M,at,want", [
+    ("8b", 65, (0, 1, 2, 3, 4), [(128, 128, 4, 128, 0), (128, 128, 8, 64, 0), (128, 128, 1, 128, 1), (128, 128, 8, 128, 0), (128, 128, 1, 64, 1)]),
+    ("8b", 128, (0, 1, 2, 3, 4), [(128, 128, 4, 128, 0), (128, 128, 8, 64, 0), (128, 128, 1, 128, 1), (128, 128, 8, 128, 0), (128, 128, 1, 64, 1)]),
+    ("8b", 129, (0, 2, 3, 4), [(256, 128, 4, 128, 0), (256, 128, 1, 128, 1), (256, 128, 8, 128, 0), (256, 128, 1, 128, 1)]),
+    ("8b", 256, (0, 2, 4), [(256, 128, 4, 128, 0), (256, 128, 1, 128, 1), (256, 128, 1, 128, 1)]),
+    ("8b", 600, (0, 1, 2, 3), [(128, 128, 2, 64, 0), (192, 256, 4, 64, 0), (192, 256, 1, 64, 0), (192, 256, 4, 64, 0)]),
+    ("wide", 65, (1, 2, 4), [(128, 128, 7, 64, 0), (128, 128, 1, 64, 0), (128, 128, 1, 64, 0)]),
+    ("wide", 129, (0, 2, 3, 4), [(256, 128, 4, 128, 0), (256, 128, 1, 128, 0), (256, 128, 8, 64, 0), (256, 128, 1, 128, 0)]),
+    ("mha", 129, (3,), [(256, 128, 4, 64, 0)]), ("mha", 256, (3,), [(256, 128, 4, 64, 0)]),
+    ("flat", 257, (2,), [(192, 256, 1, 64, 0)]), ("flat", 384, (2,), [(192, 256, 1, 64, 0)]), ("flat", 385, (2,), [(256, 256, 1, 64, 0)]),
+    ("flat", 576, (2,), [(192, 256, 1, 64, 0)]), ("flat", 577, (2,), [(192, 256, 1, 64, 0)]),
+])
+def test_tiles_that_the_gpu_tests_cover(whole_rule, model, M, at, want):
+    ps = _products(model, M)
+    assert whole_rule([(M, *ps[i][:3], ps[i][4]) for i in at]) == want
+
+
+# 33..64 rows: (cols, S, staggered)
+@pytest.mark.parametrize("model,at,want", [("8b", (0, 2, 4), [(128, 4, 0), (128, 1, 1), (256, 1, 1)]), ("wide", (2, 4), [(256, 1, 0), (256, 1, 0)]),
+                                           ("deep", (1, 3, 4), [(128, 5, 0), (128, 6, 0), (128, 1, 0)])])
+@pytest.mark.parametrize("M", [33, 48, 63, 64])
+def test_few_row_tiles_that_the_gpu_tests_cover(tmp_path, model, at, want, M):
+    ps = [_products(model, M)[i] for i in at]
+    ask = ", ".join("{%d, %d, %d, %d, %d}" % (n, k, s, d, cap or 1 << 30) for n, k, s, d, cap in ps)
+    (tmp_path / "m.cpp").write_text('#include <cstdio>\n#include "wide_tiles.hpp"\nint main() { const long q[][5] = {' + ask + '};\n'
+                                    '  for (auto& c : q) { const FewRows t = few_rows(' + str(M) + ', c[0], c[1], c[2], c[3], c[4], true);\n'
+                                    '    printf("%d %d %d\\n", t.cols, t.S, few_rows_stagger(c[1], t.S)); } }\n')
+    inc = os.path.join(ROOT, "paper_2503_01840_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
+    out = subprocess.run([str(tmp_path / "m")], capture_output=True, text=True, check=True).stdout
+    assert [tuple(map(int, line.split())) for line in out.splitlines()] == want
