@@ -6,7 +6,7 @@
 //   * a workgroup owns a (32 FM WGM) x (32 FN WGN) output tile; its WGM x WGN wavefronts each hold 2 FM x 2 FN
 //     accumulators of v_mfma_f32_16x16x32_bf16 and there is no cross-wavefront reduction.  With many rows the chip is bound by
 //     power: products alone sustain 1.88 PFLOP/s as 32x32x16 and 2.14 as 16x16x32 (the sum over 32 k stays inside the matrix
-//     unit), with their operands read from LDS 1.64 and 1.86.  The sums come out bit for bit the same;
+//     unit), with their operands read from LDS 1.64 and 1.86.  With one set of sums they come out bit for bit the same;
 //   * both operands reach LDS by direct global-to-LDS loads (global_load_lds_dwordx4: each wavefront
 //     instruction deposits 1 KiB contiguously, no staging registers).  A CU accepts roughly one cache line per
 //     four clocks whatever its size, so every request is a whole 128-byte line: activations come in 32-k slots
@@ -25,9 +25,9 @@
 //     SwiGLU (the tile interleaves gate and up rows so that both values of a pair sit in the same lane) written
 //     as fragment-major bf16 (8-byte stores).
 // 8B width, us, products as 32x32x16 with the reads and loads in bursts / now: 2048 rows gate/up 422 / 368 (1.31 PFLOP/s), down
-// 214 / 177, o 77 / 57, q/k/v 100 / 87; 512 rows gate/up 116 / 101, down 73 / 60, q/k/v 39 / 35; 256 rows gate/up 77 / 74 (69.5
-// with 128-k weight stages), 77 rows 60 / 59 (54.7).
-// Measured and not kept: 4 wavefronts of 128 x 128 each (a third fewer LDS reads: loop 4 % shorter, epilogue longer by the same);
+// 214 / 177, o 77 / 57, q/k/v 100 / 87; 512 rows gate/up 116 / 101, down 73 / 60, q/k/v 39 / 35; 256 rows gate/up 75 / 72 (68
+// with 128-k weight stages and staggered walks), 77 rows 61 / 58 (53).
+// Measured and not kept: 4 wavefronts of 128 x 128 each (a third fewer LDS reads: loop 4 % shorter, epilogue longer by the same).
 //
 // SETS: sub-stages add to so many sets of accumulators in turn, so that the sums of a long range of K are as far from 64 bits as with as many
 // ranges (28672 x 4096 at 60 rows: 3.95e-7 with one set, 1.88e-7 with four, as in gemm_skinny.hip; 0.1 us a launch).
@@ -47,7 +47,6 @@
 #include "wide_tiles.hpp"
 
 namespace {
-
 
 // Four neighbours of an output row, which need not start at a multiple of 16 bytes: one store all the same.  So a LM head of any number of
 // rows can take the 64-row tiles (128255 x 4096 behind a layer, 60 rows: 342 us, 370 with the workgroups of gemm_skinny.hip).
