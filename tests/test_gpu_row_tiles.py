@@ -30,7 +30,7 @@ def test_rows_do_not_depend_on_the_batch(B, N, group):
 # at a time
 @pytest.mark.parametrize("B,N,group", [(257, 1, 64), (64, 6, 10), (77, 5, 12), (64, 9, 7), (577, 1, 50)])
 def test_rows_at_192_row_edges(B, N, group):
-    _rows_alone_and_together(S.get_shape("c3").with_(name="flat", hidden=256, n_heads=4, n_kv_heads=2, vocab=1024), B, N, group)
+    _rows_alone_and_together(S.get_shape("c3").with_(name="flat", hidden=256, n_heads=4, n_kv_heads=2, vocab=1024), B, N, group, logits=True)
 
 
 # 65..256 rows, logits included, against at most 64 rows at a time: the first and last row count of 128 x 128 and of 256 x 128 tiles and one
@@ -42,10 +42,10 @@ def test_rows_in_wide_weight_stages(name, B, N, group):
     _rows_alone_and_together(FEW[name], B, N, group, logits=True)
 
 
-# 64-k weight stages in split products of 129..256 rows: down in four ranges of 2752
+# 64-k weight stages in split products of 129..256 rows: down in four ranges of 2752; a LM head of fewer rows than inputs, split and summed
 @pytest.mark.parametrize("B,N,group", [(129, 1, 64), (64, 3, 20), (64, 4, 16)])
 def test_rows_in_ranges_that_wide_weight_stages_do_not_divide(B, N, group):
-    _rows_alone_and_together(S.get_shape("c3").with_(name="mha", n_kv_heads=32, intermediate=11008, vocab=1024), B, N, group)
+    _rows_alone_and_together(S.get_shape("c3").with_(name="mha", n_kv_heads=32, intermediate=11008, vocab=1024), B, N, group, logits=True)
 
 
 # 33..64 rows, logits included, against at most 32 rows at a time (the few-row kernel).  8B width: q/k/v in 64 x 128 tiles in step,
