@@ -62,6 +62,14 @@ template <> struct Act<false> {
   }
 };
 
+// Row of workgroup x where a workgroup takes one row (or a part of one) and writes it as an activation.  bf16: a 128-byte line of the
+// fragment-major layout holds pieces of eight rows, and workgroups go to the XCDs in turn; eight consecutive rows go to one XCD, whose L2
+// then puts the line together.  The grid is a multiple of 64 wide (rows_grid); rows past the end do nothing.  Against rows dealt out one by one:
+// verification of 64 trees 11.14 -> 10.93 ms, 2048 tokens 26.8 -> 26.5, an 8B step 6.26 -> 6.19 (with the same in the attention merge).
+template <bool BF16>
+__device__ __forceinline__ int row_of_workgroup(int x) { return BF16 ? (x >> 6) * 64 + (x & 7) * 8 + ((x >> 3) & 7) : x; }
+inline int rows_grid(int R) { return (R + 63) / 64 * 64; }
+
 // four consecutive values of a weight-typed vector (gain) or of a row-major activation
 __device__ __forceinline__ float4 load4_f32(const float* p, size_t i) { return *(const float4*)(p + i); }
 __device__ __forceinline__ float4 load4_f32(const bf16_t* p, size_t i) {

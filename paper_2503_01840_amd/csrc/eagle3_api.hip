@@ -121,7 +121,7 @@ struct eagle3_ctx {
     depth = cv.take<int32_t>(Rall);
     mask = cv.take<uint32_t>((size_t)Rall * 4);
     slot = cv.take<int32_t>(Rall);
-    cs = cv.take<float>((size_t)Rall * c.head_dim);
+    cs = cv.take<float>((size_t)std::max(Rall, c.max_new + c.max_depth) * c.head_dim);
     seq = cv.take<SeqInfo>(std::max(c.max_batch, (chunk_max + 63) / 64));
     accept_stats = cv.take<float>(accept_scratch_floats(R_max, c.vocab));
     const int mb = std::max(c.max_batch, 1);
@@ -132,9 +132,6 @@ struct eagle3_ctx {
                                            topk_scratch_floats(mb, c.draft_vocab, 1)));
     cs_chain.top_val = cv.take<float>(mb);
     cs_chain.top_idx = cv.take<int32_t>(mb);
-    cs_chain.row_tok = cv.take<int32_t>(mb);
-    cs_chain.row_src = cv.take<int32_t>(mb);
-    cs_chain.row_pos = cv.take<int32_t>(mb);
     cs_chain.row_slot = cv.take<int32_t>(mb);
     cs_chain.row_mask = cv.take<uint32_t>((size_t)mb * 4);
     cs_chain.seq = cv.take<SeqInfo>(mb);
@@ -142,19 +139,22 @@ struct eagle3_ctx {
     ds.pool_parent = cv.take<int32_t>(pool_max);
     ds.pool_depth = cv.take<int32_t>(pool_max);
     ds.pool_score = cv.take<float>(pool_max);
-    ds.pool_mask = cv.take<uint32_t>((size_t)pool_max * 4);
     ds.frontier = cv.take<int32_t>((size_t)c.max_depth * c.max_topk);
     ds.top_val = cv.take<float>((size_t)Md_max * c.max_topk);
     ds.top_idx = cv.take<int32_t>((size_t)Md_max * c.max_topk);
-    ds.row_tok = cv.take<int32_t>(c.max_topk);
-    ds.row_src = cv.take<int32_t>(c.max_topk);
-    ds.row_pos = cv.take<int32_t>(c.max_topk);
     ds.row_slot = cv.take<int32_t>(c.max_topk);
-    ds.row_mask = cv.take<uint32_t>((size_t)c.max_topk * 4);
+    for (int i = 0; i < 2; ++i) {
+      ds.row_mask[i] = cv.take<uint32_t>((size_t)c.max_topk * 4);
+      ds.row_score[i] = cv.take<float>(c.max_topk);
+    }
     ds.seq = cv.take<SeqInfo>(1);
     chunk_taps = cv.take<float>((size_t)3 * chunk_max * k);
     chunk_g = cv.take<float>((size_t)chunk_max * k);
     ws_need = cv.off;
+  }
+
+  DraftInputArgs draft_input_args() const {
+    return {tw.embed, dw.norm_embed, dw.norm_feat, act_k, x, cs, cfg.vocab, cfg.hidden, cfg.head_dim, cfg.rms_eps, cfg.rope_theta};
   }
 
   // One projection Y = act W^T.  epi PARTIAL: result (S partial sums) in `part`; *S_out = S.
@@ -391,10 +391,10 @@ static int norm_operand(eagle3_ctx* ctx, float* x, const void* gain, int R, int 
   return EAGLE3_OK;
 }
 
-// q/k/v projection of R rows, rotated, k and v in their cache slots.  in: the projection's operand, K wide; fp32 with a gain: the
+// q/k/v projection of R rows, rotated (cs, cs_step: their rotary tables), k and v in their cache slots.  in: the projection's operand, K wide; fp32 with a gain: the
 // rows whose RMSNorm is that operand.
 static int project_qkv(eagle3_ctx* ctx, const eagle3_layer_weights& w, void* in, const void* gain, int K, int R, const int32_t* slot,
-                       const float* cs, void* kc, void* vc, hipStream_t st) {
+                       const float* cs, int cs_step, void* kc, void* vc, hipStream_t st) {
   const eagle3_config& c = ctx->cfg;
   const int H = c.n_heads, Hkv = c.n_kv_heads, d = c.head_dim;
   GemmWeights Wqkv = {{w.wq, w.wk, w.wv}, {H * d, Hkv * d, Hkv * d}, 3, 0};
@@ -402,13 +402,13 @@ static int project_qkv(eagle3_ctx* ctx, const eagle3_layer_weights& w, void* in,
     F32Fuse f;
     const float* rows;
     TRY(norm_operand(ctx, (float*)in, gain, R, (H + 2 * Hkv) * d, K, true, f, &rows, st));
-    f.cs = cs; f.slot = slot; f.kc = (float*)kc; f.vc = (float*)vc; f.H = H; f.Hkv = Hkv; f.d = d;
+    f.cs = cs; f.cs_step = cs_step; f.slot = slot; f.kc = (float*)kc; f.vc = (float*)vc; f.H = H; f.Hkv = Hkv; f.d = d;
     CK(launch_gemm_f32(rows, Wqkv, R, (H + 2 * Hkv) * d, K, GEMM_EPI_ROPE, (float*)ctx->q, st, f));
     return EAGLE3_OK;
   }
   int S = 1;
   TRY(ctx->project(in, Wqkv, R, (H + 2 * Hkv) * d, K, GEMM_EPI_PARTIAL, &S, st));
-  CK(launch_rope_kv_write(ctx->part, S, R, H, Hkv, d, cs, slot, ctx->q, kc, vc, st));
+  CK(launch_rope_kv_write(ctx->part, S, R, H, Hkv, d, cs, cs_step, slot, ctx->q, kc, vc, st));
   return EAGLE3_OK;
 }
 
@@ -514,7 +514,7 @@ static int run_layers(eagle3_ctx* ctx, int B, int N, int R, bool prefill, const 
     if (head) return norm_head(ctx, ctx->x, 0, R, ctx->tw.final_norm, nullptr, ctx->tw.lm_head, c.vocab, logits, st);
     if (l == l1) break;
     const eagle3_layer_weights& w = ctx->layers[l];
-    TRY(project_qkv(ctx, w, ctx->bf16 ? ctx->act_k : ctx->x, w.norm_attn, k, R, ctx->slot, ctx->cs, kv->k[l], kv->v[l], st));
+    TRY(project_qkv(ctx, w, ctx->bf16 ? ctx->act_k : ctx->x, w.norm_attn, k, R, ctx->slot, ctx->cs, c.head_dim, kv->k[l], kv->v[l], st));
     const Copies next = copies_at(l + 1);
     TRY(layer_tail(ctx, w, B, N, R, prefill, ctx->mask, ctx->seq, kv->k[l], kv->v[l], max_len, next.p, &S_prev, st));
   }
@@ -587,38 +587,27 @@ int eagle3_draft_expand(eagle3_ctx* ctx, const float* g_new, const int32_t* tok_
   void* kc = dkv->k[0];
   void* vc = dkv->v[0];
 
+  const DraftInputArgs in = ctx->draft_input_args();
+  CK(launch_draft_first(ctx->bf16, in, tok_new, g_new, dkv->kv_indptr, dkv->prefix_len, n_new, depth, ctx->slot, ctx->mask, ctx->seq, st));
   for (int level = 1; level <= depth; ++level) {
     const int M = level == 1 ? n_new : K;
     const int a_row0 = level == 1 ? 0 : n_new + (level - 2) * K;
-    const int32_t *pos, *slot;
-    const uint32_t* mask;
-    const SeqInfo* seq;
-    int max_len;
-    if (level == 1) {
-      CK(launch_draft_prep1(dkv->kv_indptr, dkv->prefix_len, n_new, ctx->pos1, ctx->slot, ctx->mask, ctx->seq, st));
-      pos = ctx->pos1; slot = ctx->slot; mask = ctx->mask; seq = ctx->seq;
-      max_len = dkv->max_prefix_len + n_new;
-      CK(launch_draft_input(ctx->bf16, ctx->tw.embed, c.vocab, tok_new, g_new, nullptr, M, k, ctx->dw.norm_embed,
-                            ctx->dw.norm_feat, c.rms_eps, ctx->act_k, ctx->x, pos, d, c.rope_theta, ctx->cs, st));
-    } else {
-      pos = ds.row_pos; slot = ds.row_slot; mask = ds.row_mask; seq = ds.seq;
-      max_len = dkv->max_prefix_len + n_new + (level - 1) * K;
-      CK(launch_draft_input(ctx->bf16, ctx->tw.embed, c.vocab, ds.row_tok, ctx->a_buf, ds.row_src, M, k,
-                            ctx->dw.norm_embed, ctx->dw.norm_feat, c.rms_eps, ctx->act_k, ctx->x, pos, d, c.rope_theta, ctx->cs,
-                            st));
-    }
-    TRY(project_qkv(ctx, w, ctx->act_k, nullptr, 2 * k, M, slot, ctx->cs, kc, vc, st));
+    const bool first = level == 1;
+    const int max_len = dkv->max_prefix_len + n_new + (level - 1) * K;
+    TRY(project_qkv(ctx, w, ctx->act_k, nullptr, 2 * k, M, first ? ctx->slot : ds.row_slot,
+                    first ? ctx->cs : ctx->cs + (size_t)(n_new + level - 2) * d, first ? d : 0, kc, vc, st));
     // a = y1 + MLP(...): keep it for the children, and norm it for the LM head
     float* copies[4] = {ctx->a_buf + (size_t)a_row0 * k, nullptr, nullptr, nullptr};
     int S_down = 1;
-    TRY(layer_tail(ctx, w, 1, M, M, false, mask, seq, kc, vc, max_len, copies, &S_down, st));
+    TRY(layer_tail(ctx, w, 1, M, M, false, first ? ctx->mask : ds.row_mask[level & 1], first ? ctx->seq : ds.seq, kc, vc, max_len, copies, &S_down, st));
     TRY(norm_head(ctx, ctx->x, S_down, M, ctx->dw.final_norm, copies, ctx->dw.lm_head, Vd, ctx->z, st));
-    const int row0 = level == 1 ? n_new - 1 : 0, n_rows = level == 1 ? 1 : K;
-    CK(launch_topk_rows(ctx->z, Vd, row0, n_rows, Vd, K, ctx->topk_scratch, ds.top_val, ds.top_idx, st));
-    CK(launch_draft_select(ds, ctx->dw.d2t, dkv->kv_indptr, dkv->prefix_len, level, depth, K, n_new, 0, st));
+    const DraftLogits zl = {ctx->z, first ? n_new - 1 : 0, Vd, ctx->topk_scratch};
+    if (level < depth)
+      CK(launch_draft_level(ctx->bf16, ds, zl, ctx->dw.d2t, dkv->kv_indptr, dkv->prefix_len, level, K, n_new, in, ctx->a_buf, st));
+    else
+      CK(launch_draft_finish(ds, zl, ctx->dw.d2t, tok_new, n_new, depth, K, n_nodes, tree_tok, parent, node_depth, cum_logprob,
+                             dbg ? dbg->chosen : nullptr, st));
   }
-  CK(launch_draft_rerank(ds, ctx->dw.d2t, tok_new, n_new, depth, K, n_nodes, tree_tok, parent, node_depth, cum_logprob,
-                         dbg ? dbg->chosen : nullptr, st));
   if (dbg) {
     const size_t pb = (size_t)pool * 4;
     if (dbg->pool_tok) CK(hipMemcpyAsync(dbg->pool_tok, ds.pool_tok, pb, hipMemcpyDeviceToDevice, st));
@@ -658,23 +647,17 @@ int eagle3_draft_chain(eagle3_ctx* ctx, int32_t B, const float* g_new, const int
   const ChainState& cs = ctx->cs_chain;
   void* kc = dkv->k[0];
   void* vc = dkv->v[0];
+  const DraftInputArgs in = ctx->draft_input_args();
+  CK(launch_chain_prep1(dkv->kv_indptr, dkv->prefix_len, B, rows1, ctx->pos1, ctx->slot, ctx->mask, ctx->seq, st));
+  CK(launch_draft_input(ctx->bf16, in, tok_new, g_new, ctx->pos1, B * rows1, st));
   for (int level = 1; level <= length; ++level) {
     const int rps = level == 1 ? rows1 : 1, M = B * rps;
-    const int32_t *pos, *slot;
-    const uint32_t* mask;
-    const SeqInfo* seq;
-    if (level == 1) {
-      CK(launch_chain_prep1(dkv->kv_indptr, dkv->prefix_len, B, rows1, ctx->pos1, ctx->slot, ctx->mask, ctx->seq, st));
-      pos = ctx->pos1; slot = ctx->slot; mask = ctx->mask; seq = ctx->seq;
-      CK(launch_draft_input(ctx->bf16, ctx->tw.embed, c.vocab, tok_new, g_new, nullptr, M, k, ctx->dw.norm_embed,
-                            ctx->dw.norm_feat, c.rms_eps, ctx->act_k, ctx->x, pos, d, c.rope_theta, ctx->cs, st));
-    } else {
-      pos = cs.row_pos; slot = cs.row_slot; mask = cs.row_mask; seq = cs.seq;
-      CK(launch_draft_input(ctx->bf16, ctx->tw.embed, c.vocab, cs.row_tok, ctx->a_buf, cs.row_src, M, k, ctx->dw.norm_embed,
-                            ctx->dw.norm_feat, c.rms_eps, ctx->act_k, ctx->x, pos, d, c.rope_theta, ctx->cs, st));
-    }
+    const bool first = level == 1;
+    const int32_t* slot = first ? ctx->slot : cs.row_slot;
+    const uint32_t* mask = first ? ctx->mask : cs.row_mask;
+    const SeqInfo* seq = first ? ctx->seq : cs.seq;
     const int max_len = dkv->max_prefix_len + rows1 + level;
-    TRY(project_qkv(ctx, w, ctx->act_k, nullptr, 2 * k, M, slot, ctx->cs, kc, vc, st));
+    TRY(project_qkv(ctx, w, ctx->act_k, nullptr, 2 * k, M, slot, ctx->cs, d, kc, vc, st));
     const bool gather = level == 1 && rows1 > 1;
     float* copies[4] = {gather ? nullptr : ctx->a_buf, nullptr, nullptr, nullptr};
     int S_down = 1;
@@ -687,9 +670,8 @@ int eagle3_draft_chain(eagle3_ctx* ctx, int32_t B, const float* g_new, const int
       S_down = 0;
     }
     TRY(norm_head(ctx, ctx->x, S_down, B, ctx->dw.final_norm, copies, ctx->dw.lm_head, Vd, ctx->z, st));
-    CK(launch_topk_rows(ctx->z, Vd, 0, B, Vd, 1, ctx->topk_scratch, cs.top_val, cs.top_idx, st));
-    CK(launch_chain_select(cs, ctx->dw.d2t, dkv->kv_indptr, dkv->prefix_len, n_new, tok_new, B, rows1, level, length,
-                           chain_tok, chain_logp, st));
+    CK(launch_chain_level(ctx->bf16, cs, {ctx->z, 0, Vd, ctx->topk_scratch}, ctx->dw.d2t, dkv->kv_indptr, dkv->prefix_len, n_new, tok_new, B,
+                          rows1, level, length, chain_tok, chain_logp, in, ctx->a_buf, st));
   }
   return EAGLE3_OK;
 }
@@ -726,7 +708,7 @@ int eagle3_prefill(eagle3_ctx* ctx, const int32_t* tokens, int32_t T, const eagl
     if (tail_row) {
       TRY(run_layers(ctx, blocks, blocks == 1 ? n : 64, n, true, kv, max_len, 0, L - 1, nullptr, nullptr, ctx->chunk_taps, nullptr, st, true));
       const eagle3_layer_weights& wl = ctx->layers[L - 1];
-      TRY(project_qkv(ctx, wl, ctx->bf16 ? ctx->act_k : ctx->x, wl.norm_attn, k, n, ctx->slot, ctx->cs, kv->k[L - 1], kv->v[L - 1], st));
+      TRY(project_qkv(ctx, wl, ctx->bf16 ? ctx->act_k : ctx->x, wl.norm_attn, k, n, ctx->slot, ctx->cs, d, kv->k[L - 1], kv->v[L - 1], st));
       if (last) TRY(layer_tail(ctx, wl, 1, 1, n, true, ctx->mask, ctx->seq, kv->k[L - 1], kv->v[L - 1], max_len, nullptr, &S_tail, st, true));
     } else {
       TRY(run_layers(ctx, blocks, blocks == 1 ? n : 64, n, true, kv, max_len, 0, L, nullptr, nullptr, ctx->chunk_taps, nullptr, st));
@@ -741,9 +723,8 @@ int eagle3_prefill(eagle3_ctx* ctx, const int32_t* tokens, int32_t T, const eagl
     const int m = last ? n - 1 : n;
     if (m > 0) {
       CK(launch_prefill_prep(dkv->kv_indptr, dkv->prefix_len, m, d, c.rope_theta, ctx->pos1, ctx->slot, ctx->mask, nullptr, ctx->seq, st));
-      CK(launch_draft_input(ctx->bf16, ctx->tw.embed, c.vocab, tokens + c0 + 1, ctx->chunk_g, nullptr, m, k, ctx->dw.norm_embed,
-                            ctx->dw.norm_feat, c.rms_eps, ctx->act_k, ctx->x, ctx->pos1, d, c.rope_theta, ctx->cs, st));
-      TRY(project_qkv(ctx, w, ctx->act_k, nullptr, 2 * k, m, ctx->slot, ctx->cs, dkv->k[0], dkv->v[0], st));
+      CK(launch_draft_input(ctx->bf16, ctx->draft_input_args(), tokens + c0 + 1, ctx->chunk_g, ctx->pos1, m, st));
+      TRY(project_qkv(ctx, w, ctx->act_k, nullptr, 2 * k, m, ctx->slot, ctx->cs, d, dkv->k[0], dkv->v[0], st));
       CK(launch_advance_lengths((int32_t*)dkv->prefix_len, 1, m, st));
     }
   }

@@ -4,6 +4,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "draft_row.hpp"
 #include "kernels.hpp"
 
 namespace {
@@ -20,14 +21,6 @@ __global__ __launch_bounds__(256) void embed_rows_kernel(const TW* __restrict__ 
 }
 
 struct CopyOut { float* p[4]; };
-
-// Row of workgroup x where a workgroup takes one row (or a part of one) and writes it as an activation.  bf16: a 128-byte line of the
-// fragment-major layout holds pieces of eight rows, and workgroups go to the XCDs in turn; eight consecutive rows go to one XCD, whose L2
-// then puts the line together.  The grid is a multiple of 64 wide (rows_grid); rows past the end do nothing.  Against rows dealt out one by one:
-// verification of 64 trees 11.14 -> 10.93 ms, 2048 tokens 26.8 -> 26.5, an 8B step 6.26 -> 6.19 (with the same in the attention merge).
-template <bool BF16>
-__device__ __forceinline__ int row_of_workgroup(int x) { return BF16 ? (x >> 6) * 64 + (x & 7) * 8 + ((x >> 3) & 7) : x; }
-int rows_grid(int R) { return (R + 63) / 64 * 64; }
 
 // One workgroup per row, four consecutive columns per thread (two such groups when k > 4096): the row stays
 // in registers between the partial-sum reduction and the normalised store.
@@ -82,15 +75,6 @@ __global__ __launch_bounds__(1024) void add_norm_kernel(float* __restrict__ x, c
       Act<BF16>::store4(act, r, 4 * v, k, val[j].x * inv * g[j].x, val[j].y * inv * g[j].y, val[j].z * inv * g[j].z,
                         val[j].w * inv * g[j].w);
   }
-}
-
-// cos/sin of pos * theta^(-2i/d) in fp64, stored fp32: cs[r][i] = cos, cs[r][d/2 + i] = sin
-__device__ __forceinline__ void rope_entry(float* cs, int r, int i, int d, int pos, float theta) {
-  const double inv = pow((double)theta, -2.0 * (double)i / (double)d);
-  double s, c;
-  sincos((double)pos * inv, &s, &c);
-  cs[(size_t)r * d + i] = (float)c;
-  cs[(size_t)r * d + d / 2 + i] = (float)s;
 }
 
 __global__ __launch_bounds__(256) void tree_prep_kernel(const int32_t* __restrict__ parent,
@@ -152,7 +136,7 @@ __global__ __launch_bounds__(256) void tree_prep_kernel(const int32_t* __restric
 
 // One workgroup per row; a thread handles four consecutive rotary pairs (i..i+3, i+d/2..i+d/2+3) of one head.  (fp32: gemm_f32.hip.)
 __global__ __launch_bounds__(1024) void rope_kv_write_kernel(const float* __restrict__ qkv, int S, int R, int H, int Hkv,
-                                                            int d, const float* __restrict__ cs,
+                                                            int d, const float* __restrict__ cs, int cs_step,
                                                             const int32_t* __restrict__ slot, bf16_t* __restrict__ q,
                                                             bf16_t* __restrict__ kc, bf16_t* __restrict__ vc) {
   const int r = blockIdx.x, half = d / 2, NT = (H + 2 * Hkv) * d, q4 = half / 4;
@@ -177,7 +161,7 @@ __global__ __launch_bounds__(1024) void rope_kv_write_kernel(const float* __rest
     }
     bf16_t* dst;
     if (h < H + Hkv) {
-      const float4 c = *(const float4*)(cs + (size_t)r * d + i), sn = *(const float4*)(cs + (size_t)r * d + half + i);
+      const float4 c = *(const float4*)(cs + (size_t)r * cs_step + i), sn = *(const float4*)(cs + (size_t)r * cs_step + half + i);
       const float4 o1 = make_float4(x1.x * c.x - x2.x * sn.x, x1.y * c.y - x2.y * sn.y, x1.z * c.z - x2.z * sn.z,
                                     x1.w * c.w - x2.w * sn.w);
       const float4 o2 = make_float4(x2.x * c.x + x1.x * sn.x, x2.y * c.y + x1.y * sn.y, x2.z * c.z + x1.z * sn.z,
@@ -220,66 +204,44 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
   }
 }
 
-// One workgroup per row, four consecutive columns per thread and pass, the row kept in registers between the
-// sum-of-squares pass and the normalising pass (k <= 4 * 4 * blockDim.x).
-template <bool BF16>
-__global__ __launch_bounds__(1024) void draft_input_kernel(const typename Act<BF16>::type* __restrict__ embed, int vocab,
-                                                          const int32_t* __restrict__ tok, const float* __restrict__ feat,
-                                                          const int32_t* __restrict__ src_row, int M, int k,
-                                                          const typename Act<BF16>::type* __restrict__ g_embed,
-                                                          const typename Act<BF16>::type* __restrict__ g_feat, float eps,
-                                                          typename Act<BF16>::type* __restrict__ act,
-                                                          float* __restrict__ y, const int32_t* __restrict__ pos,
-                                                          int head_dim, float theta, float* __restrict__ cs) {
-  __shared__ float red_e[17], red_f[17];
+template <bool BF16, int VPT>
+__global__ __launch_bounds__(1024) void draft_input_kernel(DraftInput<BF16> p, const int32_t* __restrict__ tok, const float* __restrict__ feat,
+                                                          const int32_t* __restrict__ pos, int M) {
+  __shared__ RowSums sums;
   const int r = row_of_workgroup<BF16>(blockIdx.x);
   if (r >= M) return;
-  const int t = min(max(tok[r], 0), vocab - 1);
-  const float* f = feat + (size_t)(src_row ? src_row[r] : r) * k;
-  float4 e[4], v[4];
-  float se = 0.f, sf = 0.f;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int c = 4 * (threadIdx.x + j * blockDim.x);
-    if (c < k) {
-      e[j] = load4_f32(embed, (size_t)t * k + c);
-      v[j] = *(const float4*)(f + c);
-      *(float4*)(y + (size_t)r * k + c) = v[j];
-      se += e[j].x * e[j].x + e[j].y * e[j].y + e[j].z * e[j].z + e[j].w * e[j].w;
-      sf += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
-    }
-  }
-  se = block_sum(se, red_e);
-  sf = block_sum(sf, red_f);
-  const float ie = 1.0f / sqrtf(se / (float)k + eps), iv = 1.0f / sqrtf(sf / (float)k + eps);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int c = 4 * (threadIdx.x + j * blockDim.x);
-    if (c < k) {
-      const float4 ge = load4_f32(g_embed, c), gf = load4_f32(g_feat, c);
-      Act<BF16>::store4(act, r, c, 2 * k, e[j].x * ie * ge.x, e[j].y * ie * ge.y, e[j].z * ie * ge.z, e[j].w * ie * ge.w);
-      Act<BF16>::store4(act, r, k + c, 2 * k, v[j].x * iv * gf.x, v[j].y * iv * gf.y, v[j].z * iv * gf.z, v[j].w * iv * gf.w);
-    }
-  }
+  DraftGains<BF16, VPT> gains;
+  load_gains(p, gains);
+  draft_input_row(p, r, tok[r], feat + (size_t)r * p.k, gains, sums);
   // the row's rotary table, for the q/k rotation that follows the projection
-  for (int i = threadIdx.x; i < head_dim / 2; i += blockDim.x) rope_entry(cs, r, i, head_dim, pos[r], theta);
+  for (int i = threadIdx.x; i < p.head_dim / 2; i += blockDim.x) rope_entry(p.cs, r, i, p.head_dim, pos[r], p.theta);
 }
 
-__global__ __launch_bounds__(64) void draft_prep1_kernel(const int32_t* __restrict__ kv_indptr,
-                                                        const int32_t* __restrict__ prefix_len, int n_new,
-                                                        int32_t* __restrict__ pos, int32_t* __restrict__ slot,
-                                                        uint32_t* __restrict__ mask, SeqInfo* __restrict__ seq) {
-  const int j = threadIdx.x, P = prefix_len[0], base = kv_indptr[0];
-  if (j < n_new) {
-    pos[j] = P + j;
-    slot[j] = base + P + j;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {                        // causal among the new rows: bits 0..j
-      const int lo = 32 * w;
-      mask[j * 4 + w] = j < lo ? 0u : (j - lo >= 31 ? 0xFFFFFFFFu : ((2u << (j - lo)) - 1u));
+// Draft forward 1 of a tree: n_new rows behind the context, causal among themselves; their bookkeeping comes with their input
+// (a launch of its own cost 4.7 us).  Further workgroups form the rotary tables of the later forwards, whose rows share one position each.
+template <bool BF16, int VPT>
+__global__ __launch_bounds__(1024) void draft_first_kernel(DraftInput<BF16> p, const int32_t* __restrict__ tok, const float* __restrict__ feat,
+                                                          const int32_t* __restrict__ kv_indptr, const int32_t* __restrict__ prefix_len,
+                                                          int n_new, int depth, int32_t* __restrict__ slot, uint32_t* __restrict__ mask,
+                                                          SeqInfo* __restrict__ seq) {
+  __shared__ RowSums sums;
+  const int r = row_of_workgroup<BF16>(blockIdx.x), tid = threadIdx.x;
+  if (r >= n_new + depth - 1) return;
+  const int P = prefix_len[0], base = kv_indptr[0];
+  if (r < n_new) {
+    if (tid < 4) {
+      const int lo = 32 * tid;
+      mask[r * 4 + tid] = r < lo ? 0u : (r - lo >= 31 ? 0xFFFFFFFFu : ((2u << (r - lo)) - 1u));     // bits 0..r
     }
+    if (tid == 0) {
+      slot[r] = base + P + r;
+      if (r == 0) { seq[0].kv_base = base; seq[0].n_prefix = P; seq[0].n_tail = n_new; seq[0].order = 0; }
+    }
+    DraftGains<BF16, VPT> gains;
+    load_gains(p, gains);
+    draft_input_row(p, r, tok[r], feat + (size_t)r * p.k, gains, sums);
   }
-  if (j == 0) { seq[0].kv_base = base; seq[0].n_prefix = P; seq[0].n_tail = n_new; seq[0].order = 0; }
+  for (int i = tid; i < p.head_dim / 2; i += blockDim.x) rope_entry(p.cs, r, i, p.head_dim, P + r, p.theta);
 }
 
 // Rows of a prefill chunk, four per workgroup: row r continues the sequence at position P + r.  For attention the chunk is
@@ -375,11 +337,11 @@ hipError_t launch_tree_prep(const int32_t* parent, const int32_t* kv_indptr, con
   return hipGetLastError();
 }
 
-hipError_t launch_rope_kv_write(const float* qkv_partial, int S, int R, int H, int Hkv, int d, const float* cs, const int32_t* slot,
-                                void* q, void* kcache, void* vcache, hipStream_t st) {
+hipError_t launch_rope_kv_write(const float* qkv_partial, int S, int R, int H, int Hkv, int d, const float* cs, int cs_step,
+                                const int32_t* slot, void* q, void* kcache, void* vcache, hipStream_t st) {
   if (d % 8) return hipErrorInvalidValue;
   const int bd = std::min(1024, ((H + 2 * Hkv) * d / 8 + 63) / 64 * 64);
-  hipLaunchKernelGGL(rope_kv_write_kernel, dim3(R), dim3(bd), 0, st, qkv_partial, S, R, H, Hkv, d, cs, slot, (bf16_t*)q,
+  hipLaunchKernelGGL(rope_kv_write_kernel, dim3(R), dim3(bd), 0, st, qkv_partial, S, R, H, Hkv, d, cs, cs_step, slot, (bf16_t*)q,
                      (bf16_t*)kcache, (bf16_t*)vcache);
   return hipGetLastError();
 }
@@ -405,23 +367,27 @@ hipError_t launch_reduce_partials(const float* partial, int S, int M, int N, flo
   return hipGetLastError();
 }
 
-hipError_t launch_draft_input(bool bf16, const void* embed, int vocab, const int32_t* tok, const float* feat,
-                              const int32_t* src_row, int M, int k, const void* g_embed, const void* g_feat, float eps,
-                              void* act, float* y, const int32_t* pos, int head_dim, float theta, float* cs, hipStream_t st) {
-  if (k % 4 || k > 16384) return hipErrorInvalidValue;
-  const int threads = std::min(1024, ((k / 4 + 63) / 64) * 64);
-  if (bf16)
-    hipLaunchKernelGGL(draft_input_kernel<true>, dim3(rows_grid(M)), dim3(threads), 0, st, (const bf16_t*)embed, vocab, tok, feat,
-                       src_row, M, k, (const bf16_t*)g_embed, (const bf16_t*)g_feat, eps, (bf16_t*)act, y, pos, head_dim, theta, cs);
-  else
-    hipLaunchKernelGGL(draft_input_kernel<false>, dim3(M), dim3(threads), 0, st, (const float*)embed, vocab, tok, feat,
-                       src_row, M, k, (const float*)g_embed, (const float*)g_feat, eps, (float*)act, y, pos, head_dim, theta, cs);
-  return hipGetLastError();
+namespace {
+int draft_input_threads(int k) { return std::min(1024, ((k / 4 + 63) / 64) * 64); }
+}  // namespace
+
+hipError_t launch_draft_input(bool bf16, const DraftInputArgs& a, const int32_t* tok, const float* feat, const int32_t* pos, int M,
+                              hipStream_t st) {
+  if (!draft_input_ok(a)) return hipErrorInvalidValue;
+  const int threads = draft_input_threads(a.k);
+  return with_input(bf16, a.k, threads, [&](auto type, auto passes) {
+    hipLaunchKernelGGL((draft_input_kernel<type.value, passes.value>), dim3(bf16 ? rows_grid(M) : M), dim3(threads), 0, st,
+                       draft_input<type.value>(a), tok, feat, pos, M);
+  });
 }
 
-hipError_t launch_draft_prep1(const int32_t* kv_indptr, const int32_t* prefix_len, int n_new, int32_t* pos, int32_t* slot,
-                              uint32_t* mask, SeqInfo* seq, hipStream_t st) {
-  if (n_new > 64) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(draft_prep1_kernel, dim3(1), dim3(64), 0, st, kv_indptr, prefix_len, n_new, pos, slot, mask, seq);
-  return hipGetLastError();
+hipError_t launch_draft_first(bool bf16, const DraftInputArgs& a, const int32_t* tok, const float* feat, const int32_t* kv_indptr,
+                              const int32_t* prefix_len, int n_new, int depth, int32_t* slot, uint32_t* mask, SeqInfo* seq,
+                              hipStream_t st) {
+  if (!draft_input_ok(a) || n_new < 1 || n_new > 64 || depth < 1) return hipErrorInvalidValue;
+  const int threads = draft_input_threads(a.k), rows = n_new + depth - 1;
+  return with_input(bf16, a.k, threads, [&](auto type, auto passes) {
+    hipLaunchKernelGGL((draft_first_kernel<type.value, passes.value>), dim3(bf16 ? rows_grid(rows) : rows), dim3(threads), 0, st,
+                       draft_input<type.value>(a), tok, feat, kv_indptr, prefix_len, n_new, depth, slot, mask, seq);
+  });
 }

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Params p) {
   for (int i = 0; i < 2; ++i) {
     if constexpr (EPI == RESIDUAL) before[i] = p.out[(size_t)mc[i] * p.N + n];
     if constexpr (EPI == ROPE) {
-      if (head < f.H + f.Hkv) { cosine[i] = f.cs[(size_t)mc[i] * f.d + pair]; sine[i] = f.cs[(size_t)mc[i] * f.d + half + pair]; }
+      if (head < f.H + f.Hkv) { cosine[i] = f.cs[(size_t)mc[i] * f.cs_step + pair]; sine[i] = f.cs[(size_t)mc[i] * f.cs_step + half + pair]; }
       slot[i] = f.slot[mc[i]];
     }
   }

@@ -43,7 +43,8 @@ struct F32Fuse {
   const float* gain = nullptr;          // x is the RMSNorm of the rows given, with this gain
   float eps = 0.f;
   float* copies[4] = {nullptr, nullptr, nullptr, nullptr};
-  const float* cs = nullptr;            // rotary table [M, d]
+  const float* cs = nullptr;            // rotary tables, cs_step from one row's to the next one's
+  int cs_step = 0;
   const int32_t* slot = nullptr;
   float* kc = nullptr;
   float* vc = nullptr;
@@ -69,20 +70,32 @@ hipError_t launch_add_norm(bool bf16, float* x, const float* partial, int S, int
 hipError_t launch_tree_prep(const int32_t* parent, const int32_t* kv_indptr, const int32_t* prefix_len, int B, int N,
                             int head_dim, float theta, int32_t* depth, uint32_t* mask, int32_t* slot, float* cs,
                             SeqInfo* seq, hipStream_t st);
-// bf16: sums the q|k|v split-K partials, rotates q and k, writes q [R,H,d] and the cache rows.
-hipError_t launch_rope_kv_write(const float* qkv_partial, int S, int R, int H, int Hkv, int d, const float* cs, const int32_t* slot,
-                                void* q, void* kcache, void* vcache, hipStream_t st);
+// bf16: sums the q|k|v split-K partials, rotates q and k, writes q [R,H,d] and the cache rows.  cs_step: from a row's rotary table to the
+// next one's (0: all rows at one position).
+hipError_t launch_rope_kv_write(const float* qkv_partial, int S, int R, int H, int Hkv, int d, const float* cs, int cs_step,
+                                const int32_t* slot, void* q, void* kcache, void* vcache, hipStream_t st);
 hipError_t launch_pack3(bool bf16, const float* a, const float* b, const float* c, int M, int k, void* act, hipStream_t st);
 hipError_t launch_reduce_partials(const float* partial, int S, int M, int N, float* out, hipStream_t st);
-// Draft layer input: act[r] = [RMSNorm(E[tok[r]]; g_embed) ; RMSNorm(f_r; g_feat)], y[r] = f_r,
-// with f_r = feat[src_row ? src_row[r] : r]; also the rotary table cs[r] of position pos[r] (positions already on
-// the device).
-hipError_t launch_draft_input(bool bf16, const void* embed, int vocab, const int32_t* tok, const float* feat,
-                              const int32_t* src_row, int M, int k, const void* g_embed, const void* g_feat, float eps,
-                              void* act, float* y, const int32_t* pos, int head_dim, float theta, float* cs, hipStream_t st);
-// Rows of draft forward 1: positions, slots, causal masks, sequence info.
-hipError_t launch_draft_prep1(const int32_t* kv_indptr, const int32_t* prefix_len, int n_new, int32_t* pos, int32_t* slot,
-                              uint32_t* mask, SeqInfo* seq, hipStream_t st);
+// Draft layer input: act[r] = [RMSNorm(E[tok[r]]; g_embed) ; RMSNorm(f_r; g_feat)], y[r] = f_r, and the rotary table cs[r] of the
+// row's position.
+struct DraftInputArgs {
+  const void* embed;
+  const void* g_embed;
+  const void* g_feat;
+  void* act;
+  float* y;
+  float* cs;
+  int vocab, k, head_dim;
+  float eps, theta;
+};
+// f_r = feat[r], positions already on the device
+hipError_t launch_draft_input(bool bf16, const DraftInputArgs& a, const int32_t* tok, const float* feat, const int32_t* pos, int M,
+                              hipStream_t st);
+// The same for draft forward 1 of a tree (the n_new positions behind the context), with slots, causal masks, sequence info, and the
+// rotary tables of the later forwards: cs[n_new + l - 2] is that of forward l.
+hipError_t launch_draft_first(bool bf16, const DraftInputArgs& a, const int32_t* tok, const float* feat, const int32_t* kv_indptr,
+                              const int32_t* prefix_len, int n_new, int depth, int32_t* slot, uint32_t* mask, SeqInfo* seq,
+                              hipStream_t st);
 
 // Rows of a prefill chunk of n positions: positions, slots, causal masks inside blocks of 64 rows, one SeqInfo per block,
 // rotary tables (cs may be null).
@@ -108,47 +121,49 @@ struct DraftState {          // device arrays owned by the workspace
   int32_t* pool_parent;      // [pool]
   int32_t* pool_depth;       // [pool]
   float* pool_score;         // [pool]
-  uint32_t* pool_mask;       // [pool][4] tail-slot mask of a candidate once it is put on a frontier
   int32_t* frontier;         // [D][K] pool ids expanded by forward l+1 (row 0 = level-1 candidates)
   float* top_val;            // [max_rows][K] log-probabilities of the per-row top-K
   int32_t* top_idx;          // [max_rows][K]
-  // inputs of the next forward
-  int32_t* row_tok;          // [K] target ids
-  int32_t* row_src;          // [K] row of the feature buffer holding the parent's output
-  int32_t* row_pos;          // [K]
+  // rows of the next forward; those of forward l at l & 1, as a launch reads one set while it writes the other
   int32_t* row_slot;         // [K]
-  uint32_t* row_mask;        // [K][4]
+  uint32_t* row_mask[2];     // [K][4]
+  float* row_score[2];       // [K] cumulative log-probability
   SeqInfo* seq;              // [1]
 };
-// Per-row log-softmax normaliser and top-K (value desc, id asc) over z[row, 0..V).
 // scratch: topk_scratch_floats(n_rows, V, K) floats.
 size_t topk_scratch_floats(int n_rows, int V, int K);
-hipError_t launch_topk_rows(const float* z, int ld, int row0, int n_rows, int V, int K, float* scratch, float* top_val,
-                            int32_t* top_idx, hipStream_t st);
-// Level bookkeeping after forward `level` (1-based): writes the new pool entries and, when level < depth,
-// picks the next frontier and the next forward's row inputs.
-hipError_t launch_draft_select(const DraftState& s, const int32_t* d2t, const int32_t* kv_indptr, const int32_t* prefix_len,
-                               int level, int depth, int K, int n_new, int feat_row0, hipStream_t st);
-hipError_t launch_draft_rerank(const DraftState& s, const int32_t* d2t, const int32_t* tok_new, int n_new, int depth, int K,
-                               int n_nodes, int32_t* tree_tok, int32_t* parent, int32_t* node_depth, float* cum_logprob,
+// What a draft forward left: logits z[rows, V] and where their top K go through.
+struct DraftLogits {
+  const float* z;
+  int row0, V;
+  float* scratch;
+};
+// After forward `level` < depth (1-based): per-row log-softmax and top-K (value desc, id asc), the new pool entries, the next frontier,
+// and the next forward's rows: bookkeeping and input (f_r = feat[row of the parent's output]), but for the rotary table.
+hipError_t launch_draft_level(bool bf16, const DraftState& s, const DraftLogits& zl, const int32_t* d2t, const int32_t* kv_indptr,
+                              const int32_t* prefix_len, int level, int K, int n_new, const DraftInputArgs& in, const float* feat,
+                              hipStream_t st);
+// After the last forward: its pool entries, then the global rerank and the tree.
+hipError_t launch_draft_finish(const DraftState& s, const DraftLogits& zl, const int32_t* d2t, const int32_t* tok_new, int n_new, int depth,
+                               int K, int n_nodes, int32_t* tree_tok, int32_t* parent, int32_t* node_depth, float* cum_logprob,
                                int32_t* chosen_dbg, hipStream_t st);
 
 // Batched chain drafting: per-sequence state of the next forward (one row per sequence), device arrays.
 struct ChainState {
   float* top_val;            // [B] log-probability of the top-1 token of every sequence's last row
   int32_t* top_idx;          // [B] its draft id
-  int32_t* row_tok;          // [B] target ids
-  int32_t* row_src;          // [B]
-  int32_t* row_pos;          // [B]
   int32_t* row_slot;         // [B]
   uint32_t* row_mask;        // [B][4]
   SeqInfo* seq;              // [B]
 };
 hipError_t launch_chain_prep1(const int32_t* kv_indptr, const int32_t* prefix_len, int B, int rows1, int32_t* pos,
                               int32_t* slot, uint32_t* mask, SeqInfo* seq, hipStream_t st);
-hipError_t launch_chain_select(const ChainState& s, const int32_t* d2t, const int32_t* kv_indptr, const int32_t* prefix_len,
-                               const int32_t* n_new, const int32_t* tok_new, int B, int rows1, int level, int length,
-                               int32_t* chain_tok, float* chain_logp, hipStream_t st);
+// After forward `level` (1-based) of a chain batch: the top-1 token of every sequence's last row extends its chain; when level < length, the
+// next forward's rows (one per sequence, f_r = feat[sequence]) are written.
+hipError_t launch_chain_level(bool bf16, const ChainState& s, const DraftLogits& zl, const int32_t* d2t, const int32_t* kv_indptr,
+                              const int32_t* prefix_len, const int32_t* n_new, const int32_t* tok_new, int B, int rows1, int level,
+                              int length, int32_t* chain_tok, float* chain_logp, const DraftInputArgs& in, const float* feat,
+                              hipStream_t st);
 hipError_t launch_chain_gather(const float* x, const int32_t* n_new, int B, int rows1, int k, float* x_out, hipStream_t st);
 
 // ---------------------------------------------------------------- acceptance (accept.hip)

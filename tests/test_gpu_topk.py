@@ -69,3 +69,27 @@ def test_draft_expand_with_undefined_logits(Vd, n_good, K, nan_bits):
     tok = tok.cpu().numpy()[:, 1:]
     d2t = W["draft"]["d2t"].cpu().numpy()
     assert np.isin(tok, d2t[good] if n_good else d2t[:1]).all()
+
+
+# Pools around the register sizes of the rerank (256, 768) and of more entries than its threads (1024); one forward only; K whose rows take
+# every wavefront (16) or leave none free for the candidates (15); rows of one and of two passes.
+@pytest.mark.parametrize("D,K,N,hidden", [(1, 1, 2, 256), (1, 4, 5, 256), (1, 16, 12, 256), (4, 9, 60, 256), (2, 15, 64, 256), (4, 16, 64, 256),
+                                          (5, 16, 64, 256), (8, 10, 60, 256), (8, 12, 64, 256), (8, 16, 33, 256), (3, 3, 9, 4352), (2, 16, 40, 8192)])
+def test_draft_expand_over_pool_sizes_and_widths(D, K, N, hidden):
+    import paper_2503_01840_amd as E
+    shape = S.get_shape("c1").with_(name=f"p{hidden}", hidden=hidden)
+    model = PL.OracleModel(shape)
+    ctx = E.Eagle3Context(shape, max_batch=1, max_nodes=64, max_depth=8, max_topk=16, max_new=4, device=DEV)
+    W = PL.device_weights(shape, device=DEV)
+    ctx.set_weights(W["target"], W["draft"])
+    inp = PL.synthetic_step_inputs(shape, n_new=3, prefix=42)
+    ks, vs, indptr, plen, P = PL.device_kv([inp["draft_kv"]], 3 + (D - 1) * K, DEV)
+    got = E.eagle3_draft_expand(ctx, inp["g_new"].to(DEV), inp["tok_new"].to(DEV), E.KVCache(ks, vs, indptr, plen, P), D, K, N, debug=True)
+    torch.cuda.synchronize()
+    got = {k: v.cpu().numpy() for k, v in got.items()}
+    ref = PL.oracle_draft(shape, model, inp, D, K, N,
+                          follow={"pool_tok": got["pool_tok"], "frontier": got["frontier"], "chosen": got["chosen"]})
+    for key in ("tree_tok", "parent", "depth", "chosen"):
+        assert np.array_equal(got[key], ref[key]), key
+    # fp32 logits and their log-sum-exp, 1e-4 for up to three levels as above, each further level adding as much as one of those
+    assert np.max(np.abs(got["score"] - ref["score"])) < 1e-4 * max(1.0, D / 3)
