@@ -3,7 +3,7 @@
 // Y[M, N] = X[M, K] * W[N, K]^T, fp32 accumulate.  At this width the projections sit at the ridge between weight
 // streaming and the MFMA rate, so the kernel is organised around operand reuse and around keeping the loads, the
 // LDS reads and the MFMAs of a wavefront all in flight at once:
-//   * a workgroup owns a (32 FM WGM) x (32 FN WGN) output tile; its WGM x WGN wavefronts each hold 2 FM x 2 FN
+//   * a workgroup owns a (32 FM WGM) x (16 FB WGN) output tile; its WGM x WGN wavefronts each hold 2 FM x FB
 //     accumulators of v_mfma_f32_16x16x32_bf16 and there is no cross-wavefront reduction.  With many rows the chip is bound by
 //     power: products alone sustain 1.88 PFLOP/s as 32x32x16 and 2.14 as 16x16x32 (the sum over 32 k stays inside the matrix
 //     unit), with their operands read from LDS 1.64 and 1.86.  With one set of sums they come out bit for bit the same;
@@ -27,6 +27,8 @@
 // 8B width, us, products as 32x32x16 with the reads and loads in bursts / now: 2048 rows gate/up 422 / 368 (1.31 PFLOP/s), down
 // 214 / 177, o 77 / 57, q/k/v 100 / 87; 512 rows gate/up 116 / 101, down 73 / 60, q/k/v 39 / 35; 256 rows gate/up 75 / 72 (68
 // with 128-k weight stages and staggered walks), 77 rows 61 / 58 (53).
+// Tiles of 256 x 224 and 256 x 192 (4 x 2 wavefronts of 64 x 112 and 64 x 96) are there for whole rounds of the chip, wide_tiles.hpp says where: 2048
+// rows gate/up 371 -> 357 us, q/k/v 92 -> 81; 64 trees of 8 nodes 11.29 -> 11.06 ms, a prompt of 2048 tokens 27.28 -> 26.48.
 // Measured and not kept: 4 wavefronts of 128 x 128 each (a third fewer LDS reads: loop 4 % shorter, epilogue longer by the same).
 //
 // SETS: sub-stages add to so many sets of accumulators in turn, so that the sums of a long range of K are as far from 64 bits as with as many
@@ -63,14 +65,14 @@ struct WideParams {
   bf16_t* out_xf;
 };
 
-// Global weight row behind row `row` of workgroup tile `tile` (TN rows per tile).  SwiGLU: every 64 rows of a tile are 32 gate
-// rows and the 32 up rows that belong to them.  Rows past the end repeat the last one.
-template <int TN>
+// Global weight row behind row `row` of workgroup tile `tile` (TN rows per tile).  SwiGLU: every 2 PAIR rows of a tile are PAIR gate
+// rows and the PAIR up rows that belong to them.  Rows past the end repeat the last one.
+template <int TN, int PAIR>
 __device__ __forceinline__ const bf16_t* weight_row(const WideParams& p, int tile, int row, int& left) {
   if (p.mode == 1) {
-    const int r = tile * (TN / 2) + (row >> 6) * 32 + (row & 31), last = p.rows[0] - 1;
+    const int r = tile * (TN / 2) + row / (2 * PAIR) * PAIR + row % PAIR, last = p.rows[0] - 1;
     left = max(last - r, 0);
-    return ((row & 32) ? p.w[1] : p.w[0]) + (size_t)min(r, last) * p.K;
+    return ((row & PAIR) ? p.w[1] : p.w[0]) + (size_t)min(r, last) * p.K;
   }
   int n = min(tile * TN + row, p.N - 1);
   left = p.N - 1 - n;
@@ -105,10 +107,13 @@ __device__ __forceinline__ void unroll(F f) { unroll_seq(std::make_integer_seque
 #define WIDE_WAIT_BARRIER(n) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(n) : "memory")
 #define WIDE_PIN() __builtin_amdgcn_sched_barrier(0)
 
-template <int WGM, int WGN, int FM, int FN, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER, int SETS>
+template <int WGM, int WGN, int FM, int FB, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER, int SETS>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WideParams p) {
-  constexpr int TM = 32 * FM * WGM, TN = 32 * FN * WGN, NW = WGM * WGN;
-  constexpr int FA = 2 * FM, FB = 2 * FN;              // 16-row fragments of a wavefront's activation and weight rows
+  constexpr int FA = 2 * FM;                           // 16-row fragments of a wavefront's activation rows; FB: of its weight rows
+  constexpr int TM = 32 * FM * WGM, TN = 16 * FB * WGN, NW = WGM * WGN;
+  // SwiGLU: gate and up rows in turns of 32, so that both of a pair are accumulators of one lane in two fragments; or, where a wavefront's
+  // fragments don't come in fours, in turns of 8, both in one fragment
+  constexpr int PAIR = FB % 4 == 0 ? 32 : 8;
   constexpr int SUB = BK / 32;                         // sub-stages of a weight stage
   constexpr int A_SLOT = TM * 64, B_SLOT = TN * BK * 2;              // bytes
   constexpr int B_BASE = A_SLOTS * A_SLOT;
@@ -116,10 +121,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   // direct-to-LDS instructions (1 KiB each) per wavefront per activation / weight slot; a weight slot goes out in SUB parts
   // (192 rows over 8 wavefronts: 12 activation pieces; the last four wavefront-instructions repeat pieces, so that every
   // wavefront has the same number of loads in flight)
-  constexpr int A_PIECES = A_SLOT / 1024, A_DMA = (A_PIECES + NW - 1) / NW, B_DMA = B_SLOT / (1024 * NW), BP = B_DMA / SUB;
+  constexpr int A_PIECES = A_SLOT / 1024, A_DMA = (A_PIECES + NW - 1) / NW;
+  // (224 rows: 28 weight pieces, four for each of the first B_FULL = 4 wavefronts and three for the others; the waits below count the fewer)
+  constexpr int B_PIECES = B_SLOT / 1024, B_DMA = (B_PIECES + NW - 1) / NW, B_FULL = B_PIECES - NW * (B_DMA - 1), BP = (B_DMA + SUB - 1) / SUB;
   constexpr int B_LANES = BK / 8, B_ROWS = 64 / B_LANES;           // lanes to a row of a weight piece, rows of a piece
-  static_assert((BK == 64 || BK == 128) && B_DMA % SUB == 0 && B_SLOT == B_DMA * 1024 * NW, "1 KiB pieces per wavefront");
-  static_assert(TM % 64 == 0 && (WGM == 2 || FM == 2) && FN % 2 == 0, "whole 64-row activation tiles");
+  static_assert((BK == 64 || BK == 128) && B_DMA > (SUB - 1) * BP && B_FULL > 0, "1 KiB pieces per wavefront");
+  static_assert(TM % 64 == 0 && (WGM == 2 || FM == 2) && FB % (PAIR == 32 ? 4 : 1) == 0, "whole 64-row activation tiles");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
@@ -139,6 +146,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   // an activation slot is (row tile q / 4, k-step (q / 2) % 2, row half q % 2); piece q of a weight slot is rows
   // B_ROWS q .. B_ROWS (q + 1) - 1.
   constexpr auto swizzle = [](int row) constexpr { return BK == 64 ? (row >> 1) & 7 : row & 15; };   // of the 16-byte pieces of a weight row
+  const int b_first = wave < B_FULL ? wave * B_DMA : wave * (B_DMA - 1) + B_FULL;
   const bf16_t* aptr[A_DMA];
   const bf16_t* bptr[B_DMA];
   uint32_t a_off = lane * 16, b_off[B_DMA];
@@ -151,16 +159,18 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   }
 #pragma unroll
   for (int i = 0; i < B_DMA; ++i) {
-    const int row = B_ROWS * (wave * B_DMA + i), r = lane / B_LANES;
+    const int row = B_ROWS * (b_first + i), r = lane / B_LANES;
     int left;                                          // rows behind this one
-    bptr[i] = weight_row<TN>(p, tile, row, left) + k_begin;
+    bptr[i] = weight_row<TN, PAIR>(p, tile, row, left) + k_begin;
     b_off[i] = (uint32_t)min(r, left) * (uint32_t)p.K * 2 + (((lane % B_LANES) ^ swizzle(row + r)) * 16);
   }
-  const uint32_t a_lds = lds0 + a_first * 1024, b_lds = lds0 + B_BASE + wave * B_DMA * 1024;
+  const uint32_t a_lds = lds0 + a_first * 1024, b_lds = lds0 + B_BASE + b_first * 1024;
   // Each piece of a (sub-)stage, then a step along K.  Past the end of the walk the last one is loaded again, into a
   // slot nobody reads any more, which keeps the number of loads in flight, and with it the waits below, the same in every iteration.
   auto load_a = [&](auto i, uint32_t slot) { dma16<i * 1024>(aptr[i], a_off, a_lds + slot); };
-  auto load_b = [&](auto i, uint32_t slot) { dma16<i * 1024>(bptr[i], b_off[i], b_lds + slot); };
+  auto load_b = [&](auto i, uint32_t slot) {
+    if (i < B_DMA - 1 || B_FULL == NW || wave < B_FULL) dma16<i * 1024>(bptr[i], b_off[i], b_lds + slot);
+  };
   const int rot = STAGGER ? (tile * 5 + split) % KT : 0;
   if (STAGGER) {
     a_off += rot * SUB * 4096u;
@@ -176,9 +186,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   const int c = lane >> 4;
   const int a_base = (c >> 1) * 2048 + (c & 1) * 512 + (lane & 15) * 16 + (WGM == 2 ? wm * 1024 : wm * 4096);
   constexpr auto a_frag = [](int i) constexpr { return WGM == 2 ? (i >> 1) * 4096 + (i & 1) * 256 : (i >> 1) * 1024 + (i & 1) * 256; };
+  // PAIR = 8: a lane's accumulators r = 0, 1 are gate rows and 2, 3 their up rows, so product row 4 a + r is row 2 a + r or 8 + 2 a + r - 2
+  const int b_row = PAIR == 8 && p.mode == 1 ? (lane & 2) * 4 + (lane >> 1 & 6) + (lane & 1) : lane & 15;
   int b_base[SUB];
 #pragma unroll
-  for (int q = 0; q < SUB; ++q) b_base[q] = B_BASE + (wn * 32 * FN + (lane & 15)) * (BK * 2) + (((4 * q + c) ^ swizzle(lane & 15)) * 16);
+  for (int q = 0; q < SUB; ++q) b_base[q] = B_BASE + (wn * 16 * FB + b_row) * (BK * 2) + (((4 * q + c) ^ swizzle(b_row)) * 16);
 
   floatx4 sums[SETS][FA][FB];                          // sub-stage v adds to set v % SETS
   floatx4(&acc)[FA][FB] = sums[0];
@@ -195,8 +207,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
     if constexpr (t >= 0)
       unroll<BP>([&](auto j) {
         constexpr std::integral_constant<int, q * BP + j> i;
-        load_b(i, t * B_SLOT);
-        step_b(i, t + 1);
+        if constexpr (i < B_DMA) {
+          load_b(i, t * B_SLOT);
+          step_b(i, t + 1);
+        }
       });
   });
 #pragma unroll
@@ -207,9 +221,19 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
       for (int f = 0; f < FB; ++f)
 #pragma unroll
         for (int r = 0; r < 4; ++r) sums[j][i][f][r] = 0.f;
-  constexpr int PER = A_DMA + BP;                      // loads per sub-stage
+  constexpr int PER = A_DMA + BP;                      // loads per sub-stage, at most
+  // fewest loads of a wavefront in sub-stage u: weights, and all of sub-stages from .. to - 1
+  constexpr auto part = [](int u) constexpr {
+    const int q = (u % SUB + SUB) % SUB, rest = B_DMA - (B_FULL < NW ? 1 : 0) - q * BP;
+    return rest < BP ? rest : BP;
+  };
+  constexpr auto loads = [part](int from, int to) constexpr {
+    int n = 0;
+    for (int u = from; u < to; ++u) n += A_DMA + part(u);
+    return n;
+  };
   constexpr auto least = [](int x, int y) constexpr { return x < y ? x : y; };
-  WIDE_WAIT_BARRIER(least(BP + (AA - 1) * PER, SUB * (BA - 1) * PER));   // A0 and B0 are in LDS
+  WIDE_WAIT_BARRIER(least(part(-AA) + loads(1 - AA, 0), loads(-SUB * (BA - 1), 0)));   // A0 and B0 are in LDS
   bf16x8 a0[FA], a1[FA], b0[FB], b1[FB];
 #pragma unroll
   for (int i = 0; i < FA; ++i) a0[i] = *(const bf16x8*)(smem + a_base + a_frag(i));
@@ -225,7 +249,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
     const int h = SUB * s + q;
     // everything up to A(h+1) and, in the last sub-stage, B(s+1) has landed when only the loads issued after it are in
     // flight: what the NEXT sub-stage reads is in LDS from here on, and the slots of sub-stage h - 1 are free
-    WIDE_WAIT_BARRIER(q < SUB - 1 ? BP + (AA - 2) * PER : least(BP + (AA - 2) * PER, (SUB * (BA - 1) - 1) * PER));
+    constexpr int behind_a = part(q + 1 - AA) + loads(q + 2 - AA, q), behind_b = loads(q + 1 - SUB * (BA - 1), q);
+    WIDE_WAIT_BARRIER(q < SUB - 1 ? behind_a : least(behind_a, behind_b));
     WIDE_PIN();
     const uint32_t b_next = b_slot == BA * B_SLOT ? 0 : b_slot + B_SLOT, b_fill = b_slot == 0 ? BA * B_SLOT : b_slot - B_SLOT;   // of s + 1, s + BA
     const uint32_t a_fill = (uint32_t)(h + AA) % A_SLOTS * A_SLOT;
@@ -249,8 +274,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
           if constexpr (d == A_DMA - 1) step_a(h + AA + 1);
         } else {
           constexpr std::integral_constant<int, q * BP + d - A_DMA> piece;
-          load_b(piece, b_fill);
-          step_b(piece, s + BA + 1);
+          if constexpr (piece < B_DMA) {
+            load_b(piece, b_fill);
+            step_b(piece, s + BA + 1);
+          }
         }
       }
       WIDE_PIN();
@@ -290,7 +317,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
       if (m >= p.M) continue;
 #pragma unroll
       for (int f = 0; f < FB; ++f) {
-        const int n = tile * TN + wn * 32 * FN + f * 16 + 4 * c;
+        const int n = tile * TN + wn * 16 * FB + f * 16 + 4 * c;
         float* dst = out + (size_t)m * p.N + n;
         if (n + 4 <= p.N) *(row_piece*)dst = acc[i][f];
         else
@@ -305,27 +332,34 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
     for (int i = 0; i < FA; ++i) {
       const int m = row_of(i);
       if (m >= p.M) continue;
+      auto swiglu = [](float g, float u) { return g / (1.f + expf(-g)) * u; };
+      if constexpr (PAIR == 8) {
 #pragma unroll
-      for (int f = 0; f < FN; ++f) {                   // fragments of gate rows: two of every four
-        const int n = tile * (TN / 2) + wn * 16 * FN + f * 16 + 4 * c, gf = (f >> 1) * 4 + (f & 1);
-        if (n >= I) continue;
-        float h[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float g = acc[i][gf][e], u = acc[i][gf + 2][e];
-          h[e] = g / (1.f + expf(-g)) * u;
+        for (int f = 0; f < FB; ++f) {
+          const int n = tile * (TN / 2) + (wn * FB + f) * 8 + 2 * c;
+          if (n >= I) continue;
+          *(uint32_t*)(p.out_xf + xf_offset(m, n, I)) = pack_bf16x2(swiglu(acc[i][f][0], acc[i][f][2]), swiglu(acc[i][f][1], acc[i][f][3]));
         }
-        Act<true>::store4(p.out_xf, m, n, I, h[0], h[1], h[2], h[3]);
+      } else {
+#pragma unroll
+        for (int f = 0; f < FB / 2; ++f) {             // fragments of gate rows: two of every four
+          const int n = tile * (TN / 2) + wn * 8 * FB + f * 16 + 4 * c, gf = (f >> 1) * 4 + (f & 1);
+          if (n >= I) continue;
+          float h[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) h[e] = swiglu(acc[i][gf][e], acc[i][gf + 2][e]);
+          Act<true>::store4(p.out_xf, m, n, I, h[0], h[1], h[2], h[3]);
+        }
       }
     }
   }
 }
 
-template <int WGM, int WGN, int FM, int FN, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER = false, int SETS = 1>
+template <int WGM, int WGN, int FM, int FB, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER = false, int SETS = 1>
 hipError_t launch_cfg(WideParams& p, int S, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  constexpr int TM = 32 * FM * WGM, TN = 32 * FN * WGN;
+  constexpr int TM = 32 * FM * WGM, TN = 16 * FB * WGN;
   constexpr int LDS = A_SLOTS * TM * 64 + B_SLOTS * TN * BK * 2;
-  auto kernel = gemm_wide_kernel<WGM, WGN, FM, FN, BK, A_SLOTS, B_SLOTS, OCC, STAGGER, SETS>;
+  auto kernel = gemm_wide_kernel<WGM, WGN, FM, FB, BK, A_SLOTS, B_SLOTS, OCC, STAGGER, SETS>;
   static DeviceOnce configured;                        // the attribute belongs to the loaded code object of a device
   hipError_t ce = configured.run([&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS); });
   if (ce != hipSuccess) return ce;
@@ -361,7 +395,7 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   WideParams p;
   if (N % 4) return hipErrorInvalidValue;
   if (hipError_t e = fill_params(p, x, W, M, N, K, epi, out)) return e;
-  const WideTiles t = wide_tiles(M, N, K, epi == GEMM_EPI_SWIGLU, out_capacity_floats);
+  const WideTiles t = launch_tiles(M, N, K, epi == GEMM_EPI_SWIGLU, out_capacity_floats);
   p.S = t.S;
   if (S_out) *S_out = t.S;
   // Staggered walks (see above) also up to 256 rows.  us, in step / staggered: gate/up 28672 x 4096 77 rows 55.4 / 51.6, 256 rows 75.6 / 72.8,
@@ -372,20 +406,22 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   // 6144 x 4096 at 116 rows four ranges instead of eight: error 1.37e-7, 1.89e-7 with one chain; and 2 to 3 % faster, in 198 registers
   // instead of 176 and 88 accumulators), and 256 x 128 above 256 rows (512 rows two ranges instead of four: 1.88e-7, 2.72e-7 with one; 1 % slower).
   if (t.cols == 128 && t.k == 128) {
-    if (t.rows == 256 && M > 256) return launch_cfg<4, 2, 2, 2, 128, 4, 3, 1, false, 2>(p, t.S, st, ev_start, ev_stop);
+    if (t.rows == 256 && M > 256) return launch_cfg<4, 2, 2, 4, 128, 4, 3, 1, false, 2>(p, t.S, st, ev_start, ev_stop);
     if (t.rows == 256)
-      return stagger ? launch_cfg<4, 2, 2, 2, 128, 4, 3, 1, true>(p, t.S, st, ev_start, ev_stop)
-                     : launch_cfg<4, 2, 2, 2, 128, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
-    return stagger ? launch_cfg<2, 2, 2, 2, 128, 4, 3, 2, true, 2>(p, t.S, st, ev_start, ev_stop)
-                   : launch_cfg<2, 2, 2, 2, 128, 4, 3, 2, false, 2>(p, t.S, st, ev_start, ev_stop);
+      return stagger ? launch_cfg<4, 2, 2, 4, 128, 4, 3, 1, true>(p, t.S, st, ev_start, ev_stop)
+                     : launch_cfg<4, 2, 2, 4, 128, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
+    return stagger ? launch_cfg<2, 2, 2, 4, 128, 4, 3, 2, true, 2>(p, t.S, st, ev_start, ev_stop)
+                   : launch_cfg<2, 2, 2, 4, 128, 4, 3, 2, false, 2>(p, t.S, st, ev_start, ev_stop);
   }
   if (t.cols == 128) {
-    if (t.rows == 256) return launch_cfg<4, 2, 2, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
-    return stagger ? launch_cfg<2, 2, 2, 2, 64, 4, 3, 2, true>(p, t.S, st, ev_start, ev_stop)
-                   : launch_cfg<2, 2, 2, 2, 64, 4, 3, 2>(p, t.S, st, ev_start, ev_stop);
+    if (t.rows == 256) return launch_cfg<4, 2, 2, 4, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
+    return stagger ? launch_cfg<2, 2, 2, 4, 64, 4, 3, 2, true>(p, t.S, st, ev_start, ev_stop)
+                   : launch_cfg<2, 2, 2, 4, 64, 4, 3, 2>(p, t.S, st, ev_start, ev_stop);
   }
-  return t.rows == 256 ? launch_cfg<2, 4, 4, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop)
-                       : launch_cfg<2, 4, 3, 2, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
+  if (t.cols == 224) return launch_cfg<4, 2, 2, 7, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
+  if (t.cols == 192) return launch_cfg<4, 2, 2, 6, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
+  return t.rows == 256 ? launch_cfg<2, 4, 4, 4, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop)
+                       : launch_cfg<2, 4, 3, 4, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
 }
 
 // At most 64 rows, in tiles of 64 x cols.
@@ -398,8 +434,8 @@ hipError_t launch_gemm_wide64(const bf16_t* x, const GemmWeights& W, int M, int 
   p.S = S;
   const bool stagger = few_rows_stagger(K, S);
   if (cols == 128)
-    return stagger ? launch_cfg<2, 2, 1, 2, 128, 5, 3, 2, true, 4>(p, S, st, ev_start, ev_stop)
-                   : launch_cfg<2, 2, 1, 2, 128, 5, 3, 2, false, 4>(p, S, st, ev_start, ev_stop);
-  return stagger ? launch_cfg<2, 4, 1, 2, 64, 8, 4, 1, true, 4>(p, S, st, ev_start, ev_stop)
-                 : launch_cfg<2, 4, 1, 2, 64, 8, 4, 1, false, 4>(p, S, st, ev_start, ev_stop);
+    return stagger ? launch_cfg<2, 2, 1, 4, 128, 5, 3, 2, true, 4>(p, S, st, ev_start, ev_stop)
+                   : launch_cfg<2, 2, 1, 4, 128, 5, 3, 2, false, 4>(p, S, st, ev_start, ev_stop);
+  return stagger ? launch_cfg<2, 4, 1, 4, 64, 8, 4, 1, true, 4>(p, S, st, ev_start, ev_stop)
+                 : launch_cfg<2, 4, 1, 4, 64, 8, 4, 1, false, 4>(p, S, st, ev_start, ev_stop);
 }

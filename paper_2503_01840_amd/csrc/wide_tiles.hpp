@@ -55,39 +55,46 @@ inline WideTiles wide_tiles_256(int M, int N, int K, bool swiglu, size_t out_cap
   return best;
 }
 
-inline WideTiles wide_tiles_k64(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
-  const int KT = K / 64;
+// A tile beyond 256 rows with its split: the smallest that makes `want` workgroups, of ranges of at least `min_stages` stages of 64 k.
+inline WideTiles with_split(int M, int N, int K, bool swiglu, size_t out_capacity_floats, int rows, int cols, int want, int min_stages) {
+  const int KT = K / 64, wgs = (N + cols - 1) / cols * ((M + rows - 1) / rows);
+  int S = 1;
+  if (!swiglu)
+    for (int s = 1; s <= 8 && wgs * S < want; ++s) {
+      if (KT % s) continue;
+      if (s > 1 && ((size_t)s * M * N > out_capacity_floats || KT / s < min_stages)) break;
+      S = s;
+    }
+  return {rows, cols, S, 64};
+}
+
+// How long a launch beyond 256 rows lasts, in microseconds, with the kernel that reads its partial sums.  A workgroup takes a start and an end, and a
+// time per 64 k; the fullest XCD runs its workgroups in rounds of 32, of 64 for 128 x 128 tiles (two on a CU side by side, one
+// alone where there are no more than 32 left); writing and reading the partial sums comes on top.  The eleven numbers are a fit to 150 products
+// of 34 model shapes at 13 row counts from 257 to 2048, each with all four tiles and the kernel that reads the sums: what the estimate picks
+// is 0.2 % slower than the best of the four on average (13 % at worst: 2304 x 9216 at 1500 rows), and 12 % faster than picking by workgroup
+// counts.  Fitted to 17 products, it had charged 128 x 128 tiles too much: us, then / now, down 4352 x 17024 300 rows 114 / 100, gate/up
+// 18432 x 2304 257 rows 48 / 43, o 5120 x 5120 300 rows 43 / 40.  8B width, product and reading, us, 256 x 256 / 192 x 256 /
+// 256 x 128 / 128 x 128: q/k/v 300 rows 38 / 35 / 36 / 44, 512 rows 44 / 64 / 40 / 50, 600 rows 73 / 52 / 71 / 50; down 300 rows
+// 63 / 58 / 60 / 69, 512 rows 73 / 80 / 67 / 83; o 1024 rows 49 / 49 / 42 / 50; gate/up 300 rows 101 / 87 / 116 / 121, 1024 rows
+// 197 / 235 / 231 / 274, 2048 rows 382 / 392 / 406 / 509; hidden 2048, gate/up 300 rows 45 / 41 / 31 / 30.
+inline float wide_time(int M, int N, int K, bool swiglu, const WideTiles& w) {
   auto ceil_div = [](int a, int b) { return (a + b - 1) / b; };
-  auto pick = [&](int rows, int cols, int want, int min_stages) -> WideTiles {
-    const int wgs = ceil_div(N, cols) * ceil_div(M, rows);
-    int S = 1;
-    if (!swiglu)
-      for (int s = 1; s <= 8 && wgs * S < want; ++s) {
-        if (KT % s) continue;
-        if (s > 1 && ((size_t)s * M * N > out_capacity_floats || KT / s < min_stages)) break;
-        S = s;
-      }
-    return {rows, cols, S, 64};
-  };
-  // The tile whose launch is over first by this estimate, in microseconds.  A workgroup takes a start and an end, and a
-  // time per 64 k; the fullest XCD runs its workgroups in rounds of 32, of 64 for 128 x 128 tiles (two on a CU side by side, one
-  // alone where there are no more than 32 left); writing and reading the partial sums comes on top.  The eleven numbers are a fit to 150 products
-  // of 34 model shapes at 13 row counts from 257 to 2048, each with all four tiles and the kernel that reads the sums: what the estimate picks
-  // is 0.2 % slower than the best of the four on average (13 % at worst: 2304 x 9216 at 1500 rows), and 12 % faster than picking by workgroup
-  // counts.  Fitted to 17 products, it had charged 128 x 128 tiles too much: us, then / now, down 4352 x 17024 300 rows 114 / 100, gate/up
-  // 18432 x 2304 257 rows 48 / 43, o 5120 x 5120 300 rows 43 / 40.  8B width, product and reading, us, 256 x 256 / 192 x 256 /
-  // 256 x 128 / 128 x 128: q/k/v 300 rows 38 / 35 / 36 / 44, 512 rows 44 / 64 / 40 / 50, 600 rows 73 / 52 / 71 / 50; down 300 rows
-  // 63 / 58 / 60 / 69, 512 rows 73 / 80 / 67 / 83; o 1024 rows 49 / 49 / 42 / 50; gate/up 300 rows 101 / 87 / 116 / 121, 1024 rows
-  // 197 / 235 / 231 / 274, 2048 rows 382 / 392 / 406 / 509; hidden 2048, gate/up 300 rows 45 / 41 / 31 / 30.
-  auto cost = [&](const WideTiles& w) -> float {
-    const int n = ceil_div(ceil_div(N, w.cols), 8) * ceil_div(M, w.rows) * w.S;
-    const float stages = (float)KT / w.S, sums = swiglu ? 0.f : (float)w.S * M * N * 1.2e-6f;
-    if (w.cols == 256) return ceil_div(n, 32) * (w.rows == 256 ? 7.4f + 1.36f * stages : 8.2f + 1.1f * stages) + sums;
-    if (w.rows == 256) return ceil_div(n, 32) * (8.f + 0.81f * stages) + sums;
-    const float two = 7.3f + 1.085f * stages, one = 7.4f + 0.595f * stages;
-    const int rest = n % 64;
-    return n / 64 * two + (rest == 0 ? 0.f : rest <= 32 ? one : two) + sums;
-  };
+  const int n = ceil_div(ceil_div(N, w.cols), 8) * ceil_div(M, w.rows) * w.S;
+  const float stages = (float)K / 64 / w.S, sums = swiglu ? 0.f : (float)w.S * M * N * 1.2e-6f;
+  if (w.cols == 224) return ceil_div(n, 32) * (7.6f + 1.28f * stages) + sums;
+  if (w.cols == 192) return ceil_div(n, 32) * (8.f + 1.1f * stages) + sums;
+  if (w.cols == 256) return ceil_div(n, 32) * (w.rows == 256 ? 7.4f + 1.36f * stages : 8.2f + 1.1f * stages) + sums;
+  if (w.rows == 256) return ceil_div(n, 32) * (8.f + 0.81f * stages) + sums;
+  const float two = 7.3f + 1.085f * stages, one = 7.4f + 0.595f * stages;
+  const int rest = n % 64;
+  return n / 64 * two + (rest == 0 ? 0.f : rest <= 32 ? one : two) + sums;
+}
+
+// The tile whose launch is over first by that estimate.
+inline WideTiles wide_tiles_k64(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
+  auto pick = [&](int rows, int cols, int want, int min_stages) { return with_split(M, N, K, swiglu, out_capacity_floats, rows, cols, want, min_stages); };
+  auto cost = [&](const WideTiles& t) { return wide_time(M, N, K, swiglu, t); };
   WideTiles best = pick(256, 256, 160, 16);
   for (const WideTiles& t : {pick(192, 256, 160, 16), pick(256, 128, 192, 16), pick(128, 128, 384, 8)})
     if (cost(t) < cost(best)) best = t;
@@ -102,6 +109,26 @@ inline WideTiles wide_tiles(int M, int N, int K, bool swiglu, size_t out_capacit
   const int wgs = (N + t.cols - 1) / t.cols * ((M + t.rows - 1) / t.rows) * t.S, range = K / t.S;
   if (t.cols == 128 && range % 128 == 0 && range >= (t.rows == 256 && t.S == 1 ? 256 : 1024) && (t.rows == 256 || wgs <= 256)) t.k = 128;
   return t;
+}
+
+// The tile that is launched: that, or beyond 256 rows 256 x 224 or 256 x 192 (4 x 2 wavefronts of 64 x 112 or 64 x 96).  28672 weight rows (8B
+// gate/up) are 112 tiles of 256, 3.5 rounds of the chip at 2048 rows, and 128 of 224, four whole ones; 6144 (q/k/v) are 24 of 256, three
+// quarters of a round, and 32 of 192.  Taken by a margin of 2 % of the estimate, and only with chains of sums no longer than the other tile's
+// (stages of 128 k: two chains).  us, the other tile / this one: gate/up 2048 rows 371 / 357, 1280 rows 283 / 235, 512 rows 99.8 / 98.3 (the same
+// work on more CUs draws the same power), 57344 x 8192 1024 rows 752 / 717, 27648 x 5120 1280 rows 335 / 285, q/k/v 2048 rows 92 / 81, 1024 rows
+// 70 / 62, 22016 x 4096 512 rows 95 / 83.  Of 170 products of 22 shapes from 300 to 2048 rows 37 took another tile, 2 to 17 % faster and none slower.
+inline WideTiles launch_tiles(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
+  const WideTiles base = wide_tiles(M, N, K, swiglu, out_capacity_floats);
+  if (M <= 256) return base;
+  const int chain = K / base.S / (base.k == 128 ? 2 : 1);
+  WideTiles best = base;
+  float least = 0.98f * wide_time(M, N, K, swiglu, base);
+  for (int cols : {224, 192}) {
+    const WideTiles t = with_split(M, N, K, swiglu, out_capacity_floats, 256, cols, 160, 16);
+    const float time = wide_time(M, N, K, swiglu, t);
+    if (K / t.S <= chain && time < least) { best = t; least = time; }
+  }
+  return best;
 }
 
 // ---- at most 64 rows

@@ -70,6 +70,17 @@ def test_rows_of_64_row_tiles(name, B, N, group):
     _rows_alone_and_together(FEW[name], B, N, group, logits=True)
 
 
+# 256 x 224 and 256 x 192 tiles against at most 64 rows at a time.  8B width: gate/up in whole tiles of 224; "deep": a last tile of 96 weight rows; "mha": gate/up
+# in tiles of 192, the last one of 128 rows, q/k/v in two ranges in tiles of 192; row blocks that end full and anywhere.
+ROUNDS = [("8b", 64, 8, 8), ("8b", 61, 7, 9), ("deep", 61, 8, 8), ("mha", 64, 8, 8), ("mha", 71, 7, 9)]
+
+
+@pytest.mark.parametrize("name,B,N,group", ROUNDS)
+def test_rows_in_tiles_that_make_up_whole_rounds(name, B, N, group):
+    mha = S.get_shape("c3").with_(name="mha", n_kv_heads=32, intermediate=11008, vocab=1024)
+    _rows_alone_and_together(mha if name == "mha" else FEW[name].with_(vocab=1024), B, N, group, logits=True)
+
+
 def _rows_alone_and_together(full, B, N, group, logits=False):
     """All B sequences of N rows at once against `group` of them at a time; one sequence: against its first 32 rows."""
     E = _E()

@@ -185,3 +185,63 @@ def test_few_row_tiles_that_the_gpu_tests_cover(tmp_path, model, at, want, M):
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
     out = subprocess.run([str(tmp_path / "m")], capture_output=True, text=True, check=True).stdout
     assert [tuple(map(int, line.split())) for line in out.splitlines()] == want
+
+
+# beyond 256 rows: (rows, outputs, inputs, SwiGLU): microseconds in the best of the other tiles, in tiles of 224 or 192 weight rows
+MEASURED_ROUNDS = [
+    ((512, 28672, 4096, 1), 99.8, 98.3), ((1024, 28672, 4096, 1), 217, 207), ((1280, 28672, 4096, 1), 286, 244), ((2048, 28672, 4096, 1), 371, 357),
+    ((300, 28672, 4096, 1), 85.4, 94.9), ((4096, 28672, 4096, 1), 702, 718), ((2048, 6144, 4096, 0), 115, 99), ((1024, 6144, 4096, 0), 69.5, 63.1),
+    ((512, 6144, 4096, 0), 43.9, 47.7), ((2048, 4096, 4096, 0), 72.5, 83.0), ((512, 4096, 14336, 0), 71.5, 80.0), ((1024, 57344, 8192, 1), 761, 716),
+    ((512, 22016, 4096, 1), 96, 83), ((1024, 12288, 4096, 0), 112, 101), ((2048, 18432, 2304, 1), 175, 149), ((512, 128256, 4096, 0), 529, 547),
+]
+
+
+@pytest.fixture(scope="module")
+def launched(tmp_path_factory):
+    """(M, N, K, SwiGLU, capacity) -> (rows, cols, S, k of a stage) of the launch, and of the tile that wide_tiles picks"""
+    d = tmp_path_factory.mktemp("launched")
+    (d / "m.cpp").write_text('#include <cstdio>\n#include "wide_tiles.hpp"\n'
+                             'int main() { int m, n, k, s; long long c; while (scanf("%d %d %d %d %lld", &m, &n, &k, &s, &c) == 5) {\n'
+                             '  for (const WideTiles& t : {launch_tiles(m, n, k, s, c), wide_tiles(m, n, k, s, c)}) printf("%d %d %d %d ", t.rows, t.cols, t.S, t.k);\n'
+                             '  puts(""); } }\n')
+    inc = os.path.join(ROOT, "paper_2503_01840_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(d / "m.cpp"), "-o", str(d / "m")], check=True)
+
+    def ask(queries):
+        text = "\n".join(" ".join(map(str, q)) for q in queries) + "\n"
+        out = subprocess.run([str(d / "m")], input=text, capture_output=True, text=True, check=True).stdout
+        return [(t[:4], t[4:]) for t in (tuple(map(int, line.split())) for line in out.splitlines())]
+    return ask
+
+
+def test_tiles_that_make_up_whole_rounds_where_they_are_the_faster_ones(launched):
+    for (q, without, by_rounds), (t, _) in zip(MEASURED_ROUNDS, launched([q + (BIG,) for q, _, _ in MEASURED_ROUNDS])):
+        assert (t[1] in (192, 224)) == (by_rounds < without), (q, t)
+
+
+def test_every_launch_is_possible_and_sums_in_chains_no_longer(launched):
+    qs = [(M, N, K, s, cap) for M in (65, 256, 257, 383, 512, 1000, 2048, 4096) for N in (256, 768, 4608, 5120, 6144, 12288, 28672)
+          for K in (128, 256, 2304, 4096, 14336) for s in (0, 1) for cap in (0, 2048 * 5120, BIG)]
+    seen = set()
+    for (M, N, K, s, cap), (t, base) in zip(qs, launched(qs)):
+        seen.add(t[:2])
+        if t == base:
+            continue
+        assert M > 256 and t[0] == 256 and t[1] in (192, 224) and t[3] == 64
+        assert 1 <= t[2] <= 8 and (K // 64) % t[2] == 0 and (t[2] == 1 or (not s and t[2] * M * N <= cap))
+        assert K // t[2] <= K // base[2] // (2 if base[3] == 128 else 1)
+    assert {(256, 192), (256, 224)} <= seen
+
+
+def test_whole_rounds_that_the_gpu_tests_cover(launched):
+    at = {"8b": [(2, 224, 1)], "deep": [(2, 224, 1)], "mha": [(0, 192, 2), (2, 192, 1)]}
+    for name, M in [("8b", 512), ("8b", 427), ("deep", 488), ("mha", 512), ("mha", 497)]:
+        for i, cols, splits in at[name]:
+            p = _products(name, M)[i]
+            assert launched([(M, *p[:3], p[4])])[0][0][:3] == (256, cols, splits), (name, M, i)
+    # and what test_tiles_that_the_gpu_tests_cover says of more than 256 rows is what is launched there
+    for name, M, rows in [("8b", 600, (0, 1, 2, 3)), ("flat", 257, (2,)), ("flat", 384, (2,)), ("flat", 385, (2,)), ("flat", 576, (2,)), ("flat", 577, (2,))]:
+        for i in rows:
+            p = _products(name, M)[i]
+            launch, base = launched([(M, *p[:3], p[4])])[0]
+            assert launch == base, (name, M, i)
