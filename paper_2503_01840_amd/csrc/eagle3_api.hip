@@ -72,7 +72,7 @@ struct eagle3_ctx {
   size_t part_floats, attn_floats;
   // workspace
   float* x; void* act_k; void* act_attn; void* act_h; void* q; float* part; float* attn_scratch;
-  int32_t* depth; uint32_t* mask; int32_t* slot; float* cs; SeqInfo* seq;
+  uint32_t* mask; int32_t* slot; float* cs; SeqInfo* seq;
   float* accept_stats;
   float* z; float* a_buf; int32_t* pos1; float* topk_scratch; DraftState ds;
   int chunk_max;                        // rows per prefill chunk: a multiple of 64, or fewer than 64
@@ -118,7 +118,6 @@ struct eagle3_ctx {
     q = cv.take<char>((size_t)Rall * Hd * act_size);
     part = cv.take<float>(part_floats);
     attn_scratch = cv.take<float>(attn_floats);
-    depth = cv.take<int32_t>(Rall);
     mask = cv.take<uint32_t>((size_t)Rall * 4);
     slot = cv.take<int32_t>(Rall);
     cs = cv.take<float>((size_t)std::max(Rall, c.max_new + c.max_depth) * c.head_dim);
@@ -412,6 +411,11 @@ static int project_qkv(eagle3_ctx* ctx, const eagle3_layer_weights& w, void* in,
   return EAGLE3_OK;
 }
 
+static int project_head(eagle3_ctx* ctx, int R, const void* head, int V, float* out, hipStream_t st) {
+  GemmWeights W = {{head, nullptr, nullptr}, {V, 0, 0}, 1, 0};
+  return ctx->project(ctx->act_k, W, R, V, ctx->cfg.hidden, GEMM_EPI_PARTIAL, nullptr, st, out);
+}
+
 // RMSNorm and LM head of R rows, to which S partial sums in `part` are added first; copies: see launch_add_norm.
 static int norm_head(eagle3_ctx* ctx, float* x, int S, int R, const void* gain, float* const copies[4], const void* head, int V, float* out,
                      hipStream_t st) {
@@ -425,7 +429,7 @@ static int norm_head(eagle3_ctx* ctx, float* x, int S, int R, const void* gain, 
     return EAGLE3_OK;
   }
   CK(launch_add_norm(true, x, S ? ctx->part : nullptr, S, R, k, gain, ctx->cfg.rms_eps, ctx->act_k, copies, st));
-  return ctx->project(ctx->act_k, W, R, V, k, GEMM_EPI_PARTIAL, nullptr, st, out);
+  return project_head(ctx, R, head, V, out, st);
 }
 
 // attention + output projection + MLP of one layer, shared by the target stack and the draft layer.
@@ -482,11 +486,11 @@ static int layer_tail(eagle3_ctx* ctx, const eagle3_layer_weights& w, int B, int
   return EAGLE3_OK;
 }
 
-// Layers [l0, l1) of the target stack over R rows, whose residual stream is in ctx->x and whose slots, masks and rotary
-// tables are prepared; attention sees them as B sequences of N rows.  logits != nullptr: finish with the final norm and the
+// Layers [l0, l1) of the target stack over R rows, from what `begin` says; attention sees them as B sequences of N rows.
+// logits != nullptr: finish with the final norm and the
 // LM head (requires l1 == n_layers).  norm_out: finish with the norm in front of layer l1.  x_out (optional) receives the residual stream after layer l1 - 1.
-static int run_layers(eagle3_ctx* ctx, int B, int N, int R, bool prefill, const eagle3_kv* kv, int max_len, int l0, int l1, float* x_out,
-                      float* logits, float* taps, float* dbg_hidden, hipStream_t st, bool norm_out = false) {
+static int run_layers(eagle3_ctx* ctx, const BeginRows& begin, int B, int N, int R, bool prefill, const eagle3_kv* kv, int max_len, int l0, int l1,
+                      float* x_out, float* logits, float* taps, float* dbg_hidden, hipStream_t st, bool norm_out = false) {
   const eagle3_config& c = ctx->cfg;
   const int k = c.hidden;
   const size_t Rk = (size_t)R * k;
@@ -504,14 +508,16 @@ static int run_layers(eagle3_ctx* ctx, int B, int N, int R, bool prefill, const 
   int S_prev = 0;                                   // bf16: partial sums of the previous layer's MLP still to be added
   for (int l = l0; l <= l1; ++l) {
     // bf16: x becomes the output of layer l-1 here, is copied, and normed for what follows.  fp32: x is complete, layer l-1 has
-    // made the copies, and the norm comes with the product that follows (norm_operand).
+    // made the copies, and the norm comes with the product that follows (norm_operand).  l0: x is formed here.
     const Copies co = copies_at(l);
-    const bool any = co.p[0] || co.p[1] || co.p[2] || co.p[3], head = l == c.n_layers && l == l1 && logits;
-    if (head && ctx->bf16) return norm_head(ctx, ctx->x, S_prev, R, ctx->tw.final_norm, co.p, ctx->tw.lm_head, c.vocab, logits, st);
-    const bool norm = l < l1 || norm_out;
-    if (ctx->bf16) CK(launch_add_norm(true, ctx->x, ctx->part, S_prev, R, k, norm ? ctx->layers[l].norm_attn : nullptr, c.rms_eps, norm ? ctx->act_k : nullptr, co.p, st));
-    else if (l == l0 && any) CK(launch_add_norm(false, ctx->x, nullptr, 0, R, k, nullptr, c.rms_eps, nullptr, co.p, st));
-    if (head) return norm_head(ctx, ctx->x, 0, R, ctx->tw.final_norm, nullptr, ctx->tw.lm_head, c.vocab, logits, st);
+    const bool head = l == c.n_layers && l == l1 && logits, norm = head || l < l1 || norm_out;
+    const void* gain = head ? ctx->tw.final_norm : norm ? ctx->layers[l].norm_attn : nullptr;
+    if (l == l0)
+      CK(launch_begin_rows(ctx->bf16, begin, ctx->x, R, k, ctx->bf16 ? gain : nullptr, c.rms_eps, ctx->act_k, co.p, st));
+    else if (ctx->bf16)
+      CK(launch_add_norm(true, ctx->x, ctx->part, S_prev, R, k, gain, c.rms_eps, norm ? ctx->act_k : nullptr, co.p, st));
+    if (head) return ctx->bf16 ? project_head(ctx, R, ctx->tw.lm_head, c.vocab, logits, st)
+                               : norm_head(ctx, ctx->x, 0, R, gain, nullptr, ctx->tw.lm_head, c.vocab, logits, st);
     if (l == l1) break;
     const eagle3_layer_weights& w = ctx->layers[l];
     TRY(project_qkv(ctx, w, ctx->bf16 ? ctx->act_k : ctx->x, w.norm_attn, k, R, ctx->slot, ctx->cs, c.head_dim, kv->k[l], kv->v[l], st));
@@ -527,13 +533,9 @@ static int verify_layers(eagle3_ctx* ctx, int B, int N, const int32_t* tree_tok,
                          float* dbg_hidden, hipStream_t st) {
   const eagle3_config& c = ctx->cfg;
   const int R = B * N;
-  CK(launch_tree_prep(parent, kv->kv_indptr, kv->prefix_len, B, N, c.head_dim, c.rope_theta, ctx->depth, ctx->mask, ctx->slot,
-                      ctx->cs, ctx->seq, st));
-  if (x_in)
-    CK(hipMemcpyAsync(ctx->x, x_in, (size_t)R * c.hidden * sizeof(float), hipMemcpyDeviceToDevice, st));
-  else
-    CK(launch_embed_rows(ctx->bf16, ctx->tw.embed, tree_tok, R, c.hidden, c.vocab, ctx->x, st));
-  return run_layers(ctx, B, N, R, false, kv, kv->max_prefix_len + N, l0, l1, x_out, logits, taps, dbg_hidden, st);
+  const BeginRows begin = {ctx->tw.embed, tree_tok, c.vocab, x_in, parent, B, N, kv->kv_indptr, kv->prefix_len, (int)c.head_dim, c.rope_theta,
+                           ctx->slot, ctx->mask, ctx->cs, ctx->seq};
+  return run_layers(ctx, begin, B, N, R, false, kv, kv->max_prefix_len + N, l0, l1, x_out, logits, taps, dbg_hidden, st);
 }
 
 static int check_verify_args(eagle3_ctx* ctx, int B, int N, const int32_t* tree_tok, const int32_t* parent,
@@ -666,10 +668,9 @@ int eagle3_draft_chain(eagle3_ctx* ctx, int32_t B, const float* g_new, const int
       // a = y1 + MLP(...) for every row, then the row of each sequence's last real position moves to row b
       if (ctx->bf16) CK(launch_add_norm(true, ctx->x, ctx->part, S_down, M, k, nullptr, c.rms_eps, nullptr, nullptr, st));
       CK(launch_chain_gather(ctx->x, n_new, B, rows1, k, ctx->a_buf, st));
-      CK(hipMemcpyAsync(ctx->x, ctx->a_buf, (size_t)B * k * sizeof(float), hipMemcpyDeviceToDevice, st));
       S_down = 0;
     }
-    TRY(norm_head(ctx, ctx->x, S_down, B, ctx->dw.final_norm, copies, ctx->dw.lm_head, Vd, ctx->z, st));
+    TRY(norm_head(ctx, gather ? ctx->a_buf : ctx->x, S_down, B, ctx->dw.final_norm, copies, ctx->dw.lm_head, Vd, ctx->z, st));
     CK(launch_chain_level(ctx->bf16, cs, {ctx->z, 0, Vd, ctx->topk_scratch}, ctx->dw.d2t, dkv->kv_indptr, dkv->prefix_len, n_new, tok_new, B,
                           rows1, level, length, chain_tok, chain_logp, in, ctx->a_buf, st));
   }
@@ -701,32 +702,31 @@ int eagle3_prefill(eagle3_ctx* ctx, const int32_t* tokens, int32_t T, const eagl
     const bool last = c0 + n == T;
     // target: the chunk on top of everything cached so far; features of every position recorded
     const size_t nk = (size_t)n * k;
-    CK(launch_prefill_prep(kv->kv_indptr, kv->prefix_len, n, d, c.rope_theta, ctx->pos1, ctx->slot, ctx->mask, ctx->cs, ctx->seq, st));
-    CK(launch_embed_rows(ctx->bf16, ctx->tw.embed, tokens + c0, n, k, c.vocab, ctx->x, st));
+    const BeginRows begin = {ctx->tw.embed, tokens + c0, c.vocab, nullptr, nullptr, 1, 0, kv->kv_indptr, kv->prefix_len, d, c.rope_theta,
+                             ctx->slot, ctx->mask, ctx->cs, ctx->seq};
     const int max_len = kv->max_prefix_len + c0 + n, L = c.n_layers;
     int S_tail = 0;
     if (tail_row) {
-      TRY(run_layers(ctx, blocks, blocks == 1 ? n : 64, n, true, kv, max_len, 0, L - 1, nullptr, nullptr, ctx->chunk_taps, nullptr, st, true));
+      TRY(run_layers(ctx, begin, blocks, blocks == 1 ? n : 64, n, true, kv, max_len, 0, L - 1, nullptr, nullptr, ctx->chunk_taps, nullptr, st, true));
       const eagle3_layer_weights& wl = ctx->layers[L - 1];
       TRY(project_qkv(ctx, wl, ctx->bf16 ? ctx->act_k : ctx->x, wl.norm_attn, k, n, ctx->slot, ctx->cs, d, kv->k[L - 1], kv->v[L - 1], st));
       if (last) TRY(layer_tail(ctx, wl, 1, 1, n, true, ctx->mask, ctx->seq, kv->k[L - 1], kv->v[L - 1], max_len, nullptr, &S_tail, st, true));
     } else {
-      TRY(run_layers(ctx, blocks, blocks == 1 ? n : 64, n, true, kv, max_len, 0, L, nullptr, nullptr, ctx->chunk_taps, nullptr, st));
+      TRY(run_layers(ctx, begin, blocks, blocks == 1 ? n : 64, n, true, kv, max_len, 0, L, nullptr, nullptr, ctx->chunk_taps, nullptr, st));
     }
-    CK(launch_advance_lengths((int32_t*)kv->prefix_len, 1, n, st));
     if (last) {                                       // next-token logits of the last position only
       TRY(norm_head(ctx, ctx->x + (size_t)(n - 1) * k, S_tail, 1, ctx->tw.final_norm, nullptr, ctx->tw.lm_head, c.vocab, logits_last, st));
     }
     // fused features of the chunk's positions; the draft cache rows of those whose next token is known
     TRY(fuse_rows(ctx, ctx->chunk_taps, ctx->chunk_taps + nk, ctx->chunk_taps + 2 * nk, n, ctx->chunk_g, st));
-    if (last) CK(hipMemcpyAsync(g_last, ctx->chunk_g + (size_t)(n - 1) * k, (size_t)k * sizeof(float), hipMemcpyDeviceToDevice, st));
     const int m = last ? n - 1 : n;
     if (m > 0) {
-      CK(launch_prefill_prep(dkv->kv_indptr, dkv->prefix_len, m, d, c.rope_theta, ctx->pos1, ctx->slot, ctx->mask, nullptr, ctx->seq, st));
-      CK(launch_draft_input(ctx->bf16, ctx->draft_input_args(), tokens + c0 + 1, ctx->chunk_g, ctx->pos1, m, st));
+      CK(launch_draft_first(ctx->bf16, ctx->draft_input_args(), tokens + c0 + 1, ctx->chunk_g, dkv->kv_indptr, dkv->prefix_len, m, 1, ctx->slot,
+                            nullptr, nullptr, st));
       TRY(project_qkv(ctx, w, ctx->act_k, nullptr, 2 * k, m, ctx->slot, ctx->cs, d, dkv->k[0], dkv->v[0], st));
-      CK(launch_advance_lengths((int32_t*)dkv->prefix_len, 1, m, st));
     }
+    CK(launch_end_prefill((int32_t*)kv->prefix_len, n, (int32_t*)dkv->prefix_len, m, ctx->chunk_g + (size_t)(n - 1) * k, k,
+                          last ? g_last : nullptr, st));
   }
   return EAGLE3_OK;
 }

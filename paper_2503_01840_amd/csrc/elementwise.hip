@@ -9,17 +9,6 @@
 
 namespace {
 
-// One pass; VEC: four consecutive columns per thread, where k is a multiple of 4 and the table is 16-byte aligned.
-template <typename TW, bool VEC>
-__global__ __launch_bounds__(256) void embed_rows_kernel(const TW* __restrict__ embed, const int32_t* __restrict__ tok,
-                                                        int k, int vocab, float* __restrict__ x) {
-  const int r = blockIdx.x, c = (VEC ? 4 : 1) * (blockIdx.y * 256 + threadIdx.x);
-  if (c >= k) return;
-  const size_t t = (size_t)min(max(tok[r], 0), vocab - 1) * k + c;
-  if constexpr (VEC) *(float4*)(x + (size_t)r * k + c) = load4_f32(embed, t);
-  else x[(size_t)r * k + c] = load_f32(embed, t);
-}
-
 struct CopyOut { float* p[4]; };
 
 // One workgroup per row, four consecutive columns per thread (two such groups when k > 4096): the row stays
@@ -77,28 +66,23 @@ __global__ __launch_bounds__(1024) void add_norm_kernel(float* __restrict__ x, c
   }
 }
 
-__global__ __launch_bounds__(256) void tree_prep_kernel(const int32_t* __restrict__ parent,
-                                                       const int32_t* __restrict__ kv_indptr,
-                                                       const int32_t* __restrict__ prefix_len, int N, int d, float theta,
-                                                       int32_t* __restrict__ depth, uint32_t* __restrict__ mask,
-                                                       int32_t* __restrict__ slot, float* __restrict__ cs,
-                                                       SeqInfo* __restrict__ seq) {
-  // Workgroup (b, y): every y walks sequence b's tree (parents staged in LDS: one memory round trip, then the walks
-  // stay on chip) and fills its share of the rotary table, whose sines and cosines are the bulk of the work; y = 0
-  // also writes the masks, depths, slots and the sequence record.
+// Part y of n_parts of sequence b's tree: every part walks the tree (parents staged in LDS: one memory round trip, then the walks
+// stay on chip) and fills its share of the rotary table, whose sines and cosines are the bulk of the work; part 0
+// also writes the masks, slots and the sequence record.
+__device__ __forceinline__ void tree_prep(const BeginRows& p, int b, int y, int n_parts) {
   __shared__ int sdepth[64], spar[64];
   __shared__ int rank;
-  const int b = blockIdx.x, y = blockIdx.y, i = threadIdx.x, B = gridDim.x;
-  const int P = prefix_len[b], base = kv_indptr[b];
-  if (i < N) spar[i] = parent[b * N + i];
+  const int i = threadIdx.x, threads = blockDim.x, B = p.B, N = p.N, d = p.head_dim;
+  const int P = p.prefix_len[b], base = p.kv_indptr[b];
+  if (i < N) spar[i] = p.parent[b * N + i];
   if (i == 0) rank = 0;
   __syncthreads();
   if (y == 0) {
     // rank of this sequence by prefix length, longest first (ties: smaller index first): attention hands out its
     // workgroups in that order, so that the long sequences start first and the short ones fill the tail
     int longer = 0;
-    for (int o = i; o < B; o += 256) {
-      const int Po = prefix_len[o];
+    for (int o = i; o < B; o += threads) {
+      const int Po = p.prefix_len[o];
       longer += (Po > P || (Po == P && o < b)) ? 1 : 0;
     }
     if (longer) atomicAdd(&rank, longer);
@@ -108,29 +92,103 @@ __global__ __launch_bounds__(256) void tree_prep_kernel(const int32_t* __restric
     int cur = i, dep = 0;
     for (int it = 0; it < N; ++it) {                     // bounded walk: malformed parents cannot loop
       m[cur >> 5] |= 1u << (cur & 31);
-      const int p = spar[cur];
-      if (p < 0 || p >= cur) break;
-      cur = p;
+      const int q = spar[cur];
+      if (q < 0 || q >= cur) break;
+      cur = q;
       ++dep;
     }
     sdepth[i] = dep;
     if (y == 0) {
       const int r = b * N + i;
-      depth[r] = dep;
-      slot[r] = base + P + i;
+      p.slot[r] = base + P + i;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) mask[r * 4 + w] = m[w];
+      for (int w = 0; w < 4; ++w) p.mask[r * 4 + w] = m[w];
     }
   }
   __syncthreads();
   if (y == 0 && i == 0) {
-    seq[rank].order = b;
-    seq[b].kv_base = base; seq[b].n_prefix = P; seq[b].n_tail = N;
+    p.seq[rank].order = b;
+    p.seq[b].kv_base = base; p.seq[b].n_prefix = P; p.seq[b].n_tail = N;
   }
   const int half = d / 2;
-  for (int e = y * 256 + i; e < N * half; e += 256 * gridDim.y) {
+  for (int e = y * threads + i; e < N * half; e += threads * n_parts) {
     const int row = e / half, f = e % half;
-    rope_entry(cs, b * N + row, f, d, P + sdepth[row], theta);
+    rope_entry(p.cs, b * N + row, f, d, P + sdepth[row], p.theta);
+  }
+}
+
+// Rows of a prefill chunk of n, one per wavefront: row r continues the sequence at position P + r.  For attention the chunk is
+// cut into blocks of 64 rows: block b sees the context and every earlier block unconditionally (n_prefix = P + 64 b) and its
+// own rows causally through the row masks, so the tree kernels run a chunk of any length as a batch of "sequences" that
+// share one cache.  The last block has the most keys, so it is handed out first.
+__device__ __forceinline__ void prefill_prep(const BeginRows& p, int r, int n) {
+  const int lane = threadIdx.x & 63;
+  if (r >= n) return;
+  const int P = p.prefix_len[0], base = p.kv_indptr[0], j = r & 63, b = r >> 6;
+  if (lane < 4) {                                        // causal inside the block: bits 0..j
+    const int lo = 32 * lane;
+    p.mask[r * 4 + lane] = j < lo ? 0u : (j - lo >= 31 ? 0xFFFFFFFFu : ((2u << (j - lo)) - 1u));
+  }
+  if (lane == 0) {
+    p.slot[r] = base + P + r;
+    if (j == 0) {
+      p.seq[b].kv_base = base; p.seq[b].n_prefix = P + r; p.seq[b].n_tail = min(64, n - r);
+      p.seq[b].order = (n + 63) / 64 - 1 - b;
+    }
+  }
+  for (int i = lane; i < p.head_dim / 2; i += 64) rope_entry(p.cs, r, i, p.head_dim, P + r, p.theta);
+}
+
+// How a pass over R rows begins: bookkeeping by the first prep_wgs workgroups (a multiple of 8: see row_of_workgroup), and each row's
+// residual, from the embedding table or from p.x_in, with its copies and, with a gain, the RMSNorm that the first projection reads.  None needs
+// another: as three launches (bookkeeping, embedding, norm: 5.7 + 4.8 + 4.9 us for 60 rows of 4096) each waited for the one before;
+// 6.0 here (8.0 with half as many, twice as large workgroups for the rotary table).  A prompt of 77 tokens 4630 -> 4616 us, with end_prefill_kernel and
+// the draft rows' bookkeeping in their input (four launches fewer), 4 trees of 29 nodes 1534 -> 1528.
+template <bool BF16>
+__global__ __launch_bounds__(1024) void begin_rows_kernel(BeginRows p, int prep_wgs, int parts, float* __restrict__ x, int R, int k,
+                                                         const typename Act<BF16>::type* __restrict__ gain, float eps,
+                                                         typename Act<BF16>::type* __restrict__ act, CopyOut co) {
+  __shared__ float red[17];
+  if ((int)blockIdx.x < prep_wgs) {
+    if (!p.parent) prefill_prep(p, blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), R);
+    else if ((int)blockIdx.x < p.B * parts) tree_prep(p, blockIdx.x / parts, blockIdx.x % parts, parts);
+    return;
+  }
+  const int r = row_of_workgroup<BF16>(blockIdx.x - prep_wgs), nvec = k >> 2, bd = blockDim.x;
+  if (r >= R) return;
+  constexpr int VPT = 2;
+  typedef typename Act<BF16>::type T;
+  const T* table = (const T*)p.embed;
+  const size_t from = p.x_in ? (size_t)r * k : (size_t)min(max(p.tok[r], 0), p.vocab - 1) * k;
+  const bool whole = ((uintptr_t)table & 15) == 0;       // the caller's table may start anywhere
+  float4 val[VPT], g[VPT];
+  float ss = 0.f;
+#pragma unroll
+  for (int j = 0; j < VPT; ++j) {
+    const int v = threadIdx.x + j * bd;
+    if (v < nvec) {
+      if (gain) g[j] = load4_f32(gain, 4 * v);
+      float4 a;
+      if (p.x_in) a = make_float4(p.x_in[from + 4 * v], p.x_in[from + 4 * v + 1], p.x_in[from + 4 * v + 2], p.x_in[from + 4 * v + 3]);
+      else if (whole) a = load4_f32(table, from + 4 * v);
+      else a = make_float4(load_f32(table, from + 4 * v), load_f32(table, from + 4 * v + 1), load_f32(table, from + 4 * v + 2), load_f32(table, from + 4 * v + 3));
+      *(float4*)(x + (size_t)r * k + 4 * v) = a;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (co.p[i]) *(float4*)(co.p[i] + (size_t)r * k + 4 * v) = a;
+      ss += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w;
+      val[j] = a;
+    }
+  }
+  if (!gain) return;
+  ss = block_sum(ss, red);
+  const float inv = 1.0f / sqrtf(ss / (float)k + eps);
+#pragma unroll
+  for (int j = 0; j < VPT; ++j) {
+    const int v = threadIdx.x + j * bd;
+    if (v < nvec)
+      Act<BF16>::store4(act, r, 4 * v, k, val[j].x * inv * g[j].x, val[j].y * inv * g[j].y, val[j].z * inv * g[j].z,
+                        val[j].w * inv * g[j].w);
   }
 }
 
@@ -217,7 +275,8 @@ __global__ __launch_bounds__(1024) void draft_input_kernel(DraftInput<BF16> p, c
   for (int i = threadIdx.x; i < p.head_dim / 2; i += blockDim.x) rope_entry(p.cs, r, i, p.head_dim, pos[r], p.theta);
 }
 
-// Draft forward 1 of a tree: n_new rows behind the context, causal among themselves; their bookkeeping comes with their input
+// Draft forward 1 of a tree: n_new rows behind the context, causal among themselves (or, without mask and seq, rows of which only the keys and
+// values are wanted); their bookkeeping comes with their input
 // (a launch of its own cost 4.7 us).  Further workgroups form the rotary tables of the later forwards, whose rows share one position each.
 template <bool BF16, int VPT>
 __global__ __launch_bounds__(1024) void draft_first_kernel(DraftInput<BF16> p, const int32_t* __restrict__ tok, const float* __restrict__ feat,
@@ -229,13 +288,13 @@ __global__ __launch_bounds__(1024) void draft_first_kernel(DraftInput<BF16> p, c
   if (r >= n_new + depth - 1) return;
   const int P = prefix_len[0], base = kv_indptr[0];
   if (r < n_new) {
-    if (tid < 4) {
+    if (mask && tid < 4) {
       const int lo = 32 * tid;
       mask[r * 4 + tid] = r < lo ? 0u : (r - lo >= 31 ? 0xFFFFFFFFu : ((2u << (r - lo)) - 1u));     // bits 0..r
     }
     if (tid == 0) {
       slot[r] = base + P + r;
-      if (r == 0) { seq[0].kv_base = base; seq[0].n_prefix = P; seq[0].n_tail = n_new; seq[0].order = 0; }
+      if (seq && r == 0) { seq[0].kv_base = base; seq[0].n_prefix = P; seq[0].n_tail = n_new; seq[0].order = 0; }
     }
     DraftGains<BF16, VPT> gains;
     load_gains(p, gains);
@@ -244,70 +303,18 @@ __global__ __launch_bounds__(1024) void draft_first_kernel(DraftInput<BF16> p, c
   for (int i = tid; i < p.head_dim / 2; i += blockDim.x) rope_entry(p.cs, r, i, p.head_dim, P + r, p.theta);
 }
 
-// Rows of a prefill chunk, four per workgroup: row r continues the sequence at position P + r.  For attention the chunk is
-// cut into blocks of 64 rows: block b sees the context and every earlier block unconditionally (n_prefix = P + 64 b) and its
-// own rows causally through the row masks, so the tree kernels run a chunk of any length as a batch of "sequences" that
-// share one cache.  The last block has the most keys, so it is handed out first.
-__global__ __launch_bounds__(256) void prefill_prep_kernel(const int32_t* __restrict__ kv_indptr,
-                                                          const int32_t* __restrict__ prefix_len, int n, int d, float theta,
-                                                          int32_t* __restrict__ pos, int32_t* __restrict__ slot,
-                                                          uint32_t* __restrict__ mask, float* __restrict__ cs,
-                                                          SeqInfo* __restrict__ seq) {
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (r >= n) return;
-  const int P = prefix_len[0], base = kv_indptr[0], j = r & 63, b = r >> 6;
-  if (lane < 4) {                                        // causal inside the block: bits 0..j
-    const int lo = 32 * lane;
-    mask[r * 4 + lane] = j < lo ? 0u : (j - lo >= 31 ? 0xFFFFFFFFu : ((2u << (j - lo)) - 1u));
-  }
-  if (lane == 0) {
-    pos[r] = P + r;
-    slot[r] = base + P + r;
-    if (j == 0) {
-      seq[b].kv_base = base; seq[b].n_prefix = P + r; seq[b].n_tail = min(64, n - r);
-      seq[b].order = (n + 63) / 64 - 1 - b;
-    }
-  }
-  if (cs)
-    for (int i = lane; i < d / 2; i += 64) rope_entry(cs, r, i, d, P + r, theta);
-}
-
-__global__ __launch_bounds__(64) void advance_lengths_kernel(int32_t* __restrict__ len, int B, int by) {
-  const int b = blockIdx.x * 64 + threadIdx.x;
-  if (b < B) len[b] += by;
+// The end of a prefill chunk: n positions are in the target's cache and m in the draft's; the last fused features go to their place.
+__global__ __launch_bounds__(256) void end_prefill_kernel(int32_t* __restrict__ len, int n, int32_t* __restrict__ draft_len, int m,
+                                                         const float* __restrict__ g, int k, float* __restrict__ g_last) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i == 0) { len[0] += n; draft_len[0] += m; }
+  if (g_last && i < k) g_last[i] = g[i];
 }
 
 }  // namespace
 
-hipError_t launch_prefill_prep(const int32_t* kv_indptr, const int32_t* prefix_len, int n, int head_dim, float theta,
-                               int32_t* pos, int32_t* slot, uint32_t* mask, float* cs, SeqInfo* seq, hipStream_t st) {
-  if (n < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(prefill_prep_kernel, dim3((n + 3) / 4), dim3(256), 0, st, kv_indptr, prefix_len, n, head_dim, theta, pos,
-                     slot, mask, cs, seq);
-  return hipGetLastError();
-}
-hipError_t launch_advance_lengths(int32_t* len, int B, int by, hipStream_t st) {
-  hipLaunchKernelGGL(advance_lengths_kernel, dim3((B + 63) / 64), dim3(64), 0, st, len, B, by);
-  return hipGetLastError();
-}
-
-#define DISPATCH_BF16(flag, KERNEL, grid, block, st, ...)                                       \
-  do {                                                                                          \
-    if (flag) hipLaunchKernelGGL(KERNEL<true>, grid, block, 0, st, __VA_ARGS__);               \
-    else hipLaunchKernelGGL(KERNEL<false>, grid, block, 0, st, __VA_ARGS__);                   \
-  } while (0)
-
-hipError_t launch_embed_rows(bool bf16, const void* embed, const int32_t* tok, int R, int k, int vocab, float* x,
-                             hipStream_t st) {
-  const bool vec = k % 4 == 0 && ((uintptr_t)embed & 15) == 0;
-  const dim3 grid(R, ((vec ? k / 4 : k) + 255) / 256);
-  if (bf16) {
-    auto kernel = vec ? embed_rows_kernel<bf16_t, true> : embed_rows_kernel<bf16_t, false>;
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, (const bf16_t*)embed, tok, k, vocab, x);
-  } else {
-    auto kernel = vec ? embed_rows_kernel<float, true> : embed_rows_kernel<float, false>;
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, (const float*)embed, tok, k, vocab, x);
-  }
+hipError_t launch_end_prefill(int32_t* len, int n, int32_t* draft_len, int m, const float* g, int k, float* g_last, hipStream_t st) {
+  hipLaunchKernelGGL(end_prefill_kernel, dim3(g_last ? (k + 255) / 256 : 1), dim3(256), 0, st, len, n, draft_len, m, g, k, g_last);
   return hipGetLastError();
 }
 
@@ -326,14 +333,20 @@ hipError_t launch_add_norm(bool bf16, float* x, const float* partial, int S, int
   return hipGetLastError();
 }
 
-hipError_t launch_tree_prep(const int32_t* parent, const int32_t* kv_indptr, const int32_t* prefix_len, int B, int N,
-                            int head_dim, float theta, int32_t* depth, uint32_t* mask, int32_t* slot, float* cs,
-                            SeqInfo* seq, hipStream_t st) {
-  if (N > 64) return hipErrorInvalidValue;
-  // enough workgroups that each thread computes one or two table entries, no more than ~1024 workgroups in all
-  const int per_seq = std::max(1, std::min((N * (head_dim / 2) + 511) / 512, std::max(1, 1024 / B)));
-  hipLaunchKernelGGL(tree_prep_kernel, dim3(B, per_seq), dim3(256), 0, st, parent, kv_indptr, prefix_len, N, head_dim, theta, depth,
-                     mask, slot, cs, seq);
+hipError_t launch_begin_rows(bool bf16, const BeginRows& b, float* x, int R, int k, const void* gain, float eps, void* act,
+                             float* const copy_out[4], hipStream_t st) {
+  if (k % 4 || k > 8192 || (b.parent && b.N > 64)) return hipErrorInvalidValue;
+  CopyOut co;
+  for (int i = 0; i < 4; ++i) co.p[i] = copy_out ? copy_out[i] : nullptr;
+  const int threads = std::min(1024, std::max((k / 4 + 63) / 64, 4) * 64);
+  // trees: 512 entries of the rotary table (fp64 sines and cosines) to a workgroup, no more than ~1024 workgroups in all; prefill: a wavefront per row
+  const int parts = std::max(1, std::min((b.N * (b.head_dim / 2) + 511) / 512, std::max(1, 1024 / std::max(1, b.B))));
+  const int prep = b.parent ? b.B * parts : (R + threads / 64 - 1) / (threads / 64), prep_wgs = (prep + 7) / 8 * 8;
+  const dim3 grid(prep_wgs + (bf16 ? rows_grid(R) : R));
+  if (bf16)
+    hipLaunchKernelGGL(begin_rows_kernel<true>, grid, dim3(threads), 0, st, b, prep_wgs, parts, x, R, k, (const bf16_t*)gain, eps, (bf16_t*)act, co);
+  else
+    hipLaunchKernelGGL(begin_rows_kernel<false>, grid, dim3(threads), 0, st, b, prep_wgs, parts, x, R, k, (const float*)gain, eps, (float*)act, co);
   return hipGetLastError();
 }
 
@@ -384,7 +397,7 @@ hipError_t launch_draft_input(bool bf16, const DraftInputArgs& a, const int32_t*
 hipError_t launch_draft_first(bool bf16, const DraftInputArgs& a, const int32_t* tok, const float* feat, const int32_t* kv_indptr,
                               const int32_t* prefix_len, int n_new, int depth, int32_t* slot, uint32_t* mask, SeqInfo* seq,
                               hipStream_t st) {
-  if (!draft_input_ok(a) || n_new < 1 || n_new > 64 || depth < 1) return hipErrorInvalidValue;
+  if (!draft_input_ok(a) || n_new < 1 || (mask && n_new > 64) || depth < 1) return hipErrorInvalidValue;
   const int threads = draft_input_threads(a.k), rows = n_new + depth - 1;
   return with_input(bf16, a.k, threads, [&](auto type, auto passes) {
     hipLaunchKernelGGL((draft_first_kernel<type.value, passes.value>), dim3(bf16 ? rows_grid(rows) : rows), dim3(threads), 0, st,

@@ -61,15 +61,31 @@ struct SeqInfo {           // one per sequence, device resident
   int32_t order;           // entry i: the sequence that attention workgroup group i works on (longest first)
 };
 
-hipError_t launch_embed_rows(bool bf16, const void* embed, const int32_t* tok, int R, int k, int vocab, float* x,
-                             hipStream_t st);
+// The first launch of a pass over R rows: bookkeeping, and the rows' residual.
+struct BeginRows {
+  const void* embed;                    // x = embed[tok], or x_in where that is given
+  const int32_t* tok;
+  int vocab;
+  const float* x_in;
+  const int32_t* parent;                // B trees of N nodes: 128-bit ancestor masks; null: a prefill chunk, causal masks in blocks of 64 rows
+  int B, N;
+  const int32_t* kv_indptr;
+  const int32_t* prefix_len;
+  int head_dim;
+  float theta;
+  int32_t* slot;                        // [R] cache slots
+  uint32_t* mask;                       // [R][4]
+  float* cs;                            // [R][head_dim] rotary tables
+  SeqInfo* seq;                         // one per tree, or block
+};
+// copies x to each non-null copy_out; with a gain: act = RMSNorm(x; gain) in the activation layout
+hipError_t launch_begin_rows(bool bf16, const BeginRows& b, float* x, int R, int k, const void* gain, float eps, void* act,
+                             float* const copy_out[4], hipStream_t st);
+// After a prefill chunk: len[0] += n, draft_len[0] += m, g_last (optional) = g.
+hipError_t launch_end_prefill(int32_t* len, int n, int32_t* draft_len, int m, const float* g, int k, float* g_last, hipStream_t st);
 // x += sum_s partial[s]; copies x to each non-null copy_out; act = RMSNorm(x; gain) in the activation layout.
 hipError_t launch_add_norm(bool bf16, float* x, const float* partial, int S, int R, int k, const void* gain, float eps,
                            void* act, float* const copy_out[4], hipStream_t st);
-// Tree bookkeeping for verification: depth, 128-bit ancestor masks, cache slot and rotary tables per row.
-hipError_t launch_tree_prep(const int32_t* parent, const int32_t* kv_indptr, const int32_t* prefix_len, int B, int N,
-                            int head_dim, float theta, int32_t* depth, uint32_t* mask, int32_t* slot, float* cs,
-                            SeqInfo* seq, hipStream_t st);
 // bf16: sums the q|k|v split-K partials, rotates q and k, writes q [R,H,d] and the cache rows.  cs_step: from a row's rotary table to the
 // next one's (0: all rows at one position).
 hipError_t launch_rope_kv_write(const float* qkv_partial, int S, int R, int H, int Hkv, int d, const float* cs, int cs_step,
@@ -92,16 +108,10 @@ struct DraftInputArgs {
 hipError_t launch_draft_input(bool bf16, const DraftInputArgs& a, const int32_t* tok, const float* feat, const int32_t* pos, int M,
                               hipStream_t st);
 // The same for draft forward 1 of a tree (the n_new positions behind the context), with slots, causal masks, sequence info, and the
-// rotary tables of the later forwards: cs[n_new + l - 2] is that of forward l.
+// rotary tables of the later forwards: cs[n_new + l - 2] is that of forward l.  Without mask and seq: any number of rows.
 hipError_t launch_draft_first(bool bf16, const DraftInputArgs& a, const int32_t* tok, const float* feat, const int32_t* kv_indptr,
                               const int32_t* prefix_len, int n_new, int depth, int32_t* slot, uint32_t* mask, SeqInfo* seq,
                               hipStream_t st);
-
-// Rows of a prefill chunk of n positions: positions, slots, causal masks inside blocks of 64 rows, one SeqInfo per block,
-// rotary tables (cs may be null).
-hipError_t launch_prefill_prep(const int32_t* kv_indptr, const int32_t* prefix_len, int n, int head_dim, float theta,
-                               int32_t* pos, int32_t* slot, uint32_t* mask, float* cs, SeqInfo* seq, hipStream_t st);
-hipError_t launch_advance_lengths(int32_t* len, int B, int by, hipStream_t st);          // len[b] += by
 
 // ---------------------------------------------------------------- attention (attention.hip)
 // Tree-masked attention of rows [B * rows_per_seq] against a (ragged) cache.
