@@ -152,6 +152,14 @@ struct eagle3_ctx {
     ws_need = cv.off;
   }
 
+  Stamp* stamp(double bytes, int kind) {               // of the next GEMM launch, where launches are timed
+    if (!profiling || stamps_used >= stamps.size()) return nullptr;
+    Stamp* sp = &stamps[stamps_used++];
+    sp->bytes = bytes;
+    sp->kind = kind;
+    return sp;
+  }
+
   DraftInputArgs draft_input_args() const {
     return {tw.embed, dw.norm_embed, dw.norm_feat, act_k, x, cs, cfg.vocab, cfg.hidden, cfg.head_dim, cfg.rms_eps, cfg.rope_theta};
   }
@@ -161,8 +169,7 @@ struct eagle3_ctx {
   int project(const void* act_in, const GemmWeights& W, int M, int N, int K, int epi, int* S_out, hipStream_t st,
               float* direct_out = nullptr) {
     if (bf16 && M > 64) {
-      Stamp* sp = profiling && stamps_used < stamps.size() ? &stamps[stamps_used++] : nullptr;
-      if (sp) { sp->bytes = 2.0 * N * K; sp->kind = EAGLE3_GEMM_MANY_ROWS; }
+      Stamp* sp = stamp(2.0 * N * K, EAGLE3_GEMM_MANY_ROWS);
       int S = 1;
       // A result that goes straight to its place is not split, except where more inputs than outputs leave CUs idle (the fusion
       // of a prompt's features, K = 3 N: the partial sums are small against the weights then).  8B width, us, unsplit / split and
@@ -184,11 +191,7 @@ struct eagle3_ctx {
       const int S = t.S;
       if (epi == GEMM_EPI_PARTIAL && direct_out == nullptr && (size_t)S * M * N > part_floats) return EAGLE3_E_STATE;
       void* out = epi == GEMM_EPI_SWIGLU ? act_h : (direct_out && S == 1 ? (void*)direct_out : (void*)part);
-      Stamp* sp = profiling && stamps_used < stamps.size() ? &stamps[stamps_used++] : nullptr;
-      if (sp) {
-        sp->bytes = 2.0 * N * K;
-        sp->kind = M <= 32 ? EAGLE3_GEMM_FEW_ROWS : t.cols == 64 ? EAGLE3_GEMM_TILE64 : EAGLE3_GEMM_TILE128;
-      }
+      Stamp* sp = stamp(2.0 * N * K, M <= 32 ? EAGLE3_GEMM_FEW_ROWS : t.cols == 64 ? EAGLE3_GEMM_TILE64 : EAGLE3_GEMM_TILE128);
       if (t.cols == 64)
         CK(launch_gemm_skinny((const bf16_t*)act_in, W, M, N, K, S, epi, out, st, sp ? sp->a : nullptr, sp ? sp->b : nullptr));
       else
@@ -403,6 +406,13 @@ static int project_qkv(eagle3_ctx* ctx, const eagle3_layer_weights& w, void* in,
     TRY(norm_operand(ctx, (float*)in, gain, R, (H + 2 * Hkv) * d, K, true, f, &rows, st));
     f.cs = cs; f.cs_step = cs_step; f.slot = slot; f.kc = (float*)kc; f.vc = (float*)vc; f.H = H; f.Hkv = Hkv; f.d = d;
     CK(launch_gemm_f32(rows, Wqkv, R, (H + 2 * Hkv) * d, K, GEMM_EPI_ROPE, (float*)ctx->q, st, f));
+    return EAGLE3_OK;
+  }
+  const int N = (H + 2 * Hkv) * d;
+  if (wide_rope_fits(R, N, K, ctx->part_floats)) {
+    const WideRope rope = {cs, cs_step, slot, H, Hkv, (bf16_t*)ctx->q, (bf16_t*)kc, (bf16_t*)vc};
+    eagle3_ctx::Stamp* sp = ctx->stamp(2.0 * N * K, EAGLE3_GEMM_MANY_ROWS);
+    CK(launch_gemm_wide_rope((const bf16_t*)in, Wqkv, R, N, K, rope, ctx->part_floats, st, sp ? sp->a : nullptr, sp ? sp->b : nullptr));
     return EAGLE3_OK;
   }
   int S = 1;

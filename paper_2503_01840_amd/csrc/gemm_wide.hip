@@ -63,11 +63,12 @@ struct WideParams {
   int tiles, groups, mblocks;           // weight tiles, ceil(tiles / 8), activation-row blocks
   float* out_f32;
   bf16_t* out_xf;
+  WideRope rope;
 };
 
 // Global weight row behind row `row` of workgroup tile `tile` (TN rows per tile).  SwiGLU: every 2 PAIR rows of a tile are PAIR gate
 // rows and the PAIR up rows that belong to them.  Rows past the end repeat the last one.
-template <int TN, int PAIR>
+template <int TN, int PAIR, bool ROPE>
 __device__ __forceinline__ const bf16_t* weight_row(const WideParams& p, int tile, int row, int& left) {
   if (p.mode == 1) {
     const int r = tile * (TN / 2) + row / (2 * PAIR) * PAIR + row % PAIR, last = p.rows[0] - 1;
@@ -76,6 +77,10 @@ __device__ __forceinline__ const bf16_t* weight_row(const WideParams& p, int til
   }
   int n = min(tile * TN + row, p.N - 1);
   left = p.N - 1 - n;
+  if (ROPE) {                                          // every 32 rows: 16 of the first half of a head and the 16 they are rotated with
+    n = (n & ~127) + (n >> 5 & 3) * 16 + (n & 15) + (n & 16) * 4;
+    left = tile * TN + row < p.N ? 7 : 0;              // N is a multiple of 128: a piece's rows (8 or 4) are there, or all of it is behind the end
+  }
   const bf16_t* w = p.w[0];
   if (p.nmat > 1 && n >= p.rows[0]) {
     n -= p.rows[0]; w = p.w[1];
@@ -107,7 +112,7 @@ __device__ __forceinline__ void unroll(F f) { unroll_seq(std::make_integer_seque
 #define WIDE_WAIT_BARRIER(n) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(n) : "memory")
 #define WIDE_PIN() __builtin_amdgcn_sched_barrier(0)
 
-template <int WGM, int WGN, int FM, int FB, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER, int SETS>
+template <int WGM, int WGN, int FM, int FB, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER, int SETS, bool ROPE>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WideParams p) {
   constexpr int FA = 2 * FM;                           // 16-row fragments of a wavefront's activation rows; FB: of its weight rows
   constexpr int TM = 32 * FM * WGM, TN = 16 * FB * WGN, NW = WGM * WGN;
@@ -161,7 +166,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   for (int i = 0; i < B_DMA; ++i) {
     const int row = B_ROWS * (b_first + i), r = lane / B_LANES;
     int left;                                          // rows behind this one
-    bptr[i] = weight_row<TN, PAIR>(p, tile, row, left) + k_begin;
+    bptr[i] = weight_row<TN, PAIR, ROPE>(p, tile, row, left) + k_begin;
     b_off[i] = (uint32_t)min(r, left) * (uint32_t)p.K * 2 + (((lane % B_LANES) ^ swizzle(row + r)) * 16);
   }
   const uint32_t a_lds = lds0 + a_first * 1024, b_lds = lds0 + B_BASE + b_first * 1024;
@@ -309,7 +314,38 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
 
   // ---- epilogue.  Accumulator r of lane l: activation row l % 16 of its fragment, weight row 4 (l / 16) + r of its own.
   auto row_of = [&](int i) { return mblock * TM + (WGM == 2 ? (i >> 1) * 64 + wm * 32 : wm * 64 + (i >> 1) * 32) + (i & 1) * 16 + (lane & 15); };
-  if (p.epi == GEMM_EPI_PARTIAL) {
+  if constexpr (ROPE) {
+    // Fragments 2 j and 2 j + 1 hold dimensions i .. i + 3 and i + 64 .. i + 67 of the same head: rotated (q, k), and straight to q or the cache.
+    const WideRope& rp = p.rope;
+#pragma unroll
+    for (int i = 0; i < FA; ++i) {
+      const int m = row_of(i);
+      if (m >= p.M) continue;
+      const float* cs = rp.cs + (size_t)m * rp.cs_step;
+      const size_t slot = (size_t)rp.slot[m];
+#pragma unroll
+      for (int f = 0; f < FB; f += 2) {
+        const int n = tile * TN + wn * 16 * FB + f * 16;
+        if (n >= p.N) continue;
+        const int head = n >> 7, d = (n >> 5 & 3) * 16 + 4 * c;
+        floatx4 x1 = acc[i][f], x2 = acc[i][f + 1];
+        if (head < rp.H + rp.Hkv) {
+          const floatx4 co = *(const floatx4*)(cs + d), si = *(const floatx4*)(cs + 64 + d);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float a = x1[e], b = x2[e];
+            x1[e] = a * co[e] - b * si[e];
+            x2[e] = b * co[e] + a * si[e];
+          }
+        }
+        bf16_t* dst = head < rp.H             ? rp.q + ((size_t)m * rp.H + head) * 128
+                      : head < rp.H + rp.Hkv ? rp.kc + (slot * rp.Hkv + head - rp.H) * 128
+                                             : rp.vc + (slot * rp.Hkv + head - rp.H - rp.Hkv) * 128;
+        store4_plain(dst, d, x1[0], x1[1], x1[2], x1[3]);
+        store4_plain(dst, d + 64, x2[0], x2[1], x2[2], x2[3]);
+      }
+    }
+  } else if (p.epi == GEMM_EPI_PARTIAL) {
     float* out = p.out_f32 + (size_t)split * p.M * p.N;
 #pragma unroll
     for (int i = 0; i < FA; ++i) {
@@ -355,11 +391,11 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   }
 }
 
-template <int WGM, int WGN, int FM, int FB, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER = false, int SETS = 1>
+template <int WGM, int WGN, int FM, int FB, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER = false, int SETS = 1, bool ROPE = false>
 hipError_t launch_cfg(WideParams& p, int S, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   constexpr int TM = 32 * FM * WGM, TN = 16 * FB * WGN;
   constexpr int LDS = A_SLOTS * TM * 64 + B_SLOTS * TN * BK * 2;
-  auto kernel = gemm_wide_kernel<WGM, WGN, FM, FB, BK, A_SLOTS, B_SLOTS, OCC, STAGGER, SETS>;
+  auto kernel = gemm_wide_kernel<WGM, WGN, FM, FB, BK, A_SLOTS, B_SLOTS, OCC, STAGGER, SETS, ROPE>;
   static DeviceOnce configured;                        // the attribute belongs to the loaded code object of a device
   hipError_t ce = configured.run([&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS); });
   if (ce != hipSuccess) return ce;
@@ -422,6 +458,29 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   if (t.cols == 192) return launch_cfg<4, 2, 2, 6, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
   return t.rows == 256 ? launch_cfg<2, 4, 4, 4, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop)
                        : launch_cfg<2, 4, 3, 4, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
+}
+
+// q/k/v of more than 256 rows, rotated and in their places, where the product is not split and its tile has fragments in pairs.  As 50 MB of fp32 results
+// and a kernel of its own that read them (rope_kv_write_kernel, whose arithmetic this is) the rotation of 2048 rows of 6144 took 16 us of a layer's 850,
+// here the product takes 2 longer: 2048 tokens 26.08 -> 25.65 ms.  224 weight rows have seven fragments to a wavefront, and 128 x 128 tiles are few
+// enough rows for the kernel: they stay with it.
+bool wide_rope_fits(int M, int N, int K, size_t out_capacity_floats) {
+  if (M <= 256 || N % 128) return false;
+  const WideTiles t = launch_tiles(M, N, K, false, out_capacity_floats);
+  return t.S == 1 && t.cols != 224 && (t.cols != 128 || (t.rows == 256 && t.k == 128));
+}
+hipError_t launch_gemm_wide_rope(const bf16_t* x, const GemmWeights& W, int M, int N, int K, const WideRope& rope, size_t out_capacity_floats,
+                                 hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  WideParams p;
+  if (!wide_rope_fits(M, N, K, out_capacity_floats)) return hipErrorInvalidValue;
+  if (hipError_t e = fill_params(p, x, W, M, N, K, GEMM_EPI_PARTIAL, nullptr)) return e;
+  p.S = 1;
+  p.rope = rope;
+  const WideTiles t = launch_tiles(M, N, K, false, out_capacity_floats);
+  if (t.cols == 192) return launch_cfg<4, 2, 2, 6, 64, 4, 3, 1, false, 1, true>(p, 1, st, ev_start, ev_stop);
+  if (t.cols == 128) return launch_cfg<4, 2, 2, 4, 128, 4, 3, 1, false, 2, true>(p, 1, st, ev_start, ev_stop);
+  return t.rows == 256 ? launch_cfg<2, 4, 4, 4, 64, 4, 3, 1, false, 1, true>(p, 1, st, ev_start, ev_stop)
+                       : launch_cfg<2, 4, 3, 4, 64, 4, 3, 1, false, 1, true>(p, 1, st, ev_start, ev_stop);
 }
 
 // At most 64 rows, in tiles of 64 x cols.

@@ -32,6 +32,20 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
                             size_t out_capacity_floats, int* S_out, hipStream_t st, hipEvent_t ev_start = nullptr,
                             hipEvent_t ev_stop = nullptr);
 
+// q/k/v (W: their three matrices, head size 128) rotated, k and v in the cache rows slot[m]; where wide_rope_fits says so.
+struct WideRope {
+  const float* cs = nullptr;            // rotary tables, cs_step from one row's to the next one's
+  int cs_step = 0;
+  const int32_t* slot = nullptr;
+  int H = 0, Hkv = 0;
+  bf16_t* q = nullptr;                  // [M, H, 128]
+  bf16_t* kc = nullptr;
+  bf16_t* vc = nullptr;
+};
+bool wide_rope_fits(int M, int N, int K, size_t out_capacity_floats);
+hipError_t launch_gemm_wide_rope(const bf16_t* x, const GemmWeights& W, int M, int N, int K, const WideRope& rope, size_t out_capacity_floats,
+                                 hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+
 // The same for at most 64 rows in tiles of 64 x cols (128 or 256), in S ranges of K.  Weights at multiples of 16 bytes.
 hipError_t launch_gemm_wide64(const bf16_t* x, const GemmWeights& W, int M, int N, int K, int cols, int S, int epi, void* out,
                               hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);

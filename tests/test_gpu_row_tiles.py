@@ -81,6 +81,18 @@ def test_rows_in_tiles_that_make_up_whole_rounds(name, B, N, group):
     _rows_alone_and_together(mha if name == "mha" else FEW[name].with_(vocab=1024), B, N, group, logits=True)
 
 
+# q/k/v rotated and put into the cache by the product, where it is not split: each tile that does so, row blocks and weight rows that end within
+# one ("ragged"), against at most 64 rows at a time.  (q heads, KV heads, hidden, sequences, rows of each)
+ROTATED = {"192": (56, 8, 512, 64, 20), "192-ragged": (56, 7, 512, 64, 20), "8b": (32, 8, 4096, 64, 20), "256x256": (64, 16, 256, 55, 20), "192x256": (48, 8, 1024, 55, 20),
+           "256x128": (32, 4, 512, 55, 20)}
+
+
+@pytest.mark.parametrize("name", list(ROTATED))
+def test_rows_rotated_by_the_product(name):
+    H, G, hidden, B, N = ROTATED[name]
+    _rows_alone_and_together(S.get_shape("c3").with_(name=f"r{name}", hidden=hidden, n_heads=H, n_kv_heads=G, intermediate=1024, vocab=1024), B, N, 64 // N)
+
+
 def _rows_alone_and_together(full, B, N, group, logits=False):
     """All B sequences of N rows at once against `group` of them at a time; one sequence: against its first 32 rows."""
     E = _E()

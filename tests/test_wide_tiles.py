@@ -245,3 +245,13 @@ def test_whole_rounds_that_the_gpu_tests_cover(launched):
             p = _products(name, M)[i]
             launch, base = launched([(M, *p[:3], p[4])])[0]
             assert launch == base, (name, M, i)
+
+
+# the tiles of test_rows_rotated_by_the_product
+def test_unsplit_tiles_that_the_gpu_tests_cover(launched):
+    for H, G, k, M, want in [(56, 8, 512, 1280, (256, 192, 1, 64)), (56, 7, 512, 1280, (256, 192, 1, 64)), (32, 8, 4096, 1280, (256, 128, 1, 128)), (64, 16, 256, 1100, (256, 256, 1, 64)),
+                             (48, 8, 1024, 1100, (192, 256, 1, 64)), (32, 4, 512, 1100, (256, 128, 1, 128))]:
+        n = (H + 2 * G) * 128
+        widest = max(n, k)
+        cap = max(1024 * widest, 4 * M * widest, 8 * M * k, 2 * 2048 * widest)
+        assert launched([(M, n, k, 0, cap)])[0][0] == want, (H, G, k, M)
