@@ -120,7 +120,7 @@ struct eagle3_ctx {
     attn_scratch = cv.take<float>(attn_floats);
     mask = cv.take<uint32_t>((size_t)Rall * 4);
     slot = cv.take<int32_t>(Rall);
-    cs = cv.take<float>((size_t)std::max(Rall, c.max_new + c.max_depth) * c.head_dim);
+    cs = cv.take<float>((size_t)Rall * c.head_dim);
     seq = cv.take<SeqInfo>(std::max(c.max_batch, (chunk_max + 63) / 64));
     accept_stats = cv.take<float>(accept_scratch_floats(R_max, c.vocab));
     const int mb = std::max(c.max_batch, 1);
@@ -600,14 +600,18 @@ int eagle3_draft_expand(eagle3_ctx* ctx, const float* g_new, const int32_t* tok_
   void* vc = dkv->v[0];
 
   const DraftInputArgs in = ctx->draft_input_args();
-  CK(launch_draft_first(ctx->bf16, in, tok_new, g_new, dkv->kv_indptr, dkv->prefix_len, n_new, depth, ctx->slot, ctx->mask, ctx->seq, st));
+  // the rotary tables of all forwards at once, or, in the smallest workspaces, one after the other
+  const bool all_tables = n_new + depth - 1 <= ctx->Rall;
+  CK(launch_draft_first(ctx->bf16, in, tok_new, g_new, dkv->kv_indptr, dkv->prefix_len, n_new, all_tables ? depth : 1, ctx->slot, ctx->mask,
+                        ctx->seq, st));
   for (int level = 1; level <= depth; ++level) {
     const int M = level == 1 ? n_new : K;
     const int a_row0 = level == 1 ? 0 : n_new + (level - 2) * K;
     const bool first = level == 1;
     const int max_len = dkv->max_prefix_len + n_new + (level - 1) * K;
+    if (!first && !all_tables) CK(launch_rope_table(ctx->cs, dkv->prefix_len, n_new + level - 2, d, c.rope_theta, st));
     TRY(project_qkv(ctx, w, ctx->act_k, nullptr, 2 * k, M, first ? ctx->slot : ds.row_slot,
-                    first ? ctx->cs : ctx->cs + (size_t)(n_new + level - 2) * d, first ? d : 0, kc, vc, st));
+                    first || !all_tables ? ctx->cs : ctx->cs + (size_t)(n_new + level - 2) * d, first ? d : 0, kc, vc, st));
     // a = y1 + MLP(...): keep it for the children, and norm it for the LM head
     float* copies[4] = {ctx->a_buf + (size_t)a_row0 * k, nullptr, nullptr, nullptr};
     int S_down = 1;

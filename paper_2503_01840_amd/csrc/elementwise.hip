@@ -303,6 +303,11 @@ __global__ __launch_bounds__(1024) void draft_first_kernel(DraftInput<BF16> p, c
   for (int i = tid; i < p.head_dim / 2; i += blockDim.x) rope_entry(p.cs, r, i, p.head_dim, P + r, p.theta);
 }
 
+__global__ __launch_bounds__(128) void rope_table_kernel(float* __restrict__ cs, const int32_t* __restrict__ prefix_len, int at, int d,
+                                                        float theta) {
+  for (int i = threadIdx.x; i < d / 2; i += 128) rope_entry(cs, 0, i, d, prefix_len[0] + at, theta);
+}
+
 // The end of a prefill chunk: n positions are in the target's cache and m in the draft's; the last fused features go to their place.
 __global__ __launch_bounds__(256) void end_prefill_kernel(int32_t* __restrict__ len, int n, int32_t* __restrict__ draft_len, int m,
                                                          const float* __restrict__ g, int k, float* __restrict__ g_last) {
@@ -312,6 +317,11 @@ __global__ __launch_bounds__(256) void end_prefill_kernel(int32_t* __restrict__ 
 }
 
 }  // namespace
+
+hipError_t launch_rope_table(float* cs, const int32_t* prefix_len, int at, int head_dim, float theta, hipStream_t st) {
+  hipLaunchKernelGGL(rope_table_kernel, dim3(1), dim3(128), 0, st, cs, prefix_len, at, head_dim, theta);
+  return hipGetLastError();
+}
 
 hipError_t launch_end_prefill(int32_t* len, int n, int32_t* draft_len, int m, const float* g, int k, float* g_last, hipStream_t st) {
   hipLaunchKernelGGL(end_prefill_kernel, dim3(g_last ? (k + 255) / 256 : 1), dim3(256), 0, st, len, n, draft_len, m, g, k, g_last);

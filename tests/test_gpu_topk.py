@@ -93,3 +93,24 @@ def test_draft_expand_over_pool_sizes_and_widths(D, K, N, hidden):
         assert np.array_equal(got[key], ref[key]), key
     # fp32 logits and their log-sum-exp, 1e-4 for up to three levels as above, each further level adding as much as one of those
     assert np.max(np.abs(got["score"] - ref["score"])) < 1e-4 * max(1.0, D / 3)
+
+
+# the smallest workspace holds fewer rotary tables than there are forwards: the same tree
+@pytest.mark.parametrize("n_new,D,K", [(4, 8, 2), (1, 5, 1), (4, 2, 2)])
+def test_draft_expand_in_the_smallest_workspace(n_new, D, K):
+    import paper_2503_01840_amd as E
+    shape = S.get_shape("c1")
+    W = PL.device_weights(shape, device=DEV)
+    inp = PL.synthetic_step_inputs(shape, n_new=n_new, prefix=42)
+    out = []
+    for small in (False, True):
+        ctx = E.Eagle3Context(shape, max_batch=1, max_nodes=4, max_depth=8, max_topk=2, max_new=4, device=DEV)
+        ctx.set_weights(W["target"], W["draft"])
+        beyond = PL.beyond_workspace(ctx, PL.shrink_workspace(ctx)) if small else None
+        ks, vs, indptr, plen, P = PL.device_kv([inp["draft_kv"]], n_new + (D - 1) * K, DEV)
+        tree = E.eagle3_draft_expand(ctx, inp["g_new"].to(DEV), inp["tok_new"].to(DEV), E.KVCache(ks, vs, indptr, plen, P), D, K, 4)
+        torch.cuda.synchronize()
+        assert beyond is None or bool((beyond == 171).all())
+        out.append((tree, ks[0], vs[0]))
+    assert all(torch.equal(out[0][0][n], out[1][0][n]) for n in out[0][0])
+    assert torch.equal(out[0][1], out[1][1]) and torch.equal(out[0][2], out[1][2])
