@@ -81,8 +81,9 @@ __device__ __forceinline__ void draft_input_row(const DraftInput<BF16>& p, int r
       sf += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
     }
   }
-  se = wave_sum_butterfly(se);
-  sf = wave_sum_butterfly(sf);
+  // sums in the order of block_sum, as every norm has them: a last bit of an input can turn over candidates that are all but tied
+  se = wave_sum(se);
+  sf = wave_sum(sf);
   if ((threadIdx.x & 63) == 0) { sums.e[threadIdx.x >> 6] = se; sums.f[threadIdx.x >> 6] = sf; }
   __syncthreads();
   se = sf = 0.f;
