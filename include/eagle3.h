@@ -165,7 +165,7 @@ int eagle3_tree_verify(eagle3_ctx* ctx, int32_t B, int32_t N, const int32_t* tre
 /* The same forward restricted to target layers [layer_begin, layer_end): the building block of a
  * layer-sharded (pipelined) deployment, and the way to check single layers at full size.
  *   x_in   fp32 [B, N, hidden] residual stream entering layer_begin; NULL = token embeddings
- *          (then layer_begin must be 0)
+ *          (then layer_begin must be 0); moved by the runtime's copy, so it may be another GPU's memory
  *   x_out  fp32 [B, N, hidden] residual stream after layer_end - 1, or NULL
  *   logits fp32 [B, N, vocab] or NULL; non-NULL requires layer_end == n_layers (final norm + LM head)
  * kv->k / kv->v are indexed by absolute layer number; only entries of the range are read.  At least one

@@ -543,7 +543,9 @@ static int verify_layers(eagle3_ctx* ctx, int B, int N, const int32_t* tree_tok,
                          float* dbg_hidden, hipStream_t st) {
   const eagle3_config& c = ctx->cfg;
   const int R = B * N;
-  const BeginRows begin = {ctx->tw.embed, tree_tok, c.vocab, x_in, parent, B, N, kv->kv_indptr, kv->prefix_len, (int)c.head_dim, c.rope_theta,
+  // by the runtime: x_in may lie in memory that no kernel of this GPU can read (another GPU's, without peer access)
+  if (x_in) CK(hipMemcpyAsync(ctx->x, x_in, (size_t)R * c.hidden * sizeof(float), hipMemcpyDeviceToDevice, st));
+  const BeginRows begin = {x_in ? nullptr : ctx->tw.embed, tree_tok, c.vocab, parent, B, N, kv->kv_indptr, kv->prefix_len, (int)c.head_dim, c.rope_theta,
                            ctx->slot, ctx->mask, ctx->cs, ctx->seq};
   return run_layers(ctx, begin, B, N, R, false, kv, kv->max_prefix_len + N, l0, l1, x_out, logits, taps, dbg_hidden, st);
 }
@@ -716,7 +718,7 @@ int eagle3_prefill(eagle3_ctx* ctx, const int32_t* tokens, int32_t T, const eagl
     const bool last = c0 + n == T;
     // target: the chunk on top of everything cached so far; features of every position recorded
     const size_t nk = (size_t)n * k;
-    const BeginRows begin = {ctx->tw.embed, tokens + c0, c.vocab, nullptr, nullptr, 1, 0, kv->kv_indptr, kv->prefix_len, d, c.rope_theta,
+    const BeginRows begin = {ctx->tw.embed, tokens + c0, c.vocab, nullptr, 1, 0, kv->kv_indptr, kv->prefix_len, d, c.rope_theta,
                              ctx->slot, ctx->mask, ctx->cs, ctx->seq};
     const int max_len = kv->max_prefix_len + c0 + n, L = c.n_layers;
     int S_tail = 0;

@@ -140,7 +140,7 @@ __device__ __forceinline__ void prefill_prep(const BeginRows& p, int r, int n) {
 }
 
 // How a pass over R rows begins: bookkeeping by the first prep_wgs workgroups (a multiple of 8: see row_of_workgroup), and each row's
-// residual, from the embedding table or from p.x_in, with its copies and, with a gain, the RMSNorm that the first projection reads.  None needs
+// residual, from the embedding table or as it lies in x, with its copies and, with a gain, the RMSNorm that the first projection reads.  None needs
 // another: as three launches (bookkeeping, embedding, norm: 5.7 + 4.8 + 4.9 us for 60 rows of 4096) each waited for the one before;
 // 6.0 here (8.0 with half as many, twice as large workgroups for the rotary table).  A prompt of 77 tokens 4630 -> 4616 us, with end_prefill_kernel and
 // the draft rows' bookkeeping in their input (four launches fewer), 4 trees of 29 nodes 1534 -> 1528.
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(1024) void begin_rows_kernel(BeginRows p, int prep_
   constexpr int VPT = 2;
   typedef typename Act<BF16>::type T;
   const T* table = (const T*)p.embed;
-  const size_t from = p.x_in ? (size_t)r * k : (size_t)min(max(p.tok[r], 0), p.vocab - 1) * k;
+  const size_t from = table ? (size_t)min(max(p.tok[r], 0), p.vocab - 1) * k : 0;
   const bool whole = ((uintptr_t)table & 15) == 0;       // the caller's table may start anywhere
   float4 val[VPT], g[VPT];
   float ss = 0.f;
@@ -169,10 +169,10 @@ __global__ __launch_bounds__(1024) void begin_rows_kernel(BeginRows p, int prep_
     if (v < nvec) {
       if (gain) g[j] = load4_f32(gain, 4 * v);
       float4 a;
-      if (p.x_in) a = make_float4(p.x_in[from + 4 * v], p.x_in[from + 4 * v + 1], p.x_in[from + 4 * v + 2], p.x_in[from + 4 * v + 3]);
+      if (!table) a = *(const float4*)(x + (size_t)r * k + 4 * v);
       else if (whole) a = load4_f32(table, from + 4 * v);
       else a = make_float4(load_f32(table, from + 4 * v), load_f32(table, from + 4 * v + 1), load_f32(table, from + 4 * v + 2), load_f32(table, from + 4 * v + 3));
-      *(float4*)(x + (size_t)r * k + 4 * v) = a;
+      if (table) *(float4*)(x + (size_t)r * k + 4 * v) = a;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (co.p[i]) *(float4*)(co.p[i] + (size_t)r * k + 4 * v) = a;

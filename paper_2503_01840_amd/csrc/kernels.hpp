@@ -77,10 +77,9 @@ struct SeqInfo {           // one per sequence, device resident
 
 // The first launch of a pass over R rows: bookkeeping, and the rows' residual.
 struct BeginRows {
-  const void* embed;                    // x = embed[tok], or x_in where that is given
+  const void* embed;                    // x = embed[tok], or null: x holds the rows
   const int32_t* tok;
   int vocab;
-  const float* x_in;
   const int32_t* parent;                // B trees of N nodes: 128-bit ancestor masks; null: a prefill chunk, causal masks in blocks of 64 rows
   int B, N;
   const int32_t* kv_indptr;
