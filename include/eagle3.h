@@ -217,7 +217,8 @@ int eagle3_draft_chain(eagle3_ctx* ctx, int32_t B, const float* g_new, const int
  *                 are read and then ADVANCED by the call (by T and by T - 1); max_prefix_len bounds the values on
  *                 entry; the caches need T (T - 1) free slots after their prefixes
  *   g_last       fp32 [hidden]  fused feature of the last prompt position: with the first sampled token it is the
- *                               n_new = 1 input of the first eagle3_draft_expand
+ *                               n_new = 1 input of the first eagle3_draft_expand; moved by the runtime's copy, so it may go
+ *                               to another GPU's memory
  *   logits_last  fp32 [vocab]   next-token logits after the prompt
  * Requires T >= 1 and both weight sets. */
 int eagle3_prefill(eagle3_ctx* ctx, const int32_t* tokens, int32_t T, const eagle3_kv* kv, const eagle3_kv* draft_kv,

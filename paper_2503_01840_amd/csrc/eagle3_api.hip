@@ -735,14 +735,15 @@ int eagle3_prefill(eagle3_ctx* ctx, const int32_t* tokens, int32_t T, const eagl
     }
     // fused features of the chunk's positions; the draft cache rows of those whose next token is known
     TRY(fuse_rows(ctx, ctx->chunk_taps, ctx->chunk_taps + nk, ctx->chunk_taps + 2 * nk, n, ctx->chunk_g, st));
+    // by the runtime, as x_in comes: g_last may lie where no kernel of this GPU can write
+    if (last) CK(hipMemcpyAsync(g_last, ctx->chunk_g + (size_t)(n - 1) * k, (size_t)k * sizeof(float), hipMemcpyDeviceToDevice, st));
     const int m = last ? n - 1 : n;
     if (m > 0) {
       CK(launch_draft_first(ctx->bf16, ctx->draft_input_args(), tokens + c0 + 1, ctx->chunk_g, dkv->kv_indptr, dkv->prefix_len, m, 1, ctx->slot,
                             nullptr, nullptr, st));
       TRY(project_qkv(ctx, w, ctx->act_k, nullptr, 2 * k, m, ctx->slot, ctx->cs, d, dkv->k[0], dkv->v[0], st));
     }
-    CK(launch_end_prefill((int32_t*)kv->prefix_len, n, (int32_t*)dkv->prefix_len, m, ctx->chunk_g + (size_t)(n - 1) * k, k,
-                          last ? g_last : nullptr, st));
+    CK(launch_end_prefill((int32_t*)kv->prefix_len, n, (int32_t*)dkv->prefix_len, m, st));
   }
   return EAGLE3_OK;
 }

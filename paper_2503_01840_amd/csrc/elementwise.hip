@@ -308,12 +308,9 @@ __global__ __launch_bounds__(128) void rope_table_kernel(float* __restrict__ cs,
   for (int i = threadIdx.x; i < d / 2; i += 128) rope_entry(cs, 0, i, d, prefix_len[0] + at, theta);
 }
 
-// The end of a prefill chunk: n positions are in the target's cache and m in the draft's; the last fused features go to their place.
-__global__ __launch_bounds__(256) void end_prefill_kernel(int32_t* __restrict__ len, int n, int32_t* __restrict__ draft_len, int m,
-                                                         const float* __restrict__ g, int k, float* __restrict__ g_last) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i == 0) { len[0] += n; draft_len[0] += m; }
-  if (g_last && i < k) g_last[i] = g[i];
+// The end of a prefill chunk: n positions are in the target's cache and m in the draft's.
+__global__ __launch_bounds__(64) void end_prefill_kernel(int32_t* len, int n, int32_t* draft_len, int m) {
+  if (threadIdx.x == 0) { len[0] += n; draft_len[0] += m; }
 }
 
 }  // namespace
@@ -323,8 +320,8 @@ hipError_t launch_rope_table(float* cs, const int32_t* prefix_len, int at, int h
   return hipGetLastError();
 }
 
-hipError_t launch_end_prefill(int32_t* len, int n, int32_t* draft_len, int m, const float* g, int k, float* g_last, hipStream_t st) {
-  hipLaunchKernelGGL(end_prefill_kernel, dim3(g_last ? (k + 255) / 256 : 1), dim3(256), 0, st, len, n, draft_len, m, g, k, g_last);
+hipError_t launch_end_prefill(int32_t* len, int n, int32_t* draft_len, int m, hipStream_t st) {
+  hipLaunchKernelGGL(end_prefill_kernel, dim3(1), dim3(64), 0, st, len, n, draft_len, m);
   return hipGetLastError();
 }
 

@@ -96,8 +96,8 @@ hipError_t launch_begin_rows(bool bf16, const BeginRows& b, float* x, int R, int
                              float* const copy_out[4], hipStream_t st);
 // cs[0] = the rotary table of position prefix_len[0] + at.
 hipError_t launch_rope_table(float* cs, const int32_t* prefix_len, int at, int head_dim, float theta, hipStream_t st);
-// After a prefill chunk: len[0] += n, draft_len[0] += m, g_last (optional) = g.
-hipError_t launch_end_prefill(int32_t* len, int n, int32_t* draft_len, int m, const float* g, int k, float* g_last, hipStream_t st);
+// After a prefill chunk: len[0] += n, draft_len[0] += m.
+hipError_t launch_end_prefill(int32_t* len, int n, int32_t* draft_len, int m, hipStream_t st);
 // x += sum_s partial[s]; copies x to each non-null copy_out; act = RMSNorm(x; gain) in the activation layout.
 hipError_t launch_add_norm(bool bf16, float* x, const float* partial, int S, int R, int k, const void* gain, float eps,
                            void* act, float* const copy_out[4], hipStream_t st);

@@ -1,5 +1,5 @@
 """Buffers that the runtime moves, so that they may lie in any memory it reaches: the residual stream that eagle3_tree_verify_layers is given may be in
-another GPU's memory, which a kernel of this one cannot read.  The library runs here without a GPU, on a stand-in of the runtime that writes down
+another GPU's memory, which a kernel of this one cannot read, and the last feature of eagle3_prefill may go there.  The library runs here without a GPU, on a stand-in of the runtime that writes down
 copies and launches; no address is dereferenced."""
 import os
 import subprocess
@@ -70,9 +70,11 @@ int main(int, char** argv) {
   NEED(eagle3_set_weights(ctx, &t, &d));
   void* caches[L] = {p, p, p};
   const eagle3_kv kv = {caches, caches, (int32_t*)p, (int32_t*)p, 40};
-  const int B = atoi(argv[4]), N = atoi(argv[5]);
+  auto number = [&](int i) { return atoi(argv[4 + i]); };
   if (*argv[3] == 's')
-    NEED(eagle3_tree_verify_layers(ctx, B, N, (int32_t*)p, (int32_t*)p, &kv, (float*)X, atoi(argv[6]), atoi(argv[7]), (float*)p, nullptr, nullptr));
+    NEED(eagle3_tree_verify_layers(ctx, number(0), number(1), (int32_t*)p, (int32_t*)p, &kv, (float*)X, number(2), number(3), (float*)p, nullptr, nullptr));
+  else
+    NEED(eagle3_prefill(ctx, (int32_t*)p, number(0), &kv, &kv, (float*)X, (float*)p, nullptr));
   return 0;
 }
 """
@@ -103,3 +105,10 @@ def test_a_stage_reads_its_residual_stream_through_the_runtime(calls, dtype, B, 
     assert [lines[i] for i in moved] == [f"copy {B * N * 512 * 4} bytes from the caller's buffer to elsewhere"]
     begins = [i for i, line in enumerate(lines) if "begin_rows_kernel" in line]
     assert len(begins) == 1 and begins[0] > moved[0] and "caller" not in lines[begins[0]]
+
+
+# one chunk and several (256 rows in fp32, 2048 in bf16)
+@pytest.mark.parametrize("dtype,T", [(0, 1), (0, 77), (0, 513), (1, 1), (1, 77), (1, 300), (1, 4100)])
+def test_the_last_feature_of_a_prompt_leaves_through_the_runtime(calls, dtype, T):
+    lines = calls(dtype, "prompt", T)
+    assert [line for line in lines if line.startswith("copy")] == [f"copy {512 * 4} bytes from elsewhere to the caller's buffer"]
