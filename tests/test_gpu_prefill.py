@@ -49,7 +49,18 @@ def test_prefill_with_a_split_fusion(hidden, T):
     _check(SMALL.with_(name=f"h{hidden}", hidden=hidden), "bf16", T)
 
 
-def _check(shape, dtype, T, part=1.0, base=0):
+# queries, keys and values rotated and put into the cache by the product (above 256 rows, unsplit): each tile that does so, row blocks and weight
+# rows that end within one.  w_q times 8, so that attention depends on its queries: without the last query head of layer 0 (planted in the oracle)
+# keys and values of layer 1 are 0.22 off and more.
+ROTATED = [(64, 16, 256, 300), (64, 16, 256, 650), (64, 16, 256, 1000), (56, 7, 512, 1200)]
+
+
+@pytest.mark.parametrize("H,Hkv,hidden,T", ROTATED)
+def test_prefill_rotated_by_the_product(H, Hkv, hidden, T):
+    _check(SMALL.with_(name=f"r{H}x{hidden}", hidden=hidden, n_heads=H, n_kv_heads=Hkv), "bf16", T, q_scale=8.0)
+
+
+def _check(shape, dtype, T, part=1.0, base=0, q_scale=1.0):
     E = _E()
     rounding = "none" if dtype == "fp32" else "bf16"
     # fp32: the exact path's 1e-4; bf16: the 2-layer bounds of the two-chunk test (one bf16 ulp of a rotated key at |k| < 8
@@ -57,7 +68,7 @@ def _check(shape, dtype, T, part=1.0, base=0):
     tol_k, tol = (1e-4, 1e-4) if dtype == "fp32" else (4e-2, 2e-2)
     model = PL.OracleModel(shape)
     prompt = S.uniform_ints(S.SEED + T, S.TensorIds.PREFIX_TOK, (T,), 0, shape.vocab).numpy()
-    pre = O.prefill(shape, model.layer, model.globals(), prompt, rounding=rounding)
+    pre = O.prefill(shape, lambda l: dict(model.layer(l), wq=model.layer(l)["wq"] * q_scale), model.globals(), prompt, rounding=rounding)
     dw, emb = model.draft(), model.globals()["embed"]
     g_all = O.fuse_features(dw["w_fc"], pre["taps"][0], pre["taps"][1], pre["taps"][2], rounding=rounding)
     Kd = np.zeros((T - 1, shape.n_kv_heads, shape.head_dim)); Vd = np.zeros_like(Kd)
@@ -66,6 +77,8 @@ def _check(shape, dtype, T, part=1.0, base=0):
     ctx = E.Eagle3Context(shape, max_batch=1, max_nodes=8, max_depth=2, max_topk=2, max_new=4, device=DEV)
     left = PL.shrink_workspace(ctx, part) if part < 1.0 else None
     W = PL.device_weights(shape, device=DEV)
+    for w in W["target"]["layers"]:
+        w["wq"] *= q_scale
     ctx.set_weights(W["target"], W["draft"])
     i32 = lambda v: torch.tensor(v, dtype=torch.int32, device=DEV)
     z = lambda n: torch.full((n, shape.n_kv_heads, shape.head_dim), 7.0, dtype=ctx.storage_dtype, device=DEV)

@@ -90,11 +90,15 @@ ROTATED = {"192": (56, 8, 512, 64, 20), "192-ragged": (56, 7, 512, 64, 20), "8b"
 @pytest.mark.parametrize("name", list(ROTATED))
 def test_rows_rotated_by_the_product(name):
     H, G, hidden, B, N = ROTATED[name]
-    _rows_alone_and_together(S.get_shape("c3").with_(name=f"r{name}", hidden=hidden, n_heads=H, n_kv_heads=G, intermediate=1024, vocab=1024), B, N, 64 // N)
+    # up to 1024 columns a residual below the attention's share of the layer's output: without the last query head (planted in the oracle) that output is
+    # 0.05 to 0.14 off, where bf16 rounding makes 0.004 and the bound is 0.02; at 4096 columns it is 1.2 off behind a residual of 8, bound 0.16
+    _rows_alone_and_together(S.get_shape("c3").with_(name=f"r{name}", hidden=hidden, n_heads=H, n_kv_heads=G, intermediate=1024, vocab=1024), B, N, 64 // N,
+                             scale=0.25 if hidden <= 1024 else 8.0)
 
 
-def _rows_alone_and_together(full, B, N, group, logits=False):
-    """All B sequences of N rows at once against `group` of them at a time; one sequence: against its first 32 rows."""
+def _rows_alone_and_together(full, B, N, group, logits=False, scale=8.0):
+    """All B sequences of N rows at once against `group` of them at a time; one sequence: against its first 32 rows.  Layer output, the cache with
+    what must stay as it was, logits."""
     E = _E()
     shape = full.with_(n_layers=1, taps=(0, 0, 0))
     W = {k: v.to(DEV) for k, v in S.layer_weights(full, 3).items()}
@@ -104,7 +108,7 @@ def _rows_alone_and_together(full, B, N, group, logits=False):
     gen = torch.Generator(device=DEV)
     gen.manual_seed(B)
     i32 = lambda v: torch.as_tensor(np.asarray(v), dtype=torch.int32, device=DEV)
-    x_in = 8.0 * torch.randn(B, N, full.hidden, device=DEV, generator=gen)
+    x_in = scale * torch.randn(B, N, full.hidden, device=DEV, generator=gen)
     parent = i32(np.tile(np.arange(-1, N - 1), (B, 1)))
     tok = torch.zeros(B, N, dtype=torch.int32, device=DEV)
     P = 40
@@ -118,14 +122,19 @@ def _rows_alone_and_together(full, B, N, group, logits=False):
         x_out, lg = E.eagle3_tree_verify_layers(ctx, tok[b0:b1, :n_rows].contiguous(), parent[b0:b1, :n_rows].contiguous(), kv,
                                                x_in[b0:b1, :n_rows].contiguous(), 0, 1, want_logits=True)
         torch.cuda.synchronize()
-        return x_out.cpu().numpy(), k.float().cpu().numpy(), lg.float().cpu().numpy() if logits else None
+        for t, t0 in ((k, k0[at]), (v, v0[at])):
+            assert all(torch.equal(t[b * (P + N):][:P], t0[b * (P + N):][:P]) for b in range(n)), "rows beside the new ones were written"
+        return x_out.cpu().numpy(), k.float().cpu().numpy(), v.float().cpu().numpy(), lg.float().cpu().numpy() if logits else None
 
-    x, k, lg = run(0, B)
+    x, k, v, lg = run(0, B)
     rows = N if B > 1 else 32
     for b0 in range(0, B, group):
         b1 = min(B, b0 + group)
-        xr, kr, lr = run(b0, b1, rows)
+        xr, kr, vr, lr = run(b0, b1, rows)
         assert np.max(np.abs(x[b0:b1, :rows] - xr)) < TOL * max(1.0, _rms(xr))
-        assert np.max(np.abs(k[b0 * (P + N):b0 * (P + N) + len(kr)] - kr)) < 4e-2
+        at = slice(b0 * (P + N), b0 * (P + N) + len(kr))
+        assert np.max(np.abs(k[at] - kr)) < 4e-2
+        # sums in another order may round to the bf16 neighbour: 2^-5 below 8, twice that above
+        assert np.max(np.abs(v[at] - vr) / np.maximum(1.0, np.abs(vr) / 8.0)) < 4e-2
         if logits:
             assert np.max(np.abs(lg[b0:b1, :rows] - lr)) < TOL * max(1.0, _rms(lr))

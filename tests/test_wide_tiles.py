@@ -255,3 +255,11 @@ def test_unsplit_tiles_that_the_gpu_tests_cover(launched):
         widest = max(n, k)
         cap = max(1024 * widest, 4 * M * widest, 8 * M * k, 2 * 2048 * widest)
         assert launched([(M, n, k, 0, cap)])[0][0] == want, (H, G, k, M)
+
+
+# the tiles of test_prefill_rotated_by_the_product: target and draft product
+def test_unsplit_tiles_of_prompts_that_the_gpu_tests_cover(launched):
+    for H, G, k, T, want in [(64, 16, 256, 300, ((256, 128, 1, 128), (256, 128, 1, 128))), (64, 16, 256, 650, ((192, 256, 1, 64), (192, 256, 1, 64))),
+                             (64, 16, 256, 1000, ((256, 256, 1, 64), (256, 192, 1, 64))), (56, 7, 512, 1200, ((256, 192, 1, 64), (256, 192, 1, 64)))]:
+        n = (H + 2 * G) * 128
+        assert [t for t, _ in launched([(T, n, k, 0, 2 * 2048 * n), (T - 1, n, 2 * k, 0, 2 * 2048 * n)])] == list(want), (H, G, k, T)
