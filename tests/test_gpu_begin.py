@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import eagle3_synth as S
+from oracle import eagle3_oracle as O
 import pipeline as PL
 
 pytestmark = pytest.mark.gpu
@@ -53,7 +54,8 @@ def test_residual_rows_from_anywhere(dtype, hidden, B, N):
         assert all(torch.equal(a, b) for a, b in zip(o, out[0]))
 
 
-# the same prompt at once and in two calls: bookkeeping of the rows of a chunk, lengths and last features
+# the same prompt at once and in two calls: bookkeeping of the rows of a chunk, lengths, last features, and the draft's cache: each call adds the rows
+# of its positions but the last, those of the second call behind those of the first
 @pytest.mark.parametrize("T,cut", [(2, 1), (5, 4), (17, 16), (18, 1), (65, 33)])
 def test_prompts_in_two_calls(T, cut):
     import paper_2503_01840_amd as E
@@ -72,7 +74,20 @@ def test_prompts_in_two_calls(T, cut):
     assert (int(kv2.prefix_len[0]), int(dkv2.prefix_len[0])) == (cut, cut - 1)
     g2, logits2 = E.eagle3_prefill(ctx, tokens[cut:], kv2, dkv2)
     torch.cuda.synchronize()
-    assert (int(kv.prefix_len[0]), int(dkv.prefix_len[0])) == (T, T - 1) and int(kv2.prefix_len[0]) == T
+    assert (int(kv.prefix_len[0]), int(dkv.prefix_len[0])) == (T, T - 1) and (int(kv2.prefix_len[0]), int(dkv2.prefix_len[0])) == (T, T - 2)
+    model = PL.OracleModel(shape)
+    dw, emb, toks = model.draft(), model.globals()["embed"], tokens.cpu().numpy()
+    pre = O.prefill(shape, model.layer, model.globals(), toks)
+    g_all = O.fuse_features(dw["w_fc"], *pre["taps"])
+    Kd = np.zeros((T, shape.n_kv_heads, shape.head_dim)); Vd = np.zeros_like(Kd)
+    for lo, hi, at in [(0, cut - 1, 0), (cut, T - 1, cut - 1)]:        # positions, and their place in the draft's cache
+        if hi > lo:
+            O.draft_forward(shape, dw, emb, g_all[lo:hi], toks[lo + 1:hi + 1], at + np.arange(hi - lo), Kd, Vd, at, at, np.tril(np.ones((hi - lo, hi - lo), bool)),
+                            lambda a: a)
+    for got, want in [(dkv2.k_layers[0], Kd), (dkv2.v_layers[0], Vd)]:
+        assert np.max(np.abs(got.cpu().numpy() - want)) < 1e-4          # zeros behind the last row among them
+    for got, want in [(dkv2.k_layers[0], dkv.k_layers[0]), (dkv2.v_layers[0], dkv.v_layers[0])]:
+        assert torch.allclose(got[:cut - 1], want[:cut - 1], rtol=1e-4, atol=1e-4)
     # fp32 sums of other row groups: a few last bits of values of order one
     for a, b in [(g, g2), (logits, logits2), (kv.k_layers[0], kv2.k_layers[0]), (kv.v_layers[0], kv2.v_layers[0])]:
         assert torch.allclose(a, b, rtol=1e-4, atol=1e-4)
