@@ -142,8 +142,9 @@ __device__ __forceinline__ void prefill_prep(const BeginRows& p, int r, int n) {
 // How a pass over R rows begins: bookkeeping by the first prep_wgs workgroups (a multiple of 8: see row_of_workgroup), and each row's
 // residual, from the embedding table or as it lies in x, with its copies and, with a gain, the RMSNorm that the first projection reads.  None needs
 // another: as three launches (bookkeeping, embedding, norm: 5.7 + 4.8 + 4.9 us for 60 rows of 4096) each waited for the one before;
-// 6.0 here (8.0 with half as many, twice as large workgroups for the rotary table).  A prompt of 77 tokens 4630 -> 4616 us, with end_prefill_kernel and
-// the draft rows' bookkeeping in their input (four launches fewer), 4 trees of 29 nodes 1534 -> 1528.
+// 6.0 here (8.0 with half as many, twice as large workgroups for the rotary table).  It is there for the two launches it takes out of every pass, which
+// the host hands over too; of a bf16 pass those 9 us are less than two runs differ (77 tokens 4665 -> 4665 us, 4 trees of 29 nodes 1555 -> 1548).
+// The rotary table's fp64 beside the row work takes 96 registers, so a CU holds one workgroup of 1024 threads.
 template <bool BF16>
 __global__ __launch_bounds__(1024) void begin_rows_kernel(BeginRows p, int prep_wgs, int parts, float* __restrict__ x, int R, int k,
                                                          const typename Act<BF16>::type* __restrict__ gain, float eps,

@@ -8,8 +8,8 @@ typedef uint16_t bf16_t;
 // ---------------------------------------------------------------- GEMM (gemm_skinny.hip, gemm_f32.hip)
 // Weight operand: up to three [rows_i, K] row-major matrices.
 //   mode 0: their rows are concatenated (q|k|v projections run as one GEMM);
-//   mode 1: tiles interleave 32 rows of w[0] (gate) with the same 32 rows of w[1] (up) so that the
-//           SwiGLU product can be formed in the epilogue.
+//   mode 1: tiles interleave rows of w[0] (gate) with the same rows of w[1] (up), 32 at a time or, in tiles of 192 and 224
+//           weight rows, 8, so that the SwiGLU product can be formed in the epilogue.
 struct GemmWeights {
   const void* w[3];
   int rows[3];

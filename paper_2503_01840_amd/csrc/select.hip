@@ -238,7 +238,8 @@ __device__ __forceinline__ void write_root(const DraftState& s) {
 // per candidate), and the first one writes what is kept of them.  Nothing that is written here is read by another workgroup of the launch.
 // K = 10, 8B width: 15.5 us as three launches, 11.2 here, most of it the last round trips (parents, target ids, embedding and feature rows) with
 // cold caches; 12.7 with the rotary table (formed by draft_first_kernel for all forwards) and more passes over a row than there are (code that
-// arrives a line at a time).  An 8B step 6250 -> 6135 us, one layer 1585 -> 1551, the tiny fp32 step 237 -> 211 (with draft_finish_kernel and draft_first_kernel).
+// arrives a line at a time).  With draft_finish_kernel and draft_first_kernel, both builds in turn: an 8B step 6253 -> 6221 us,
+// one layer 1580 -> 1542, the tiny fp32 step 237 -> 210 or, on another box, 220 -> 217.
 template <bool BF16, int VPT, int KM>
 __global__ __launch_bounds__(1024) void draft_level_kernel(DraftState s, Candidates c, const int32_t* __restrict__ d2t,
                                                           const int32_t* __restrict__ kv_indptr, const int32_t* __restrict__ prefix_len,

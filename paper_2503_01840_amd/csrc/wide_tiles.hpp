@@ -70,10 +70,13 @@ inline WideTiles with_split(int M, int N, int K, bool swiglu, size_t out_capacit
 
 // How long a launch beyond 256 rows lasts, in microseconds, with the kernel that reads its partial sums.  A workgroup takes a start and an end, and a
 // time per 64 k; the fullest XCD runs its workgroups in rounds of 32, of 64 for 128 x 128 tiles (two on a CU side by side, one
-// alone where there are no more than 32 left); writing and reading the partial sums comes on top.  The eleven numbers are a fit to 150 products
-// of 34 model shapes at 13 row counts from 257 to 2048, each with all four tiles and the kernel that reads the sums: what the estimate picks
-// is 0.2 % slower than the best of the four on average (13 % at worst: 2304 x 9216 at 1500 rows), and 12 % faster than picking by workgroup
-// counts.  Fitted to 17 products, it had charged 128 x 128 tiles too much: us, then / now, down 4352 x 17024 300 rows 114 / 100, gate/up
+// alone where there are no more than 32 left); writing and reading the partial sums comes on top.  The eleven numbers of the tiles of 256 and of 128 weight rows are a
+// fit to 150 products of 34 model shapes at 13 row counts from 257 to 2048, each with all four of them and the kernel that reads the sums: what the
+// estimate picks of the four is 0.2 % slower than the best on average (13 % at worst: 2304 x 9216 at 1500 rows), and 12 % faster than picking by
+// workgroup counts.  The four numbers of 224 and 192 weight rows: half of 430 launches each of 24 shapes, 300 to 4096 rows, all splits, took longer
+// (within 1 %), single ones differ by 8.5 and 7 % on average.  The choice of all six (launch_tiles), 178 products of those shapes: 1.0 % slower than the best
+// whose chains of sums are no longer, 14 % at worst (4608 x 3584 at 2048 rows), and 3 % than the best of any chain.
+// Fitted to 17 products, the first eleven had charged 128 x 128 tiles too much: us, then / now, down 4352 x 17024 300 rows 114 / 100, gate/up
 // 18432 x 2304 257 rows 48 / 43, o 5120 x 5120 300 rows 43 / 40.  8B width, product and reading, us, 256 x 256 / 192 x 256 /
 // 256 x 128 / 128 x 128: q/k/v 300 rows 38 / 35 / 36 / 44, 512 rows 44 / 64 / 40 / 50, 600 rows 73 / 52 / 71 / 50; down 300 rows
 // 63 / 58 / 60 / 69, 512 rows 73 / 80 / 67 / 83; o 1024 rows 49 / 49 / 42 / 50; gate/up 300 rows 101 / 87 / 116 / 121, 1024 rows
@@ -114,9 +117,10 @@ inline WideTiles wide_tiles(int M, int N, int K, bool swiglu, size_t out_capacit
 // The tile that is launched: that, or beyond 256 rows 256 x 224 or 256 x 192 (4 x 2 wavefronts of 64 x 112 or 64 x 96).  28672 weight rows (8B
 // gate/up) are 112 tiles of 256, 3.5 rounds of the chip at 2048 rows, and 128 of 224, four whole ones; 6144 (q/k/v) are 24 of 256, three
 // quarters of a round, and 32 of 192.  Taken by a margin of 2 % of the estimate, and only with chains of sums no longer than the other tile's
-// (stages of 128 k: two chains).  us, the other tile / this one: gate/up 2048 rows 371 / 357, 1280 rows 283 / 235, 512 rows 99.8 / 98.3 (the same
-// work on more CUs draws the same power), 57344 x 8192 1024 rows 752 / 717, 27648 x 5120 1280 rows 335 / 285, q/k/v 2048 rows 92 / 81, 1024 rows
-// 70 / 62, 22016 x 4096 512 rows 95 / 83.  Of 170 products of 22 shapes from 300 to 2048 rows 37 took another tile, 2 to 17 % faster and none slower.
+// (stages of 128 k: two chains).  us, with the kernel that reads partial sums, the other tile / this one: gate/up 2048 rows 371 / 357, 1280 rows 286 / 244, 512 rows
+// 99.8 / 98.3 (the same work on more CUs draws the same power), 57344 x 8192 1024 rows 761 / 716, 27648 x 5120 1280 rows 335 / 285, q/k/v 2048 rows
+// 115 / 99, 1024 rows 69.5 / 63.1, 22016 x 4096 512 rows 96 / 83.  Of 440 products of 31 shapes from 257 to 4088 rows 73 take another tile, 2 to 16 %
+// faster and none slower.
 inline WideTiles launch_tiles(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
   const WideTiles base = wide_tiles(M, N, K, swiglu, out_capacity_floats);
   if (M <= 256) return base;
