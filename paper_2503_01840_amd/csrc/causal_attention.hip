@@ -15,16 +15,17 @@
 //     as its values are read one block later than its scores; scores are
 //     produced transposed (S^T = K Q^T) so that a lane owns one query; the V^T operand comes from the transposing LDS
 //     read; exp(S) enters the value product as a bf16 head plus a bf16 tail.
-//   * One block is a matrix-unit time of 24 products (8 score + 16 value, 768 cycles) against ~450 issue cycles of softmax.  Run
-//     one after the other they add up (all wavefronts pass the same barrier, so they stay in phase); here the softmax of
-//     block i runs between the score products of block i + 1 and the value products of block i - 1, none of which
-//     depend on it.
+//   * One block is a matrix-unit time of 24 products (8 score + 16 value, 768 cycles) against ~700 issue cycles of everything else (4 a vector
+//     instruction, 8 an exponential or a product).  Run one after the other they add up (all wavefronts pass the same barrier, so they stay in
+//     phase); here the softmax of block i runs between the score products of block i + 1 and the value products of block i - 1, none of which
+//     depend on it, its last four weights a block later, so that both halves of a block have about as much to issue as to multiply.  No v_dot2 among
+//     them, which stops the matrix unit, and the direct loads one by one: 85 k -> 70 k cycles for 16 tiles, of which 50 k are products.
 //   * Only tiles that reach past a workgroup's first query need a mask.
 //   * The own keys of the simulated steps come last; their rows arrive while the last block is worked on.
 //   * Workgroups of later queries walk over more keys: they are handed out first, and the KV head is the fastest index,
 //     so that with 8 KV heads each XCD keeps one head's keys in its L2.
-// What bounds it: the chip's power where every CU has two workgroups and more (at T = 2048, 32 heads over 8, the clock drops to 1.86 GHz, at
-// T = 4096 to 1.53), and the walk of the longest workgroup with its start, own keys and merge where there are fewer.  The softmax
+// What bounds it: the chip's power where every CU has two workgroups and more (at T = 2048, 32 heads over 8, the clock in the loop is 1.9 GHz,
+// and was 2.15 with the 18 % more cycles), and the walk of the longest workgroup with its start, own keys and merge where there are fewer.  The softmax
 // must stay in the gaps it is written into: with the sum of the weights formed behind the block, copies between registers, a last
 // tile taken whole and the output rescaled at every own key it was 29.0 instead of 22.6 us (T = 517, 64 heads, s = 5), 72 instead
 // of 67 (T = 2048, 32 heads over 8, s = 5) and 36.0 instead of 32.6 (T = 2048, 8 heads, s = 0).  Measured against a kernel of one head x 64 queries per workgroup (4 wavefronts, scores,
@@ -139,20 +140,27 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
     koff[i] = key_bytes + (uint32_t)(((lane & 15) ^ (4 * (j & 3) + lkey)) * 16);
     voff[i] = key_bytes + vpiece;
   }
-  auto issue = [&](const bf16_t* base, const uint32_t (&off)[IPW], int t, uint32_t slot_base) INLINE_LAMBDA {   // slot at slot_base
-    const bf16_t* b0 = base + (size_t)t * KT * row_stride;
-    const uint32_t slot = lds0 + slot_base + wave * IPW * 1024;
-    if ((t + 1) * KT <= L) {
+  auto clamp_offsets = [&](uint32_t (&off)[IPW], int t) INLINE_LAMBDA {      // for the tile t that the keys end in
+    const int last = L - 1 - t * KT;
 #pragma unroll
-      for (int i = 0; i < IPW; ++i) dma16(b0, off[i], slot + i * 1024);
-    } else {
-      const int last = L - 1 - t * KT;
-#pragma unroll
-      for (int i = 0; i < IPW; ++i) {
-        const int key = 4 * (wave * IPW + i) + lkey;
-        dma16(b0, off[i] - (uint32_t)(key - min(key, last)) * (uint32_t)(row_stride * 2), slot + i * 1024);
-      }
+    for (int i = 0; i < IPW; ++i) {
+      const int key = 4 * (wave * IPW + i) + lkey;
+      off[i] -= (uint32_t)(key - min(key, last)) * (uint32_t)(row_stride * 2);
     }
+  };
+  // Load r of tile t: its K, then its V
+  auto load = [&](int r, int t, uint32_t k_at, uint32_t v_at) INLINE_LAMBDA {
+    const size_t first = (size_t)t * KT * row_stride;
+    if (r < IPW) dma16(kbase + first, koff[r], lds0 + k_at + wave * IPW * 1024 + r * 1024);
+    else dma16(vbase + first, voff[r - IPW], lds0 + v_at + wave * IPW * 1024 + (r - IPW) * 1024);
+  };
+  auto issue = [&](int t, uint32_t k_at, uint32_t v_at) INLINE_LAMBDA {
+    if ((t + 1) * KT > L) {
+      clamp_offsets(koff, t);
+      clamp_offsets(voff, t);
+    }
+#pragma unroll
+    for (int r = 0; r < 2 * IPW; ++r) load(r, t, k_at, v_at);
   };
   // The simulated steps' own rows: up to hg steps x QB rows = ROWS_WG rows of K and of V at a time go through free tile
   // slots as whole 256-byte rows, piece c of staged row i at position c ^ (i & 15), one copy for all heads and wavefronts.
@@ -186,16 +194,11 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
       *(u32x4*)(smem + Q_BASE + j * 1024 + lane * 16) = piece;
     }
   }
-  issue(kbase, koff, 0, 0);
-  issue(vbase, voff, 0, V_BASE);
-  if (n_tiles > 1) {
-    issue(kbase, koff, 1, TILE_BYTES);
-    issue(vbase, voff, 1, V_BASE + TILE_BYTES);
-  }
+  issue(0, 0, V_BASE);
+  if (n_tiles > 1) issue(1, TILE_BYTES, V_BASE + TILE_BYTES);
 
-  uint32_t minus_lo = 0x0000BF80u, minus_hi = 0xBF800000u;   // bf16 pairs (-1, 0) and (0, -1), kept in registers
-  uint32_t ones = 0x3F803F80u;
-  asm volatile("" : "+v"(minus_lo), "+v"(minus_hi), "+v"(ones));
+  uint32_t ones = 0x3F803F80u;                 // a bf16 pair, kept in a register
+  asm volatile("" : "+v"(ones));
 
   floatx16 o[4];
 #pragma unroll
@@ -241,14 +244,14 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
   };
   // Two weights as bf16 heads and tails (p = hi + lo, 16 significant bits): rounding them to a single bf16 would put a 2^-9
   // relative error on the output.  The sum takes what the value products take, so that a rounded weight stays a weight: its
-  // error only reaches the output through the distance of its value from the mean.
+  // error only reaches the output through the distance of its value from the mean.  Plain instructions but for one: the matrix unit
+  // stands still while a v_dot2 runs (64 cycles for a product of 32 with five of them behind it, 33 with five of any other kind).
   auto split_pair = [&](float p0, float p1, uint32_t& h, uint32_t& l, float& sum) INLINE_LAMBDA {
     h = pack_bf16x2(p0, p1);
-    // tail = p - head, one v_dot2c_f32_bf16 each: p + head.lo * -1 + head.hi * 0 (exact)
-    const float t0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, h), __builtin_bit_cast(bf16x2_t, minus_lo), p0, false);
-    const float t1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, h), __builtin_bit_cast(bf16x2_t, minus_hi), p1, false);
-    sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, h), __builtin_bit_cast(bf16x2_t, ones), sum, false);
-    l = pack_bf16x2(t0, t1);
+    const float h0 = bf16_lo(h), h1 = bf16_hi(h);
+    l = pack_bf16x2(p0 - h0, p1 - h1);
+    sum += h0;
+    sum += h1;
     sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, l), __builtin_bit_cast(bf16x2_t, ones), sum, false);
     asm volatile("" : "+v"(h), "+v"(l), "+v"(sum));          // here, among the products, and not where they are used
   };
@@ -264,17 +267,33 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
   u32x4 va[4];                                 // value operands n of the block in work at n & 3
 
   // Softmax of the block of scores in s (first key kb) among the products of its neighbours: values of the previous block
-  // (weights w; V at v_at, its first two operands already in va) and scores of the next one (K at k_at, into sn).  Leaves
-  // this block's weights in wn and its first two value operands (V at v_next) in va.  The order is written out and pinned:
+  // (weights w; V at v_at, its first two operands already in va) and scores of the next one (K at k_at, into sn).  A block is a
+  // matrix-unit time of 24 products (768 cycles) and nearly as many issue cycles of everything else, so the softmax is spread over all of them: weights
+  // 0..11 of this block here, and 12..15 of the previous one, whose scores are still in sn, during the search for the max.  Leaves what
+  // there is of this block's weights in wn and its first two value operands (V at v_next) in va.  LOAD: the direct loads of tile t_load too, one behind every
+  // other product: behind the barrier, all together, they kept the wavefronts from issuing.  The order is written out and pinned:
   // the compiler on its own puts the products first and the exponentials after them.
-  auto block = [&](auto has_prev, auto has_next, floatx16& s, floatx16& sn, const Weights& w, Weights& wn, int kb, uint32_t k_at, uint32_t v_at,
-                   uint32_t v_next) INLINE_LAMBDA {
-    constexpr bool PREV = decltype(has_prev)::value, NEXT = decltype(has_next)::value;
+  constexpr int LATE = 12;
+  auto put_pair = [&](float p0, float p1, int n, Weights& w, float& sum) INLINE_LAMBDA {      // weights 2 n and 2 n + 1
+    uint32_t h, l;
+    split_pair(p0, p1, h, l, sum);
+    w.h[n >> 2][n & 3] = h;
+    w.l[n >> 2][n & 3] = l;
+  };
+  auto block = [&](auto has_prev, auto has_next, auto has_load, floatx16& s, floatx16& sn, Weights& w, Weights& wn, int kb, uint32_t k_at, uint32_t v_at,
+                   uint32_t v_next, int t_load, uint32_t k_fill, uint32_t v_fill) INLINE_LAMBDA {
+    constexpr bool PREV = decltype(has_prev)::value, NEXT = decltype(has_next)::value, LOAD = decltype(has_load)::value;
     auto value = [&](int n, bool tail) INLINE_LAMBDA {
       if constexpr (PREV) o[n & 3] = mfma(va[n & 3], tail ? w.l[n >> 2] : w.h[n >> 2], o[n & 3]);
     };
     auto fetch = [&](int n) INLINE_LAMBDA {
       if constexpr (PREV) va[n & 3] = v_operand(v_at, n);
+    };
+    auto loads = [&](int at) INLINE_LAMBDA {   // at 0..15
+      if constexpr (LOAD)
+#pragma unroll
+        for (int r = 0; r < 2 * IPW; ++r)
+          if (r * 16 / (2 * IPW) == at) load(r, t_load, k_fill, v_fill);
     };
     u32x4 kf[3];
     fetch(2);
@@ -290,38 +309,62 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
       for (int r = 0; r < 16; ++r) s[r] = ((vis >> (8 * (r >> 2) + (r & 3))) & 1u) ? s[r] : -INFINITY;
     }
     CAUSAL_PIN();
-    // first half: eight value products over the search for the max
+    // first half: eight value products over the search for the max and the previous block's last weights
+    float late[4] = {0.f, 0.f, 0.f, 0.f}, e[LATE];
+    auto late_weight = [&](int i) INLINE_LAMBDA {
+      if constexpr (PREV) late[i] = weight(sn[LATE + i], m_run);
+    };
     value(0, false);
+    loads(0);
     float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
-    CAUSAL_PIN();
-    value(1, false);
     mx = fmaxf(fmaxf(mx, s[3]), s[4]); mx = fmaxf(fmaxf(mx, s[5]), s[6]);
     CAUSAL_PIN();
-    value(0, true);
+    value(1, false);
+    loads(1);
+    late_weight(0);
     mx = fmaxf(fmaxf(mx, s[7]), s[8]); mx = fmaxf(fmaxf(mx, s[9]), s[10]);
     CAUSAL_PIN();
-    value(1, true);
-    fetch(4);
+    value(0, true);
+    loads(2);
+    late_weight(1);
     mx = fmaxf(fmaxf(mx, s[11]), s[12]); mx = fmaxf(fmaxf(fmaxf(mx, s[13]), s[14]), s[15]);
     CAUSAL_PIN();
-    value(2, false);
-    fetch(5);
+    value(1, true);
+    loads(3);
+    fetch(4);
     bool grows;
     const float m_new = new_max(mx, grows);
     CAUSAL_PIN();
+    value(2, false);
+    loads(4);
+    fetch(5);
+    if constexpr (PREV) put_pair(late[0], late[1], LATE / 2, w, l_run);
+    CAUSAL_PIN();
     value(3, false);
+    loads(5);
+    late_weight(2);
+    late_weight(3);
     CAUSAL_PIN();
     value(2, true);
-    float p0 = weight(s[0], m_new);
+    loads(6);
+    if constexpr (PREV) put_pair(late[2], late[3], LATE / 2 + 1, w, l_run);
     CAUSAL_PIN();
     value(3, true);
-    float p1 = weight(s[1], m_new);
+    loads(7);
+    e[0] = weight(s[0], m_new);
+    e[1] = weight(s[1], m_new);
     CAUSAL_PIN();
-    // second half: eight score products and eight value products, one exponential each
+    // second half: eight score products and eight value products; weight 2 + i behind score product at_of[i] / 2 or, odd, value product at_of[i] / 2, and
+    // pair pair_at[j] is split behind value product j
+    constexpr int at_of[LATE - 2] = {0, 1, 3, 4, 6, 7, 9, 10, 12, 13}, pair_at[8] = {0, 1, -1, 2, 3, -1, 4, 5};
     float ls = 0.f;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      float next0 = 0.f, next1 = 0.f;
+      auto weights = [&](int at) INLINE_LAMBDA {
+#pragma unroll
+        for (int i = 0; i < LATE - 2; ++i)
+          if (at_of[i] == at) e[2 + i] = weight(s[2 + i], m_new);
+      };
       if constexpr (NEXT) {
         if (j == 0) {
 #pragma unroll
@@ -330,20 +373,16 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
         sn = mfma(kf[j % 3], qf[j], sn);
         if (j < 6) kf[(j + 2) % 3] = k_operand(k_at, j + 2);
       }
-      if (j < 7) next0 = weight(s[2 * j + 2], m_new);
+      weights(2 * j);
+      loads(8 + j);
       CAUSAL_PIN();
       value(4 + (j & 1) + 2 * (j >> 2), (j >> 1) & 1);
       if (j == 1) fetch(6);
       if (j == 2) fetch(7);
       if (j == 6) va[0] = v_operand(v_next, 0);
       if (j == 7) va[1] = v_operand(v_next, 1);
-      if (j < 7) next1 = weight(s[2 * j + 3], m_new);
-      uint32_t h, l;
-      split_pair(p0, p1, h, l, ls);
-      p0 = next0;
-      p1 = next1;
-      wn.h[j >> 2][j & 3] = h;
-      wn.l[j >> 2][j & 3] = l;
+      weights(2 * j + 1);
+      if (pair_at[j] >= 0) put_pair(e[2 * pair_at[j]], e[2 * pair_at[j] + 1], pair_at[j], wn, ls);
       CAUSAL_PIN();
     }
     if (grows) {
@@ -357,8 +396,10 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
     }
     l_run += ls;
   };
-  // the last block's values: its first two operands are in va
-  auto finish = [&](const Weights& w, uint32_t v_at) INLINE_LAMBDA {
+  // the last block's (scores s) last weights and its values: its first two operands are in va
+  auto finish = [&](const floatx16& s, Weights& w, uint32_t v_at) INLINE_LAMBDA {
+    put_pair(weight(s[LATE], m_run), weight(s[LATE + 1], m_run), LATE / 2, w, l_run);
+    put_pair(weight(s[LATE + 2], m_run), weight(s[LATE + 3], m_run), LATE / 2 + 1, w, l_run);
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
       if (n > 1) va[n & 3] = v_operand(v_at, n);
@@ -378,63 +419,73 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
   // be read a block ahead.
   int kb = sb * 32;
   uint32_t k_slot = 0, v_slot = 0;             // of tile t
-  block(Flag<false>(), Flag<true>(), s0, s1, w0, w0, kb, k_rd + BLOCK, v_rd, v_rd);
-#pragma unroll 1
-  for (int t = 0; t + 1 < n_tiles; ++t) {
+  block(Flag<false>(), Flag<true>(), Flag<false>(), s0, s1, w0, w0, kb, k_rd + BLOCK, v_rd, v_rd, 0, 0, 0);
+  auto tile = [&](auto has_load, int t) INLINE_LAMBDA {
     CAUSAL_WAIT_LOADS(0);
     __syncthreads();
     const uint32_t v_1 = v_slot == 2 * TILE_BYTES ? 0 : v_slot + TILE_BYTES;         // V slots of tiles t + 1, t + 2
-    if (t + 2 < n_tiles) {
-      const uint32_t v_2 = v_1 == 2 * TILE_BYTES ? 0 : v_1 + TILE_BYTES;
-      issue(kbase, koff, t + 2, k_slot);
-      issue(vbase, voff, t + 2, V_BASE + v_2);
+    const uint32_t v_2 = v_1 == 2 * TILE_BYTES ? 0 : v_1 + TILE_BYTES;
+    if (decltype(has_load)::value && (t + 3) * KT > L) {
+      clamp_offsets(koff, t + 2);
+      clamp_offsets(voff, t + 2);
     }
     const uint32_t k_1 = k_slot ^ TILE_BYTES;
-    block(Flag<true>(), Flag<true>(), s1, s0, w0, w1, kb + 64, k_rd + k_1, v_rd + v_slot, v_rd + v_slot + BLOCK);
+    block(Flag<true>(), Flag<true>(), has_load, s1, s0, w0, w1, kb + 64, k_rd + k_1, v_rd + v_slot, v_rd + v_slot + BLOCK, t + 2, k_slot, V_BASE + v_2);
     kb += KT;
-    block(Flag<true>(), Flag<true>(), s0, s1, w1, w0, kb, k_rd + k_1 + BLOCK, v_rd + v_slot + BLOCK, v_rd + v_1);
+    block(Flag<true>(), Flag<true>(), Flag<false>(), s0, s1, w1, w0, kb, k_rd + k_1 + BLOCK, v_rd + v_slot + BLOCK, v_rd + v_1, 0, 0, 0);
     k_slot = k_1;
     v_slot = v_1;
-  }
+  };
+  int t = 0;
+#pragma unroll 1
+  for (; t + 2 < n_tiles; ++t) tile(Flag<true>(), t);
+  if (t + 1 < n_tiles) tile(Flag<false>(), t);
   // The last tile's second block, where any query of the workgroup sees a key of it.  K's other slot and V's next were last read
   // before the last barrier: the own rows go there.
-  const uint32_t own_k = k_slot ^ TILE_BYTES, own_v = V_BASE + (v_slot == 2 * TILE_BYTES ? 0 : v_slot + TILE_BYTES);
+  uint32_t own_k = k_slot ^ TILE_BYTES, own_v = V_BASE + (v_slot == 2 * TILE_BYTES ? 0 : v_slot + TILE_BYTES), own_v_other = V_BASE + v_slot;
   if (!PREFILL && p.s > 0) issue_own(1, own_k, own_v);
   if (kb + 64 < L) {
-    block(Flag<true>(), Flag<false>(), s1, s0, w0, w1, kb + 64, 0, v_rd + v_slot, v_rd + v_slot + BLOCK);
-    finish(w1, v_rd + v_slot + BLOCK);
+    block(Flag<true>(), Flag<false>(), Flag<false>(), s1, s0, w0, w1, kb + 64, 0, v_rd + v_slot, v_rd + v_slot + BLOCK, 0, 0, 0);
+    finish(s1, w1, v_rd + v_slot + BLOCK);
   } else {
-    finish(w0, v_rd + v_slot);
+    finish(s0, w0, v_rd + v_slot);
   }
 
   // The query's own key of every simulated step: one dot product and one scaled row of values each, the two key halves
   // taking alternate steps.  Last, as they are exact in fp32 against any max; taken first, their max would be in force for
   // the first keys, whose largest weight is then no longer 1 but carried with 16 bits (twice the error in the first rows).  This lane holds the query's entries 16 ks + 8 kg + 0..7 (its partner lane ^ 32 the other
   // half) and the output entries 32 db + 8 gq + 4 kg + 0..3.
+  // Batches of hg steps go through the two free slots and the last tile's own in turn, each requested when the one before it is worked on (behind the
+  // first batch's barrier nobody reads the last tile any more).
+  auto own_step = [&](int i, float& sc, uint2 (&vv)[16]) INLINE_LAMBDA {          // score and values of staged row i
+    const unsigned char* kr = smem + own_k + i * ROWB;
+    const unsigned char* vr = smem + own_v + i * ROWB + kg * 8;
+    u32x4 kk[8];
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) kk[ks] = *(const u32x4*)(kr + (((2 * ks + kg) ^ (i & 15)) * 16));
+#pragma unroll
+    for (int c = 0; c < 16; ++c) vv[c] = *(const uint2*)(vr + ((c ^ (i & 15)) * 16));
+    float dot[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        dot[e] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, (uint32_t)qf[ks][e]), __builtin_bit_cast(bf16x2_t, (uint32_t)kk[ks][e]), dot[e], false);
+    float xa, xb;
+    pair_values((dot[0] + dot[1]) + (dot[2] + dot[3]), xa, xb);
+    sc = (xa + xb) * p.scale_log2;
+  };
 #pragma unroll 1
   for (int t0 = 1; !PREFILL && t0 <= p.s; t0 += p.hg) {
-    if (t0 > 1) {
-      __syncthreads();
-      issue_own(t0, own_k, own_v);
-    }
     CAUSAL_WAIT_LOADS(0);
     __syncthreads();
+    const uint32_t next_k = own_k ^ TILE_BYTES, next_v = own_v_other;
+    if (t0 + p.hg <= p.s) issue_own(t0 + p.hg, next_k, next_v);
 #pragma unroll 1
     for (int t = t0 + ((t0 + sb + 1) & 1); t < t0 + p.hg && t <= p.s; t += 2) {
-      const int i = (t - t0) * QB + q_wave - q_first + (lane & 31);
-      const unsigned char* kr = smem + own_k + i * ROWB;
-      const unsigned char* vr = smem + own_v + i * ROWB + kg * 8;
-      float dot[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        const u32x4 kk = *(const u32x4*)(kr + (((2 * ks + kg) ^ (i & 15)) * 16));
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          dot[e] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, (uint32_t)qf[ks][e]), __builtin_bit_cast(bf16x2_t, (uint32_t)kk[e]), dot[e], false);
-      }
-      float xa, xb;
-      pair_values((dot[0] + dot[1]) + (dot[2] + dot[3]), xa, xb);
-      const float sc = (xa + xb) * p.scale_log2;
+      float sc;
+      uint2 vv[16];
+      own_step((t - t0) * QB + q_wave - q_first + (lane & 31), sc, vv);
       if (__any(sc - m_run > MAX_SLACK)) {     // as in new_max
         const float m_new = fmaxf(m_run, sc), alpha = __builtin_amdgcn_exp2f(m_run - m_new);
         m_run = m_new;
@@ -448,14 +499,16 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
       l_run += kg == 0 ? pw : 0.f;
 #pragma unroll
       for (int c = 0; c < 16; ++c) {
-        const uint2 vv = *(const uint2*)(vr + ((c ^ (i & 15)) * 16));
         const int db = c >> 2, r = 4 * (c & 3);
-        o[db][r] = fmaf(pw, bf16_lo(vv.x), o[db][r]);
-        o[db][r + 1] = fmaf(pw, bf16_hi(vv.x), o[db][r + 1]);
-        o[db][r + 2] = fmaf(pw, bf16_lo(vv.y), o[db][r + 2]);
-        o[db][r + 3] = fmaf(pw, bf16_hi(vv.y), o[db][r + 3]);
+        o[db][r] = fmaf(pw, bf16_lo(vv[c].x), o[db][r]);
+        o[db][r + 1] = fmaf(pw, bf16_hi(vv[c].x), o[db][r + 1]);
+        o[db][r + 2] = fmaf(pw, bf16_lo(vv[c].y), o[db][r + 2]);
+        o[db][r + 3] = fmaf(pw, bf16_hi(vv[c].y), o[db][r + 3]);
       }
     }
+    own_v_other = own_v;
+    own_k = next_k;
+    own_v = next_v;
   }
   CAUSAL_WAIT_LOADS(0);
 
