@@ -166,11 +166,6 @@ __global__ __launch_bounds__(128 * CW, CW == 1 ? 1 : 2) void attn_tree_bf16_kern
   const int vcol = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);         // piece within the 32-wide head-dim block
   const int v_half = (lane & 1) * 8;
 
-  // bf16 pairs (-1, 0) and (0, -1), kept in registers: written as literals the compiler folds them into an
-  // inline constant whose two halves the instruction does not read that way
-  uint32_t minus_lo = 0x0000BF80u, minus_hi = 0xBF800000u;
-  asm volatile("" : "+v"(minus_lo), "+v"(minus_hi));
-
   floatx16 o[4];
 #pragma unroll
   for (int db = 0; db < 4; ++db)
@@ -270,9 +265,8 @@ __global__ __launch_bounds__(128 * CW, CW == 1 ? 1 : 2) void attn_tree_bf16_kern
         const float p0 = s[8 * m + 2 * j], p1 = s[8 * m + 2 * j + 1];
         const uint32_t h = pack_bf16x2(p0, p1);
         ph[m][j] = h;
-        // tail = p - head, one v_dot2c_f32_bf16 each: p + head.lo * -1 + head.hi * 0 (exact)
-        const float t0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, h), __builtin_bit_cast(bf16x2_t, minus_lo), p0, false);
-        const float t1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, h), __builtin_bit_cast(bf16x2_t, minus_hi), p1, false);
+        // tail = p - head (exact), in plain instructions: the matrix unit stands still while a v_dot2 runs
+        const float t0 = p0 - __uint_as_float(h << 16), t1 = p1 - __uint_as_float(h & 0xFFFF0000u);
         pl[m][j] = pack_bf16x2(t0, t1);
       }
   };
