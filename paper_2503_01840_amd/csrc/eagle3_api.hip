@@ -175,7 +175,7 @@ struct eagle3_ctx {
       // of a prompt's features, K = 3 N: the partial sums are small against the weights then).  8B width, us, unsplit / split and
       // summed: 77 rows 136 / 28 + 6, 512 rows 139 / 56 + 15, 1024 rows 145 / 95 + 17.
       const bool split = direct_out && N < K && ((N + 127) / 128) * ((M + 127) / 128) <= 256 &&
-                         launch_tiles(M, N, K, false, part_floats).S > 1;
+                         many_tiles(M, N, K, false, part_floats).S > 1;
       void* out = epi == GEMM_EPI_SWIGLU ? act_h : (direct_out && !split ? (void*)direct_out : (void*)part);
       CK(launch_gemm_wide((const bf16_t*)act_in, W, M, N, K, epi, out, direct_out && !split ? 0 : part_floats, &S, st,
                           sp ? sp->a : nullptr, sp ? sp->b : nullptr));

@@ -3,7 +3,7 @@
 // Y[M, N] = X[M, K] * W[N, K]^T, fp32 accumulate.  At this width the projections sit at the ridge between weight
 // streaming and the MFMA rate, so the kernel is organised around operand reuse and around keeping the loads, the
 // LDS reads and the MFMAs of a wavefront all in flight at once:
-//   * a workgroup owns a (32 FM WGM) x (16 FB WGN) output tile; its WGM x WGN wavefronts each hold 2 FM x FB
+//   * a workgroup owns a (32 FM WGM) x (16 FB WGN) output tile (FM = 1: the last of its 64-row activation tiles may be half a one); its WGM x WGN wavefronts each hold 2 FM x FB
 //     accumulators of v_mfma_f32_16x16x32_bf16 and there is no cross-wavefront reduction.  With many rows the chip is bound by
 //     power: products alone sustain 1.88 PFLOP/s as 32x32x16 and 2.14 as 16x16x32 (the sum over 32 k stays inside the matrix
 //     unit), with their operands read from LDS 1.64 and 1.86.  With one set of sums they come out bit for bit the same;
@@ -119,6 +119,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   // SwiGLU: gate and up rows in turns of 32, so that both of a pair are accumulators of one lane in two fragments; or, where a wavefront's
   // fragments don't come in fours, in turns of 8, both in one fragment
   constexpr int PAIR = FB % 4 == 0 ? 32 : 8;
+  constexpr bool HALF = TM % 64 != 0;                  // the last 64-row activation tile is half a one
   constexpr int SUB = BK / 32;                         // sub-stages of a weight stage
   constexpr int A_SLOT = TM * 64, B_SLOT = TN * BK * 2;              // bytes
   constexpr int B_BASE = A_SLOTS * A_SLOT;
@@ -130,8 +131,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   // (224 rows: 28 weight pieces, four for each of the first B_FULL = 4 wavefronts and three for the others; the waits below count the fewer)
   constexpr int B_PIECES = B_SLOT / 1024, B_DMA = (B_PIECES + NW - 1) / NW, B_FULL = B_PIECES - NW * (B_DMA - 1), BP = (B_DMA + SUB - 1) / SUB;
   constexpr int B_LANES = BK / 8, B_ROWS = 64 / B_LANES;           // lanes to a row of a weight piece, rows of a piece
-  static_assert((BK == 64 || BK == 128) && B_DMA > (SUB - 1) * BP && B_FULL > 0, "1 KiB pieces per wavefront");
-  static_assert(TM % 64 == 0 && (WGM == 2 || FM == 2) && FB % (PAIR == 32 ? 4 : 1) == 0, "whole 64-row activation tiles");
+  static_assert((BK == 64 || BK == 128) && B_FULL > 0 && TM % 32 == 0, "1 KiB pieces per wavefront");
+  static_assert(FM == 1 || (!HALF && (WGM == 2 || FM == 2)), "a wavefront's 32-row blocks are one, one of every pair, or two neighbours");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
@@ -160,7 +161,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
 #pragma unroll
   for (int i = 0; i < A_DMA; ++i) {
     const int q = a_first + i, rt = min(mblock * (TM / 64) + (q >> 2), MT - 1);
-    aptr[i] = p.x + (((size_t)rt * (p.K >> 4) + (k_begin >> 4) + ((q >> 1) & 1)) * 2 + (q & 1)) * 512;
+    const bool half = HALF && q >= TM / 64 * 4;                      // its two pieces are the k-steps of row half 0
+    aptr[i] = p.x + (((size_t)rt * (p.K >> 4) + (k_begin >> 4) + (half ? q & 1 : (q >> 1) & 1)) * 2 + (half ? 0 : q & 1)) * 512;
   }
 #pragma unroll
   for (int i = 0; i < B_DMA; ++i) {
@@ -189,7 +191,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   // ---- operand fragments (16 rows x 32 k: lane l holds row l % 16, k 8 (l / 16) .. + 7) inside their slots.  The 32-row
   // blocks of a wavefront: one of every pair (WGM = 2), so that their distances are constants, or two neighbours.
   const int c = lane >> 4;
-  const int a_base = (c >> 1) * 2048 + (c & 1) * 512 + (lane & 15) * 16 + (WGM == 2 ? wm * 1024 : wm * 4096);
+  const int a_base = (c >> 1) * (HALF && wm == WGM - 1 ? 1024 : 2048) + (c & 1) * 512 + (lane & 15) * 16 +
+                     (FM == 1 ? (wm >> 1) * 4096 + (wm & 1) * 1024 : WGM == 2 ? wm * 1024 : wm * 4096);
   constexpr auto a_frag = [](int i) constexpr { return WGM == 2 ? (i >> 1) * 4096 + (i & 1) * 256 : (i >> 1) * 1024 + (i & 1) * 256; };
   // PAIR = 8: a lane's accumulators r = 0, 1 are gate rows and 2, 3 their up rows, so product row 4 a + r is row 2 a + r or 8 + 2 a + r - 2
   const int b_row = PAIR == 8 && p.mode == 1 ? (lane & 2) * 4 + (lane >> 1 & 6) + (lane & 1) : lane & 15;
@@ -230,7 +233,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   // fewest loads of a wavefront in sub-stage u: weights, and all of sub-stages from .. to - 1
   constexpr auto part = [](int u) constexpr {
     const int q = (u % SUB + SUB) % SUB, rest = B_DMA - (B_FULL < NW ? 1 : 0) - q * BP;
-    return rest < BP ? rest : BP;
+    return rest < 0 ? 0 : rest < BP ? rest : BP;
   };
   constexpr auto loads = [part](int from, int to) constexpr {
     int n = 0;
@@ -313,7 +316,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   });
 
   // ---- epilogue.  Accumulator r of lane l: activation row l % 16 of its fragment, weight row 4 (l / 16) + r of its own.
-  auto row_of = [&](int i) { return mblock * TM + (WGM == 2 ? (i >> 1) * 64 + wm * 32 : wm * 64 + (i >> 1) * 32) + (i & 1) * 16 + (lane & 15); };
+  auto row_of = [&](int i) { return mblock * TM + (FM == 1 ? wm * 32 : WGM == 2 ? (i >> 1) * 64 + wm * 32 : wm * 64 + (i >> 1) * 32) + (i & 1) * 16 + (lane & 15); };
   if constexpr (ROPE) {
     // Fragments 2 j and 2 j + 1 hold dimensions i .. i + 3 and i + 64 .. i + 67 of the same head: rotated (q, k), and straight to q or the cache.
     const WideRope& rp = p.rope;
@@ -431,7 +434,7 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   WideParams p;
   if (N % 4) return hipErrorInvalidValue;
   if (hipError_t e = fill_params(p, x, W, M, N, K, epi, out)) return e;
-  const WideTiles t = launch_tiles(M, N, K, epi == GEMM_EPI_SWIGLU, out_capacity_floats);
+  const WideTiles t = many_tiles(M, N, K, epi == GEMM_EPI_SWIGLU, out_capacity_floats);
   p.S = t.S;
   if (S_out) *S_out = t.S;
   // Staggered walks (see above) also up to 256 rows.  us, in step / staggered: gate/up 28672 x 4096 77 rows 55.4 / 51.6, 256 rows 75.6 / 72.8,
@@ -442,6 +445,9 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   // 6144 x 4096 at 116 rows four ranges instead of eight: error 1.37e-7, 1.89e-7 with one chain; and 2 to 3 % faster, in 198 registers
   // instead of 176 and 88 accumulators), and 256 x 128 above 256 rows (512 rows two ranges instead of four: 1.88e-7, 2.72e-7 with one; 1 % slower).
   if (t.cols == 128 && t.k == 128) {
+    if (t.rows == 96)
+      return stagger ? launch_cfg<3, 2, 1, 4, 128, 8, 3, 1, true, 2>(p, t.S, st, ev_start, ev_stop)
+                     : launch_cfg<3, 2, 1, 4, 128, 8, 3, 1, false, 2>(p, t.S, st, ev_start, ev_stop);
     if (t.rows == 256 && M > 256) return launch_cfg<4, 2, 2, 4, 128, 4, 3, 1, false, 2>(p, t.S, st, ev_start, ev_stop);
     if (t.rows == 256)
       return stagger ? launch_cfg<4, 2, 2, 4, 128, 4, 3, 1, true>(p, t.S, st, ev_start, ev_stop)
@@ -456,8 +462,17 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   }
   if (t.cols == 224) return launch_cfg<4, 2, 2, 7, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
   if (t.cols == 192) return launch_cfg<4, 2, 2, 6, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
-  return t.rows == 256 ? launch_cfg<2, 4, 4, 4, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop)
-                       : launch_cfg<2, 4, 3, 4, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
+  if (t.rows == 96)
+    return stagger ? launch_cfg<3, 2, 1, 8, 64, 8, 3, 1, true, 2>(p, t.S, st, ev_start, ev_stop)
+                   : launch_cfg<3, 2, 1, 8, 64, 8, 3, 1, false, 2>(p, t.S, st, ev_start, ev_stop);
+  if (t.rows == 128)
+    return stagger ? launch_cfg<2, 4, 2, 4, 64, 6, 3, 1, true, 2>(p, t.S, st, ev_start, ev_stop)
+                   : launch_cfg<2, 4, 2, 4, 64, 6, 3, 1, false, 2>(p, t.S, st, ev_start, ev_stop);
+  if (t.rows == 256)
+    return stagger ? launch_cfg<2, 4, 4, 4, 64, 4, 3, 1, true>(p, t.S, st, ev_start, ev_stop)
+                   : launch_cfg<2, 4, 4, 4, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
+  return stagger ? launch_cfg<2, 4, 3, 4, 64, 4, 3, 1, true>(p, t.S, st, ev_start, ev_stop)
+                 : launch_cfg<2, 4, 3, 4, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
 }
 
 // q/k/v of more than 256 rows, rotated and in their places, where the product is not split and its tile has fragments in pairs.  As 50 MB of fp32 results

@@ -27,7 +27,7 @@ inline bool wide_stagger(int M, int K, const WideTiles& t) { return M <= 256 && 
 // but gate/up 28672 x 4096 77 rows 53 / 57, LM head 151936 x 3584 77 rows 248 / 267.
 // 129, 160, 200 and 256 rows: 0.3 % and 9 %.  Stages of 64 k are left there for splits whose ranges 128 does not divide: 4096 x 11008
 // in four of 2752, 200 rows 54 us, in two of 5504 80; 3584 x 18944 in eight of 2368 53, in four 74.
-inline WideTiles wide_tiles_256(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
+inline WideTiles wide_tiles_256(int M, int N, int K, bool swiglu, size_t out_capacity_floats, float* time = nullptr) {
   const bool few = M <= 128;
   const int rows = few ? 128 : 256, per_xcd = ((N + 127) / 128 + 7) / 8;
   const float slower = 1.f + 0.0008f * (M - 77);                       // up to 128 rows
@@ -52,6 +52,7 @@ inline WideTiles wide_tiles_256(int M, int N, int K, bool swiglu, size_t out_cap
       }
       if (least == 0.f || t < least) { least = t; best = {rows, 128, S, k}; }
     }
+  if (time) *time = least;
   return best;
 }
 
@@ -133,6 +134,63 @@ inline WideTiles launch_tiles(int M, int N, int K, bool swiglu, size_t out_capac
     if (K / t.S <= chain && time < least) { best = t; least = time; }
   }
   return best;
+}
+
+// What is launched up to 256 rows: that, or a tile with fewer activation lines for each weight line.  A CU has some 200 lines on their way at a time and
+// they come back in order, so a line of activations from L2 keeps its place as long as the weight lines from HBM in front of it; neither the products (left
+// out: 77 rows 54 us as with them) nor where the activations come from (one line again and again: 54 us) matter.  So
+//   up to 96 rows, 96 x 128 in six wavefronts with eight activation slots instead of 128 x 128 with stages of 128 k;
+//   256 weight rows to a workgroup, stages of 64 k, where they are enough workgroups: 96, 128, 192 or 256 rows.
+// us: 28672 x 4096 77 rows 52.8 / 47.9, down 4096 x 14336 32.8 / 30.1, o 15.3 / 14.1, q/k/v 19.1 / 18.1; LM head 128256 x 4096 77 rows 217 / 200, 116 rows
+// 224 / 209, 256 rows 307 / 280; 57344 x 8192 77 rows 187 / 168, 116 rows 189 / 177, 256 rows 266 / 229.  Tiles of 112 weight rows, which are 256 for 8B
+// gate/up instead of 224, gave nothing (77 rows 50, 256 rows 69), nor did wavefronts that load activations only and weights only (116 rows 59).
+// The estimates, a start, a time per stage that grows with the workgroups on the fullest XCD, and the partial sums, are fits to 72 products of 15 model
+// shapes, all splits, at two row counts each (0.05 to 0.06 in the logarithm).  Against the estimate of wide_tiles_256, which comes out 2 to 10 % low for unsplit products
+// in stages of 64 k up to 128 rows, the margins are 3 % the other way elsewhere and for 96 x 128.  Chains of sums are no longer than before (128 x 128 with stages
+// of 128 k, and the new ones up to 128 rows: two sets); 256 weight rows only where an XCD has more than 16 workgroups (28672 x 4096, 14 of them: 68, 48 in
+// 96 x 128), with ranges of at least 1024 k, and in a split not of a multiple of 4 KB (in step: 8192 x 28672 in seven ranges 77 rows 112, 100 otherwise).
+// Time against that of wide_tiles_256, 142 products each: 65..96 rows 0.942, 97..128 0.984, 129..192 0.973, 193..256 0.979; slower by more than 1 %: 65792 x 4352 at
+// 160 and 192 rows (4.5 and 2.4).
+inline WideTiles stream_tiles(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
+  struct Fit { int cols, k, sets; float start, stage, busy, sums; };   // us; of a stage, more of it with all CUs busy, per million partial sums
+  static constexpr Fit strips = {128, 128, 2, 4.53f, 0.89f, 0.58f, 2.29f};                                               // 96 rows
+  static constexpr Fit wide[4] = {{256, 64, 2, 5.44f, 0.76f, 0.64f, 2.05f}, {256, 64, 2, 5.87f, 0.8f, 0.66f, 1.89f},     // 96, 128 rows
+                                  {256, 64, 1, 7.77f, 0.9f, 0.7f, 1.65f}, {256, 64, 1, 9.69f, 0.93f, 0.76f, 1.61f}};     // 192, 256 rows
+  auto per_xcd = [&](const Fit& f, int S) { return ((N + f.cols - 1) / f.cols + 7) / 8 * S; };
+  auto time = [&](const Fit& f, int S) {
+    const int n = per_xcd(f, S), last = n > 32 && n % 32 < 12 ? 12 : n % 32;       // a few workgroups behind whole rounds have no CU less to wait for
+    const float stages = (float)K / S / f.k;
+    return n / 32 * (f.start + (f.stage + f.busy) * stages) + (n % 32 ? f.start + stages * (f.stage + f.busy * last / 32) : 0.f) +
+           (swiglu ? 0.f : (float)S * M * N * f.sums * 1e-6f);
+  };
+  float least = 0.f;
+  WideTiles best = wide_tiles_256(M, N, K, swiglu, out_capacity_floats, &least);
+  const int chain = K / best.S / (M <= 128 && best.k == 128 ? 2 : 1);
+  const bool small_stages = M <= 128 && best.k == 64;
+  if (M <= 96 && best.k == 128) {
+    best.rows = 96;
+    least = time(strips, best.S);
+  } else {
+    least *= small_stages ? 1.05f : 0.97f;
+  }
+  auto consider = [&](const Fit& f, int rows, float margin) {
+    for (int S = 1; S <= (swiglu ? 1 : 8); ++S) {
+      const int range = K / S;
+      if (K % (f.k * S) || range < 512 || range > chain * f.sets || (S > 1 && (size_t)S * M * N > out_capacity_floats)) continue;
+      if (f.cols == 256 && (per_xcd(f, S) <= 16 || range < 1024 || (S > 1 && range % 2048 == 0))) continue;
+      const float t = margin * time(f, S);
+      if (t < least) { least = t; best = {rows, f.cols, S, f.k}; }
+    }
+  };
+  if (M <= 96 && (!small_stages || K > 1024)) consider(strips, 96, small_stages ? 1.08f : 1.f);      // (1536 x 512 9.0, 9.4 in 96 x 128)
+  const int i = M <= 96 ? 0 : M <= 128 ? 1 : M <= 192 ? 2 : 3;
+  consider(wide[i], i == 0 ? 96 : 64 * (i + 1), 1.f);
+  return best;
+}
+
+// Of more than 64 rows: what is launched.
+inline WideTiles many_tiles(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
+  return M <= 256 ? stream_tiles(M, N, K, swiglu, out_capacity_floats) : launch_tiles(M, N, K, swiglu, out_capacity_floats);
 }
 
 // ---- at most 64 rows
