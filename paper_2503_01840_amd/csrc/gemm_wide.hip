@@ -19,7 +19,7 @@
 //     are dealt out between the products one by one, so that neither a full load queue nor a burst of reads holds up the matrix
 //     pipe (256 x 256 tiles: 2390 cycles per 64 k, of which 2048 are products; 2600 with them in bursts);
 //   * the workgroups that share a weight tile (one per 256 activation rows) are launched next to each other on
-//     the same XCD, so the tile leaves HBM once;
+//     the same XCD, so the tile leaves HBM once; in split products of many activations an XCD has one K range, or two or four, of them all;
 //   * the weights are the MFMA's first operand: a lane then holds, for ONE activation row, runs of four
 //     consecutive output columns, which is what both epilogues store: fp32 split-K partials (16-byte stores), or
 //     SwiGLU (the tile interleaves gate and up rows so that both values of a pair sit in the same lane) written
@@ -60,7 +60,8 @@ struct WideParams {
   int rows[3];
   int nmat, mode;
   int M, N, K, S, epi;
-  int tiles, groups, mblocks;           // weight tiles, ceil(tiles / 8), activation-row blocks
+  int tiles, groups, mblocks;           // weight tiles, those of an XCD, activation-row blocks
+  int ranges;                           // 1, 2, 4 or 8: XCD x has the K ranges x % ranges + ranges i only
   float* out_f32;
   bf16_t* out_xf;
   WideRope rope;
@@ -140,7 +141,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   // XCD take the activation-row blocks of ONE weight tile, so that the tile is fetched into that L2 once.
   int j = blockIdx.x >> 3;
   const int mblock = j % p.mblocks;  j /= p.mblocks;
-  const int tile = (j % p.groups) * 8 + (blockIdx.x & 7), split = j / p.groups;
+  const int xcd = blockIdx.x & 7, tile = (j % p.groups) * (8 / p.ranges) + xcd / p.ranges, split = j / p.groups * p.ranges + xcd % p.ranges;
   if (tile >= p.tiles) return;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -403,9 +404,13 @@ hipError_t launch_cfg(WideParams& p, int S, hipStream_t st, hipEvent_t ev_start,
   hipError_t ce = configured.run([&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS); });
   if (ce != hipSuccess) return ce;
   p.tiles = (p.N + TN - 1) / TN;
-  p.groups = (p.tiles + 7) / 8;
+  // Activations that an XCD's 4 MB of L2 cannot hold are fetched by each of them again, unless it has some of the K ranges only.  Product alone, us, all ranges / its
+  // own: down 4096 x 14336 256 rows 44.2 / 42.5, 512 rows 66.8 / 64.4, 2048 rows 184 / 178; but o 4096 x 4096 512 rows (4.2 MB) 25.6 / 26.0, q/k/v 37.9 / 38.1.
+  p.ranges = 1;
+  while (p.ranges < 8 && S % (2 * p.ranges) == 0 && (size_t)p.M * p.K * sizeof(bf16_t) > ((size_t)6 << 20)) p.ranges *= 2;
+  p.groups = (p.tiles + 8 / p.ranges - 1) / (8 / p.ranges);
   p.mblocks = (p.M + TM - 1) / TM;
-  launch_with_events(kernel, dim3(8 * p.groups * p.mblocks * S), dim3(64 * WGM * WGN), LDS, st, ev_start, ev_stop, p);
+  launch_with_events(kernel, dim3(8 * p.groups * p.mblocks * (S / p.ranges)), dim3(64 * WGM * WGN), LDS, st, ev_start, ev_stop, p);
   return hipGetLastError();
 }
 
