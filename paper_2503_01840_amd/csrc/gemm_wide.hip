@@ -60,8 +60,9 @@ struct WideParams {
   int rows[3];
   int nmat, mode;
   int M, N, K, S, epi;
-  int tiles, groups, mblocks;           // weight tiles, those of an XCD, activation-row blocks
-  int ranges;                           // 1, 2, 4 or 8: XCD x has the K ranges x % ranges + ranges i only
+  int tiles, mblocks;                   // weight tiles, activation-row blocks
+  uint32_t inv_mblocks;                 // 2^20 / mblocks, rounded up, or 0: divide
+  int ranges;                           // log2 of 1, 2, 4 or 8: XCD x has the K ranges x % 2^ranges + 2^ranges i only
   float* out_f32;
   bf16_t* out_xf;
   WideRope rope;
@@ -139,9 +140,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
 
   // Workgroups go to the XCDs round-robin by their linear id: id % 8 is the XCD.  Consecutive workgroups of one
   // XCD take the activation-row blocks of ONE weight tile, so that the tile is fetched into that L2 once.
-  int j = blockIdx.x >> 3;
-  const int mblock = j % p.mblocks;  j /= p.mblocks;
-  const int xcd = blockIdx.x & 7, tile = (j % p.groups) * (8 / p.ranges) + xcd / p.ranges, split = j / p.groups * p.ranges + xcd % p.ranges;
+  const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+  const int group = p.mblocks == 1 ? j : p.inv_mblocks ? (int)((uint64_t)j * p.inv_mblocks >> 20) : j / p.mblocks, mblock = j - group * p.mblocks;
+  const int tile = (group << (3 - p.ranges)) + (xcd >> p.ranges), split = ((int)blockIdx.y << p.ranges) + (xcd & ((1 << p.ranges) - 1));
   if (tile >= p.tiles) return;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -406,11 +407,13 @@ hipError_t launch_cfg(WideParams& p, int S, hipStream_t st, hipEvent_t ev_start,
   p.tiles = (p.N + TN - 1) / TN;
   // Activations that an XCD's 4 MB of L2 cannot hold are fetched by each of them again, unless it has some of the K ranges only.  Product alone, us, all ranges / its
   // own: down 4096 x 14336 256 rows 44.2 / 42.5, 512 rows 66.8 / 64.4, 2048 rows 184 / 178; but o 4096 x 4096 512 rows (4.2 MB) 25.6 / 26.0, q/k/v 37.9 / 38.1.
-  p.ranges = 1;
-  while (p.ranges < 8 && S % (2 * p.ranges) == 0 && (size_t)p.M * p.K * sizeof(bf16_t) > ((size_t)6 << 20)) p.ranges *= 2;
-  p.groups = (p.tiles + 8 / p.ranges - 1) / (8 / p.ranges);
+  p.ranges = 0;
+  while (p.ranges < 3 && S % (2 << p.ranges) == 0 && (size_t)p.M * p.K * sizeof(bf16_t) > ((size_t)6 << 20)) ++p.ranges;
+  const int groups = (p.tiles + (8 >> p.ranges) - 1) >> (3 - p.ranges);
   p.mblocks = (p.M + TM - 1) / TM;
-  launch_with_events(kernel, dim3(8 * p.groups * p.mblocks * (S / p.ranges)), dim3(64 * WGM * WGN), LDS, st, ev_start, ev_stop, p);
+  p.inv_mblocks = ((1u << 20) + p.mblocks - 1) / p.mblocks;
+  if ((int64_t)groups * p.mblocks * p.mblocks >= 1 << 20) p.inv_mblocks = 0;               // what j * inv_mblocks >> 20 is exact for
+  launch_with_events(kernel, dim3(8 * groups * p.mblocks, S >> p.ranges), dim3(64 * WGM * WGN), LDS, st, ev_start, ev_stop, p);
   return hipGetLastError();
 }
 
