@@ -498,11 +498,11 @@ __global__ __launch_bounds__(256) void attn_tree_f32_kernel(const float* __restr
 template <int LPK>
 __global__ __launch_bounds__(256) void attn_tree_f32_rows_kernel(const float* __restrict__ q, const float* __restrict__ kc,
                                                                 const float* __restrict__ vc, const SeqInfo* __restrict__ seq,
-                                                                const uint32_t* __restrict__ mask, int N, int H, int Hkv, float scale,
-                                                                float* __restrict__ out) {
+                                                                const uint32_t* __restrict__ mask, Divisor by_rows, Divisor by_heads, int H, int Hkv,
+                                                                float scale, float* __restrict__ out) {
   constexpr int D4 = LPK, DH = 4 * LPK, G = 256 / LPK, U = 5;
   __shared__ float go[G][DH], gm[G], gl[G];
-  const int r = blockIdx.x, h = blockIdx.y, b = r / N, g = h * Hkv / H, tid = threadIdx.x;
+  const int r = blockIdx.x, h = blockIdx.y, b = r / by_rows, g = h * Hkv / by_heads, tid = threadIdx.x;
   const int grp = tid / D4, at = 4 * (tid % D4);
   const SeqInfo si = seq[b];
   const int L = si.n_prefix + si.n_tail;
@@ -617,7 +617,7 @@ hipError_t launch_tree_attention(bool bf16, const void* q, const void* kcache, c
     if ((d == 64 || d == 128) && (((uintptr_t)q | (uintptr_t)kcache | (uintptr_t)vcache | (uintptr_t)mask) & 15) == 0) {
       auto kernel = d == 64 ? attn_tree_f32_rows_kernel<16> : attn_tree_f32_rows_kernel<32>;
       hipLaunchKernelGGL(kernel, dim3(R, H), dim3(256), 0, st, (const float*)q, (const float*)kcache, (const float*)vcache, seq, mask,
-                         rows_per_seq, H, Hkv, scale, (float*)out);
+                         divisor(rows_per_seq), divisor(H), H, Hkv, scale, (float*)out);
       return hipGetLastError();
     }
     hipLaunchKernelGGL(attn_tree_f32_kernel, dim3(R, H), dim3(256), lds, st, (const float*)q, (const float*)kcache,

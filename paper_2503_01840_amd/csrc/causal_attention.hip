@@ -60,7 +60,8 @@ struct CausalParams {
   const bf16_t* v;
   const SeqInfo* seq;     // prefill: kv_base and n_prefix of the sequence
   int T, H, Hkv, s;
-  int hg, n_groups, n_qblocks;      // query heads per workgroup, KV heads x head groups, query blocks
+  int hg, qb_log2, n_qblocks, G;    // query heads per workgroup, log2 of its queries, query blocks, query heads per KV head
+  Divisor by_groups, by_kv_heads;   // KV heads x head groups; KV heads
   float scale_log2;
   bool q_aligned;         // to 16 bytes
   void* out;              // training: fp32 [T, H, D]; prefill: fragment-major bf16 [T, H * D]
@@ -111,12 +112,12 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
   constexpr int IPW_ROWS = ROWS_WG / 4 / NW;                 // and for one row of each of the workgroup's queries
   const int rg = wave % RG, sb = wave / RG;                  // row group, key half
   const int kg = lane >> 5;
-  const int gh = blockIdx.x % p.n_groups;
-  const int qb = p.n_qblocks - 1 - (int)blockIdx.x / p.n_groups;
-  const int g = gh % p.Hkv, G = p.H / p.Hkv;
-  const int QB = ROWS_WG / p.hg;                             // queries per workgroup
-  const int head = g * G + (gh / p.Hkv) * p.hg + rg * 32 / QB;
-  const int q_first = qb * QB, q_wave = q_first + (rg * 32) % QB;
+  const int gh = (int)blockIdx.x % p.by_groups;
+  const int qb = p.n_qblocks - 1 - (int)blockIdx.x / p.by_groups;
+  const int first_head = gh % p.by_kv_heads * p.G + gh / p.by_kv_heads * p.hg, g = gh % p.by_kv_heads;
+  const int QB = 1 << p.qb_log2;                             // queries per workgroup
+  const int head = first_head + (rg * 32 >> p.qb_log2);
+  const int q_first = qb * QB, q_wave = q_first + (rg * 32 & (QB - 1));
   const int T = p.T;
   const int pos0 = PREFILL ? p.seq[0].n_prefix : 0;          // position of query 0
   const int pos_wave = pos0 + q_wave, pos = pos_wave + (lane & 31);
@@ -169,8 +170,8 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
   auto issue_own = [&](int t0, uint32_t k_slot, uint32_t v_slot) INLINE_LAMBDA {
 #pragma unroll
     for (int i = 0; i < IPW_ROWS; ++i) {
-      const int j = wave * IPW_ROWS + i, r = (4 * j) % QB + lkey;             // staged rows 4j .. 4j+3: one step
-      const int t = min(t0 + 4 * j / QB, p.s);
+      const int j = wave * IPW_ROWS + i, r = (4 * j & (QB - 1)) + lkey;       // staged rows 4j .. 4j+3: one step
+      const int t = min(t0 + (4 * j >> p.qb_log2), p.s);
       const size_t base = ((size_t)t * T + q_first) * row_stride;
       const uint32_t off = (uint32_t)(min(q_first + r, T - 1) - q_first) * (uint32_t)(row_stride * 2) +
                            (uint32_t)(((lane & 15) ^ (4 * (j & 3) + lkey)) * 16);
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(128 * RG) void causal_attn_bf16_kernel(CausalParams
 #pragma unroll
   for (int i = 0; i < IPW_ROWS; ++i) {
     const int j = wave * IPW_ROWS + i, r = 4 * j + lkey, rgj = j >> 3;
-    const int h = g * G + (gh / p.Hkv) * p.hg + rgj * 32 / QB, qr = min(q_first + (rgj * 32) % QB + (r & 31), T - 1);
+    const int h = first_head + (rgj * 32 >> p.qb_log2), qr = min(q_first + (rgj * 32 & (QB - 1)) + (r & 31), T - 1);
     const uint32_t off = (uint32_t)(qr - q_first) * (uint32_t)(p.H * ROWB) + (uint32_t)(((lane & 15) ^ (r & 15)) * 16);
     const bf16_t* src = p.q + ((size_t)q_first * p.H + h) * D;
     if (__builtin_expect(p.q_aligned, 1)) {
@@ -719,11 +720,14 @@ hipError_t launch_causal(CausalParams& p, hipStream_t st) {
   hipError_t ce = configured.run([&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES); });
   if (ce != hipSuccess) return ce;
   p.hg = heads_per_wg(p.H, p.Hkv, RG);
-  p.n_groups = p.H / p.hg;
-  p.n_qblocks = workgroups(p.T, p.H, p.Hkv, RG) / p.n_groups;
+  const int groups = p.H / p.hg;
+  p.n_qblocks = workgroups(p.T, p.H, p.Hkv, RG) / groups;
+  p.qb_log2 = (RG == 4 ? 7 : 6) - (p.hg == 4 ? 2 : p.hg == 2 ? 1 : 0);         // 32 RG / hg
+  p.G = p.H / p.Hkv;
+  p.by_groups = divisor(groups); p.by_kv_heads = divisor(p.Hkv);
   p.scale_log2 = 1.4426950408889634f / sqrtf((float)D);
   p.q_aligned = ((uintptr_t)p.q & 15) == 0;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)p.n_groups * p.n_qblocks), dim3(128 * RG), LDS_BYTES, st, p);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)groups * p.n_qblocks), dim3(128 * RG), LDS_BYTES, st, p);
   return hipGetLastError();
 }
 

@@ -193,15 +193,16 @@ __global__ __launch_bounds__(1024) void begin_rows_kernel(BeginRows p, int prep_
   }
 }
 
-// One workgroup per row; a thread handles four consecutive rotary pairs (i..i+3, i+d/2..i+d/2+3) of one head.  (fp32: gemm_f32.hip.)
+// One workgroup per row; a thread handles four consecutive rotary pairs (i..i+3, i+d/2..i+d/2+3) of one head of d = 128.  (fp32: gemm_f32.hip.)
 __global__ __launch_bounds__(1024) void rope_kv_write_kernel(const float* __restrict__ qkv, int S, int R, int H, int Hkv,
-                                                            int d, const float* __restrict__ cs, int cs_step,
+                                                            const float* __restrict__ cs, int cs_step,
                                                             const int32_t* __restrict__ slot, bf16_t* __restrict__ q,
                                                             bf16_t* __restrict__ kc, bf16_t* __restrict__ vc) {
-  const int r = blockIdx.x, half = d / 2, NT = (H + 2 * Hkv) * d, q4 = half / 4;
+  constexpr int d = 128, half = d / 2, q4 = half / 4;
+  const int r = blockIdx.x, NT = (H + 2 * Hkv) * d;
   const size_t sl = (size_t)slot[r];
   for (int e = threadIdx.x; e < (H + 2 * Hkv) * q4; e += blockDim.x) {
-    const int h = e / q4, i = (e % q4) * 4;
+    const int h = (unsigned)e / q4, i = (unsigned)e % q4 * 4;
     float4 x1 = make_float4(0.f, 0.f, 0.f, 0.f), x2 = x1;
     for (int s0 = 0; s0 < S; s0 += 4) {                 // four partial sums per memory round trip, added in order
       float4 a[4], b[4];
@@ -360,9 +361,9 @@ hipError_t launch_begin_rows(bool bf16, const BeginRows& b, float* x, int R, int
 
 hipError_t launch_rope_kv_write(const float* qkv_partial, int S, int R, int H, int Hkv, int d, const float* cs, int cs_step,
                                 const int32_t* slot, void* q, void* kcache, void* vcache, hipStream_t st) {
-  if (d % 8) return hipErrorInvalidValue;
+  if (d != 128) return hipErrorInvalidValue;
   const int bd = std::min(1024, ((H + 2 * Hkv) * d / 8 + 63) / 64 * 64);
-  hipLaunchKernelGGL(rope_kv_write_kernel, dim3(R), dim3(bd), 0, st, qkv_partial, S, R, H, Hkv, d, cs, cs_step, slot, (bf16_t*)q,
+  hipLaunchKernelGGL(rope_kv_write_kernel, dim3(R), dim3(bd), 0, st, qkv_partial, S, R, H, Hkv, cs, cs_step, slot, (bf16_t*)q,
                      (bf16_t*)kcache, (bf16_t*)vcache);
   return hipGetLastError();
 }

@@ -21,6 +21,7 @@ struct F32Params {
   const float* w[3];
   int rows[3];
   int nmat, M, N, K;
+  Divisor by_half;             // half a head, for rotary pairs
   float* out;
   F32Fuse f;
 };
@@ -101,7 +102,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Params p) {
   const float* wr[NW];
   const F32Fuse& f = p.f;
   const int half = f.d / 2;
-  const int head = EPI == ROPE ? n / half : 0, pair = EPI == ROPE ? n - head * half : 0;
+  const int head = EPI == ROPE ? n / p.by_half : 0, pair = EPI == ROPE ? n - head * half : 0;
   if constexpr (EPI == SWIGLU) {
     wr[0] = p.w[0] + (size_t)n * p.K;
     wr[1] = p.w[1] + (size_t)n * p.K;
@@ -183,6 +184,7 @@ hipError_t launch_gemm_f32(const float* x, const GemmWeights& W, int M, int N, i
   p.nmat = W.nmat; p.M = M; p.N = epi == GEMM_EPI_SWIGLU || epi == GEMM_EPI_ROPE ? N / 2 : N; p.K = K;
   p.out = out;
   p.f = fuse;
+  p.by_half = divisor(epi == GEMM_EPI_ROPE ? fuse.d / 2 : 1);
   const dim3 grid((p.N + 3) / 4, (M + RM - 1) / RM);
   auto run = [&](auto e) {
     constexpr int E = decltype(e)::value;
