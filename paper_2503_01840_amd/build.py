@@ -9,7 +9,9 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libeagle3.so")
 SOURCES = ["eagle3_api.hip", "gemm_skinny.hip", "gemm_wide.hip", "gemm_f32.hip", "elementwise.hip", "attention.hip", "select.hip",
            "accept.hip", "commit.hip", "causal_attention.hip"]
-FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+# Kernel arguments, as far as they fit (14 registers), are in registers when a wavefront starts instead of behind its first memory round trip.  That is for
+# arguments of their own, not for members of a struct: what a kernel needs for its first loads comes first in its list.
+FLAGS = ["-O3", "-mllvm", "-amdgpu-kernarg-preload-count=16", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 
 
