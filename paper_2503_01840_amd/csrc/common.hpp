@@ -222,9 +222,9 @@ struct DeviceOnce {
 
 // Launch with an optional start/stop event pair attached to the dispatch itself: the events then carry the
 // kernel's own begin and end timestamps (what a kernel trace reports), not the time between two stream markers.
-template <typename Kernel, typename Params>
+template <typename Kernel, typename... Args>
 inline void launch_with_events(Kernel kernel, dim3 grid, dim3 block, unsigned lds_bytes, hipStream_t st, hipEvent_t ev_start,
-                               hipEvent_t ev_stop, const Params& p) {
-  if (ev_start && ev_stop) hipExtLaunchKernelGGL(kernel, grid, block, lds_bytes, st, ev_start, ev_stop, 0, p);
-  else hipLaunchKernelGGL(kernel, grid, block, lds_bytes, st, p);
+                               hipEvent_t ev_stop, const Args&... args) {
+  if (ev_start && ev_stop) hipExtLaunchKernelGGL(kernel, grid, block, lds_bytes, st, ev_start, ev_stop, 0, args...);
+  else hipLaunchKernelGGL(kernel, grid, block, lds_bytes, st, args...);
 }

@@ -29,45 +29,48 @@ constexpr int SMEM_BYTES = 4 * 64 * RED_LD * 4 > 2 * BN * WROW ? 4 * 64 * RED_LD
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// What is behind the arguments that a wavefront has in registers from the start (as one struct with them, behind a memory round trip: together with
+// gemm_wide.hip an 8B step 6140 us, 6097 now)
 struct GemmParams {
-  const bf16_t* x;
-  const bf16_t* w[3];
-  int rows[3];
-  int nmat, mode;
-  int M, N, K, S, epi;
+  const bf16_t* w2;
+  int rows0, rows1;
+  int M, epi;
   float* out_f32;
   bf16_t* out_xf;
 };
 
-__device__ __forceinline__ const bf16_t* weight_row(const GemmParams& p, int tile, int row) {
-  if (p.mode == 1) {                                   // 32 gate rows | 32 up rows
-    int r = tile * 32 + (row & 31);
-    r = min(r, p.rows[0] - 1);
-    return p.w[row >> 5] + (size_t)r * p.K;
-  }
-  int n = min(tile * BN + row, p.N - 1);
-  int m = 0;
-  while (m + 1 < p.nmat && n >= p.rows[m]) { n -= p.rows[m]; ++m; }
-  return p.w[m] + (size_t)n * p.K;
-}
-
 template <int MH>
-__global__ __launch_bounds__(256, 2) void gemm_skinny_kernel(GemmParams p) {
+__global__ __launch_bounds__(256, 2) void gemm_skinny_kernel(const bf16_t* x, const bf16_t* w0, const bf16_t* w1, int K, int S, int N, int kind, GemmParams p) {
+  const int mode = kind & 1, nmat = kind >> 1;         // kind: 2 x matrices + mode
   __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM_BYTES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tile = blockIdx.x, split = blockIdx.y, mtile = blockIdx.z;
-  const int Kc = p.K / p.S, k_begin = split * Kc, KT = Kc / BK;
+  const int Kc = K / S, k_begin = split * Kc, KT = Kc / BK;
+  auto weight_row = [&](int row) {
+    if (mode == 1) {                                   // 32 gate rows | 32 up rows
+      const int r = min(tile * 32 + (row & 31), p.rows0 - 1);
+      return (row >> 5 ? w1 : w0) + (size_t)r * K;
+    }
+    int n = min(tile * BN + row, N - 1);
+    const bf16_t* w = w0;
+    if (nmat > 1 && n >= p.rows0) {
+      n -= p.rows0;
+      w = w1;
+      if (nmat > 2 && n >= p.rows1) { n -= p.rows1; w = p.w2; }
+    }
+    return w + (size_t)n * K;
+  };
 
   const bf16_t* wptr[WCH];
   int wlds[WCH];
 #pragma unroll
   for (int i = 0; i < WCH; ++i) {
     const int c = tid + 256 * i, row = c / CPR, col = c % CPR;
-    wptr[i] = weight_row(p, tile, row) + k_begin + col * 8;
+    wptr[i] = weight_row(row) + k_begin + col * 8;
     wlds[i] = row * WROW + col * 16;
   }
   // A-operand blocks of this wavefront: k-steps (k_begin + kt*BK + wave*(BK/4))/16 + {0..KSW-1}, halves 0..MH-1
-  const bf16_t* xptr = p.x + (((size_t)mtile * (p.K >> 4) + ((k_begin + wave * (BK / 4)) >> 4)) * 2 * 64 + lane) * 8;
+  const bf16_t* xptr = x + (((size_t)mtile * (K >> 4) + ((k_begin + wave * (BK / 4)) >> 4)) * 2 * 64 + lane) * 8;
 
   u32x4 wreg[PF][WCH];
   u32x4 xreg[PF][KSW][MH];
@@ -171,10 +174,10 @@ __global__ __launch_bounds__(256, 2) void gemm_skinny_kernel(GemmParams p) {
       const float v = red[tok * RED_LD + f] + red[(64 + tok) * RED_LD + f] + red[(128 + tok) * RED_LD + f] +
                       red[(192 + tok) * RED_LD + f];
       const int row = mtile * 64 + tok, n = tile * BN + f;
-      if (row < p.M && n < p.N) p.out_f32[((size_t)split * p.M + row) * p.N + n] = v;
+      if (row < p.M && n < N) p.out_f32[((size_t)split * p.M + row) * N + n] = v;
     }
   } else {
-    const int I = p.N >> 1;
+    const int I = N >> 1;
 #pragma unroll
     for (int e = 0; e < 4 * MH; ++e) {
       const int idx = tid + 256 * e, tok = idx >> 5, f = idx & 31;
@@ -197,16 +200,17 @@ hipError_t launch_gemm_skinny(const bf16_t* x, const GemmWeights& W, int M, int 
   if (M <= 0 || N <= 0 || K <= 0 || S <= 0 || K % (BK * S) != 0) return hipErrorInvalidValue;
   if (epi == GEMM_EPI_SWIGLU && (S != 1 || W.mode != 1)) return hipErrorInvalidValue;
   GemmParams p;
-  p.x = x;
-  for (int i = 0; i < 3; ++i) { p.w[i] = (const bf16_t*)W.w[i]; p.rows[i] = W.rows[i]; }
-  p.nmat = W.nmat; p.mode = W.mode;
-  p.M = M; p.N = N; p.K = K; p.S = S; p.epi = epi;
+  const bf16_t *w0 = (const bf16_t*)W.w[0], *w1 = (const bf16_t*)W.w[1];
+  p.w2 = (const bf16_t*)W.w[2];
+  p.rows0 = W.rows[0]; p.rows1 = W.rows[1];
+  p.M = M; p.epi = epi;
+  const int kind = 2 * W.nmat + W.mode;
   p.out_f32 = (float*)out; p.out_xf = (bf16_t*)out;
   const int tiles = W.mode == 1 ? (N / 2 + 31) / 32 : (N + BN - 1) / BN;
   dim3 grid(tiles, S, (M + 63) / 64);
   if (M <= 32)
-    launch_with_events(gemm_skinny_kernel<1>, grid, dim3(256), 0, st, ev_start, ev_stop, p);
+    launch_with_events(gemm_skinny_kernel<1>, grid, dim3(256), 0, st, ev_start, ev_stop, x, w0, w1, K, S, N, kind, p);
   else
-    launch_with_events(gemm_skinny_kernel<2>, grid, dim3(256), 0, st, ev_start, ev_stop, p);
+    launch_with_events(gemm_skinny_kernel<2>, grid, dim3(256), 0, st, ev_start, ev_stop, x, w0, w1, K, S, N, kind, p);
   return hipGetLastError();
 }

@@ -60,7 +60,7 @@ struct WideParams {
   int rows[3];
   int nmat, mode;
   int M, N, K, S, epi;
-  int tiles, mblocks;                   // weight tiles, activation-row blocks
+  int mblocks;                          // activation-row blocks
   uint32_t inv_mblocks;                 // 2^20 / mblocks, rounded up, or 0: divide
   int ranges;                           // log2 of 1, 2, 4 or 8: XCD x has the K ranges x % 2^ranges + 2^ranges i only
   float* out_f32;
@@ -115,7 +115,14 @@ __device__ __forceinline__ void unroll(F f) { unroll_seq(std::make_integer_seque
 #define WIDE_PIN() __builtin_amdgcn_sched_barrier(0)
 
 template <int WGM, int WGN, int FM, int FB, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER, int SETS, bool ROPE>
-__global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WideParams p) {
+__global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(const bf16_t* x, const bf16_t* w0, const bf16_t* w1, int K, int S, int N, int M, int rows0,
+                                                                        uint32_t place, uint32_t inv_mblocks, WideParams rest) {
+  // what the first loads need comes as arguments of their own, which are in registers from the start; place: see launch_cfg
+  WideParams p = rest;
+  p.x = x; p.w[0] = w0; p.w[1] = w1; p.rows[0] = rows0;
+  p.K = K; p.S = S; p.N = N; p.M = M;
+  p.mode = place & 1; p.nmat = place >> 1 & 3; p.ranges = place >> 3 & 3; p.mblocks = place >> 5;
+  p.inv_mblocks = inv_mblocks;
   constexpr int FA = 2 * FM;                           // 16-row fragments of a wavefront's activation rows; FB: of its weight rows
   constexpr int TM = 32 * FM * WGM, TN = 16 * FB * WGN, NW = WGM * WGN;
   // SwiGLU: gate and up rows in turns of 32, so that both of a pair are accumulators of one lane in two fragments; or, where a wavefront's
@@ -143,7 +150,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(WidePara
   const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
   const int group = p.mblocks == 1 ? j : p.inv_mblocks ? (int)((uint64_t)j * p.inv_mblocks >> 20) : j / p.mblocks, mblock = j - group * p.mblocks;
   const int tile = (group << (3 - p.ranges)) + (xcd >> p.ranges), split = ((int)blockIdx.y << p.ranges) + (xcd & ((1 << p.ranges) - 1));
-  if (tile >= p.tiles) return;
+  if (tile >= (N + TN - 1) / TN) return;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
@@ -404,16 +411,17 @@ hipError_t launch_cfg(WideParams& p, int S, hipStream_t st, hipEvent_t ev_start,
   static DeviceOnce configured;                        // the attribute belongs to the loaded code object of a device
   hipError_t ce = configured.run([&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS); });
   if (ce != hipSuccess) return ce;
-  p.tiles = (p.N + TN - 1) / TN;
+  const int tiles = (p.N + TN - 1) / TN;
   // Activations that an XCD's 4 MB of L2 cannot hold are fetched by each of them again, unless it has some of the K ranges only.  Product alone, us, all ranges / its
   // own: down 4096 x 14336 256 rows 44.2 / 42.5, 512 rows 66.8 / 64.4, 2048 rows 184 / 178; but o 4096 x 4096 512 rows (4.2 MB) 25.6 / 26.0, q/k/v 37.9 / 38.1.
   p.ranges = 0;
   while (p.ranges < 3 && S % (2 << p.ranges) == 0 && (size_t)p.M * p.K * sizeof(bf16_t) > ((size_t)6 << 20)) ++p.ranges;
-  const int groups = (p.tiles + (8 >> p.ranges) - 1) >> (3 - p.ranges);
+  const int groups = (tiles + (8 >> p.ranges) - 1) >> (3 - p.ranges);
   p.mblocks = (p.M + TM - 1) / TM;
   p.inv_mblocks = ((1u << 20) + p.mblocks - 1) / p.mblocks;
   if ((int64_t)groups * p.mblocks * p.mblocks >= 1 << 20) p.inv_mblocks = 0;               // what j * inv_mblocks >> 20 is exact for
-  launch_with_events(kernel, dim3(8 * groups * p.mblocks, S >> p.ranges), dim3(64 * WGM * WGN), LDS, st, ev_start, ev_stop, p);
+  launch_with_events(kernel, dim3(8 * groups * p.mblocks, S >> p.ranges), dim3(64 * WGM * WGN), LDS, st, ev_start, ev_stop, p.x, p.w[0], p.w[1], p.K, S, p.N, p.M, p.rows[0],
+                     (uint32_t)(p.mode | p.nmat << 1 | p.ranges << 3 | p.mblocks << 5), p.inv_mblocks, p);
   return hipGetLastError();
 }
 
