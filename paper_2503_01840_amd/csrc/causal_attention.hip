@@ -30,7 +30,8 @@
 // tile taken whole and the output rescaled at every own key it was 29.0 instead of 22.6 us (T = 517, 64 heads, s = 5), 72 instead
 // of 67 (T = 2048, 32 heads over 8, s = 5) and 36.0 instead of 32.6 (T = 2048, 8 heads, s = 0).  Measured against a kernel of one head x 64 queries per workgroup (4 wavefronts, scores,
 // softmax and values one after the other, own keys read from global memory by every lane for itself): T = 2048, s = 2:
-// 108 -> 65 us; T = 517, 64 heads, s = 5: 61 -> 22.6 us.
+// 108 -> 65 us; T = 517, 64 heads, s = 5: 61 -> 22.6 us.  Then with the weights' tails by plain instructions, the softmax and the direct loads dealt out and no divisions in front
+// of the first load, before / now: T = 2048 s = 2 60.5 -> 57.2, T = 4096 s = 1 207 -> 192, T = 1000 s = 3 27.8 -> 24.9, T = 517 s = 5 21.9 -> 19.7, T = 300 s = 1 10.8 -> 9.8.
 // fp32 kernel: one workgroup per (query, head), exact arithmetic, for small checks.
 #include <algorithm>
 

@@ -59,7 +59,7 @@ struct WideParams {
   const bf16_t* w[3];
   int rows[3];
   int nmat, mode;
-  int M, N, K, S, epi;
+  int M, N, K, epi;
   int mblocks;                          // activation-row blocks
   uint32_t inv_mblocks;                 // 2^20 / mblocks, rounded up, or 0: divide
   int ranges;                           // log2 of 1, 2, 4 or 8: XCD x has the K ranges x % 2^ranges + 2^ranges i only
@@ -115,13 +115,13 @@ __device__ __forceinline__ void unroll(F f) { unroll_seq(std::make_integer_seque
 #define WIDE_PIN() __builtin_amdgcn_sched_barrier(0)
 
 template <int WGM, int WGN, int FM, int FB, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER, int SETS, bool ROPE>
-__global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(const bf16_t* x, const bf16_t* w0, const bf16_t* w1, int K, int S, int N, int M, int rows0,
-                                                                        uint32_t place, uint32_t inv_mblocks, WideParams rest) {
+__global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(const bf16_t* x, const bf16_t* w0, const bf16_t* w1, int K, int range, int N, int M, int rows0,
+                                                                        uint32_t place, uint32_t inv_mblocks, uint32_t stages_mul, WideParams rest) {
   // what the first loads need comes as arguments of their own, which are in registers from the start; place: see launch_cfg
   WideParams p = rest;
   p.x = x; p.w[0] = w0; p.w[1] = w1; p.rows[0] = rows0;
-  p.K = K; p.S = S; p.N = N; p.M = M;
-  p.mode = place & 1; p.nmat = place >> 1 & 3; p.ranges = place >> 3 & 3; p.mblocks = place >> 5;
+  p.K = K; p.N = N; p.M = M;
+  p.mode = place & 1; p.nmat = place >> 1 & 3; p.ranges = place >> 3 & 3; p.mblocks = place >> 10;
   p.inv_mblocks = inv_mblocks;
   constexpr int FA = 2 * FM;                           // 16-row fragments of a wavefront's activation rows; FB: of its weight rows
   constexpr int TM = 32 * FM * WGM, TN = 16 * FB * WGN, NW = WGM * WGN;
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(const bf
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
-  const int Kc = p.K / p.S, k_begin = split * Kc, KT = Kc / BK;   // KT weight stages = SUB KT sub-stages
+  const int k_begin = split * range, KT = (unsigned)range / BK;   // KT weight stages = SUB KT sub-stages
   const int MT = (p.M + 63) >> 6;                      // 64-row activation tiles that exist
 
   // ---- global sources: one address per piece for the wavefront, and the place in K as part of the lanes' offsets.  Piece q of
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(const bf
   auto load_b = [&](auto i, uint32_t slot) {
     if (i < B_DMA - 1 || B_FULL == NW || wave < B_FULL) dma16<i * 1024>(bptr[i], b_off[i], b_lds + slot);
   };
-  const int rot = STAGGER ? (tile * 5 + split) % KT : 0;
+  const int rot = STAGGER ? (tile * 5 + split) % Divisor{stages_mul, place >> 5 & 31, KT} : 0;
   if (STAGGER) {
     a_off += rot * SUB * 4096u;
 #pragma unroll
@@ -420,8 +420,9 @@ hipError_t launch_cfg(WideParams& p, int S, hipStream_t st, hipEvent_t ev_start,
   p.mblocks = (p.M + TM - 1) / TM;
   p.inv_mblocks = ((1u << 20) + p.mblocks - 1) / p.mblocks;
   if ((int64_t)groups * p.mblocks * p.mblocks >= 1 << 20) p.inv_mblocks = 0;               // what j * inv_mblocks >> 20 is exact for
-  launch_with_events(kernel, dim3(8 * groups * p.mblocks, S >> p.ranges), dim3(64 * WGM * WGN), LDS, st, ev_start, ev_stop, p.x, p.w[0], p.w[1], p.K, S, p.N, p.M, p.rows[0],
-                     (uint32_t)(p.mode | p.nmat << 1 | p.ranges << 3 | p.mblocks << 5), p.inv_mblocks, p);
+  const Divisor by_stages = divisor(p.K / S / BK);
+  launch_with_events(kernel, dim3(8 * groups * p.mblocks, S >> p.ranges), dim3(64 * WGM * WGN), LDS, st, ev_start, ev_stop, p.x, p.w[0], p.w[1], p.K, p.K / S, p.N, p.M, p.rows[0],
+                     (uint32_t)p.mode | p.nmat << 1 | p.ranges << 3 | by_stages.shift << 5 | (uint32_t)p.mblocks << 10, p.inv_mblocks, by_stages.mul, p);
   return hipGetLastError();
 }
 
@@ -451,7 +452,6 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   if (N % 4) return hipErrorInvalidValue;
   if (hipError_t e = fill_params(p, x, W, M, N, K, epi, out)) return e;
   const WideTiles t = many_tiles(M, N, K, epi == GEMM_EPI_SWIGLU, out_capacity_floats);
-  p.S = t.S;
   if (S_out) *S_out = t.S;
   // Staggered walks (see above) also up to 256 rows.  us, in step / staggered: gate/up 28672 x 4096 77 rows 55.4 / 51.6, 256 rows 75.6 / 72.8,
   // LM head 128256 x 4096 77 rows 252 / 227, 256 rows 329 / 302, 8192 x 8192 in four ranges 77 rows 35.0 / 30.6, 256 rows 48.9 / 49.3; stages of
@@ -505,7 +505,6 @@ hipError_t launch_gemm_wide_rope(const bf16_t* x, const GemmWeights& W, int M, i
   WideParams p;
   if (!wide_rope_fits(M, N, K, out_capacity_floats)) return hipErrorInvalidValue;
   if (hipError_t e = fill_params(p, x, W, M, N, K, GEMM_EPI_PARTIAL, nullptr)) return e;
-  p.S = 1;
   p.rope = rope;
   const WideTiles t = launch_tiles(M, N, K, false, out_capacity_floats);
   if (t.cols == 192) return launch_cfg<4, 2, 2, 6, 64, 4, 3, 1, false, 1, true>(p, 1, st, ev_start, ev_stop);
@@ -521,7 +520,6 @@ hipError_t launch_gemm_wide64(const bf16_t* x, const GemmWeights& W, int M, int 
   if (hipError_t e = fill_params(p, x, W, M, N, K, epi, out)) return e;
   if (M > 64 || S < 1 || (cols != 128 && cols != 256) || K % (S * (cols == 128 ? 128 : 64)) || (epi == GEMM_EPI_SWIGLU && S != 1))
     return hipErrorInvalidValue;
-  p.S = S;
   const bool stagger = few_rows_stagger(K, S);
   if (cols == 128)
     return stagger ? launch_cfg<2, 2, 1, 4, 128, 5, 3, 2, true, 4>(p, S, st, ev_start, ev_stop)
