@@ -5,6 +5,8 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include "divisor.hpp"
+
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -30,17 +32,6 @@ template <typename T> __device__ __forceinline__ void store_from_f32(T* p, size_
 template <> __device__ __forceinline__ void store_from_f32<float>(float* p, size_t i, float v) { p[i] = v; }
 template <> __device__ __forceinline__ void store_from_f32<bf16_t>(bf16_t* p, size_t i, float v) { p[i] = f32_to_bf16(v); }
 
-// Division by a size of the launch, exact for 0 <= n < 2^31: three instructions.  What the compiler makes of n / d are some thirty that depend on each
-// other, 0.1 to 0.2 us in front of a workgroup's first load (four of them: 0.5 us of every many-row product).
-struct Divisor {
-  uint32_t mul, shift;
-  int d;
-};
-inline Divisor divisor(int d) {
-  uint32_t s = 0;
-  while ((1ull << s) < (uint64_t)d) ++s;
-  return {(uint32_t)((((1ull << s) - (uint64_t)d) << 32) / (uint64_t)d + 1), s, d};
-}
 __device__ __forceinline__ int operator/(int n, const Divisor& by) { return (int)((__umulhi((uint32_t)n, by.mul) + (uint32_t)n) >> by.shift); }
 __device__ __forceinline__ int operator%(int n, const Divisor& by) { return n - n / by * by.d; }
 
