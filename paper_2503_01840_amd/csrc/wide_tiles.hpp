@@ -136,6 +136,21 @@ inline WideTiles launch_tiles(int M, int N, int K, bool swiglu, size_t out_capac
   return best;
 }
 
+// Whether 256 weight rows to a workgroup leave so few workgroups (1 to 16 of the fullest XCD's n) for a last round of its 32 CUs that 128 weight rows, with twice as many
+// of half the length, are over first.  A last round takes nearly as long as a whole one, which the estimates of stream_tiles, fitted to products that mostly end in fuller
+// ones, don't know.  us, 256 / 128 weight rows (with stages of 128 k unless stated), n = 33 where not: 80 rows 66816 x 4096 155 / 134, 96 rows 66816 x 1024 49.6 / 43.8,
+// SwiGLU 65 rows 66816 x 5120 191 / 163, 65 rows 142592 x 3072 (n = 70) 204 / 193; 112 rows 66816 x 4096 162 / 148, 97536 x 3072 (48) 147 / 141, 66816 x 1024 51.6 / 45.3 with
+// 64 k, 128 rows 132352 x 3072 (65) 225 / 216 with 64 k; 160 rows 66816 x 2560 129 / 124, but 66816 x 4096, with staggered walks, 176 / 177; 224 rows 66816 x 3072 164 / 154, SwiGLU 256 rows
+// 66816 x 4608 223 / 208.  More than half full: 80 rows 113920 x 2048 (56) 103 / 114, 224 rows 101632 x 3072 (50) 178 / 210.  2796 LM heads and gate/up products of K
+// 1024..8192 above 32 such workgroups, 65..256 rows: the 992 that take another tile by this 5 % faster, 20 of them slower by more than 2 % (3.7 at most).
+inline bool few_left(int M, int n, int K) {
+  const int left = n % 32;
+  if (n <= 32 || left == 0 || left > 16) return false;
+  if (M <= 96) return n < 96;
+  if (M <= 128) return n < 64 ? left < 16 || K > 1024 : left <= 2 && K % 2048 != 0;
+  return n < 64 && (M > 192 || (K > 2048 && K < 7168 && K % 2048 != 0));
+}
+
 // What is launched up to 256 rows: that, or a tile with fewer activation lines for each weight line.  A CU has some 200 lines on their way at a time and
 // they come back in order, so a line of activations from L2 keeps its place as long as the weight lines from HBM in front of it; neither the products (left
 // out: 77 rows 54 us as with them) nor where the activations come from (one line again and again: 54 us) matter.  So
@@ -149,8 +164,9 @@ inline WideTiles launch_tiles(int M, int N, int K, bool swiglu, size_t out_capac
 // in stages of 64 k up to 128 rows, the margins are 3 % the other way elsewhere and for 96 x 128.  Chains of sums are no longer than before (128 x 128 with stages
 // of 128 k, and the new ones up to 128 rows: two sets); 256 weight rows only where an XCD has more than 16 workgroups (28672 x 4096, 14 of them: 68, 48 in
 // 96 x 128), with ranges of at least 1024 k, and in a split not of a multiple of 4 KB (in step: 8192 x 28672 in seven ranges 77 rows 112, 100 otherwise).
-// Time against that of wide_tiles_256, 142 products each: 65..96 rows 0.942, 97..128 0.984, 129..192 0.973, 193..256 0.979; slower by more than 1 %: 65792 x 4352 at
-// 160 and 192 rows (4.5 and 2.4).
+// Time against that of wide_tiles_256, 142 products each: 65..96 rows 0.942, 97..128 0.984, 129..192 0.973, 193..256 0.979.  Where a last round has few workgroups (few_left)
+// 256 weight rows don't come into question, and up to 128 rows unsplit products take stages of 128 k: those of 64 k side by side only where they are the faster ones, us,
+// 112 rows, 64 / 128 k: 66816 x 1024 45.3 / 47.2, 81152 x 2048 105 / 92.
 inline WideTiles stream_tiles(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
   struct Fit { int cols, k, sets; float start, stage, busy, sums; };   // us; of a stage, more of it with all CUs busy, per million partial sums
   static constexpr Fit strips = {128, 128, 2, 4.53f, 0.89f, 0.58f, 2.29f};                                               // 96 rows
@@ -177,13 +193,18 @@ inline WideTiles stream_tiles(int M, int N, int K, bool swiglu, size_t out_capac
     for (int S = 1; S <= (swiglu ? 1 : 8); ++S) {
       const int range = K / S;
       if (K % (f.k * S) || range < 512 || range > chain * f.sets || (S > 1 && (size_t)S * M * N > out_capacity_floats)) continue;
-      if (f.cols == 256 && (per_xcd(f, S) <= 16 || range < 1024 || (S > 1 && range % 2048 == 0))) continue;
+      if (f.cols == 256 && (per_xcd(f, S) <= 16 || few_left(M, per_xcd(f, S), K) || range < 1024 || (S > 1 && range % 2048 == 0))) continue;
       const float t = margin * time(f, S);
       if (t < least) { least = t; best = {rows, f.cols, S, f.k}; }
     }
   };
   if (M <= 96 && (!small_stages || K > 1024)) consider(strips, 96, small_stages ? 1.08f : 1.f);      // (1536 x 512 9.0, 9.4 in 96 x 128)
-  const int i = M <= 96 ? 0 : M <= 128 ? 1 : M <= 192 ? 2 : 3;
+  const int i = M <= 96 ? 0 : M <= 128 ? 1 : M <= 192 ? 2 : 3, n = per_xcd(wide[i], 1);
+  if (K >= 1024 && few_left(M, n, K) && best.S == 1 && M <= 128) {
+    if (M <= 96) best = {96, 128, 1, 128};
+    else if (n < 64 && K > 1024 && (!swiglu || K > 1536 || n >= 42)) best = {128, 128, 1, 128};
+    return best;
+  }
   consider(wide[i], i == 0 ? 96 : 64 * (i + 1), 1.f);
   return best;
 }

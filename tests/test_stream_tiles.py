@@ -53,6 +53,23 @@ def test_256_weight_rows_where_they_are_the_faster_ones(rule, q, other, wide):
     assert (rule([q + (BIG if q[1] < 20000 else 0,)])[0][0][1] == 256) == (wide < other)
 
 
+# unsplit, where 256 weight rows leave 1 to 16 workgroups of the fullest XCD for a last round, and beside that: microseconds in 128 weight rows (of 96 rows and 128 k up to 96
+# rows; of 64 k where that is noted), in 256
+@pytest.mark.parametrize("q,narrow,wide,k", [
+    ((80, 66816, 4096, 0), 134, 155, 128), ((96, 66816, 1024, 0), 43.8, 49.6, 128), ((80, 81152, 2048, 0), 84.3, 89.8, 128), ((65, 66816, 5120, 1), 163, 191, 128),
+    ((65, 142592, 3072, 0), 193, 204, 128), ((80, 113920, 2048, 0), 114, 103, 128), ((112, 66816, 4096, 0), 148, 162, 128), ((97, 66816, 5120, 1), 177, 195, 128),
+    ((112, 66816, 1024, 0), 45.3, 51.6, 64), ((112, 97536, 3072, 0), 141, 147, 128), ((112, 113920, 3072, 0), 169, 157, 128), ((128, 132352, 3072, 0), 214, 225, 64),
+    ((160, 66816, 2560, 0), 124, 129, 128), ((160, 65792, 4352, 0), 188, 199, 128), ((192, 65792, 4352, 0), 192, 200, 128), ((160, 66816, 4096, 0), 177, 176, 128),
+    ((224, 66816, 3072, 0), 154, 164, 128), ((224, 81152, 3072, 1), 150, 156, 128), ((256, 66816, 4608, 1), 208, 223, 128), ((224, 101632, 3072, 0), 210, 178, 128)])
+def test_128_weight_rows_where_256_leave_few_workgroups_for_a_last_round(rule, q, narrow, wide, k):
+    M = q[0]
+    rows, cols, S, stage, _ = rule([q + (0,)])[0][0]
+    if narrow < wide:
+        assert (rows, cols, S, stage) == (96 if M <= 96 else 128 if M <= 128 else 256, 128, 1, k)
+    else:
+        assert (rows, cols, S, stage) == (96 if M <= 96 else 64 * ((M + 63) // 64), 256, 1, 64)
+
+
 MODELS["split"] = (5120, 40, 8, 17408, 20484)
 
 
