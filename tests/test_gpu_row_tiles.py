@@ -33,9 +33,9 @@ def test_rows_at_192_row_edges(B, N, group):
     _rows_alone_and_together(S.get_shape("c3").with_(name="flat", hidden=256, n_heads=4, n_kv_heads=2, vocab=1024), B, N, group, logits=True)
 
 
-# 65..256 rows, logits included, against at most 64 rows at a time: the first and last row count of 128 x 128 and of 256 x 128 tiles and one
-# between.  8B width: q/k/v and down in ranges and gate/up staggered with 128-k weight stages, o in ranges of 64-k stages up to 128 rows,
-# LM head staggered, with 64-k stages up to 128 rows.  "wide" (in FEW): the same in step, gate/up with 64-k stages up to 128 rows.
+# 65..256 rows, logits included, against at most 64 rows at a time: the first and last row count of 128 x 128 (split, and gate/up) and of 256 x 128 tiles and
+# one between.  8B width: q/k/v and down in ranges and gate/up staggered with 128-k weight stages, o in ranges of 64-k stages from 97 to 128 rows.
+# "wide" (in FEW): q/k/v and down in step.  Up to 96 rows, and where 256 weight rows are taken (the LM heads, gate/up of "wide"): test_gpu_stream_tiles.py.
 @pytest.mark.parametrize("name", ["8b", "wide"])
 @pytest.mark.parametrize("B,N,group", [(65, 1, 64), (43, 3, 21), (128, 1, 64), (129, 1, 64), (64, 3, 20), (64, 4, 16)])
 def test_rows_in_wide_weight_stages(name, B, N, group):
