@@ -15,7 +15,7 @@ struct WideTiles {
 // Whether the K walks of a launch of 65..256 rows start at a stage of each workgroup's own (gemm_wide.hip has the figures).
 inline bool wide_stagger(int M, int K, const WideTiles& t) { return M <= 256 && K / t.S % 2048 == 0 && (t.k == 128 || t.S == 1); }
 
-// 65..256 rows: 128 weight rows to a workgroup, so that every weight line enters one CU, and one block of 128
+// 65..256 rows, where activation lines don't count (what is launched: stream_tiles): 128 weight rows to a workgroup, so that every weight line enters one CU, and one block of 128
 // or 256 activation rows.  Stages of 128 k, whose row pieces of 256 bytes HBM delivers faster than pieces of 128, take all of a CU's LDS;
 // with stages of 64 k two 128 x 128 workgroups run side by side.  The kind and the split whose launch is over first by this estimate,
 // in microseconds: a start and an end, a time per stage that grows with the workgroups that stream at once, in rounds of 32 workgroups
@@ -108,14 +108,13 @@ inline WideTiles wide_tiles_k64(int M, int N, int K, bool swiglu, size_t out_cap
 // Stages of 128 k beyond 256 rows: where one workgroup has a CU to itself, 256 x 128 always, 128 x 128 up to 256 workgroups (300 rows LM
 // head, 3006 workgroups: 457 us with 64, 530 with 128).  A workgroup's walk has to be long enough, as fewer and larger stages start later.
 inline WideTiles wide_tiles(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
-  if (M <= 256) return wide_tiles_256(M, N, K, swiglu, out_capacity_floats);
   WideTiles t = wide_tiles_k64(M, N, K, swiglu, out_capacity_floats);
   const int wgs = (N + t.cols - 1) / t.cols * ((M + t.rows - 1) / t.rows) * t.S, range = K / t.S;
   if (t.cols == 128 && range % 128 == 0 && range >= (t.rows == 256 && t.S == 1 ? 256 : 1024) && (t.rows == 256 || wgs <= 256)) t.k = 128;
   return t;
 }
 
-// The tile that is launched: that, or beyond 256 rows 256 x 224 or 256 x 192 (4 x 2 wavefronts of 64 x 112 or 64 x 96).  28672 weight rows (8B
+// The tile that is launched beyond 256 rows: that, or 256 x 224 or 256 x 192 (4 x 2 wavefronts of 64 x 112 or 64 x 96).  28672 weight rows (8B
 // gate/up) are 112 tiles of 256, 3.5 rounds of the chip at 2048 rows, and 128 of 224, four whole ones; 6144 (q/k/v) are 24 of 256, three
 // quarters of a round, and 32 of 192.  Taken by a margin of 2 % of the estimate, and only with chains of sums no longer than the other tile's
 // (stages of 128 k: two chains).  us, with the kernel that reads partial sums, the other tile / this one: gate/up 2048 rows 371 / 357, 1280 rows 286 / 244, 512 rows
@@ -124,7 +123,6 @@ inline WideTiles wide_tiles(int M, int N, int K, bool swiglu, size_t out_capacit
 // faster and none slower.
 inline WideTiles launch_tiles(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
   const WideTiles base = wide_tiles(M, N, K, swiglu, out_capacity_floats);
-  if (M <= 256) return base;
   const int chain = K / base.S / (base.k == 128 ? 2 : 1);
   WideTiles best = base;
   float least = 0.98f * wide_time(M, N, K, swiglu, base);
@@ -151,7 +149,7 @@ inline bool few_left(int M, int n, int K) {
   return n < 64 && (M > 192 || (K > 2048 && K < 7168 && K % 2048 != 0));
 }
 
-// What is launched up to 256 rows: that, or a tile with fewer activation lines for each weight line.  A CU has some 200 lines on their way at a time and
+// What is launched up to 256 rows: the tile of wide_tiles_256, or one with fewer activation lines for each weight line.  A CU has some 200 lines on their way at a time and
 // they come back in order, so a line of activations from L2 keeps its place as long as the weight lines from HBM in front of it; neither the products (left
 // out: 77 rows 54 us as with them) nor where the activations come from (one line again and again: 54 us) matter.  So
 //   up to 96 rows, 96 x 128 in six wavefronts with eight activation slots instead of 128 x 128 with stages of 128 k;
