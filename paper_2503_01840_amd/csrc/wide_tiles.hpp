@@ -198,7 +198,7 @@ inline WideTiles stream_tiles(int M, int N, int K, bool swiglu, size_t out_capac
   };
   if (M <= 96 && (!small_stages || K > 1024)) consider(strips, 96, small_stages ? 1.08f : 1.f);      // (1536 x 512 9.0, 9.4 in 96 x 128)
   const int i = M <= 96 ? 0 : M <= 128 ? 1 : M <= 192 ? 2 : 3, n = per_xcd(wide[i], 1);
-  if (K >= 1024 && few_left(M, n, K) && best.S == 1 && M <= 128) {
+  if (K >= 1024 && K % 128 == 0 && few_left(M, n, K) && best.S == 1 && M <= 128) {
     if (M <= 96) best = {96, 128, 1, 128};
     else if (n < 64 && K > 1024 && (!swiglu || K > 1536 || n >= 42)) best = {128, 128, 1, 128};
     return best;
