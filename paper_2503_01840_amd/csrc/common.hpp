@@ -32,9 +32,6 @@ template <typename T> __device__ __forceinline__ void store_from_f32(T* p, size_
 template <> __device__ __forceinline__ void store_from_f32<float>(float* p, size_t i, float v) { p[i] = v; }
 template <> __device__ __forceinline__ void store_from_f32<bf16_t>(bf16_t* p, size_t i, float v) { p[i] = f32_to_bf16(v); }
 
-__device__ __forceinline__ int operator/(int n, const Divisor& by) { return (int)((__umulhi((uint32_t)n, by.mul) + (uint32_t)n) >> by.shift); }
-__device__ __forceinline__ int operator%(int n, const Divisor& by) { return n - n / by * by.d; }
-
 // Fragment-major layout of a bf16 activation matrix X[rows, K] (K % 16 == 0), as the MFMA GEMMs read it:
 // rows are grouped in tiles of 64, K in steps of 16; the 32 rows x 16 k of one (tile, k-step, half)
 // form one 1 KiB block holding, for lane l of a wavefront, the 8 values X[32*half + l%32][16*step + 8*(l/32) .. +7]

@@ -46,6 +46,7 @@
 
 #include "common.hpp"
 #include "kernels.hpp"
+#include "wide_places.hpp"
 #include "wide_tiles.hpp"
 
 namespace {
@@ -60,9 +61,15 @@ struct WideParams {
   int rows[3];
   int nmat, mode;
   int M, N, K, epi;
-  int mblocks;                          // activation-row blocks
-  uint32_t inv_mblocks;                 // 2^20 / mblocks, rounded up, or 0: divide
-  int ranges;                           // log2 of 1, 2, 4 or 8: XCD x has the K ranges x % 2^ranges + 2^ranges i only
+  float* out_f32;
+  bf16_t* out_xf;
+  WideRope rope;
+};
+
+// What of it comes behind the arguments that a wavefront has in registers from the start
+struct WideRest {
+  const bf16_t* w2;
+  int rows1, epi;
   float* out_f32;
   bf16_t* out_xf;
   WideRope rope;
@@ -116,13 +123,9 @@ __device__ __forceinline__ void unroll(F f) { unroll_seq(std::make_integer_seque
 
 template <int WGM, int WGN, int FM, int FB, int BK, int A_SLOTS, int B_SLOTS, int OCC, bool STAGGER, int SETS, bool ROPE>
 __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(const bf16_t* x, const bf16_t* w0, const bf16_t* w1, int K, int range, int N, int M, int rows0,
-                                                                        uint32_t place, uint32_t inv_mblocks, uint32_t stages_mul, WideParams rest) {
-  // what the first loads need comes as arguments of their own, which are in registers from the start; place: see launch_cfg
-  WideParams p = rest;
-  p.x = x; p.w[0] = w0; p.w[1] = w1; p.rows[0] = rows0;
-  p.K = K; p.N = N; p.M = M;
-  p.mode = place & 1; p.nmat = place >> 1 & 3; p.ranges = place >> 3 & 3; p.mblocks = place >> 10;
-  p.inv_mblocks = inv_mblocks;
+                                                                        uint32_t place, uint32_t mblocks_mul, uint32_t stages_mul, WideRest rest) {
+  // place: mode, matrices, log2 of the K ranges dealt to XCDs, shifts of the divisors (at most 31): launch_cfg
+  const WideParams p = {x, {w0, w1, rest.w2}, {rows0, rest.rows1, 0}, (int)(place >> 1 & 3), (int)(place & 1), M, N, K, rest.epi, rest.out_f32, rest.out_xf, rest.rope};
   constexpr int FA = 2 * FM;                           // 16-row fragments of a wavefront's activation rows; FB: of its weight rows
   constexpr int TM = 32 * FM * WGM, TN = 16 * FB * WGN, NW = WGM * WGN;
   // SwiGLU: gate and up rows in turns of 32, so that both of a pair are accumulators of one lane in two fragments; or, where a wavefront's
@@ -145,11 +148,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_wide_kernel(const bf
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
-  // Workgroups go to the XCDs round-robin by their linear id: id % 8 is the XCD.  Consecutive workgroups of one
-  // XCD take the activation-row blocks of ONE weight tile, so that the tile is fetched into that L2 once.
-  const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-  const int group = p.mblocks == 1 ? j : p.inv_mblocks ? (int)((uint64_t)j * p.inv_mblocks >> 20) : j / p.mblocks, mblock = j - group * p.mblocks;
-  const int tile = (group << (3 - p.ranges)) + (xcd >> p.ranges), split = ((int)blockIdx.y << p.ranges) + (xcd & ((1 << p.ranges) - 1));
+  const WidePlace at = wide_place(blockIdx.x, blockIdx.y, place >> 3 & 3, Divisor{mblocks_mul, place >> 10 & 31, (int)((unsigned)(M + TM - 1) / TM)});
+  const int tile = at.tile, mblock = at.mblock, split = at.split;
   if (tile >= (N + TN - 1) / TN) return;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -412,17 +412,13 @@ hipError_t launch_cfg(WideParams& p, int S, hipStream_t st, hipEvent_t ev_start,
   hipError_t ce = configured.run([&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS); });
   if (ce != hipSuccess) return ce;
   const int tiles = (p.N + TN - 1) / TN;
-  // Activations that an XCD's 4 MB of L2 cannot hold are fetched by each of them again, unless it has some of the K ranges only.  Product alone, us, all ranges / its
-  // own: down 4096 x 14336 256 rows 44.2 / 42.5, 512 rows 66.8 / 64.4, 2048 rows 184 / 178; but o 4096 x 4096 512 rows (4.2 MB) 25.6 / 26.0, q/k/v 37.9 / 38.1.
-  p.ranges = 0;
-  while (p.ranges < 3 && S % (2 << p.ranges) == 0 && (size_t)p.M * p.K * sizeof(bf16_t) > ((size_t)6 << 20)) ++p.ranges;
-  const int groups = (tiles + (8 >> p.ranges) - 1) >> (3 - p.ranges);
-  p.mblocks = (p.M + TM - 1) / TM;
-  p.inv_mblocks = ((1u << 20) + p.mblocks - 1) / p.mblocks;
-  if ((int64_t)groups * p.mblocks * p.mblocks >= 1 << 20) p.inv_mblocks = 0;               // what j * inv_mblocks >> 20 is exact for
-  const Divisor by_stages = divisor(p.K / S / BK);
-  launch_with_events(kernel, dim3(8 * groups * p.mblocks, S >> p.ranges), dim3(64 * WGM * WGN), LDS, st, ev_start, ev_stop, p.x, p.w[0], p.w[1], p.K, p.K / S, p.N, p.M, p.rows[0],
-                     (uint32_t)p.mode | p.nmat << 1 | p.ranges << 3 | by_stages.shift << 5 | (uint32_t)p.mblocks << 10, p.inv_mblocks, by_stages.mul, p);
+  const int ranges = dealt_ranges(p.M, p.K, S);
+  const Divisor by_mblocks = divisor((p.M + TM - 1) / TM), by_stages = divisor(p.K / S / BK);
+  const WideGrid grid = wide_grid(tiles, by_mblocks.d, S, ranges);
+  const uint32_t place = (uint32_t)p.mode | (uint32_t)p.nmat << 1 | (uint32_t)ranges << 3 | by_stages.shift << 5 | by_mblocks.shift << 10;
+  const WideRest rest = {p.w[2], p.rows[1], p.epi, p.out_f32, p.out_xf, p.rope};
+  launch_with_events(kernel, dim3(grid.x, grid.y), dim3(64 * WGM * WGN), LDS, st, ev_start, ev_stop, p.x, p.w[0], p.w[1], p.K, p.K / S, p.N, p.M, p.rows[0], place,
+                     by_mblocks.mul, by_stages.mul, rest);
   return hipGetLastError();
 }
 

@@ -12,6 +12,15 @@ struct WideTiles {
   int k;               // width of a weight stage: 64, or 128 for tiles of 128 weight rows
 };
 
+// log2 of the K ranges of a split product that are dealt to different XCDs (wide_places.hpp).  Activations that an XCD's 4 MB of L2 cannot hold are fetched by each of
+// them again, unless it has some of the K ranges only.  Product alone, us, all ranges / its own: down 4096 x 14336 256 rows 44.2 / 42.5, 512 rows 66.8 / 64.4,
+// 2048 rows 184 / 178; but o 4096 x 4096 512 rows (4.2 MB) 25.6 / 26.0, q/k/v 37.9 / 38.1.
+inline int dealt_ranges(int M, int K, int S) {
+  int ranges = 0;
+  while (ranges < 3 && S % (2 << ranges) == 0 && (size_t)M * K * 2 > ((size_t)6 << 20)) ++ranges;
+  return ranges;
+}
+
 // Whether the K walks of a launch of 65..256 rows start at a stage of each workgroup's own (gemm_wide.hip has the figures).
 inline bool wide_stagger(int M, int K, const WideTiles& t) { return M <= 256 && K / t.S % 2048 == 0 && (t.k == 128 || t.S == 1); }
 

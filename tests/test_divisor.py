@@ -8,12 +8,13 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 def test_division_by_multiplication_is_exact(tmp_path):
     (tmp_path / "m.cpp").write_text('''#include <cstdio>
+#include <initializer_list>
 #include "divisor.hpp"
 static long bad = 0;
 static void at(uint64_t n, int d, const Divisor& by) {
   if (n >> 31) return;
-  const uint32_t q = ((uint32_t)((n * by.mul) >> 32) + (uint32_t)n) >> by.shift;                  // operator/ of common.hpp
-  if (q != n / d) { if (!bad++) printf("%llu / %d: %u\\n", (unsigned long long)n, d, q); }
+  const int q = (int)n / by, r = (int)n % by;                       // the expressions that the kernels use
+  if (q != (int)(n / d) || r != (int)(n % d)) { if (!bad++) printf("%llu / %d: %d, %d\\n", (unsigned long long)n, d, q, r); }
 }
 int main() {
   for (int64_t d = 1; d < (1ll << 31); d += d < 70000 ? 1 : d / 1000) {
@@ -29,6 +30,6 @@ int main() {
 }
 ''')
     inc = os.path.join(ROOT, "paper_2503_01840_amd", "csrc")
-    subprocess.run(["g++", "-std=c++17", "-O2", "-include", "initializer_list", "-I", inc, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-I", inc, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
     r = subprocess.run([str(tmp_path / "m")], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout

@@ -81,6 +81,12 @@ def test_rows_in_tiles_that_make_up_whole_rounds(name, B, N, group):
     _rows_alone_and_together(mha if name == "mha" else FEW[name].with_(vocab=1024), B, N, group, logits=True)
 
 
+# 8B width, 1100 rows: q/k/v, o and down in two K ranges, each the work of four XCDs (four and eight ranges, of two and of one: 600 and 65..256 rows above)
+@pytest.mark.parametrize("B,N,group", [(55, 20, 3)])
+def test_rows_in_two_ranges_dealt_to_xcds(B, N, group):
+    _rows_alone_and_together(FEW["8b"].with_(vocab=1024), B, N, group, logits=True)
+
+
 # q/k/v rotated and put into the cache by the product, where it is not split: each tile that does so, row blocks and weight rows that end within
 # one ("ragged"), against at most 64 rows at a time.  (q heads, KV heads, hidden, sequences, rows of each)
 ROTATED = {"192": (56, 8, 512, 64, 20), "192-ragged": (56, 7, 512, 64, 20), "8b": (32, 8, 4096, 64, 20), "256x256": (64, 16, 256, 55, 20), "192x256": (48, 8, 1024, 55, 20),

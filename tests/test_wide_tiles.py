@@ -245,6 +245,20 @@ def test_whole_rounds_that_the_gpu_tests_cover(launched):
             assert launch == base, (name, M, i)
 
 
+# K ranges, and log2 of those dealt to different XCDs, of products that the GPU tests of test_gpu_row_tiles.py and test_gpu_stream_tiles.py run
+@pytest.mark.parametrize("model,M,at,want", [("8b", 1100, (0, 1, 3), [(2, 1), (2, 1), (2, 1)]), ("8b", 600, (3,), [(4, 2)]), ("8b", 512, (3,), [(4, 2)]),
+                                             ("8b", 256, (3,), [(7, 0)]), ("wide", 256, (3,), [(8, 3)])])
+def test_dealt_ranges_that_the_gpu_tests_cover(tmp_path, model, M, at, want):
+    ask = ", ".join("{%d, %d, %d, %d}" % (p[0], p[1], p[2], p[4]) for p in (_products(model, M)[i] for i in at))
+    (tmp_path / "m.cpp").write_text('#include <cstdio>\n#include "wide_tiles.hpp"\nint main() { const long q[][4] = {' + ask + '};\n'
+                                    '  for (auto& c : q) { const WideTiles t = many_tiles(' + str(M) + ', c[0], c[1], c[2], c[3]);\n'
+                                    '    printf("%d %d\\n", t.S, dealt_ranges(' + str(M) + ', c[1], t.S)); } }\n')
+    inc = os.path.join(ROOT, "paper_2503_01840_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", inc, str(tmp_path / "m.cpp"), "-o", str(tmp_path / "m")], check=True)
+    out = subprocess.run([str(tmp_path / "m")], capture_output=True, text=True, check=True).stdout
+    assert [tuple(map(int, line.split())) for line in out.splitlines()] == want
+
+
 # the tiles of test_rows_rotated_by_the_product
 def test_unsplit_tiles_that_the_gpu_tests_cover(launched):
     for H, G, k, M, want in [(56, 8, 512, 1280, (256, 192, 1, 64)), (56, 7, 512, 1280, (256, 192, 1, 64)), (32, 8, 4096, 1280, (256, 128, 1, 128)), (64, 16, 256, 1100, (256, 256, 1, 64)),
