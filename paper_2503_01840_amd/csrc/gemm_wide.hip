@@ -469,8 +469,7 @@ hipError_t launch_gemm_wide(const bf16_t* x, const GemmWeights& W, int M, int N,
   }
   if (t.cols == 128) {
     if (t.rows == 256) return launch_cfg<4, 2, 2, 4, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
-    return stagger ? launch_cfg<2, 2, 2, 4, 64, 4, 3, 2, true>(p, t.S, st, ev_start, ev_stop)
-                   : launch_cfg<2, 2, 2, 4, 64, 4, 3, 2>(p, t.S, st, ev_start, ev_stop);
+    return launch_cfg<2, 2, 2, 4, 64, 4, 3, 2>(p, t.S, st, ev_start, ev_stop);        // never staggered: stream_tiles
   }
   if (t.cols == 224) return launch_cfg<4, 2, 2, 7, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);
   if (t.cols == 192) return launch_cfg<4, 2, 2, 6, 64, 4, 3, 1>(p, t.S, st, ev_start, ev_stop);

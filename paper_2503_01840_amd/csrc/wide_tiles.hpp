@@ -173,7 +173,8 @@ inline bool few_left(int M, int n, int K) {
 // 96 x 128), with ranges of at least 1024 k, and in a split not of a multiple of 4 KB (in step: 8192 x 28672 in seven ranges 77 rows 112, 100 otherwise).
 // Time against that of wide_tiles_256, 142 products each: 65..96 rows 0.942, 97..128 0.984, 129..192 0.973, 193..256 0.979.  Where a last round has few workgroups (few_left)
 // 256 weight rows don't come into question, and up to 128 rows unsplit products take stages of 128 k: those of 64 k side by side only where they are the faster ones, us,
-// 112 rows, 64 / 128 k: 66816 x 1024 45.3 / 47.2, 81152 x 2048 105 / 92.
+// 112 rows, 64 / 128 k: 66816 x 1024 45.3 / 47.2, 81152 x 2048 105 / 92.  Staggered walks side by side were left to gate/up of K = 2048 and 4096 and 131 k to 159 k weight rows,
+// where stages of 128 k are as fast (112 rows, K = 2048, 131216 weight rows 127 / 133, 139920 136 / 136, 149200 144 / 140, 159120 149 / 145; K = 4096 280 / 262): those take them.
 inline WideTiles stream_tiles(int M, int N, int K, bool swiglu, size_t out_capacity_floats) {
   struct Fit { int cols, k, sets; float start, stage, busy, sums; };   // us; of a stage, more of it with all CUs busy, per million partial sums
   static constexpr Fit strips = {128, 128, 2, 4.53f, 0.89f, 0.58f, 2.29f};                                               // 96 rows
@@ -213,6 +214,7 @@ inline WideTiles stream_tiles(int M, int N, int K, bool swiglu, size_t out_capac
     return best;
   }
   consider(wide[i], i == 0 ? 96 : 64 * (i + 1), 1.f);
+  if (best.rows == 128 && best.cols == 128 && wide_stagger(M, K, best)) best.k = 128;
   return best;
 }
 

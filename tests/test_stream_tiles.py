@@ -30,9 +30,11 @@ def test_every_choice_can_be_launched_and_sums_in_chains_no_longer(rule):
     qs = [(M, N, K, s, cap) for M in (65, 80, 96, 97, 128, 129, 192, 193, 256) for N in (8, 256, 768, 4096, 5120, 10240, 28672, 64000, 128256)
           for K in (128, 256, 512, 1408, 2304, 4096, 7168, 11008, 14336, 28672) for s in (0, 1) for cap in (0, 2048 * 5120, BIG)]
     qs += [(M, N, K, s, 0) for M in (65, 96, 97, 128, 129, 256) for N in (66816, 97536) for K in (1088, 2112) for s in (0, 1)]      # odd numbers of 64-k stages
+    qs += [(M, N, K, 1, 0) for M in (97, 112, 128) for N in (131216, 149200, 159120) for K in (2048, 4096)]
     seen = set()
-    for (M, N, K, s, cap), ((rows, cols, S, k, _), base) in zip(qs, rule(qs)):
+    for (M, N, K, s, cap), ((rows, cols, S, k, staggered), base) in zip(qs, rule(qs)):
         seen.add((rows, cols, k))
+        assert not (staggered and (rows, cols, k) == (128, 128, 64))                       # there is no such kernel
         assert M <= rows and (rows, cols, k) in {(96, 128, 128), (96, 256, 64), (128, 128, 64), (128, 128, 128), (128, 256, 64), (192, 256, 64), (256, 128, 64),
                                                  (256, 128, 128), (256, 256, 64)}
         assert K % (S * k) == 0 and 1 <= S <= 8 and (S == 1 or (not s and S * M * N <= cap))
