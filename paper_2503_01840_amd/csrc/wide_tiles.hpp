@@ -1,7 +1,11 @@
 // Which output tile the many-row product takes, and into how many K ranges it is cut.  Host arithmetic only.
 //
 // Workgroups of one weight tile go to one XCD (32 CUs): a launch lasts as many rounds as the fullest XCD has workgroups per CU,
-// and that XCD has ceil(weight tiles / 8) of them for every row block and K range.
+// and that XCD has at most ceil(weight tiles / 8) of them for every row block and K range: exactly that many, unless K ranges are dealt to XCDs (dealt_ranges: then
+// ceil(weight tiles / (8 / ranges)) for each of its own ranges, 20 tiles in four ranges 10 and not 12).  The estimates below count the former, and their fits are of
+// launches without dealt ranges: of products in dealt ranges they tell the order less well.  1586 split products of 16 model shapes beyond 256 rows: what they pick is 2.1 % slower
+// than the best of the tiles on average; counting what an XCD has, and a tile of 192 or 224 weight rows without its margin there, 1.2 %, but 43 of the 263 products
+// that take another tile then are slower, by 1 to 10 %, and others sum in longer chains.
 #pragma once
 #include <cstddef>
 #include <initializer_list>
@@ -14,7 +18,9 @@ struct WideTiles {
 
 // log2 of the K ranges of a split product that are dealt to different XCDs (wide_places.hpp).  Activations that an XCD's 4 MB of L2 cannot hold are fetched by each of
 // them again, unless it has some of the K ranges only.  Product alone, us, all ranges / its own: down 4096 x 14336 256 rows 44.2 / 42.5, 512 rows 66.8 / 64.4,
-// 2048 rows 184 / 178; but o 4096 x 4096 512 rows (4.2 MB) 25.6 / 26.0, q/k/v 37.9 / 38.1.
+// 2048 rows 184 / 178.  255 split products of 16 model shapes with 6 to 40 MB of activations: 2.0 % faster on average, 161 of them by more than 1 %, 15 slower by more (worst
+// 3072 x 8192 at 640 rows 41.3 / 44.0).  Below, where the line was drawn after two products of 4.2 MB (o 4096 x 4096 512 rows 25.6 / 26.0, q/k/v 37.9 / 38.1), 224 others
+// with 2 to 6 MB would gain 1.5 % on average: the line could lie lower.
 inline int dealt_ranges(int M, int K, int S) {
   int ranges = 0;
   while (ranges < 3 && S % (2 << ranges) == 0 && (size_t)M * K * 2 > ((size_t)6 << 20)) ++ranges;
