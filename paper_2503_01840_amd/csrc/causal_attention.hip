@@ -35,6 +35,7 @@
 // fp32 kernel: one workgroup per (query, head), exact arithmetic, for small checks.
 #include <algorithm>
 
+#include "causal_rules.hpp"
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -44,7 +45,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef short short8v __attribute__((ext_vector_type(8)));
 constexpr int D = 128;
-constexpr int KT = 128;                       // keys per tile: two halves of two 32-key blocks
+constexpr int KT = CAUSAL_KEYS;               // keys per tile: two halves of two 32-key blocks
 constexpr int ROWB = D * 2;
 constexpr int TILE_BYTES = KT * ROWB;         // of K, and again of V
 constexpr int V_BASE = 2 * TILE_BYTES;        // two K slots, then three V slots: all of a CU's 160 KB
@@ -685,44 +686,15 @@ __global__ __launch_bounds__(256) void ttt_attn_f32_kernel(const float* __restri
   }
 }
 
-// 32 RG rows per workgroup: as many heads of one KV head as divide its group (4, 2 or 1, and no more than RG) x the matching
-// number of queries
-int heads_per_wg(int H, int Hkv, int RG) {
-  const int G = H / Hkv;
-  return G % 4 == 0 && RG >= 4 ? 4 : G % 2 == 0 ? 2 : 1;
-}
-int workgroups(int T, int H, int Hkv, int RG) {
-  const int hg = heads_per_wg(H, Hkv, RG), qb = 32 * RG / hg;
-  return H / hg * ((T + qb - 1) / qb);
-}
-
-// Workgroups of 64 rows instead of 128 where those leave CUs idle: one wavefront per SIMD then takes 1.81 us per tile instead of the
-// 2.39 us that two take side by side, and there are twice as many workgroups.  Up to 256 of them each has a CU to itself (64-row
-// form against 128-row form, us: 4 heads 4000 positions 60 / 80, 8 heads 2048 positions 33 / 44, 32 heads over 8 300
-// positions 10.3 / 12.5).  Up to 512, the shorter half of them (workgroup i of w walks over 1 - i / w of the tiles) starts on the CUs that are
-// done with the longer half's shorter ones, and pays the start, the own keys and the merge again: 8 heads 3000 positions 47 / 62,
-// 32 over 8 517 positions 13.4 / 17.0, but 64 over 8 300 positions with 3 simulated steps 18.6 / 14.8, and 1000 positions of 32 over 8
-// with 3 steps 30.5 / 28.2.  The constants are fitted to both forms at 75 sizes; what they pick is 0.1 % slower than the better form on
-// average, 4 % at worst.  Beyond 512 the shared tiles win: 2048 positions 84 / 61.
-bool half_workgroups(int T, int H, int Hkv, int s) {
-  const int w = workgroups(T, H, Hkv, 2);
-  if (w <= 256) return true;
-  if (w > 512) return false;
-  const float tiles = 0.5f * ((T + KT / 2 - 1) / (KT / 2));    // a last tile of no more than 64 keys takes half of a tile's time
-  auto fixed = [&](int RG, float start, float batch) { const int hg = heads_per_wg(H, Hkv, RG); return start + batch * ((s + hg - 1) / hg); };
-  const float start2 = fixed(2, 5.2f, 1.7f), two = 2.f * (1.81f * tiles * (1.f - 256.f / w) + start2);
-  return std::max(1.81f * tiles + start2, two) < 2.39f * tiles + fixed(4, 6.5f, 1.8f);
-}
-
 template <bool PREFILL, int RG>
 hipError_t launch_causal(CausalParams& p, hipStream_t st) {
   auto kernel = causal_attn_bf16_kernel<PREFILL, RG>;
   static DeviceOnce configured;                  // the attribute belongs to the loaded code object of a device
   hipError_t ce = configured.run([&] { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES); });
   if (ce != hipSuccess) return ce;
-  p.hg = heads_per_wg(p.H, p.Hkv, RG);
+  p.hg = causal_heads_per_wg(p.H, p.Hkv, RG);
   const int groups = p.H / p.hg;
-  p.n_qblocks = workgroups(p.T, p.H, p.Hkv, RG) / groups;
+  p.n_qblocks = causal_workgroups(p.T, p.H, p.Hkv, RG) / groups;
   p.qb_log2 = (RG == 4 ? 7 : 6) - (p.hg == 4 ? 2 : p.hg == 2 ? 1 : 0);         // 32 RG / hg
   p.G = p.H / p.Hkv;
   p.by_groups = divisor(groups); p.by_kv_heads = divisor(p.Hkv);
@@ -750,19 +722,7 @@ hipError_t launch_ttt_attention(bool bf16, const void* q, const void* k, const v
   p.seq = nullptr;
   p.T = T; p.H = H; p.Hkv = Hkv; p.s = s;
   p.out = out;
-  return half_workgroups(T, H, Hkv, s) ? launch_causal<false, 2>(p, st) : launch_causal<false, 4>(p, st);
-}
-
-// This kernel against the tree kernel, which cuts the keys into splits and merges them (us, 32 heads over 8 unless stated):
-//   enough workgroups for most CUs: 192 (768 rows) 22 against 38 with no context, 382 against 448 behind 16 k positions;
-//     512 (2048 rows) 70 against 112, 813 against 981; 128 (512 rows) 373 against 253 behind 16 k positions;
-//   walks so short that the merge costs more than the idle CUs: 1 tile 7.3 against 9.8-11.9, 4 tiles (512 rows) 16 against
-//     25, and with 8 heads over 2 (32 workgroups) 14.6 against 15.2; 8 tiles there (64 workgroups) 24.7 against 23.5;
-//   between the two the line runs near 10 workgroups per tile of walk: 64 and 6 tiles 20.3 against 21.5, 128 and 12 tiles 37
-//     against 42, but 64 and 10 tiles 30 against 26, 128 and 20 tiles 59 against 55.
-bool prefill_attention_fits(int n, int H, int Hkv, int max_len) {
-  const int wgs = workgroups(n, H, Hkv, 4), tiles = (max_len + KT - 1) / KT;
-  return wgs >= 192 || tiles <= 4 || wgs >= 10 * tiles;
+  return causal_half_workgroups(T, H, Hkv, s) ? launch_causal<false, 2>(p, st) : launch_causal<false, 4>(p, st);
 }
 
 hipError_t launch_prefill_attention(const void* q, const void* kcache, const void* vcache, const SeqInfo* seq, int n, int H, int Hkv,

@@ -11,6 +11,7 @@
 
 #include "../../include/eagle3.h"
 #include "../../include/eagle3_measure.h"
+#include "causal_rules.hpp"
 #include "common.hpp"
 #include "kernels.hpp"
 #include "wide_tiles.hpp"

@@ -215,5 +215,3 @@ hipError_t launch_ttt_attention(bool bf16, const void* q, const void* k, const v
 // cache rows, the chunk's own included, are written.  q [n, H, d] bf16, out fragment-major bf16 [n, H * d].
 hipError_t launch_prefill_attention(const void* q, const void* kcache, const void* vcache, const SeqInfo* seq, int n, int H, int Hkv,
                                     int d, void* out, hipStream_t st);
-// Whether that kernel, which does not split the keys, is the better one for n rows that see up to max_len keys.
-bool prefill_attention_fits(int n, int H, int Hkv, int max_len);
