@@ -35,14 +35,18 @@ inline bool causal_half_workgroups(int T, int H, int Hkv, int s) {
 }
 
 // Whether this kernel, which does not split the keys, is the better one for n rows of a prompt that see up to max_len keys.  Against the tree kernel, which cuts the keys
-// into splits and merges them (us, 32 heads over 8 unless stated):
-//   enough workgroups for most CUs: 192 (768 rows) 22 against 38 with no context, 382 against 448 behind 16 k positions;
-//     512 (2048 rows) 70 against 112, 813 against 981; 128 (512 rows) 373 against 253 behind 16 k positions;
-//   walks so short that the merge costs more than the idle CUs: 1 tile 7.3 against 9.8-11.9, 4 tiles (512 rows) 16 against
-//     25, and with 8 heads over 2 (32 workgroups) 14.6 against 15.2; 8 tiles there (64 workgroups) 24.7 against 23.5;
-//   between the two the line runs near 10 workgroups per tile of walk: 64 and 6 tiles 20.3 against 21.5, 128 and 12 tiles 37
-//     against 42, but 64 and 10 tiles 30 against 26, 128 and 20 tiles 59 against 55.
+// into splits and merges them (us, 32 heads over 8 unless stated, tree / this kernel):
+//   more than 128 workgroups: the tree kernel has two for each of them, more than CUs, and the last few take as long as all, at any
+//     length: 640 rows (160) behind 1500 positions 58 / 37, 513 rows (136) behind 16 k 340 / 257, 1024 rows behind 2048 83 / 63; but 449 rows (120) behind 16 k
+//     196 / 254;
+//   walks so short that the merge costs more than the idle CUs: up to 4 tiles, 100 rows behind 128 positions 13.3 / 8.7, 384 rows behind 64 21.6 / 12.0;
+//   between the two the line runs near 6.5 workgroups per tile of walk: 300 rows (80) and 11 tiles 35.7 / 25.2, 256 rows (64) and 10 tiles 24.0 / 24.3.  Where a
+//     group has one head, or an odd number, so that a workgroup's rows are of one head, the tree kernel's are the fuller ones and it is near 10: 16 heads over 16 300
+//     rows (48) and 8 tiles 16.6 / 20.2, 32 over 32 160 rows (64) and 9 tiles 18.5 / 21.8.
+// What it picks of both at 2504 prompts (17..1025 rows behind 0 to 16 k positions, 8 to 64 heads over 2 to 32) is 1.5 % slower than the better one on average.  (The line of the former
+// kernels, 192 workgroups or 10 to a tile, 5.2 %; 284 of them take the other kernel now, 24 % faster, and 2 of those are slower, by 2 %.)  The error against 64 bits is
+// that of rounding the output to bf16 in both (1.660e-3 each).
 inline bool prefill_attention_fits(int n, int H, int Hkv, int max_len) {
   const int wgs = causal_workgroups(n, H, Hkv, 4), tiles = (max_len + CAUSAL_KEYS - 1) / CAUSAL_KEYS;
-  return wgs >= 192 || tiles <= 4 || wgs >= 10 * tiles;
+  return wgs > 128 || tiles <= 4 || 2 * wgs >= (causal_heads_per_wg(H, Hkv, 4) == 1 ? 20 : 13) * tiles;
 }

@@ -71,10 +71,21 @@ def test_ttt_attention_with_queries_at_any_address(H, Hkv, shift, T):
 # take the causal kernel (few tiles of keys) or the split one (long context, few rows)
 @pytest.mark.parametrize("P,n", [(1, 63), (64, 64), (77, 130), (127, 1), (200, 312), (700, 20), (1000, 500)])
 def test_prefill_continues_a_cached_prefix(P, n):
+    from test_gpu_edges import SMALL
+    _prompt_in_two_calls(SMALL, P, n)
+
+
+# just more than 128 workgroups of the causal kernel behind a context of twelve tiles; fewer, but enough for its length
+@pytest.mark.parametrize("P,n", [(1500, 530), (400, 230)])
+def test_prefill_of_many_workgroups_behind_a_prefix(P, n):
+    from test_gpu_edges import SMALL
+    _prompt_in_two_calls(SMALL.with_(name="h32", n_heads=32, n_kv_heads=8), P, n)
+
+
+def _prompt_in_two_calls(shape, P, n):
     import pipeline as PL
-    from test_gpu_edges import SMALL, _E
+    from test_gpu_edges import _E
     E = _E()
-    shape = SMALL
     ctx = E.Eagle3Context(shape, max_batch=1, max_nodes=8, max_depth=2, max_topk=2, max_new=4, device=DEV)
     W = PL.device_weights(shape, device=DEV)
     ctx.set_weights(W["target"], W["draft"])
