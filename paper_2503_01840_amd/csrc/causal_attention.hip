@@ -18,14 +18,15 @@
 //   * One block is a matrix-unit time of 24 products (8 score + 16 value, 768 cycles) against ~700 issue cycles of everything else (4 a vector
 //     instruction, 8 an exponential or a product).  Run one after the other they add up (all wavefronts pass the same barrier, so they stay in
 //     phase); here the softmax of block i runs between the score products of block i + 1 and the value products of block i - 1, none of which
-//     depend on it, its last four weights a block later, so that both halves of a block have about as much to issue as to multiply.  No v_dot2 among
-//     them, which stops the matrix unit, and the direct loads one by one: 85 k -> 70 k cycles for 16 tiles, of which 50 k are products.
+//     depend on it, its last four weights a block later, so that both halves of a block have about as much to issue as to multiply.  One v_dot2 for every
+//     two weights among them and no more, as they stop the matrix unit, and the direct loads one by one: 85 k -> 70 k cycles for 16 tiles, of which 50 k are products.
 //   * Only tiles that reach past a workgroup's first query need a mask.
 //   * The own keys of the simulated steps come last; their rows arrive while the last block is worked on.
 //   * Workgroups of later queries walk over more keys: they are handed out first, and the KV head is the fastest index,
 //     so that with 8 KV heads each XCD keeps one head's keys in its L2.
 // What bounds it: the chip's power where every CU has two workgroups and more (at T = 2048, 32 heads over 8, the clock in the loop is 1.9 GHz,
-// and was 2.15 with the 18 % more cycles), and the walk of the longest workgroup with its start, own keys and merge where there are fewer.  The softmax
+// and was 2.15 with the 18 % more cycles), and the walk of the longest workgroup with its start, own keys and merge where there are fewer.  A workgroup has all of a CU's LDS, so that these
+// never run under another one's tiles: of 58 us at T = 2048 with s = 2 some 39 are tiles (17 to a CU, by the cycles above).  The softmax
 // must stay in the gaps it is written into: with the sum of the weights formed behind the block, copies between registers, a last
 // tile taken whole and the output rescaled at every own key it was 29.0 instead of 22.6 us (T = 517, 64 heads, s = 5), 72 instead
 // of 67 (T = 2048, 32 heads over 8, s = 5) and 36.0 instead of 32.6 (T = 2048, 8 heads, s = 0).  Measured against a kernel of one head x 64 queries per workgroup (4 wavefronts, scores,

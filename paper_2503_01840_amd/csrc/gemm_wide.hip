@@ -26,7 +26,7 @@
 //     as fragment-major bf16 (8-byte stores).
 // 8B width, us, products as 32x32x16 with the reads and loads in bursts / now: 2048 rows gate/up 422 / 368 (1.31 PFLOP/s), down
 // 214 / 177, o 77 / 57, q/k/v 100 / 87; 512 rows gate/up 116 / 101, down 73 / 60, q/k/v 39 / 35; 256 rows gate/up 75 / 72 (68
-// with 128-k weight stages and staggered walks), 77 rows 61 / 58 (53).
+// with 128-k weight stages and staggered walks), 77 rows 61 / 58 (53; 48 in tiles of 96 rows).
 // Tiles of 256 x 224 and 256 x 192 (4 x 2 wavefronts of 64 x 112 and 64 x 96) are there for whole rounds of the chip, wide_tiles.hpp says where: 2048
 // rows gate/up 371 -> 357 us, q/k/v 92 -> 81, a prompt of 2048 tokens 27.28 -> 26.48 ms; 512 rows gate/up 99.8 -> 98.3 us.
 // Measured and not kept: 4 wavefronts of 128 x 128 each (a third fewer LDS reads: loop 4 % shorter, epilogue longer by the same).
